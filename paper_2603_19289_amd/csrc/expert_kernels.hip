@@ -555,6 +555,178 @@ __global__ __launch_bounds__(kBlock) void expert_mfma_kernel(const ExpertArgs a,
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Prefill with many positions per expert: the expert FFN as a tiled matrix product.  A workgroup
+// owns 128 positions of one expert and 256 weight rows (gate/up: 128 rows of W_gate and the same 128
+// of W_up, so that both factors of the SwiGLU product meet in one lane; down: 256 rows of W_down), and
+// walks the reduction 64 columns at a time through two LDS buffers: the next 64 columns travel to
+// registers while the current ones are multiplied.  A wavefront multiplies 64 positions with 64 weight
+// rows.  expert_mfma_kernel, which feeds every MFMA from global memory, re-reads each weight row once
+// per 64 positions and stops where the caches do.
+// Sums: every 512 columns the accumulators are added to a second set and start again from zero, so that
+// no float32 chain is longer than those of expert_mfma_kernel (one chain of 4096 columns moved half as
+// many SwiGLU values more to the neighbouring bf16 value).
+// The tiles of all experts of the launch form one list that one workgroup per compute unit walks:
+// positions per expert are known on the device only.
+constexpr int kTileBlock = 512;
+constexpr int kTilePos = 128, kTileRows = 256, kTileK = 64;
+constexpr int kTileSteps = 8;                  // steps of 64 columns per chain of sums
+constexpr int kTileGroup = 8;                  // row tiles that share a group of position tiles in an L2
+
+template <bool GATEUP>
+__global__ __launch_bounds__(kTileBlock, 2) void expert_tile_kernel(const ExpertArgs a, const ActiveList act,
+                                                                    const uint16_t *act_q, uint16_t *hq_out) {
+  // rows of 64 columns: positions first, then weight rows.  The 16-byte chunk c of row r lies at chunk
+  // c ^ (r % 8): eight lanes that read the same chunk of eight rows touch all banks once.
+  constexpr int kBuf = (kTilePos + kTileRows) * (kTileK / 8);
+  __shared__ uint4 tile[2 * kBuf];
+  __shared__ int list[kTilePos];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int m = lane & 15, g = lane >> 4;
+  const int K = GATEUP ? a.H : a.I;
+  const int R = GATEUP ? a.I : a.H;
+  constexpr int kRowsOut = GATEUP ? kTileRows / 2 : kTileRows;         // output rows per tile
+  const int row_tiles = (R + kRowsOut - 1) / kRowsOut;
+  const int chunk = tid & 7, ld_row = tid >> 3;                        // this thread's chunk and first row when loading
+  const int ld_at = ld_row * 8 + (chunk ^ (ld_row & 7));
+  const int wave_pos = (wave & 1) * 64;
+  const int wave_row = (wave >> 1) * (GATEUP ? 32 : 64);
+  // workgroups go round the eight XCDs: the ones of an XCD take neighbouring tiles, which share rows and positions
+  const int per_xcd = gridDim.x / 8;
+  const int slot = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+
+  for (long t = slot;; t += gridDim.x) {
+    // ---- which expert, positions and rows
+    long left = t;
+    int e = -1, n_all = 0, n_pt = 0, which = 0;
+    for (int i = 0; i < act.n; ++i) {
+      const int cnt = a.pos_count[act.expert[i]];
+      const int pt = (cnt + kTilePos - 1) / kTilePos;
+      const long tiles = long(pt) * row_tiles;
+      if (left < tiles) { e = act.expert[i]; n_all = cnt; n_pt = pt; which = i; break; }
+      left -= tiles;
+    }
+    if (e < 0) return;                         // past the last tile: the same for the whole workgroup
+    const int group = int(left / (long(kTileGroup) * n_pt));
+    const int in_group = int(left - long(group) * kTileGroup * n_pt);
+    const int group_rows = min(kTileGroup, row_tiles - group * kTileGroup);
+    const int pos0 = in_group / group_rows * kTilePos;
+    const int row0 = (group * kTileGroup + in_group % group_rows) * kRowsOut;
+    const int n = min(kTilePos, n_all - pos0);
+    __syncthreads();                           // the previous tile's readers of list and tile are done
+    if (tid < n) list[tid] = a.pos_list[size_t(e) * a.list_stride + pos0 + tid];
+    __syncthreads();
+
+    const uint16_t *wbase = reinterpret_cast<const uint16_t *>(a.pool + size_t(act.slot[which]) * a.slot_bytes) +
+                            (GATEUP ? size_t(0) : size_t(2) * a.I * a.H);
+    const uint16_t *xp[2];
+    uint32_t woff[4];                          // an expert block holds fewer than 2^30 weights
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int p = ld_row + 64 * i;
+      const int f = list[p < n ? p : 0];       // rows past the end repeat one and are not stored
+      xp[i] = act_q + size_t(GATEUP ? f / a.k : f) * K + chunk * 8;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = ld_row + 64 * i;
+      const int in = r & (kRowsOut - 1);
+      woff[i] = uint32_t(min(row0 + in, R - 1)) * uint32_t(K) + (GATEUP && r >= kRowsOut ? uint32_t(a.I) * uint32_t(a.H) : 0u) + chunk * 8;
+    }
+    f32x4_t total[4][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) total[j][p] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    uint4 held[6];
+    auto fetch = [&](int k0) {                 // columns past the end are zeros on both sides
+      const bool inside = k0 + chunk * 8 < K;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) held[i] = make_uint4(0u, 0u, 0u, 0u);
+      if (inside) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) held[i] = *reinterpret_cast<const uint4 *>(xp[i] + k0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) held[2 + i] = *reinterpret_cast<const uint4 *>(wbase + woff[i] + k0);
+      }
+    };
+    auto keep = [&](int buf) {
+#pragma unroll
+      for (int i = 0; i < 6; ++i) tile[buf * kBuf + ld_at + i * 64 * 8] = held[i];
+    };
+    fetch(0);
+    keep(0);
+    __syncthreads();
+    int buf = 0;
+    for (int k_first = 0; k_first < K; k_first += kTileSteps * kTileK) {
+      f32x4_t acc[4][4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) acc[j][p] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      const int k_end = min(K, k_first + kTileSteps * kTileK);
+      for (int k0 = k_first; k0 < k_end; k0 += kTileK) {
+        const bool more = k0 + kTileK < K;
+        if (more) fetch(k0 + kTileK);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const uint4 *at = tile + buf * kBuf + m * 8 + ((kk * 4 + g) ^ (m & 7));
+          bf16x8_t x[4], w[4];
+#pragma unroll
+          for (int p = 0; p < 4; ++p) x[p] = __builtin_bit_cast(bf16x8_t, at[(wave_pos + p * 16) * 8]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int r = GATEUP ? wave_row + (j & 1) * 16 + (j >> 1) * kRowsOut : wave_row + j * 16;
+            w[j] = __builtin_bit_cast(bf16x8_t, at[(kTilePos + r) * 8]);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) acc[j][p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[j], x[p], acc[j][p], 0, 0, 0);
+        }
+        buf ^= 1;
+        if (more) keep(buf);                   // its last readers passed the barrier of the step before
+        __syncthreads();
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) total[j][p] += acc[j][p];
+    }
+
+    // ---- accumulator layout: lane = position lane % 16, rows 4 (lane / 16) .. + 3
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const int idx = wave_pos + p * 16 + m;
+      if (idx < n) {
+        const int f = list[idx];
+#pragma unroll
+        for (int j = 0; j < (GATEUP ? 2 : 4); ++j) {
+          const int r = row0 + wave_row + j * 16 + 4 * g;             // four rows, all inside or all outside
+          if (r < R) {
+            if (GATEUP) {
+              uint16_t q[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const float s0 = total[j][p][i], s1 = total[GATEUP ? j + 2 : j][p][i];
+                q[i] = uint16_t(__float_as_uint(round_to_bf16(s0 / (1.f + expf(-s0)) * s1)) >> 16);
+              }
+              uint2 packed;
+              packed.x = uint32_t(q[0]) | (uint32_t(q[1]) << 16);
+              packed.y = uint32_t(q[2]) | (uint32_t(q[3]) << 16);
+              *reinterpret_cast<uint2 *>(hq_out + size_t(f) * R + r) = packed;
+            } else {
+              *reinterpret_cast<float4 *>(a.y + size_t(f) * R + r) =
+                  make_float4(total[j][p][0], total[j][p][1], total[j][p][2], total[j][p][3]);
+            }
+          }
+        }
+      }
+    }
+  }
+}
+
 // Positions f = b*k + j of an id table [tokens, k], grouped by expert, ascending inside a group:
 // pos[e*stride + i] for i < count[e].  One workgroup per expert; each wavefront counts and then
 // writes its own contiguous quarter of the table.
@@ -769,12 +941,45 @@ hipError_t launch_expert_mfma_k(const ExpertArgs &a, const ActiveList &act, cons
   return hipGetLastError();
 }
 
+// Compute units of the current device.
+hipError_t compute_units(int *n) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  return e != hipSuccess ? e : hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev);
+}
+
+// Prefill: the tiled kernel, or position lists through expert_mfma_kernel?  A tile takes about 1.5 us per 64
+// columns however many of its positions are real (one workgroup per compute unit, the loads of one step in
+// flight), the other kernel's time goes with the positions (about 170 TFLOP/s once its weights are read): tiles
+// pay once a round of them holds about a quarter of the device's worth of real positions, taking the experts as
+// equally loaded.  Measured, expert_mfma_kernel against tiles: gate/up of 8 experts 768 x 2048 with 128
+// positions each 50 / 58 us, with 256 87 / 58 us; down (2048 x 768) with 64 24 / 28, with 128 38 / 30; one expert
+// 14336 x 4096 with 64 positions 120 / 101, with 128 201 / 101, its down with 256 259 / 341, with 8192 7784 / 1428
+// (gate/up 9492 / 2618 us, 735 TFLOP/s).
+bool tiles_pay(const ExpertArgs &a, int n_experts, bool gateup, int cus) {
+  const long rows = gateup ? a.I : a.H, rows_out = gateup ? kTileRows / 2 : kTileRows;
+  const long row_tiles = (rows + rows_out - 1) / rows_out;
+  const long pos = long(a.list_tokens) * a.k / a.E;      // per expert
+  const long tiles = n_experts * ((pos + kTilePos - 1) / kTilePos) * row_tiles;
+  const long rounds = (tiles + cus - 1) / cus;
+  return pos > 0 && n_experts * pos * row_tiles * 4 >= rounds * cus * kTilePos;
+}
+
 // Wavefronts per 16-row tile by the length of the reduction: each should still walk at least
 // eight 64-column steps, below that the shared start-up (token lists, partial sums) outweighs
 // what the extra parallelism wins.
 template <bool GATEUP>
 hipError_t launch_expert_mfma(const ExpertArgs &a, const ActiveList &act, const uint16_t *act_q, uint16_t *hq,
                               hipStream_t st) {
+  if (a.pos_list) {
+    int cus = 0;
+    if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
+    if (tiles_pay(a, act.n, GATEUP, cus)) {
+      const int wgs = (cus + 7) / 8 * 8;                 // one per compute unit: 97 KB of LDS
+      hipLaunchKernelGGL((expert_tile_kernel<GATEUP>), dim3(wgs), dim3(kTileBlock), 0, st, a, act, act_q, hq);
+      return hipGetLastError();
+    }
+  }
   const int steps = ((GATEUP ? a.H : a.I) + 63) / 64;
   if (steps >= 32) return launch_expert_mfma_k<GATEUP, 4>(a, act, act_q, hq, st);
   if (steps >= 16) return launch_expert_mfma_k<GATEUP, 2>(a, act, act_q, hq, st);

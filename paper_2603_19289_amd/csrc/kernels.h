@@ -115,12 +115,12 @@ struct ExpertArgs {
   float *h;                   // [B,k,I] SwiGLU products
   float *y;                   // [B,k,H] un-gated expert outputs
   float *out;                 // [B,H]
-  int B, k, H, I, bf16;
+  int B, k, H, I, bf16, E;
   // matrix-core kernels over more than one decode batch (prefill): positions grouped by expert as
   // written by launch_expert_lists for list_tokens tokens; null: the [B,k] table exec_ids is searched
   const int32_t *pos_list;    // [E, list_stride]
   const int32_t *pos_count;   // [E]
-  int list_stride, list_tokens;
+  int list_stride, list_tokens;   // E is read with them: positions per expert on average
 };
 
 // Host-to-device gather copy: each entry moves one expert block from the pinned pool to a slot.

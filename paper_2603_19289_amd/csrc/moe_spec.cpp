@@ -1249,6 +1249,7 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
         xa.pos_count = c->at<int32_t>(c->lay.pf_count);
         xa.list_stride = P;
         xa.list_tokens = P;
+        xa.E = E;
         if ((e = launch_gateup_mfma(xa, act, sq_all, hq, c->compute)) != hipSuccess)
           return c->hip_fail(e, "gate/up MFMA kernel");
         if ((e = launch_down_mfma(xa, act, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");

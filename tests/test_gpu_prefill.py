@@ -80,6 +80,19 @@ def test_prefill_pool_larger_than_expert_count():
     run_prefill(wl, P=21, max_batch=16, label="S>2E", copy_engine=M.COPY_KERNEL)
 
 
+@pytest.mark.parametrize("hidden,inter,experts,top_k,P", [
+    (72, 136, 4, 2, 4300),        # one chain of sums, a reduction that ends inside a step, rows past the matrix
+    (520, 264, 6, 3, 2900),       # two chains of sums, two and three row tiles
+    (64, 1032, 3, 1, 8300),       # the down projection's reduction ends inside its third chain
+    (128, 128, 64, 1, 9000),      # whole tiles of rows; many experts with about one tile of positions each
+])
+def test_prefill_tiled_matrix_product(hidden, inter, experts, top_k, P):
+    """Prompts long enough for the tiled kernel in the gate/up or the down launch (or both): positions per expert
+    around its 128-position tile, remainders of its 64-column steps and of its row tiles."""
+    wl = small_workload(n_layers=1, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype="bf16", slots=2 * experts)
+    run_prefill(wl, P=P, max_batch=64, label="tiles", copy_engine=M.COPY_DMA2)
+
+
 @pytest.mark.parametrize("name,P,layers", [("c2_qwen3_30b_a3b", 150, 2), ("c3_gpt_oss_20b", 70, 1)])
 def test_prefill_at_full_layer_shape(name, P, layers):
     """The benchmark's layer shape and slot count, micro-batches of 64 tokens plus a ragged tail."""
