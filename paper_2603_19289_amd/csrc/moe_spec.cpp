@@ -6,8 +6,11 @@
 //   copy stream   : [wait done(l+1) of the previous token] -> H2D of the missing experts of
 //                   layer l+1 -> record ready(l+1)
 // The host learns expert ids through a pinned mailbox the routing kernels write; it needs them
-// to decide which slots to fill.  done(l) is recorded after the last kernel that reads pool l, and
-// every copy into pool l waits for it, so a slot is never overwritten while it is being read.
+// to decide which slots to fill.  Ids posted by a routing launch also say that every launch before it on
+// the compute stream has ended, the kernels that read pool l+1 one token earlier among them, so an ordinary
+// step needs no event between those kernels and the copies (an event recorded behind a kernel holds the next
+// one up by 5.6 us).  Where the host has not seen that (further cache waves of a step), done(l) is recorded
+// when a copy needs it and every copy into pool l waits for it: a slot is never overwritten while it is read.
 #include "../../include/moe_spec.h"
 
 #include <hip/hip_runtime.h>
@@ -177,6 +180,10 @@ struct moe_spec_ctx {
   std::vector<Pool> pools;
   std::vector<hipEvent_t> ready, done;
   std::vector<char> done_recorded, ready_recorded;
+  std::vector<char> ready_pending;              // copies into this pool that the compute stream has not waited for yet
+  std::vector<uint64_t> read_step;              // routing step whose expert kernels last read this pool; 0: none
+  uint64_t step_seq = 0;                        // decode layer steps launched (their routing launches)
+  uint64_t seen_seq = 0;                        // latest of them whose expert ids the host has seen
   Mailbox *mb_true = nullptr, *mb_next = nullptr, *mb_look = nullptr;       // pinned host
   Mailbox *mb_true_dev = nullptr, *mb_next_dev = nullptr, *mb_look_dev = nullptr;
   volatile unsigned int *wait_status = nullptr;         // pinned host word after the mailboxes: a kernel's bounded wait ran out
@@ -281,6 +288,7 @@ struct moe_spec_ctx {
       }
     }
     __atomic_thread_fence(__ATOMIC_ACQUIRE);
+    seen_seq = step_seq;
     return MOE_SPEC_OK;
   }
 
@@ -334,6 +342,25 @@ struct moe_spec_ctx {
     for (hipStream_t q : copy_aux) if (w == hipSuccess) w = hipStreamWaitEvent(q, ev, 0);
     return w == hipSuccess ? MOE_SPEC_OK : hip_fail(w, "copy stream wait");
   }
+  // Copies into the layer's pool go behind the kernels that read it.  Kernels of step n have ended once the host
+  // has seen ids of a later step's routing launch (same stream, in order); otherwise an event, recorded now.
+  int copies_behind_readers(int layer) {
+    if (read_step[layer] != 0 && read_step[layer] >= seen_seq) {
+      hipError_t r = hipEventRecord(done[layer], compute);
+      if (r != hipSuccess) return hip_fail(r, "record done event");
+      done_recorded[layer] = 1;
+    }
+    read_step[layer] = 0;
+    if (!done_recorded[layer]) return MOE_SPEC_OK;
+    done_recorded[layer] = 0;                    // every queue waits below: later copies are behind it as well
+    return copy_queues_wait(done[layer]);
+  }
+  // The compute stream goes behind the copies into the layer's pool, if there were any since it last did.
+  hipError_t compute_behind_copies(int layer) {
+    if (!ready_pending[layer]) return hipSuccess;
+    ready_pending[layer] = 0;
+    return hipStreamWaitEvent(compute, ready[layer], 0);
+  }
 
   // Cache request for at most S experts (ascending ids): hits are stamped, each miss takes the
   // least recently used slot that holds no requested expert and is copied in on the copy stream.
@@ -366,11 +393,7 @@ struct moe_spec_ctx {
       if (victim < 0) return fail(MOE_SPEC_ESTATE, "no evictable slot (request larger than the pool)");
       const char *src = host_expert[size_t(layer) * cfg.n_experts + e];
       if (copies == 0) {
-        if (done_recorded[layer]) {
-          hipError_t w = hipStreamWaitEvent(copy, done[layer], 0);
-          for (hipStream_t q : copy_aux) if (w == hipSuccess) w = hipStreamWaitEvent(q, done[layer], 0);
-          if (w != hipSuccess) return hip_fail(w, "copy stream wait");
-        }
+        if (int rc = copies_behind_readers(layer)) return rc;
         if (ready_recorded[layer]) {
           // further queues: also behind the previous request on this pool (its slots may be reused
           // by this one before any kernel ran, e.g. a true request right after a mispredicted prefetch)
@@ -399,6 +422,7 @@ struct moe_spec_ctx {
       hipError_t r = hipEventRecord(ready[layer], copy);
       if (r != hipSuccess) return hip_fail(r, "record ready event");
       ready_recorded[layer] = 1;
+      ready_pending[layer] = 1;
     }
     for (int e : experts) {
       act->expert[act->n] = int16_t(e);
@@ -512,6 +536,8 @@ int moe_spec_create(const moe_spec_config *cfg, moe_spec_ctx **out) {
   for (auto &p : c->pools) { p.slot_expert.assign(S, -1); p.slot_stamp.assign(S, -1); p.where.assign(E, -1); }
   c->done_recorded.assign(L, 0);
   c->ready_recorded.assign(L, 0);
+  c->ready_pending.assign(L, 0);
+  c->read_step.assign(L, 0);
 
   auto bail = [&](hipError_t err, const char *what) {
     g_create_error = std::string(what) + ": " + hipGetErrorString(err);
@@ -694,11 +720,11 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   const bool prefetching = spec_mode || hint_mode;
   const bool do_pred = !last && (prefetching || cfg.predict_in_on_demand);
   const bool exec_pred = spec_mode && c->have_pending;
-  const bool hinted = hint_mode && c->have_pending;      // a prefetch for this layer may be in flight
   const size_t wbytes = cfg.dtype == MOE_SPEC_BF16 ? 2 : 4;
   hipError_t e;
 
   if (int rc = c->check_waits()) return rc;
+  c->step_seq += 1;
   TimedSpan *sp_route = c->open_span(0, c->compute);
 
   const bool use_est = do_pred && c->est.set && !c->est_use.empty() && c->est_use[layer];
@@ -956,21 +982,19 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   for (size_t w0 = 0, wave = 0; w0 < exec_union.size(); w0 += S, ++wave) {
     ActiveList act{};
     int copies = 0;
-    bool need_wait;
     if (exec_pred && wave == 0) {
-      act = c->pending_wave0;
-      need_wait = true;                         // the prefetch may still be in flight
+      act = c->pending_wave0;                   // requested one step earlier; its copies may still be in flight
     } else {
       std::vector<int> req(exec_union.begin() + w0, exec_union.begin() + std::min(exec_union.size(), w0 + S));
       int rc = c->request(layer, req, &act, &copies);
       if (rc) return rc;
-      need_wait = copies > 0 || (hinted && wave == 0);
     }
-    if (need_wait) {
+    if (c->ready_pending[layer]) {
       TimedSpan *sp_stall = c->open_span(2, c->compute);
-      if ((e = hipStreamWaitEvent(c->compute, c->ready[layer], 0)) != hipSuccess) return c->hip_fail(e, "compute stream wait");
+      if ((e = c->compute_behind_copies(layer)) != hipSuccess) return c->hip_fail(e, "compute stream wait");
       c->close_span(sp_stall, c->compute);
     }
+    c->read_step[layer] = c->step_seq;
     c->st.cache_waves += 1;
     TimedSpan *sp_exec = c->open_span(0, c->compute);
     TimedSpan *sp_gu = c->open_span(3, c->compute);
@@ -1001,8 +1025,6 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
                                         c->at<unsigned long long>(c->lay.dacc_cnt) + size_t(layer) * E,
                                         c->compute)) != hipSuccess)
       return c->hip_fail(e, "default-vector accumulation");
-    if ((e = hipEventRecord(c->done[layer], c->compute)) != hipSuccess) return c->hip_fail(e, "record done event");
-    c->done_recorded[layer] = 1;
     c->st.hbm_bytes_algorithmic += int64_t(act.n) * int64_t(c->expert_bytes);
     c->close_span(sp_exec, c->compute);
   }
@@ -1025,11 +1047,6 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     int copies = 0;
     rc = c->request(layer + 1, req, &c->pending_wave0, &copies);
     if (rc) return rc;
-    if (copies == 0) {
-      // nothing to copy: make the wait at the next step a no-op that is still well defined
-      if ((e = hipEventRecord(c->ready[layer + 1], c->copy)) != hipSuccess) return c->hip_fail(e, "record ready event");
-      c->ready_recorded[layer + 1] = 1;
-    }
   }
   if (score_look) {
     // recall@k of what layer l-2 predicted for this layer; the true ids were posted before the predicted ones
@@ -1187,7 +1204,7 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
   std::fill(p.slot_stamp.begin(), p.slot_stamp.end(), -1);
   std::fill(p.where.begin(), p.where.end(), -1);
   p.clock = 0;
-  if (c->done_recorded[layer]) { int rc = c->copy_queues_wait(c->done[layer]); if (rc) return rc; }
+  if (int rc = c->copies_behind_readers(layer)) return rc;
   if (c->ready_recorded[layer]) {
     for (hipStream_t q : c->copy_aux)
       if ((e = hipStreamWaitEvent(q, c->ready[layer], 0)) != hipSuccess) return c->hip_fail(e, "copy queue wait");
