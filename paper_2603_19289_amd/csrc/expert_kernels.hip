@@ -8,6 +8,7 @@
 // weight rows with 16-byte loads per lane, reducing across the 64 lanes with shuffles.
 // Weights are read once per token tile; at batch 1 that is exactly once.
 #include "device_utils.h"
+#include "gateup_b1.h"
 #include "kernels.h"
 
 namespace moe_spec {
@@ -171,139 +172,15 @@ __global__ __launch_bounds__(kBlock) void down_kernel(const ExpertArgs a, const 
 // Batch-1 kernels: no token lists, no staging barrier in the gate/up kernel, combine fused into
 // the down kernel.  These are the kernels of the headline workload.
 
-// hq[pos, row] for the one token of the batch, stored in the weight dtype for the down kernel.
-// `act` is in execution-position order, so blockIdx.y is the position.  Each lane keeps its NCH
-// chunks of s_l in registers; a wavefront owns `rpw` consecutive rows and keeps the 2*NCH
-// 16-byte loads of the next row in flight while it reduces the current one.
 template <typename WT, int NCH>
 __global__ __launch_bounds__(kBlock) void gateup_b1_kernel(const ExpertArgs a, const ActiveList act,
                                                            const int rpw) {
-  using R = Packed<WT>;
-  constexpr int VN = R::N;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int H = a.H, I = a.I;
-  const int row0 = (blockIdx.x * kWaves + wave) * rpw;
-  if (row0 >= I) return;
-  const int row_end = min(row0 + rpw, I);
-  const int pos = blockIdx.y;
-  const WT *wg = reinterpret_cast<const WT *>(a.pool + size_t(act.slot[pos]) * a.slot_bytes);
-  const WT *wu = wg + size_t(I) * H;
-  WT *hq = reinterpret_cast<WT *>(a.h) + size_t(pos) * I;
-
-  int col[NCH];
-  bool live[NCH];
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-    col[ch] = (ch * kWave + lane) * VN;
-    live[ch] = col[ch] < H;
-    if (!live[ch]) col[ch] = 0;                // dead lanes re-read column 0 and multiply by zero
-  }
-  typename R::Raw rg[NCH], ru[NCH];
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-    rg[ch] = load_stream<typename R::Raw>(wg + size_t(row0) * H + col[ch]);
-    ru[ch] = load_stream<typename R::Raw>(wu + size_t(row0) * H + col[ch]);
-  }
-  float sv[NCH][VN];
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-#pragma unroll
-    for (int x = 0; x < VN; x += 4) {
-      const float4 f = *reinterpret_cast<const float4 *>(a.s + col[ch] + x);
-      const float m = live[ch] ? 1.f : 0.f;
-      sv[ch][x] = f.x * m; sv[ch][x + 1] = f.y * m; sv[ch][x + 2] = f.z * m; sv[ch][x + 3] = f.w * m;
-    }
-  }
-  for (int row = row0; row < row_end; ++row) {
-    float ag = 0.f, au = 0.f;
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      float fg[VN], fu[VN];
-      R::unpack(rg[ch], fg);
-      R::unpack(ru[ch], fu);
-#pragma unroll
-      for (int x = 0; x < VN; ++x) { ag += fg[x] * sv[ch][x]; au += fu[x] * sv[ch][x]; }
-    }
-    if (row + 1 < row_end) {
-#pragma unroll
-      for (int ch = 0; ch < NCH; ++ch) {
-        rg[ch] = load_stream<typename R::Raw>(wg + size_t(row + 1) * H + col[ch]);
-        ru[ch] = load_stream<typename R::Raw>(wu + size_t(row + 1) * H + col[ch]);
-      }
-    }
-    const float g = wave_sum(ag);
-    const float u = wave_sum(au);
-    if (lane == 0) {
-      float hv = g / (1.f + expf(-g)) * u;
-      if (a.bf16) hv = round_to_bf16(hv);
-      hq[row] = R::pack_one(hv);
-    }
-  }
+  gateup_b1_body<WT, NCH, false>(a, act, blockIdx.y, blockIdx.x, rpw, nullptr, nullptr);
 }
 
-// Small launches (all wavefronts resident at once): a wavefront owns two consecutive rows and
-// issues the 4*NCH 16-byte loads of both before it reduces anything.
 template <typename WT, int NCH>
 __global__ __launch_bounds__(kBlock) void gateup_b1_pair_kernel(const ExpertArgs a, const ActiveList act) {
-  using R = Packed<WT>;
-  constexpr int VN = R::N;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int H = a.H, I = a.I;
-  const int row0 = (blockIdx.x * kWaves + wave) * 2;
-  if (row0 >= I) return;
-  const int pos = blockIdx.y;
-  const WT *wg = reinterpret_cast<const WT *>(a.pool + size_t(act.slot[pos]) * a.slot_bytes);
-  const WT *wu = wg + size_t(I) * H;
-  WT *hq = reinterpret_cast<WT *>(a.h) + size_t(pos) * I;
-
-  int col[NCH];
-  bool live[NCH];
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-    col[ch] = (ch * kWave + lane) * VN;
-    live[ch] = col[ch] < H;
-    if (!live[ch]) col[ch] = 0;                // dead lanes re-read column 0 and multiply by zero
-  }
-  typename R::Raw rg[2][NCH], ru[2][NCH];
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int row = min(row0 + r, I - 1);      // an odd last row is loaded twice and stored once
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      rg[r][ch] = load_stream<typename R::Raw>(wg + size_t(row) * H + col[ch]);
-      ru[r][ch] = load_stream<typename R::Raw>(wu + size_t(row) * H + col[ch]);
-    }
-  }
-  float sv[NCH][VN];
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) {
-#pragma unroll
-    for (int x = 0; x < VN; x += 4) {
-      const float4 f = *reinterpret_cast<const float4 *>(a.s + col[ch] + x);
-      const float m = live[ch] ? 1.f : 0.f;
-      sv[ch][x] = f.x * m; sv[ch][x + 1] = f.y * m; sv[ch][x + 2] = f.z * m; sv[ch][x + 3] = f.w * m;
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    if (row0 + r >= I) break;
-    float ag = 0.f, au = 0.f;
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      float fg[VN], fu[VN];
-      R::unpack(rg[r][ch], fg);
-      R::unpack(ru[r][ch], fu);
-#pragma unroll
-      for (int x = 0; x < VN; ++x) { ag += fg[x] * sv[ch][x]; au += fu[x] * sv[ch][x]; }
-    }
-    const float g = wave_sum(ag);
-    const float u = wave_sum(au);
-    if (lane == 0) {
-      float hv = g / (1.f + expf(-g)) * u;
-      if (a.bf16) hv = round_to_bf16(hv);
-      hq[row0 + r] = R::pack_one(hv);
-    }
-  }
+  gateup_b1_pair_body<WT, NCH>(a, act, blockIdx.y, blockIdx.x);
 }
 
 // O[row] = sum_j gate_j * (W_down_{e_j}[row,:] . hq[j,:]) for the one token of the batch: the down
@@ -872,18 +749,10 @@ hipError_t launch_down_t(const ExpertArgs &a, const ActiveList &act, hipStream_t
 
 template <typename WT, int NCH>
 void launch_gateup_b1_n(const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
-  const dim3 block(kBlock);
-  // up to 4096 wavefronts of two rows each are all resident at once (137 registers at NCH = 4)
-  if (NCH <= 4 && long(a.I) * act.n <= 8192) {
-    const dim3 grid((a.I + 2 * kWaves - 1) / (2 * kWaves), act.n);
-    hipLaunchKernelGGL((gateup_b1_pair_kernel<WT, NCH>), grid, block, 0, st, a, act);
-    return;
-  }
-  // one row per wavefront until that would exceed about 6144 wavefronts (24 per compute unit)
-  long rpw = (long(a.I) * act.n + 6143) / 6144;
-  if (rpw < 1) rpw = 1;
-  const dim3 grid((a.I + kWaves * rpw - 1) / (kWaves * rpw), act.n);
-  hipLaunchKernelGGL((gateup_b1_kernel<WT, NCH>), grid, block, 0, st, a, act, int(rpw));
+  const GateupSplit split = gateup_b1_split(NCH, a.I, act.n);
+  const dim3 grid(split.blocks, act.n), block(kBlock);
+  if (split.rpw == 0) hipLaunchKernelGGL((gateup_b1_pair_kernel<WT, NCH>), grid, block, 0, st, a, act);
+  else hipLaunchKernelGGL((gateup_b1_kernel<WT, NCH>), grid, block, 0, st, a, act, split.rpw);
 }
 
 // Returns false when H needs more register chunks than the batch-1 kernel is built for.

@@ -15,6 +15,7 @@
 // launcher checks to fit on the device together (groups are dispatched in order, so the earliest
 // unfinished group always gets the next free compute units).
 #include "device_utils.h"
+#include "gateup_b1.h"
 #include "kernels.h"
 
 namespace moe_spec {
@@ -165,28 +166,26 @@ __device__ __forceinline__ double select_gates(int k, SelectShared &sel, int tid
 
 // SPLIT wavefronts share one router row (4 / SPLIT rows per workgroup); NCH 16-byte chunks of the row
 // per lane, loaded into registers for both routers at the top of the kernel so that their latency
-// overlaps the normalisation.  blockIdx.y is the token; the workgroups of a token form a group that
+// overlaps the normalisation.  b is the token; the workgroups of a token form a group that
 // exchanges logits through the token's slots and computes everything else redundantly (the norm, the
 // top-k, the default-vector sum), so that nothing but the 8-byte logits crosses between workgroups.
 // Workgroup 0 of a token finishes the prediction; the last one reports the true routing, off the path
 // that the prediction waits on.
 template <typename WT, int SPLIT, int NCH, int ROWS>
-__global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs a) {
+__device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const int wg, const int n_wg, const int b,
+                                                const int n_tokens, double *vec_lds, RouteShared &sh) {
   static_assert(ROWS == 1 || SPLIT == 1, "several rows per wavefront only with one wavefront per row");
   // The router input being built, double precision, H values.  Threads own groups of VN consecutive columns (in
   // the norms: group tid, tid + 256, ...; in the products: the groups of the wavefront's chunks); column x of
   // group o lives at word x * G + o, so that the lanes of a wavefront, which hold consecutive groups, touch
   // consecutive words whatever x is (with the columns in their natural order every access of a wavefront fell
   // on a few banks)
-  extern __shared__ double vec_lds[];
-  __shared__ RouteShared sh;
   using P = Packed<WT>;
   using Raw = typename P::Raw;
   constexpr int VN = P::N;
   constexpr int RPW = kWaves / SPLIT * ROWS;   // rows per workgroup
 
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int wg = blockIdx.x, b = blockIdx.y;
   const int H = a.H, E = a.E, k = a.k;
   const int G = H / VN;                        // column groups (H is a multiple of 8)
 #define V(c, x) vec_lds[(x) * G + (c) / VN]
@@ -221,7 +220,7 @@ __global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs 
   }
   // re-arm the whole set of slots the next launch will use (last read by the previous launch, which has
   // ended), for every token the context allows: the next launch may carry a larger batch than this one
-  for (int i = (b * gridDim.x + wg) * kBlock + tid; i < a.arm_count; i += gridDim.x * gridDim.y * kBlock) {
+  for (int i = (b * n_wg + wg) * kBlock + tid; i < a.arm_count; i += n_wg * n_tokens * kBlock) {
     arm64(a.z_true_next + i);
     arm64(a.z_pred_next + i);
   }
@@ -320,7 +319,7 @@ __global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs 
   };
   publish_rows(rt, wt, a.z_true);
   STAGE(2);
-  const int reporter = gridDim.x - 1;
+  const int reporter = n_wg - 1;
   if (!pred && wg != reporter) return;
 
   // ---- (E_l, G_l): every workgroup of the token selects for itself
@@ -468,6 +467,31 @@ __global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs 
 #undef V
 }
 
+template <typename WT, int SPLIT, int NCH, int ROWS>
+__global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs a) {
+  extern __shared__ double vec_lds[];
+  __shared__ RouteShared sh;
+  route_pair_body<WT, SPLIT, NCH, ROWS>(a, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, vec_lds, sh);
+}
+
+// The routing of a layer and the gate/up projection of its experts, which were predicted one layer earlier, in one
+// launch for a batch of one.  The first n_route workgroups route (they are dispatched first, so they are resident
+// together), the others stream expert rows; these form s_l themselves.  NCH: chunks of a weight row per lane.
+template <typename WT, int NCH>
+__global__ __launch_bounds__(kBlock, 2)
+void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const ActiveList act, const int n_route,
+                            const int blocks, const int rpw) {
+  extern __shared__ double vec_lds[];
+  __shared__ RouteShared sh;
+  if (int(blockIdx.x) < n_route) {
+    route_pair_body<WT, kWaves, (NCH + 3) / 4, 1>(ra, blockIdx.x, n_route, 0, 1, vec_lds, sh);
+    return;
+  }
+  const int i = blockIdx.x - n_route;
+  float *s_lds = reinterpret_cast<float *>(vec_lds);
+  gateup_b1_body<WT, NCH, true>(a, act, i / blocks, i % blocks, rpw, s_lds, sh.red);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Launchers
 
@@ -534,7 +558,65 @@ hipError_t launch_route_pair_t(const RoutePairArgs &a, hipStream_t st) {
   return launch_route_pair_s<WT, 4, 1>(a, need4, st);
 }
 
+// How the gate/up rows are dealt to wavefronts beside the routing.  The routing is a chain of dependent memory accesses
+// (11 us alone) and every one of them queues behind the weight loads in flight: with all rows asked for at once its
+// first loads came back after 9 us instead of 2.4 and the launch took 20.5 us on 128 experts of 768 x 2048 (50 MB).
+// Up to 64 MB of weights one gate/up workgroup goes on each compute unit that does not route: 2.7 TB/s, at which the
+// routing takes its usual time, 18.6 us together.  Up to 256 MB the workgroups fill the device once, so that none is
+// left over for a second round (32 experts of 2880 x 2880, 133 MB: a token's eight layers 666 -> 628 us).  Beyond,
+// the routing is short beside the stream and the split of the plain launch is the best (470 MB: 688 us for six
+// layers, 700 when filled once).  Two rows per wavefront (pairs) 335 us, this rule 321 us for six layers of the first.
+GateupSplit beside_routing_split(int nch, const ExpertArgs &a, int n, size_t wbytes, int n_route, int blocks_per_cu) {
+  const size_t bytes = size_t(2) * a.I * a.H * n * wbytes;
+  if (bytes > size_t(256) << 20) return gateup_b1_split(nch, a.I, n);
+  const int wgs = bytes <= size_t(64) << 20 ? std::max(g_compute_units / 4, g_compute_units - n_route)
+                                            : blocks_per_cu * g_compute_units - n_route;
+  const int rpw = int((long(a.I) * n + long(kB1Waves) * wgs - 1) / (long(kB1Waves) * wgs));
+  return {rpw, (a.I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
+}
+
+template <typename WT, int NCH>
+hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
+  const size_t lds = size_t(ra.H) * sizeof(double);
+  const int n_route = ra.E;                    // one workgroup per router row
+  static int blocks_per_cu = -1;               // per instantiation
+  static size_t checked_lds = 0;
+  if (blocks_per_cu < 0 || lds > checked_lds) {
+    int n = 0;
+    hipError_t e = prepare_kernel(route_gateup_b1_kernel<WT, NCH>, lds, &n);
+    if (e != hipSuccess) return e;
+    blocks_per_cu = n;
+    checked_lds = lds;
+  }
+  // the routing workgroups wait for one another: they must fit on the device together
+  if (long(n_route) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
+  const GateupSplit split = beside_routing_split(NCH, a, act.n, sizeof(WT), n_route, blocks_per_cu);
+  hipLaunchKernelGGL((route_gateup_b1_kernel<WT, NCH>), dim3(n_route + split.blocks * act.n), dim3(kBlock), lds, st, ra,
+                     a, act, n_route, split.blocks, split.rpw);
+  return hipGetLastError();
+}
+
+template <typename WT>
+hipError_t launch_route_gateup_b1_t(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
+  const int need = (a.H + kWave * Packed<WT>::N - 1) / (kWave * Packed<WT>::N);
+  if (need <= 1) return launch_route_gateup_b1_n<WT, 1>(ra, a, act, st);
+  if (need <= 2) return launch_route_gateup_b1_n<WT, 2>(ra, a, act, st);
+  if (need <= 4) return launch_route_gateup_b1_n<WT, 4>(ra, a, act, st);
+  if (need <= 6) return launch_route_gateup_b1_n<WT, 6>(ra, a, act, st);
+  if (need <= 8) return launch_route_gateup_b1_n<WT, 8>(ra, a, act, st);
+  return hipErrorInvalidValue;
+}
+
 }  // namespace
+
+// Rows of up to 8 chunks per lane: beyond, the LDS that the routing needs would leave the gate/up workgroups too few
+// places.
+bool route_gateup_b1_supported(int H, int dtype) { return H <= kWave * 8 * (dtype == 1 ? 8 : 4); }
+
+hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,
+                                  hipStream_t st) {
+  return dtype == 1 ? launch_route_gateup_b1_t<uint16_t>(ra, a, act, st) : launch_route_gateup_b1_t<float>(ra, a, act, st);
+}
 
 // H up to 64 * 4 * 8 chunks of 16 bytes per row (8192 columns of either dtype).
 bool route_pair_supported(int H, int dtype) {

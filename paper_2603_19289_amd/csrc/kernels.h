@@ -115,6 +115,9 @@ struct ExpertArgs {
   float *h;                   // [B,k,I] SwiGLU products
   float *y;                   // [B,k,H] un-gated expert outputs
   float *out;                 // [B,H]
+  const float *r;             // [H] and
+  const float *gain;          // [H]: the residual of a batch of one and its norm's gain, where s_l is formed beside the
+  float eps;                  // routing (launch_route_gateup_b1)
   int B, k, H, I, bf16, E;
   // matrix-core kernels over more than one decode batch (prefill): positions grouped by expert as
   // written by launch_expert_lists for list_tokens tokens; null: the [B,k] table exec_ids is searched
@@ -122,6 +125,12 @@ struct ExpertArgs {
   const int32_t *pos_count;   // [E]
   int list_stride, list_tokens;   // E is read with them: positions per expert on average
 };
+
+// A batch of one whose executed experts are known before the layer's routing and are resident: the routing of the layer
+// (and the prediction) and the gate/up launch side by side in one launch; `act` in execution-position order.
+bool route_gateup_b1_supported(int H, int dtype);
+hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,
+                                  hipStream_t st);
 
 // Host-to-device gather copy: each entry moves one expert block from the pinned pool to a slot.
 constexpr int kCopyListMax = 32;

@@ -355,6 +355,13 @@ struct moe_spec_ctx {
     done_recorded[layer] = 0;                    // every queue waits below: later copies are behind it as well
     return copy_queues_wait(done[layer]);
   }
+  // Whether every copy into the layer's pool has ended: nothing is left to wait for then.
+  bool copies_landed(int layer) {
+    if (!ready_pending[layer]) return true;
+    if (hipEventQuery(ready[layer]) != hipSuccess) { (void)hipGetLastError(); return false; }   // "not ready" is no failure
+    ready_pending[layer] = 0;
+    return true;
+  }
   // The compute stream goes behind the copies into the layer's pool, if there were any since it last did.
   hipError_t compute_behind_copies(int layer) {
     if (!ready_pending[layer]) return hipSuccess;
@@ -740,6 +747,34 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   if (look2 && !c->router_w[layer + 2]) return c->fail(MOE_SPEC_ESTATE, "resident tables of layer %d were never set", layer + 2);
   const bool score_look = cfg.lookahead == 2 && !c->look_ids[layer % 3].empty();
   const bool true_ids_to_host = !exec_pred || score_look;
+
+  ExpertArgs xa{};
+  xa.pool = c->pool_base(layer);
+  xa.slot_bytes = c->slot_stride;
+  xa.s = c->at<float>(c->lay.s_buf);
+  xa.h = c->at<float>(c->lay.h);
+  xa.y = c->at<float>(c->lay.y);
+  xa.out = static_cast<float *>(out_dev);
+  xa.r = static_cast<const float *>(r_dev);
+  xa.gain = static_cast<const float *>(c->gain[layer]);
+  xa.eps = cfg.rms_eps;
+  xa.B = batch; xa.k = k; xa.H = H; xa.I = I;
+  xa.bf16 = cfg.dtype == MOE_SPEC_BF16;
+  const bool fast_b1 = batch == 1 && b1_supported(H, cfg.dtype) && !cfg.accumulate_defaults;
+  const bool use_mfma = cfg.dtype == MOE_SPEC_BF16 && batch >= kMfmaMinBatch;
+  ActiveList by_pos{};                          // batch 1: the slots in position order (the k experts are one cache wave)
+  auto slots_by_position = [&](const std::vector<int> &ids) {
+    by_pos.n = k;
+    for (int j = 0; j < k; ++j) {
+      by_pos.expert[j] = int16_t(ids[j]);
+      by_pos.slot[j] = int16_t(c->pools[layer].where[ids[j]]);
+    }
+  };
+  // Predicted experts that are all in their slots by now do not wait for this layer's routing: their gate/up
+  // projection goes into the same launch.  While a copy is still on its way the routing goes first, alone: the next
+  // layer's copies hang on it.  (profile = 1 brackets routing and experts separately.)
+  const bool beside_routing = fast_b1 && exec_pred && fused_route && !cfg.profile &&
+                              route_gateup_b1_supported(H, cfg.dtype) && c->copies_landed(layer);
   if (fused_route) {
     RoutePairArgs pa{};
     pa.r = static_cast<const float *>(r_dev);
@@ -778,7 +813,14 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     pa.bf16 = cfg.dtype == MOE_SPEC_BF16;
     pa.from_normalized = cfg.q_from_normalized;
     pa.spin_limit = c->spin_limit;
-    if ((e = launch_route_pair(pa, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "routing kernel");
+    if (beside_routing) {
+      slots_by_position(c->pending_ids);
+      c->read_step[layer] = c->step_seq;
+      e = launch_route_gateup_b1(pa, xa, by_pos, cfg.dtype, c->compute);
+    } else {
+      e = launch_route_pair(pa, cfg.dtype, c->compute);
+    }
+    if (e != hipSuccess) return c->hip_fail(e, "routing kernel");
     c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes;
     if (do_pred) c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes + int64_t(batch) * k * H * wbytes;
     if (look2) {
@@ -962,20 +1004,8 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       return c->hip_fail(e, "copy exec gates");
   }
 
-  ExpertArgs xa{};
-  xa.pool = c->pool_base(layer);
-  xa.slot_bytes = c->slot_stride;
-  xa.s = c->at<float>(c->lay.s_buf);
   xa.exec_ids = exec_ids_dev;
   xa.exec_gates = exec_gates_dev;
-  xa.h = c->at<float>(c->lay.h);
-  xa.y = c->at<float>(c->lay.y);
-  xa.out = static_cast<float *>(out_dev);
-  xa.B = batch; xa.k = k; xa.H = H; xa.I = I;
-  xa.bf16 = cfg.dtype == MOE_SPEC_BF16;
-
-  const bool fast_b1 = batch == 1 && b1_supported(H, cfg.dtype) && !cfg.accumulate_defaults;
-  const bool use_mfma = cfg.dtype == MOE_SPEC_BF16 && batch >= kMfmaMinBatch;
 
   // --- cache waves: make resident (unless prefetched), wait, run
   // profile = 1: every cache wave's wait for its copies is a stall span, its kernels a compute span
@@ -999,14 +1029,10 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     TimedSpan *sp_exec = c->open_span(0, c->compute);
     TimedSpan *sp_gu = c->open_span(3, c->compute);
     if (fast_b1) {
-      // batch 1: the k executed experts are one wave; hand the kernels the slots in position order
-      ActiveList by_pos{};
-      by_pos.n = k;
-      for (int j = 0; j < k; ++j) {
-        by_pos.expert[j] = int16_t(exec_ids_host[j]);
-        by_pos.slot[j] = int16_t(c->pools[layer].where[exec_ids_host[j]]);
+      if (!beside_routing) {
+        slots_by_position(exec_ids_host);
+        if ((e = launch_gateup_b1(xa, by_pos, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");
       }
-      if ((e = launch_gateup_b1(xa, by_pos, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");
       if ((e = launch_down_combine_b1(xa, by_pos, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "down kernel");
       c->close_span(sp_gu, c->compute);
     } else if (use_mfma) {

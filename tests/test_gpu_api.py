@@ -428,3 +428,40 @@ def test_random_call_sequences_leave_a_working_context():
         finally:
             eng.close()
             ref.close()
+
+
+@pytest.mark.parametrize("dtype,hidden,inter,experts,top_k", [
+    ("bf16", 8, 8, 1, 1), ("f32", 264, 72, 6, 2), ("bf16", 520, 200, 9, 3), ("bf16", 2048, 1056, 9, 8),
+    ("bf16", 2056, 40, 200, 16), ("f32", 2048, 24, 70, 5), ("bf16", 4096, 16, 256, 4), ("bf16", 4104, 16, 12, 3)])
+def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inter, experts, top_k):
+    """Predicted experts that are in their slots share a launch with the routing; with profile = 1 the two are always
+    separate launches.  Same ids, same output bits, whichever ran, at every chunk count of the rows (and one beyond
+    what the shared launch takes); waiting after every step lets the copies land, so that the first engine takes
+    the shared launch wherever it may."""
+    from paper_2603_19289_amd import moe_spec as M
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(name="beside", n_layers=3, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype=dtype,
+                        tokens=2, slots=experts, seed=41)
+    print(f"[case] beside routing H={hidden} I={inter} E={experts} k={top_k} {dtype}", flush=True)
+    res, ex, _ = build(wl, "random")
+    x0, eps = W.make_inputs(wl)
+    got = []
+    for profile in (0, 1):
+        eng = engine_for(wl, M.MODE_SPECULATIVE, res, ex, profile=profile)
+        log = []
+        try:
+            for t in range(wl.tokens):
+                eng.begin_token()
+                for l in range(wl.n_layers):
+                    r = torch.from_numpy(x0[t] + 0.3 * eps[t, l]).cuda()
+                    out, ids = eng.layer_step(l, r, want_ids=True)
+                    torch.cuda.synchronize()
+                    log.append([out.cpu()] + [ids[n].cpu() for n in ("true_ids", "exec_ids", "next_ids")])
+            stats = {n: eng.stats()[n] for n in ("hits", "predictions", "cache_hits", "cache_misses", "hbm_bytes_algorithmic")}
+        finally:
+            eng.close()
+        got.append((log, stats))
+    assert got[0][1] == got[1][1]
+    for step, (a, b) in enumerate(zip(got[0][0], got[1][0])):
+        for x, y in zip(a, b):
+            assert torch.equal(x.view(torch.int32), y.view(torch.int32)), step
