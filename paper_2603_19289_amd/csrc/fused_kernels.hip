@@ -171,7 +171,9 @@ __device__ __forceinline__ double select_gates(int k, SelectShared &sel, int tid
 // top-k, the default-vector sum), so that nothing but the 8-byte logits crosses between workgroups.
 // Workgroup 0 of a token finishes the prediction; the last one reports the true routing, off the path
 // that the prediction waits on.
-template <typename WT, int SPLIT, int NCH, int ROWS>
+// PROJ: the estimator's projection takes the place of the prediction (a kernel of its own: the other path measures 3 %
+// slower with the branch in it).
+template <typename WT, int SPLIT, int NCH, int ROWS, bool PROJ>
 __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const int wg, const int n_wg, const int b,
                                                 const int n_tokens, double *vec_lds, RouteShared &sh) {
   static_assert(ROWS == 1 || SPLIT == 1, "several rows per wavefront only with one wavefront per row");
@@ -190,7 +192,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
   const int G = H / VN;                        // column groups (H is a multiple of 8)
 #define V(c, x) vec_lds[(x) * G + (c) / VN]
   const int row = wg * RPW + wave / SPLIT * ROWS, part = wave % SPLIT;   // this wavefront's (first) row
-  const bool pred = a.w_next != nullptr;
+  const bool pred = PROJ || a.w_next != nullptr;
   const WT *wt = static_cast<const WT *>(a.w_true);
   const WT *wn = static_cast<const WT *>(a.w_next);
   const float *rrow = a.r + size_t(b) * H;
@@ -215,7 +217,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
     for (int ch = 0; ch < NCH; ++ch) {
       const int c = ((ch * SPLIT + part) * kWave + lane) * VN;
       rt[ch] = *reinterpret_cast<const Raw *>(wt + size_t(row) * H + (c < H ? c : 0));
-      if (pred) rn[ch] = *reinterpret_cast<const Raw *>(wn + size_t(row) * H + (c < H ? c : 0));
+      if (!PROJ && pred) rn[ch] = *reinterpret_cast<const Raw *>(wn + size_t(row) * H + (c < H ? c : 0));
     }
   }
   // re-arm the whole set of slots the next launch will use (last read by the previous launch, which has
@@ -445,6 +447,52 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
     __syncthreads();
   }
   STAGE(7);
+  if constexpr (PROJ) {
+    // One wavefront per row of the projection, the wavefronts of the token's workgroups taking rows in turn; four
+    // chunks of a row per step, the next step's on their way meanwhile.  The products take q_l as float, as it is
+    // handed on wherever it is stored.  q_l is here anyway: a launch of its own for it (a whole second routing,
+    // 14.7 us for 4 tokens of 128 experts) and one for this product (7.4 us) against 9 us more in this one.
+    const WT *proj = static_cast<const WT *>(a.proj);
+    const int steps = (H + 4 * kWave * VN - 1) / (4 * kWave * VN), stride = n_wg * kWaves;
+    const int first = wg * kWaves + wave, mine = first < a.proj_rows ? (a.proj_rows - 1 - first) / stride + 1 : 0;
+    auto fetch = [&](int i, Raw (&dst)[4]) {   // step i of this wavefront's list of rows x steps
+      const WT *src = proj + size_t(first + i / steps * stride) * H;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = ((i % steps * 4 + u) * kWave + lane) * VN;
+        dst[u] = *reinterpret_cast<const Raw *>(src + (c < H ? c : 0));
+      }
+    };
+    Raw cur[4], next[4];
+    if (mine > 0) fetch(0, cur);
+    double acc = 0.0;
+    for (int i = 0; i < mine * steps; ++i) {
+      if (i + 1 < mine * steps) fetch(i + 1, next);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = ((i % steps * 4 + u) * kWave + lane) * VN;
+        if (c < H) {
+          float wf[VN];
+          P::unpack(cur[u], wf);
+#pragma unroll
+          for (int x = 0; x < VN; ++x) acc += double(wf[x]) * double(float(V(c, x)));
+        }
+      }
+      if (i % steps == steps - 1) {
+        const double sum = wave_sum(acc);
+        const int r = first + i / steps * stride;
+        if (lane == 0) {
+          float add[VN];
+          load_chunk<WT>(static_cast<const WT *>(a.proj_add) + r / VN * VN, add);
+          a.proj_out[size_t(b) * a.proj_rows + r] = sum + double(add[r % VN]);
+        }
+        acc = 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cur[u] = next[u];
+    }
+    return;
+  }
   publish_rows(rn, wn, a.z_pred);
   STAGE(8);
   if (wg != 0) return;
@@ -467,11 +515,11 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
 #undef V
 }
 
-template <typename WT, int SPLIT, int NCH, int ROWS>
+template <typename WT, int SPLIT, int NCH, int ROWS, bool PROJ>
 __global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs a) {
   extern __shared__ double vec_lds[];
   __shared__ RouteShared sh;
-  route_pair_body<WT, SPLIT, NCH, ROWS>(a, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, vec_lds, sh);
+  route_pair_body<WT, SPLIT, NCH, ROWS, PROJ>(a, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, vec_lds, sh);
 }
 
 // The routing of a layer and the gate/up projection of its experts, which were predicted one layer earlier, in one
@@ -484,7 +532,7 @@ void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const Ac
   extern __shared__ double vec_lds[];
   __shared__ RouteShared sh;
   if (int(blockIdx.x) < n_route) {
-    route_pair_body<WT, kWaves, (NCH + 3) / 4, 1>(ra, blockIdx.x, n_route, 0, 1, vec_lds, sh);
+    route_pair_body<WT, kWaves, (NCH + 3) / 4, 1, false>(ra, blockIdx.x, n_route, 0, 1, vec_lds, sh);
     return;
   }
   const int i = blockIdx.x - n_route;
@@ -510,8 +558,8 @@ hipError_t prepare_kernel(K kernel, size_t lds, int *blocks_per_cu) {
   return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, kernel, kBlock, lds);
 }
 
-template <typename WT, int SPLIT, int NCH, int ROWS>
-hipError_t launch_route_pair_n(const RoutePairArgs &a, hipStream_t st) {
+template <typename WT, int SPLIT, int NCH, int ROWS, bool PROJ>
+hipError_t launch_route_pair_p(const RoutePairArgs &a, hipStream_t st) {
   constexpr int RPW = kWaves / SPLIT * ROWS;
   const size_t lds = size_t(a.H) * sizeof(double);
   const int n_wg = (a.E + RPW - 1) / RPW;
@@ -519,15 +567,21 @@ hipError_t launch_route_pair_n(const RoutePairArgs &a, hipStream_t st) {
   static size_t checked_lds = 0;
   if (blocks_per_cu < 0 || lds > checked_lds) {
     int n = 0;
-    hipError_t e = prepare_kernel(route_pair_kernel<WT, SPLIT, NCH, ROWS>, lds, &n);
+    hipError_t e = prepare_kernel(route_pair_kernel<WT, SPLIT, NCH, ROWS, PROJ>, lds, &n);
     if (e != hipSuccess) return e;
     blocks_per_cu = n;
     checked_lds = lds;
   }
   // the workgroups of a token wait for one another: they must fit on the device together
   if (long(n_wg) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
-  hipLaunchKernelGGL((route_pair_kernel<WT, SPLIT, NCH, ROWS>), dim3(n_wg, a.B), dim3(kBlock), lds, st, a);
+  hipLaunchKernelGGL((route_pair_kernel<WT, SPLIT, NCH, ROWS, PROJ>), dim3(n_wg, a.B), dim3(kBlock), lds, st, a);
   return hipGetLastError();
+}
+
+template <typename WT, int SPLIT, int NCH, int ROWS>
+hipError_t launch_route_pair_n(const RoutePairArgs &a, hipStream_t st) {
+  return a.proj ? launch_route_pair_p<WT, SPLIT, NCH, ROWS, true>(a, st)
+                : launch_route_pair_p<WT, SPLIT, NCH, ROWS, false>(a, st);
 }
 
 template <typename WT, int SPLIT, int ROWS>

@@ -76,6 +76,12 @@ struct RoutePairArgs {
   const void *w_true, *w_next;            // [E,H] routers of layers l and l+1; w_next null: no prediction
   const float *gain_true, *gain_next;     // [H] gains of LN_l and LN_{l+1}
   const void *dvec;                       // [E,H] default vectors d_{l,e}
+  // instead of the prediction (w_next null): the estimator's first step on the quasi-hidden vector,
+  // proj_out = proj q_l + proj_add, with gain_next and dvec as above; or null
+  const void *proj;                       // [proj_rows,H]
+  const void *proj_add;                   // [proj_rows]
+  double *proj_out;                       // [B,proj_rows]
+  int proj_rows;
   unsigned long long *z_true, *z_pred;    // [B,E] logit slots of this launch, armed
   unsigned long long *z_true_next, *z_pred_next;   // the other set, armed by this launch
   int arm_count;                          // slots per set (largest batch * E)

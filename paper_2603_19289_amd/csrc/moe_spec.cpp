@@ -870,6 +870,8 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   ra.eps = cfg.rms_eps;
   ra.bf16 = cfg.dtype == MOE_SPEC_BF16;
   ra.spec = 0;
+  // the estimator's input and first step ride along with the true routing
+  const bool est_beside = use_est && !cfg.diagnostics && route_pair_supported(H, cfg.dtype) && cfg.predict_signal == 0;
   if (!cfg.diagnostics && route_pair_supported(H, cfg.dtype)) {
     // the fused kernel, asked for the true routing only (it is the faster of the two at that); the prediction
     // below comes from the estimator or the baseline signal and keeps its own launches
@@ -898,6 +900,15 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     ta.eps = cfg.rms_eps;
     ta.bf16 = ra.bf16;
     ta.spin_limit = c->spin_limit;
+    if (est_beside) {
+      ta.gain_next = static_cast<const float *>(c->gain[layer + 1]);
+      ta.dvec = c->dvecs[layer];
+      ta.from_normalized = cfg.q_from_normalized;
+      ta.proj = c->est.proj;
+      ta.proj_add = static_cast<const char *>(c->est.layer_emb) + size_t(layer) * cfg.est_latent * wbytes;
+      ta.proj_out = c->at<double>(c->lay.est_u);
+      ta.proj_rows = cfg.est_latent;
+    }
     if ((e = launch_route_pair(ta, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "routing kernel");
   } else {
     c->prep_route(ra);
@@ -930,20 +941,22 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     if (use_est) {
       // The routing launch only produces the predicting signal; the estimator's four steps turn it
       // into logits, and its last step (the routing kernel in LayerNorm mode) selects and hands over.
-      RouteArgs sa = pa;
-      sa.vec_out = c->at<float>(c->lay.sig);
-      sa.user_ids = nullptr;
-      sa.user_gates = nullptr;
-      sa.mailbox = nullptr;
-      c->prep_route(sa);
-      if ((e = launch_route(sa, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "signal kernel");
       const int dm = cfg.est_latent, F = cfg.est_ffn;
       GemvArgs g{};
-      g.B = batch;
-      g.w = c->est.proj; g.x_f32 = c->at<float>(c->lay.sig); g.rows = dm; g.cols = H;
-      g.add_w = static_cast<const char *>(c->est.layer_emb) + size_t(layer) * dm * wbytes;
-      g.y = c->at<double>(c->lay.est_u);
-      if ((e = launch_gemv64(g, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "estimator projection");
+      if (!est_beside) {
+        RouteArgs sa = pa;
+        sa.vec_out = c->at<float>(c->lay.sig);
+        sa.user_ids = nullptr;
+        sa.user_gates = nullptr;
+        sa.mailbox = nullptr;
+        c->prep_route(sa);
+        if ((e = launch_route(sa, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "signal kernel");
+        g.B = batch;
+        g.w = c->est.proj; g.x_f32 = c->at<float>(c->lay.sig); g.rows = dm; g.cols = H;
+        g.add_w = static_cast<const char *>(c->est.layer_emb) + size_t(layer) * dm * wbytes;
+        g.y = c->at<double>(c->lay.est_u);
+        if ((e = launch_gemv64(g, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "estimator projection");
+      }
       g = GemvArgs{};
       g.B = batch;
       g.w = c->est.ffn_in; g.x_f64 = c->at<double>(c->lay.est_u); g.rows = F; g.cols = dm; g.silu = 1;

@@ -172,6 +172,20 @@ def test_estimator_predictions(layers, dtype, B):
                        estimator=est, estimator_layers=use)
 
 
+@pytest.mark.parametrize("dtype,B,hidden,experts,m", [
+    ("bf16", 1, 2056, 3, 1),      # two steps per row, more rows than wavefronts; four wavefronts per router row
+    ("f32", 2, 1032, 5, 1),       # the same for float32 chunks, one workgroup and a second that is nearly empty
+    ("bf16", 33, 72, 40, 9),      # latent size 8: most wavefronts have no row
+    ("bf16", 64, 256, 200, 4)])   # several router rows per wavefront
+def test_estimator_projection_beside_the_routing(dtype, B, hidden, experts, m):
+    # the launch that routes a layer also forms the quasi-hidden vector and projects it for the estimator
+    wl = small_workload(name="estimator_rows", n_layers=3, hidden=hidden, n_experts=experts, top_k=2, inter=24,
+                        dtype=dtype, batch=B, tokens=2, slots=experts, seed=53)
+    est = W.make_estimator(wl, m=m, n=2)
+    run_teacher_forced(wl, O.MODE_SPECULATIVE, oracle_kw=dict(estimator=O.Estimator(**est), estimator_layers=[0, 1, 2]),
+                       estimator=est, estimator_layers=[0, 1, 2])
+
+
 @pytest.mark.parametrize("mode", ["speculative", "prefetch_hint"])
 @pytest.mark.parametrize("dtype,B,S,engine", [("bf16", 1, 4, "COPY_DMA2"), ("f32", 3, 5, "COPY_KERNEL"), ("bf16", 20, 6, "COPY_DMA"),
                                              ("bf16", 1, 3, "COPY_DMA2")])
