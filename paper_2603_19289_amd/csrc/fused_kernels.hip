@@ -15,6 +15,7 @@
 // launcher checks to fit on the device together (groups are dispatched in order, so the earliest
 // unfinished group always gets the next free compute units).
 #include "device_utils.h"
+#include "expert_mfma.h"
 #include "gateup_b1.h"
 #include "kernels.h"
 
@@ -164,6 +165,121 @@ __device__ __forceinline__ double select_gates(int k, SelectShared &sel, int tid
   return denom;
 }
 
+// Products of rows first, first + stride, ... of mat [n_rows,H] with the vector in LDS (laid out as in route_pair_body)
+// by one wavefront: sink(row, sum) in every lane.  Four chunks of two rows per step, the next step's on their way
+// meanwhile.  AS_FLOAT: the products take the vector's values as float, as it is handed on wherever it is stored.
+template <typename WT, bool AS_FLOAT, typename Sink>
+__device__ __forceinline__ void rows_dot(const WT *mat, int n_rows, int H, int first, int stride, const double *vec_lds,
+                                         Sink sink) {
+  using P = Packed<WT>;
+  using Raw = typename P::Raw;
+  constexpr int VN = P::N;
+  const int lane = threadIdx.x & (kWave - 1), G = H / VN;
+  const int steps = (H + 4 * kWave * VN - 1) / (4 * kWave * VN);
+  const int mine = first < n_rows ? (n_rows - 1 - first) / stride + 1 : 0;
+  const int total = (mine + 1) / 2 * steps;
+  auto fetch = [&](int i, Raw (&dst)[2][4]) {  // step i of this wavefront's list of row pairs x steps
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {              // an odd last row is read twice
+      const WT *src = mat + size_t(first + min(i / steps * 2 + p, mine - 1) * stride) * H;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int c = ((i % steps * 4 + u) * kWave + lane) * VN;
+        dst[p][u] = *reinterpret_cast<const Raw *>(src + (c < H ? c : 0));
+      }
+    }
+  };
+  Raw cur[2][4], next[2][4];
+  if (mine > 0) fetch(0, cur);
+  double acc[2] = {0.0, 0.0};
+  for (int i = 0; i < total; ++i) {
+    if (i + 1 < total) fetch(i + 1, next);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = ((i % steps * 4 + u) * kWave + lane) * VN;
+      if (c < H) {
+        float w0[VN], w1[VN];
+        P::unpack(cur[0][u], w0);
+        P::unpack(cur[1][u], w1);
+#pragma unroll
+        for (int x = 0; x < VN; ++x) {
+          double v = vec_lds[x * G + c / VN];
+          if (AS_FLOAT) v = double(float(v));
+          acc[0] += double(w0[x]) * v;
+          acc[1] += double(w1[x]) * v;
+        }
+      }
+    }
+    if (i % steps == steps - 1) {
+      const int j = i / steps * 2;
+      sink(first + j * stride, wave_sum(acc[0]));
+      const double second = wave_sum(acc[1]);
+      if (j + 1 < mine) sink(first + (j + 1) * stride, second);
+      acc[0] = acc[1] = 0.0;
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cur[p][u] = next[p][u];
+  }
+}
+
+// proj_out = proj q_l + proj_add, the rows of one wavefront.
+template <typename WT>
+__device__ __forceinline__ void project_rows(const RoutePairArgs &a, int b, int first, int stride, const double *vec_lds) {
+  constexpr int VN = Packed<WT>::N;
+  const int lane = threadIdx.x & (kWave - 1);
+  rows_dot<WT, true>(static_cast<const WT *>(a.proj), a.proj_rows, a.H, first, stride, vec_lds, [&](int r, double sum) {
+    if (lane == 0) {
+      float add[VN];
+      load_chunk<WT>(static_cast<const WT *>(a.proj_add) + r / VN * VN, add);
+      a.proj_out[size_t(b) * a.proj_rows + r] = sum + double(add[r % VN]);
+    }
+  });
+}
+
+// The true routing of token b, written out by the workgroup that reports it.
+__device__ __forceinline__ void report_true(const RoutePairArgs &a, int b, SelectShared &sel, double denom, int tid) {
+  const int k = a.k;
+  if (tid < k) {
+    const int id = sel.top_i[tid];
+    const double g64 = sel.top_e[tid] / denom;
+    const float g = static_cast<float>(g64);
+    const size_t o = size_t(b) * k + tid;
+    if (a.mb_true) a.mb_true->ids[o] = id;     // the host waits for every word it armed
+    a.true_ids[o] = id;
+    a.true_gates[o] = g;
+    if (a.true_gates64) a.true_gates64[o] = g64;
+    if (a.user_true_ids) a.user_true_ids[o] = id;
+    if (a.user_true_gates) a.user_true_gates[o] = g;
+    if (a.cmp_ids) {                           // recall@k of the prediction made one layer earlier (Sec. 3.3)
+      int hit = 0;
+      for (int j = 0; j < k; ++j) hit |= (a.cmp_ids[size_t(b) * k + j] == id);
+      if (hit) atomicAdd(&sel.hits, 1);
+    }
+  }
+  if (a.cmp_ids) {
+    __syncthreads();
+    if (tid == 0) {
+      atomicAdd(&a.diag->hits, static_cast<unsigned long long>(sel.hits));
+      atomicAdd(&a.diag->preds, static_cast<unsigned long long>(k));
+    }
+  }
+}
+
+// The prediction of token b, written out (its ids went to the host when they were selected).
+__device__ __forceinline__ void report_next(const RoutePairArgs &a, int b, SelectShared &sel, double denom, int tid) {
+  if (tid < a.k) {
+    const int id = sel.top_i[tid];
+    const float g = static_cast<float>(sel.top_e[tid] / denom);
+    const size_t o = size_t(b) * a.k + tid;
+    a.next_ids[o] = id;
+    a.next_gates[o] = g;
+    if (a.user_next_ids) a.user_next_ids[o] = id;
+    if (a.user_next_gates) a.user_next_gates[o] = g;
+  }
+}
+
 // SPLIT wavefronts share one router row (4 / SPLIT rows per workgroup); NCH 16-byte chunks of the row
 // per lane, loaded into registers for both routers at the top of the kernel so that their latency
 // overlaps the normalisation.  b is the token; the workgroups of a token form a group that
@@ -171,7 +287,7 @@ __device__ __forceinline__ double select_gates(int k, SelectShared &sel, int tid
 // top-k, the default-vector sum), so that nothing but the 8-byte logits crosses between workgroups.
 // Workgroup 0 of a token finishes the prediction; the last one reports the true routing, off the path
 // that the prediction waits on.
-// PROJ: the estimator's projection takes the place of the prediction (a kernel of its own: the other path measures 3 %
+// PROJ: the estimator's projection takes the place of the prediction (a kernel of its own: the other path measured 3 %
 // slower with the branch in it).
 template <typename WT, int SPLIT, int NCH, int ROWS, bool PROJ>
 __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const int wg, const int n_wg, const int b,
@@ -343,32 +459,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
     }
   }
   const double denom = select_gates(k, sh.sel, tid);
-  if (wg == reporter) {
-    if (tid < k) {
-      const int id = sh.sel.top_i[tid];
-      const double g64 = sh.sel.top_e[tid] / denom;
-      const float g = static_cast<float>(g64);
-      const size_t o = size_t(b) * k + tid;
-      if (a.mb_true) a.mb_true->ids[o] = id;     // the host waits for every word it armed
-      a.true_ids[o] = id;
-      a.true_gates[o] = g;
-      if (a.true_gates64) a.true_gates64[o] = g64;
-      if (a.user_true_ids) a.user_true_ids[o] = id;
-      if (a.user_true_gates) a.user_true_gates[o] = g;
-      if (a.cmp_ids) {                           // recall@k of the prediction made one layer earlier (Sec. 3.3)
-        int hit = 0;
-        for (int j = 0; j < k; ++j) hit |= (a.cmp_ids[size_t(b) * k + j] == id);
-        if (hit) atomicAdd(&sh.sel.hits, 1);
-      }
-    }
-    if (a.cmp_ids) {
-      __syncthreads();
-      if (tid == 0) {
-        atomicAdd(&a.diag->hits, static_cast<unsigned long long>(sh.sel.hits));
-        atomicAdd(&a.diag->preds, static_cast<unsigned long long>(k));
-      }
-    }
-  }
+  if (wg == reporter) report_true(a, b, sh.sel, denom, tid);
   STAGE(5);
   if (!pred) return;
 
@@ -448,49 +539,10 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
   }
   STAGE(7);
   if constexpr (PROJ) {
-    // One wavefront per row of the projection, the wavefronts of the token's workgroups taking rows in turn; four
-    // chunks of a row per step, the next step's on their way meanwhile.  The products take q_l as float, as it is
-    // handed on wherever it is stored.  q_l is here anyway: a launch of its own for it (a whole second routing,
-    // 14.7 us for 4 tokens of 128 experts) and one for this product (7.4 us) against 9 us more in this one.
-    const WT *proj = static_cast<const WT *>(a.proj);
-    const int steps = (H + 4 * kWave * VN - 1) / (4 * kWave * VN), stride = n_wg * kWaves;
-    const int first = wg * kWaves + wave, mine = first < a.proj_rows ? (a.proj_rows - 1 - first) / stride + 1 : 0;
-    auto fetch = [&](int i, Raw (&dst)[4]) {   // step i of this wavefront's list of rows x steps
-      const WT *src = proj + size_t(first + i / steps * stride) * H;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = ((i % steps * 4 + u) * kWave + lane) * VN;
-        dst[u] = *reinterpret_cast<const Raw *>(src + (c < H ? c : 0));
-      }
-    };
-    Raw cur[4], next[4];
-    if (mine > 0) fetch(0, cur);
-    double acc = 0.0;
-    for (int i = 0; i < mine * steps; ++i) {
-      if (i + 1 < mine * steps) fetch(i + 1, next);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = ((i % steps * 4 + u) * kWave + lane) * VN;
-        if (c < H) {
-          float wf[VN];
-          P::unpack(cur[u], wf);
-#pragma unroll
-          for (int x = 0; x < VN; ++x) acc += double(wf[x]) * double(float(V(c, x)));
-        }
-      }
-      if (i % steps == steps - 1) {
-        const double sum = wave_sum(acc);
-        const int r = first + i / steps * stride;
-        if (lane == 0) {
-          float add[VN];
-          load_chunk<WT>(static_cast<const WT *>(a.proj_add) + r / VN * VN, add);
-          a.proj_out[size_t(b) * a.proj_rows + r] = sum + double(add[r % VN]);
-        }
-        acc = 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) cur[u] = next[u];
-    }
+    // One wavefront per row of the projection, the wavefronts of the token's workgroups taking rows in turn.  q_l is
+    // here anyway: a launch of its own for it (a whole second routing, 14.7 us for 4 tokens of 128 experts) and one
+    // for this product (7.4 us) against 9 us more in this one.
+    project_rows<WT>(a, b, wg * kWaves + wave, n_wg * kWaves, vec_lds);
     return;
   }
   publish_rows(rn, wn, a.z_pred);
@@ -502,15 +554,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
                  a.mb_next ? a.mb_next->ids + size_t(b) * k : nullptr);                  // the host starts the prefetch on these
   const double denom_next = select_gates(k, sh.sel, tid);
   STAGE(10);
-  if (tid < k) {
-    const int id = sh.sel.top_i[tid];
-    const float g = static_cast<float>(sh.sel.top_e[tid] / denom_next);
-    const size_t o = size_t(b) * k + tid;
-    a.next_ids[o] = id;
-    a.next_gates[o] = g;
-    if (a.user_next_ids) a.user_next_ids[o] = id;
-    if (a.user_next_gates) a.user_next_gates[o] = g;
-  }
+  report_next(a, b, sh.sel, denom_next, tid);
   STAGE(11);
 #undef V
 }
@@ -520,6 +564,111 @@ __global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs 
   extern __shared__ double vec_lds[];
   __shared__ RouteShared sh;
   route_pair_body<WT, SPLIT, NCH, ROWS, PROJ>(a, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, vec_lds, sh);
+}
+
+// The same routing for a launch in which expert workgroups hide its latency: the same sums in the same order, but
+// nothing is kept in registers or asked for early, so that it does not take registers away from them (about 200 in
+// route_pair_body).  Router rows are dealt over the wavefronts of the token's n_wg workgroups, any number of them.
+template <typename WT, bool PROJ>
+__device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const int wg, const int n_wg, const int b,
+                                                const int n_tokens, double *vec_lds, RouteShared &sh) {
+  using P = Packed<WT>;
+  using Raw = typename P::Raw;
+  constexpr int VN = P::N;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int H = a.H, E = a.E, k = a.k, G = H / VN;
+#define V(c, x) vec_lds[(x) * G + (c) / VN]
+  const bool pred = PROJ || a.w_next != nullptr;
+  const float *rrow = a.r + size_t(b) * H;
+  const int c0 = tid * VN, first = wg * kWaves + wave, stride = n_wg * kWaves;
+  for (int i = (b * n_wg + wg) * kBlock + tid; i < a.arm_count; i += n_wg * n_tokens * kBlock) {
+    arm64(a.z_true_next + i);
+    arm64(a.z_pred_next + i);
+  }
+  auto finish_norm = [&](double ss, bool write) {      // V holds x * gain
+    const double tot = block_sum(ss, sh.red, lane, wave);
+    const double inv = 1.0 / sqrt(tot / double(H) + double(a.eps));
+    for (int c = c0; c < H; c += kBlock * VN) {
+#pragma unroll
+      for (int x = 0; x < VN; ++x) {
+        double n = V(c, x) * inv;
+        if (a.bf16) n = round_to_bf16_fast(n);
+        V(c, x) = n;
+      }
+      if (write) {
+#pragma unroll
+        for (int x = 0; x < VN; x += 4)
+          *reinterpret_cast<float4 *>(a.s_out + size_t(b) * H + c + x) =
+              make_float4(float(V(c, x)), float(V(c, x + 1)), float(V(c, x + 2)), float(V(c, x + 3)));
+      }
+    }
+    __syncthreads();
+  };
+  double ss = 0.0;
+  for (int c = c0; c < H; c += kBlock * VN) {
+#pragma unroll
+    for (int x = 0; x < VN; ++x) {
+      const double r = double(rrow[c + x]);
+      V(c, x) = r * double(a.gain_true[c + x]);
+      ss += r * r;
+    }
+  }
+  finish_norm(ss, wg == 0);
+  auto publish_rows = [&](const void *router, unsigned long long *slots) {
+    rows_dot<WT, false>(static_cast<const WT *>(router), E, H, first, stride, vec_lds, [&](int r, double sum) {
+      if (lane == 0) publish64(slots + size_t(b) * E + r, sum);
+    });
+  };
+  publish_rows(a.w_true, a.z_true);
+  const int reporter = n_wg - 1;
+  if (!pred && wg != reporter) return;
+
+  select_ids_any(a, 3, a.z_true + size_t(b) * E, E, k, sh.sel, tid);
+  const double denom = select_gates(k, sh.sel, tid);
+  if (wg == reporter) report_true(a, b, sh.sel, denom, tid);
+  if (!pred) return;
+
+  const WT *dv = static_cast<const WT *>(a.dvec);
+  const double inv_denom = 1.0 / denom;
+  ss = 0.0;
+  for (int c = c0; c < H; c += kBlock * VN) {
+    double d[VN];
+#pragma unroll
+    for (int x = 0; x < VN; ++x) d[x] = 0.0;
+    for (int j0 = 0; j0 < k; j0 += 4) {                // four default-vector rows in flight
+      Raw dr[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) dr[q] = *reinterpret_cast<const Raw *>(dv + size_t(sh.sel.top_i[min(j0 + q, k - 1)]) * H + c);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (j0 + q < k) {
+          const double g = sh.sel.top_e[j0 + q] * inv_denom;
+          float dvf[VN];
+          P::unpack(dr[q], dvf);
+#pragma unroll
+          for (int x = 0; x < VN; ++x) d[x] += g * double(dvf[x]);
+        }
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < VN; ++x) {
+      const double ux = (a.from_normalized ? V(c, x) : double(rrow[c + x])) + d[x];
+      V(c, x) = ux * double(a.gain_next[c + x]);
+      ss += ux * ux;
+    }
+  }
+  finish_norm(ss, false);
+  if constexpr (PROJ) {
+    project_rows<WT>(a, b, first, stride, vec_lds);
+    return;
+  }
+  publish_rows(a.w_next, a.z_pred);
+  if (wg != 0) return;
+
+  select_ids_any(a, 9, a.z_pred + size_t(b) * E, E, k, sh.sel, tid, a.mb_next ? a.mb_next->ids + size_t(b) * k : nullptr);
+  const double denom_next = select_gates(k, sh.sel, tid);
+  report_next(a, b, sh.sel, denom_next, tid);
+#undef V
 }
 
 // The routing of a layer and the gate/up projection of its experts, which were predicted one layer earlier, in one
@@ -538,6 +687,48 @@ void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const Ac
   const int i = blockIdx.x - n_route;
   float *s_lds = reinterpret_cast<float *>(vec_lds);
   gateup_b1_body<WT, NCH, true>(a, act, i / blocks, i % blocks, rpw, s_lds, sh.red);
+}
+
+// s_l = LN_l(r_l) as bf16, one workgroup per token: what the expert workgroups of the launch below read.
+template <int NG>
+__global__ __launch_bounds__(kBlock) void norm_rows_kernel(const ExpertArgs a, uint16_t *s_q) {
+  extern __shared__ float s_lds[];
+  __shared__ double red[kWaves];
+  const int tid = threadIdx.x, b = blockIdx.x;
+  ExpertArgs row = a;
+  row.r = a.r + size_t(b) * a.H;
+  InputNorm<uint16_t, NG> norm;
+  norm.load(row, tid);
+  norm.finish(row, s_lds, red, tid);
+  for (int c = tid * 8; c < a.H; c += kBlock * 8) {
+    uint32_t w[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+      w[x] = (__float_as_uint(s_lds[c + 2 * x]) >> 16) | (__float_as_uint(s_lds[c + 2 * x + 1]) & 0xffff0000u);
+    *reinterpret_cast<uint4 *>(s_q + size_t(b) * a.H + c) = make_uint4(w[0], w[1], w[2], w[3]);
+  }
+}
+
+// The routing of a layer and the matrix-core gate/up projection of its experts, predicted one layer earlier, in one
+// launch.  The first n_route workgroups route, n_wg per token (dispatched first: a token's are resident together).
+// Measured, routing + gate/up as two launches against this one and the norm before it: 8 tokens of 32 experts of
+// 2880 x 2880 16 + 124 / 4.7 + 120 us, 32 tokens of 128 experts of 768 x 2048 19 + 47 / 4.7 + 53.7 us, 4 tokens of
+// those with the estimator's projection 16.5 + 31 / 4.6 + 37 us.  One router row and two default-vector rows in flight
+// per wavefront instead of two and four: 56 us for the second.
+template <int NT, int KSPLIT, bool PROJ>
+__global__ __launch_bounds__(kBlock, NT <= 2 ? 4 : 2)
+void route_gateup_mfma_kernel(const RoutePairArgs ra, const ExpertArgs a, const ActiveList act, const uint16_t *s_q,
+                              uint16_t *hq, const int n_wg, const int n_route, const int row_blocks) {
+  extern __shared__ __align__(16) unsigned char beside_lds[];
+  if (int(blockIdx.x) < n_route) {
+    RouteShared &sh = *reinterpret_cast<RouteShared *>(beside_lds);
+    double *vec_lds = reinterpret_cast<double *>(beside_lds + (sizeof(RouteShared) + 15) / 16 * 16);
+    route_lean_body<uint16_t, PROJ>(ra, blockIdx.x % n_wg, n_wg, blockIdx.x / n_wg, n_route / n_wg, vec_lds, sh);
+    return;
+  }
+  const int i = blockIdx.x - n_route;
+  expert_mfma_body<true, NT, KSPLIT>(a, act, s_q, hq, i % row_blocks, i / row_blocks, 0,
+                                     *reinterpret_cast<ExpertMfmaShared<true, NT, KSPLIT> *>(beside_lds));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -661,6 +852,47 @@ hipError_t launch_route_gateup_b1_t(const RoutePairArgs &ra, const ExpertArgs &a
   return hipErrorInvalidValue;
 }
 
+template <int NT, int KSPLIT, bool PROJ>
+hipError_t launch_route_gateup_mfma_n(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act,
+                                      const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
+  const size_t route_lds = (sizeof(RouteShared) + 15) / 16 * 16 + size_t(ra.H) * sizeof(double);
+  const size_t lds = std::max(route_lds, sizeof(ExpertMfmaShared<true, NT, KSPLIT>));
+  static int blocks_per_cu = -1;               // per instantiation
+  static size_t checked_lds = 0;
+  if (blocks_per_cu < 0 || lds > checked_lds) {
+    int n = 0;
+    hipError_t e = prepare_kernel(route_gateup_mfma_kernel<NT, KSPLIT, PROJ>, lds, &n);
+    if (e != hipSuccess) return e;
+    blocks_per_cu = n;
+    checked_lds = lds;
+  }
+  // workgroups per token: about one per compute unit in all (half as many: 2 % slower at 32 tokens, a quarter 16 %;
+  // twice as many 1 %), at least a router row for every wavefront
+  const int n_wg = std::max(1, std::min(g_compute_units / ra.B, (ra.E + kWaves - 1) / kWaves));
+  if (long(n_wg) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
+  constexpr int rows_per_wg = 16 * kMfmaWaves / KSPLIT;
+  const int row_blocks = (a.I + rows_per_wg - 1) / rows_per_wg, n_route = n_wg * ra.B;
+  hipLaunchKernelGGL((route_gateup_mfma_kernel<NT, KSPLIT, PROJ>), dim3(n_route + row_blocks * act.n), dim3(kBlock), lds,
+                     st, ra, a, act, s_q, hq, n_wg, n_route, row_blocks);
+  return hipGetLastError();
+}
+
+template <int NT, int KSPLIT>
+hipError_t launch_route_gateup_mfma_k(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act,
+                                      const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
+  return ra.proj ? launch_route_gateup_mfma_n<NT, KSPLIT, true>(ra, a, act, s_q, hq, st)
+                 : launch_route_gateup_mfma_n<NT, KSPLIT, false>(ra, a, act, s_q, hq, st);
+}
+
+template <int NT>
+hipError_t launch_route_gateup_mfma_t(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act,
+                                      const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
+  const int ksplit = mfma_ksplit(a.H);
+  if (ksplit == 4) return launch_route_gateup_mfma_k<NT, 4>(ra, a, act, s_q, hq, st);
+  if (ksplit == 2) return launch_route_gateup_mfma_k<NT, 2>(ra, a, act, s_q, hq, st);
+  return launch_route_gateup_mfma_k<NT, 1>(ra, a, act, s_q, hq, st);
+}
+
 }  // namespace
 
 // Rows of up to 8 chunks per lane: beyond, the LDS that the routing needs would leave the gate/up workgroups too few
@@ -670,6 +902,22 @@ bool route_gateup_b1_supported(int H, int dtype) { return H <= kWave * 8 * (dtyp
 hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,
                                   hipStream_t st) {
   return dtype == 1 ? launch_route_gateup_b1_t<uint16_t>(ra, a, act, st) : launch_route_gateup_b1_t<float>(ra, a, act, st);
+}
+
+bool route_gateup_mfma_supported(int H) { return H <= 4096; }   // beyond, LDS for two workgroups per compute unit only
+
+hipError_t launch_route_gateup_mfma(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, uint16_t *s_q,
+                                    uint16_t *hq, hipStream_t st) {
+  const size_t lds = size_t(a.H) * sizeof(float);
+  if (a.H <= 2048) hipLaunchKernelGGL(norm_rows_kernel<1>, dim3(a.B), dim3(kBlock), lds, st, a, s_q);
+  else hipLaunchKernelGGL(norm_rows_kernel<2>, dim3(a.B), dim3(kBlock), lds, st, a, s_q);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  switch ((a.B + 15) / 16) {
+    case 1: return launch_route_gateup_mfma_t<1>(ra, a, act, s_q, hq, st);
+    case 2: return launch_route_gateup_mfma_t<2>(ra, a, act, s_q, hq, st);
+    case 3: return launch_route_gateup_mfma_t<3>(ra, a, act, s_q, hq, st);
+    default: return launch_route_gateup_mfma_t<4>(ra, a, act, s_q, hq, st);
+  }
 }
 
 // H up to 64 * 4 * 8 chunks of 16 bytes per row (8192 columns of either dtype).

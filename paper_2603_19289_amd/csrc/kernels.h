@@ -121,9 +121,9 @@ struct ExpertArgs {
   float *h;                   // [B,k,I] SwiGLU products
   float *y;                   // [B,k,H] un-gated expert outputs
   float *out;                 // [B,H]
-  const float *r;             // [H] and
-  const float *gain;          // [H]: the residual of a batch of one and its norm's gain, where s_l is formed beside the
-  float eps;                  // routing (launch_route_gateup_b1)
+  const float *r;             // [B,H] and
+  const float *gain;          // [H]: the residual and its norm's gain, where s_l is formed beside the routing
+  float eps;
   int B, k, H, I, bf16, E;
   // matrix-core kernels over more than one decode batch (prefill): positions grouped by expert as
   // written by launch_expert_lists for list_tokens tokens; null: the [B,k] table exec_ids is searched
@@ -137,6 +137,11 @@ struct ExpertArgs {
 bool route_gateup_b1_supported(int H, int dtype);
 hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,
                                   hipStream_t st);
+
+// The same for bf16 batches on the matrix cores (s_q, hq as for launch_gateup_mfma, s_q written here); `act` as there.
+bool route_gateup_mfma_supported(int H);
+hipError_t launch_route_gateup_mfma(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, uint16_t *s_q,
+                                    uint16_t *hq, hipStream_t st);
 
 // Host-to-device gather copy: each entry moves one expert block from the pinned pool to a slot.
 constexpr int kCopyListMax = 32;

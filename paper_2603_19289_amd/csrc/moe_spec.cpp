@@ -773,8 +773,24 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   // Predicted experts that are all in their slots by now do not wait for this layer's routing: their gate/up
   // projection goes into the same launch.  While a copy is still on its way the routing goes first, alone: the next
   // layer's copies hang on it.  (profile = 1 brackets routing and experts separately.)
-  const bool beside_routing = fast_b1 && exec_pred && fused_route && !cfg.profile &&
-                              route_gateup_b1_supported(H, cfg.dtype) && c->copies_landed(layer);
+  const bool est_beside = use_est && !cfg.diagnostics && route_pair_supported(H, cfg.dtype) && cfg.predict_signal == 0;
+  const bool beside_routing =
+      exec_pred && !cfg.profile && c->pending_union.size() <= size_t(S) &&
+      ((fast_b1 && fused_route && route_gateup_b1_supported(H, cfg.dtype)) ||
+       (use_mfma && (fused_route || est_beside) && route_gateup_mfma_supported(H))) && c->copies_landed(layer);
+  // The layer's first routing launch, with or without the experts beside it.
+  auto launch_first_routing = [&](RoutePairArgs &ra) {
+    if (!beside_routing) return launch_route_pair(ra, cfg.dtype, c->compute);
+    c->read_step[layer] = c->step_seq;
+    if (fast_b1) {
+      slots_by_position(c->pending_ids);
+      return launch_route_gateup_b1(ra, xa, by_pos, cfg.dtype, c->compute);
+    }
+    ra.s_out_q = nullptr;                       // written for the expert workgroups before the launch
+    xa.exec_ids = c->at<int32_t>(c->lay.pend_ids[layer & 1]);
+    return launch_route_gateup_mfma(ra, xa, c->pending_wave0, c->at<uint16_t>(c->lay.s_q), c->at<uint16_t>(c->lay.h),
+                                    c->compute);
+  };
   if (fused_route) {
     RoutePairArgs pa{};
     pa.r = static_cast<const float *>(r_dev);
@@ -813,14 +829,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     pa.bf16 = cfg.dtype == MOE_SPEC_BF16;
     pa.from_normalized = cfg.q_from_normalized;
     pa.spin_limit = c->spin_limit;
-    if (beside_routing) {
-      slots_by_position(c->pending_ids);
-      c->read_step[layer] = c->step_seq;
-      e = launch_route_gateup_b1(pa, xa, by_pos, cfg.dtype, c->compute);
-    } else {
-      e = launch_route_pair(pa, cfg.dtype, c->compute);
-    }
-    if (e != hipSuccess) return c->hip_fail(e, "routing kernel");
+    if ((e = launch_first_routing(pa)) != hipSuccess) return c->hip_fail(e, "routing kernel");
     c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes;
     if (do_pred) c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes + int64_t(batch) * k * H * wbytes;
     if (look2) {
@@ -870,8 +879,6 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   ra.eps = cfg.rms_eps;
   ra.bf16 = cfg.dtype == MOE_SPEC_BF16;
   ra.spec = 0;
-  // the estimator's input and first step ride along with the true routing
-  const bool est_beside = use_est && !cfg.diagnostics && route_pair_supported(H, cfg.dtype) && cfg.predict_signal == 0;
   if (!cfg.diagnostics && route_pair_supported(H, cfg.dtype)) {
     // the fused kernel, asked for the true routing only (it is the faster of the two at that); the prediction
     // below comes from the estimator or the baseline signal and keeps its own launches
@@ -900,7 +907,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     ta.eps = cfg.rms_eps;
     ta.bf16 = ra.bf16;
     ta.spin_limit = c->spin_limit;
-    if (est_beside) {
+    if (est_beside) {                           // the estimator's input and first step ride along
       ta.gain_next = static_cast<const float *>(c->gain[layer + 1]);
       ta.dvec = c->dvecs[layer];
       ta.from_normalized = cfg.q_from_normalized;
@@ -909,7 +916,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       ta.proj_out = c->at<double>(c->lay.est_u);
       ta.proj_rows = cfg.est_latent;
     }
-    if ((e = launch_route_pair(ta, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "routing kernel");
+    if ((e = launch_first_routing(ta)) != hipSuccess) return c->hip_fail(e, "routing kernel");
   } else {
     c->prep_route(ra);
     if ((e = launch_route(ra, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "routing kernel");
@@ -1050,7 +1057,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       c->close_span(sp_gu, c->compute);
     } else if (use_mfma) {
       uint16_t *hq = c->at<uint16_t>(c->lay.h);
-      if ((e = launch_gateup_mfma(xa, act, c->at<uint16_t>(c->lay.s_q), hq, c->compute)) != hipSuccess)
+      if (!beside_routing && (e = launch_gateup_mfma(xa, act, c->at<uint16_t>(c->lay.s_q), hq, c->compute)) != hipSuccess)
         return c->hip_fail(e, "gate/up MFMA kernel");
       if ((e = launch_down_mfma(xa, act, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");
       c->close_span(sp_gu, c->compute);

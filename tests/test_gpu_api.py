@@ -430,19 +430,21 @@ def test_random_call_sequences_leave_a_working_context():
             ref.close()
 
 
-@pytest.mark.parametrize("dtype,hidden,inter,experts,top_k", [
-    ("bf16", 8, 8, 1, 1), ("f32", 264, 72, 6, 2), ("bf16", 520, 200, 9, 3), ("bf16", 2048, 1056, 9, 8),
-    ("bf16", 2056, 40, 200, 16), ("f32", 2048, 24, 70, 5), ("bf16", 4096, 16, 256, 4), ("bf16", 4104, 16, 12, 3)])
-def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inter, experts, top_k):
+@pytest.mark.parametrize("dtype,hidden,inter,experts,top_k,batch", [
+    ("bf16", 8, 8, 1, 1, 1), ("f32", 264, 72, 6, 2, 1), ("bf16", 520, 200, 9, 3, 1), ("bf16", 2048, 1056, 9, 8, 1),
+    ("bf16", 2056, 40, 200, 16, 1), ("f32", 2048, 24, 70, 5, 1), ("bf16", 4096, 16, 256, 4, 1), ("bf16", 4104, 16, 12, 3, 1),
+    ("bf16", 8, 8, 1, 1, 2), ("bf16", 264, 72, 6, 2, 3), ("bf16", 1032, 200, 9, 3, 17), ("bf16", 2056, 40, 70, 5, 40),
+    ("bf16", 4096, 16, 256, 16, 64), ("bf16", 4104, 16, 12, 3, 5)])
+def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inter, experts, top_k, batch):
     """Predicted experts that are in their slots share a launch with the routing; with profile = 1 the two are always
-    separate launches.  Same ids, same output bits, whichever ran, at every chunk count of the rows (and one beyond
-    what the shared launch takes); waiting after every step lets the copies land, so that the first engine takes
+    separate launches.  Same ids, same output bits, whichever ran, at every chunk count of the rows, every count of
+    token tiles (and sizes beyond what the shared launches take); waiting after every step lets the copies land, so that the first engine takes
     the shared launch wherever it may."""
     from paper_2603_19289_amd import moe_spec as M
     from paper_2603_19289_amd.engine import engine_for
     wl = small_workload(name="beside", n_layers=3, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype=dtype,
-                        tokens=2, slots=experts, seed=41)
-    print(f"[case] beside routing H={hidden} I={inter} E={experts} k={top_k} {dtype}", flush=True)
+                        batch=batch, tokens=2, slots=experts, seed=41)
+    print(f"[case] beside routing H={hidden} I={inter} E={experts} k={top_k} B={batch} {dtype}", flush=True)
     res, ex, _ = build(wl, "random")
     x0, eps = W.make_inputs(wl)
     got = []
