@@ -577,6 +577,11 @@ void launch_down_combine_b1(const ExpertArgs &a, const ActiveList &act, hipStrea
   else launch_down_combine_b1_n<WT, 4, 4>(a, act, st);
 }
 
+// Tiles of 16 positions that an expert may need in one launch (or one plane of 64).
+int mfma_token_tiles(const ExpertArgs &a) {
+  return ((a.pos_list ? std::min(a.list_tokens, kMaxBatch) : a.B) + 15) / 16;
+}
+
 template <bool GATEUP, int KSPLIT>
 hipError_t launch_expert_mfma_k(const ExpertArgs &a, const ActiveList &act, const uint16_t *act_q, uint16_t *hq,
                                 hipStream_t st) {
@@ -584,8 +589,7 @@ hipError_t launch_expert_mfma_k(const ExpertArgs &a, const ActiveList &act, cons
   const int rows_per_wg = 16 * kWaves / KSPLIT;
   const int planes = a.pos_list ? (a.list_tokens + kMaxBatch - 1) / kMaxBatch : 1;
   const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg, act.n, planes), block(kBlock);
-  const int nt = a.pos_list ? (std::min(a.list_tokens, kMaxBatch) + 15) / 16 : (a.B + 15) / 16;
-  switch (nt) {
+  switch (mfma_token_tiles(a)) {
     case 1: hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, 1, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
     case 2: hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, 2, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
     case 3: hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, 3, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
@@ -630,7 +634,7 @@ hipError_t launch_expert_mfma(const ExpertArgs &a, const ActiveList &act, const 
       return hipGetLastError();
     }
   }
-  const int ksplit = mfma_ksplit(GATEUP ? a.H : a.I);
+  const int ksplit = mfma_ksplit(GATEUP ? a.H : a.I, mfma_token_tiles(a));
   if (ksplit == 4) return launch_expert_mfma_k<GATEUP, 4>(a, act, act_q, hq, st);
   if (ksplit == 2) return launch_expert_mfma_k<GATEUP, 2>(a, act, act_q, hq, st);
   return launch_expert_mfma_k<GATEUP, 1>(a, act, act_q, hq, st);

@@ -887,7 +887,7 @@ hipError_t launch_route_gateup_mfma_k(const RoutePairArgs &ra, const ExpertArgs 
 template <int NT>
 hipError_t launch_route_gateup_mfma_t(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act,
                                       const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
-  const int ksplit = mfma_ksplit(a.H);
+  const int ksplit = mfma_ksplit(a.H, NT);
   if (ksplit == 4) return launch_route_gateup_mfma_k<NT, 4>(ra, a, act, s_q, hq, st);
   if (ksplit == 2) return launch_route_gateup_mfma_k<NT, 2>(ra, a, act, s_q, hq, st);
   return launch_route_gateup_mfma_k<NT, 1>(ra, a, act, s_q, hq, st);
