@@ -33,10 +33,15 @@ TRACE_FILE = os.path.join(ROOT, "profiles", "kernel_trace_by_leg.json")
 
 # time_kernel modes (include/moe_spec.h) -> name in the output, and the kernel's name in a profile
 K_GATEUP, K_DOWN, K_ROUTE_OLD, K_READ_GU, K_MFMA_GU, K_MFMA_DOWN, K_ROUTE_TRUE, K_ROUTE_PAIR, K_READ_DOWN = 0, 1, 2, 3, 4, 5, 6, 7, 9
+# kernels a launch may run under, by substrings of their names: with resident predicted experts the gate/up projection
+# shares the routing's launch
+ROUTE_SYM = "route_pair_kernel or route_gateup"
+MFMA_DOWN_SYM = "expert_mfma_kernel<false or expert_tile_kernel<false"
+MFMA_GU_SYM = "expert_mfma_kernel<true or route_gateup_mfma or expert_tile_kernel<true"
 KERNEL_NAMES = {K_GATEUP: ("expert_gateup_gemv", "gateup_b1"), K_DOWN: ("expert_down_combine_gemv", "down_combine_b1"),
                 K_READ_GU: ("pure_read_of_the_gateup_bytes", "stream_read"), K_READ_DOWN: ("pure_read_of_the_down_bytes", "stream_read"),
-                K_MFMA_GU: ("expert_gateup_mfma", "expert_mfma_kernel<true"), K_MFMA_DOWN: ("expert_down_mfma", "expert_mfma_kernel<false"),
-                K_ROUTE_TRUE: ("route_true_only", "route_pair_kernel"), K_ROUTE_PAIR: ("route_true_and_prediction", "route_pair_kernel")}
+                K_MFMA_GU: ("expert_gateup_mfma", MFMA_GU_SYM), K_MFMA_DOWN: ("expert_down_mfma", MFMA_DOWN_SYM),
+                K_ROUTE_TRUE: ("route_true_only", ROUTE_SYM), K_ROUTE_PAIR: ("route_true_and_prediction", ROUTE_SYM)}
 
 
 def log(*a):
@@ -176,13 +181,13 @@ class Bench:
                             r = eng.advance(r, out, eps[t, l], wl.res_a, wl.res_b, rbuf[l & 1])
 
         fast_b1 = B == 1
-        MFMA = ("expert_mfma_kernel<true", "expert_mfma_kernel<false")
+        MFMA = (MFMA_GU_SYM, MFMA_DOWN_SYM)
 
         def token_loop_counts(n_tokens, fused_route=True):
             steps = n_tokens * L
             c = {"advance_kernel": n_tokens * (L - 1)}
             if fused_route:
-                c["route_pair_kernel"] = steps
+                c[ROUTE_SYM] = steps
             if fast_b1:
                 c.update({"gateup_b1": steps, "down_combine_b1": steps})
             return c
@@ -365,7 +370,7 @@ class Bench:
             n_pairs = 3 * L * ((wl.n_experts + group - 1) // group)
             micro = min(64, P)                                        # tokens per routing launch
             self.leg(f"{wl.name}/prefill", dict({"advance_kernel": 3 * (L - 1),
-                                                 "route_pair_kernel": 3 * L * ((P + micro - 1) // micro)},
+                                                 ROUTE_SYM: 3 * L * ((P + micro - 1) // micro)},
                                                 **({m: n_pairs for m in MFMA} if wl.dtype == "bf16" else {})))
             prompt_pass()
             torch.cuda.synchronize()
@@ -396,9 +401,9 @@ class Bench:
         for mode in ("speculative", "on_demand"):
             eng = make(mode, 0)
             self.leg(f"{wl.name}/{mode}/per_layer_misses",
-                     dict({"route_pair_kernel": n_tokens * L, "advance_kernel": n_tokens * (L - 1)},
+                     dict({ROUTE_SYM: n_tokens * L, "advance_kernel": n_tokens * (L - 1)},
                           **({"gateup_b1": n_tokens * L, "down_combine_b1": n_tokens * L} if B == 1 else {})),
-                     () if B == 1 else ("expert_mfma_kernel<true", "expert_mfma_kernel<false"))
+                     () if B == 1 else (MFMA_GU_SYM, MFMA_DOWN_SYM))
             out = torch.empty((B, H), dtype=torch.float32, device=self.dev)
             rbuf = [torch.empty((B, H), dtype=torch.float32, device=self.dev) for _ in range(2)]
             per_layer = [0] * L           # transfers issued during the call for layer l (speculative: the prefetch for l+1)

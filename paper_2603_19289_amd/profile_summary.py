@@ -40,6 +40,11 @@ def read_csv(directory, suffix):
     return rows
 
 
+def named(kernel, symbol):
+    """symbol: substrings of kernel names, separated by " or "."""
+    return any(part in kernel for part in symbol.split(" or "))
+
+
 def cut_by_legs(sequence, legs, symbol):
     """sequence: the symbol's dispatches in order.  Returns {leg name: slice}.  Legs name a count for the symbol,
     or list it under "uncounted" (at most one run of consecutive such legs can be resolved: it gets the rest)."""
@@ -117,8 +122,8 @@ def main():
     ap.add_argument("--out", default="profiles")
     ap.add_argument("--tag", required=True)
     a = ap.parse_args()
-    symbols = ["route_pair_kernel", "gateup_b1", "down_combine_b1", "stream_read", "expert_mfma_kernel<true",
-               "expert_mfma_kernel<false", "advance_kernel"]
+    symbols = ["route_pair_kernel or route_gateup", "gateup_b1", "down_combine_b1", "stream_read", "expert_mfma_kernel<true or route_gateup_mfma or expert_tile_kernel<true",
+               "expert_mfma_kernel<false or expert_tile_kernel<false", "advance_kernel"]
 
     if a.trace:
         legs = json.load(open(a.legs))
@@ -136,7 +141,7 @@ def main():
                       f"on-demand TPOT {bench['on_demand']['tpot_ms']:.2f} ms.\n")
         md += ["| workload | leg | kernel | launches | mean (us) | median (us) | min (us) | max (us) |", "|---|---|---|---|---|---|---|---|"]
         for sym in symbols:
-            seq = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in rows if sym in r["Kernel_Name"]]
+            seq = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in rows if named(r["Kernel_Name"], sym)]
             if not seq:
                 continue
             for leg_name, durs in cut_by_legs(seq, legs["legs"], sym).items():
@@ -177,7 +182,7 @@ def main():
                 raise SystemExit("no calibration copy in the PMC run (bench.py --calibrate-copy)")
             scale[ctr] = CAL_BYTES / cal[-1]              # bytes per count
             for sym in symbols:
-                seq = [v for n, v in disp if sym in n]
+                seq = [v for n, v in disp if named(n, sym)]
                 if not seq:
                     continue
                 for leg_name, vals in cut_by_legs(seq, legs["legs"], sym).items():
