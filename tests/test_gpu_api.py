@@ -436,10 +436,10 @@ def test_random_call_sequences_leave_a_working_context():
     ("bf16", 8, 8, 1, 1, 2), ("bf16", 264, 72, 6, 2, 3), ("bf16", 1032, 200, 9, 3, 17), ("bf16", 2056, 40, 70, 5, 40),
     ("bf16", 4096, 16, 256, 16, 64), ("bf16", 4104, 16, 12, 3, 5)])
 def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inter, experts, top_k, batch):
-    """Predicted experts that are in their slots share a launch with the routing; with profile = 1 the two are always
+    """Predicted experts that needed no copy share a launch with the routing; with profile = 1 the two are always
     separate launches.  Same ids, same output bits, whichever ran, at every chunk count of the rows, every count of
-    token tiles (and sizes beyond what the shared launches take); waiting after every step lets the copies land, so that the first engine takes
-    the shared launch wherever it may."""
+    token tiles (and sizes beyond what the shared launches take).  The second token repeats the first, so that all its
+    experts are in their slots and the first engine takes the shared launch wherever it may."""
     from paper_2603_19289_amd import moe_spec as M
     from paper_2603_19289_amd.engine import engine_for
     wl = small_workload(name="beside", n_layers=3, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype=dtype,
@@ -455,7 +455,7 @@ def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inte
             for t in range(wl.tokens):
                 eng.begin_token()
                 for l in range(wl.n_layers):
-                    r = torch.from_numpy(x0[t] + 0.3 * eps[t, l]).cuda()
+                    r = torch.from_numpy(x0[0] + 0.3 * eps[0, l]).cuda()
                     out, ids = eng.layer_step(l, r, want_ids=True)
                     torch.cuda.synchronize()
                     log.append([out.cpu()] + [ids[n].cpu() for n in ("true_ids", "exec_ids", "next_ids")])
