@@ -803,23 +803,6 @@ hipError_t launch_route_pair_t(const RoutePairArgs &a, hipStream_t st) {
   return launch_route_pair_s<WT, 4, 1>(a, need4, st);
 }
 
-// How the gate/up rows are dealt to wavefronts beside the routing.  The routing is a chain of dependent memory accesses
-// (11 us alone) and every one of them queues behind the weight loads in flight: with all rows asked for at once its
-// first loads came back after 9 us instead of 2.4 and the launch took 20.5 us on 128 experts of 768 x 2048 (50 MB).
-// Up to 64 MB of weights one gate/up workgroup goes on each compute unit that does not route: 2.7 TB/s, at which the
-// routing takes its usual time, 18.6 us together.  Up to 256 MB the workgroups fill the device once, so that none is
-// left over for a second round (32 experts of 2880 x 2880, 133 MB: a token's eight layers 666 -> 628 us).  Beyond,
-// the routing is short beside the stream and the split of the plain launch is the best (470 MB: 688 us for six
-// layers, 700 when filled once).  Two rows per wavefront (pairs) 335 us, this rule 321 us for six layers of the first.
-GateupSplit beside_routing_split(int nch, const ExpertArgs &a, int n, size_t wbytes, int n_route, int blocks_per_cu) {
-  const size_t bytes = size_t(2) * a.I * a.H * n * wbytes;
-  if (bytes > size_t(256) << 20) return gateup_b1_split(nch, a.I, n);
-  const int wgs = bytes <= size_t(64) << 20 ? std::max(g_compute_units / 4, g_compute_units - n_route)
-                                            : blocks_per_cu * g_compute_units - n_route;
-  const int rpw = int((long(a.I) * n + long(kB1Waves) * wgs - 1) / (long(kB1Waves) * wgs));
-  return {rpw, (a.I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
-}
-
 template <typename WT, int NCH>
 hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
   const size_t lds = size_t(ra.H) * sizeof(double);
@@ -835,7 +818,7 @@ hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a
   }
   // the routing workgroups wait for one another: they must fit on the device together
   if (long(n_route) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
-  const GateupSplit split = beside_routing_split(NCH, a, act.n, sizeof(WT), n_route, blocks_per_cu);
+  const GateupSplit split = beside_routing_split(NCH, a.I, a.H, act.n, sizeof(WT), n_route, blocks_per_cu, g_compute_units);
   hipLaunchKernelGGL((route_gateup_b1_kernel<WT, NCH>), dim3(n_route + split.blocks * act.n), dim3(kBlock), lds, st, ra,
                      a, act, n_route, split.blocks, split.rpw);
   return hipGetLastError();

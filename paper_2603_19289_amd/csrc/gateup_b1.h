@@ -1,15 +1,14 @@
 // Gate/up projection and SwiGLU of a batch of one, as device functions: expert_kernels.hip launches them by
 // themselves, fused_kernels.hip beside the routing of the same layer.
 #pragma once
-#include <algorithm>
-
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch_rules.h"
 
 namespace moe_spec {
 
 constexpr int kB1Block = 256;
-constexpr int kB1Waves = kB1Block / kWave;
+static_assert(kB1Waves == kB1Block / kWave, "the launch rules count wavefronts");
 
 // s_l = LN_l(r_l), rounded as the router input is, into LDS [H] by the whole workgroup: the routing of the layer
 // runs beside this workgroup and cannot hand its own copy over in time.  NG = groups of 256 chunks per row.  Split
@@ -205,19 +204,6 @@ __device__ __forceinline__ void gateup_b1_pair_body(const ExpertArgs &a, const A
       hq[row0 + r] = R::pack_one(hv);
     }
   }
-}
-
-// How a gate/up launch of its own deals the I rows of each of n experts to wavefronts.  Up to 4096 wavefronts of two rows each are all
-// resident at once (137 registers at NCH = 4): pairs.  Beyond, one row per wavefront until that would exceed about
-// 6144 wavefronts (24 per compute unit), then more rows each.
-struct GateupSplit {
-  int rpw;                                     // 0: pairs
-  int blocks;                                  // workgroups per expert
-};
-inline GateupSplit gateup_b1_split(int nch, int I, int n) {
-  if (nch <= 4 && long(I) * n <= 8192) return {0, (I + 2 * kB1Waves - 1) / (2 * kB1Waves)};
-  const int rpw = int(std::max(1l, (long(I) * n + 6143) / 6144));
-  return {rpw, (I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
 }
 
 }  // namespace moe_spec

@@ -1,0 +1,43 @@
+// How much work a launch gives each workgroup: arithmetic on sizes alone, host code without a GPU call in it.
+#pragma once
+#include <algorithm>
+#include <cstddef>
+
+namespace moe_spec {
+
+constexpr int kB1Waves = 4;                    // wavefronts per workgroup of the batch-one gate/up projection
+
+// How a gate/up launch of its own deals the I rows of each of n experts to wavefronts.  Up to 4096 wavefronts of two
+// rows each are all resident at once (137 registers at NCH = 4): pairs.  Beyond, one row per wavefront until that would
+// exceed about 6144 wavefronts (24 per compute unit), then more rows each.
+struct GateupSplit {
+  int rpw;                                     // 0: pairs
+  int blocks;                                  // workgroups per expert
+};
+inline GateupSplit gateup_b1_split(int nch, int I, int n) {
+  if (nch <= 4 && long(I) * n <= 8192) return {0, (I + 2 * kB1Waves - 1) / (2 * kB1Waves)};
+  const int rpw = int(std::max(1l, (long(I) * n + 6143) / 6144));
+  return {rpw, (I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
+}
+
+// How the gate/up rows are dealt to wavefronts beside the routing.  The routing is a chain of dependent memory accesses
+// (11 us alone) and every one of them queues behind the weight loads in flight: with all rows asked for at once its
+// first loads came back after 9 us instead of 2.4 and the launch took 20.5 us on 128 experts of 768 x 2048 (50 MB).
+// Up to 64 MB of weights one gate/up workgroup goes on each compute unit that does not route: 2.7 TB/s, at which the
+// routing takes its usual time, 18.6 us together.  Up to 256 MB the workgroups fill the device once, so that none is
+// left over for a second round (32 experts of 2880 x 2880, 133 MB: a token's eight layers 666 -> 628 us).  Beyond,
+// the routing is short beside the stream and the split of the plain launch is the best (470 MB: 688 us for six
+// layers, 700 when filled once).  Two rows per wavefront (pairs) 335 us, this rule 321 us for six layers of the first.
+// Never fewer workgroups than a quarter of the compute units, however many of them the routing takes: with routing that
+// fills the device there would be none.  Never pairs: those end at 67 MB.
+inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_t wbytes, int n_route, int blocks_per_cu,
+                                        int cus) {
+  const std::size_t bytes = std::size_t(2) * I * H * n * wbytes;
+  if (bytes > std::size_t(256) << 20) return gateup_b1_split(nch, I, n);
+  const int places = bytes <= std::size_t(64) << 20 ? cus : blocks_per_cu * cus;
+  const int wgs = std::max(1, std::max(cus / 4, places - n_route));
+  const int rpw = int((long(I) * n + long(kB1Waves) * wgs - 1) / (long(kB1Waves) * wgs));
+  return {rpw, (I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
+}
+
+}  // namespace moe_spec

@@ -1,0 +1,37 @@
+"""The rules that deal a launch's work to workgroups (csrc/launch_rules.h), swept on the CPU over the sizes the library
+takes and over the compute-unit counts of a whole device and of its partitions."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def sweep(tmp_path, body):
+    """Compiles a program around the rules and runs it: it prints the cases that break a rule and returns their number."""
+    src, exe = tmp_path / "sweep.cpp", tmp_path / "sweep"
+    src.write_text('#include <cstdio>\n#include "launch_rules.h"\nusing namespace moe_spec;\nint main() {\n  int bad = 0;\n'
+                   + body + "\n  return bad ? 1 : 0;\n}\n")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2603_19289_amd", "csrc"),
+                    str(src), "-o", str(exe)], check=True)
+    done = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, (done.returncode, done.stdout[-2000:])
+
+
+def test_gate_up_rows_beside_the_routing_are_dealt_whatever_the_routing_takes(tmp_path):
+    # every row belongs to exactly one wavefront, at least one row each (the body takes no pairs), and no workgroup is
+    # left with more than its share of a quarter of the device, also where the routing takes every place
+    sweep(tmp_path, r"""
+  for (int cus : {32, 64, 128, 256}) for (int per_cu : {1, 2, 4, 8}) for (int E = 1; E <= 256; ++E) {
+    if (long(E) > long(per_cu) * cus) continue;               // refused by the launcher
+    for (int H : {8, 512, 1024, 2048, 2880, 4096}) for (int I : {8, 768, 2880, 14336, 32768}) for (int k : {1, 2, 8, 16}) {
+      for (int wbytes : {2, 4}) {
+        const int nch = (H + 64 * (16 / wbytes) - 1) / (64 * (16 / wbytes));
+        const GateupSplit s = beside_routing_split(nch, I, H, k, wbytes, E, per_cu, cus);
+        const long wgs = long(s.blocks) * k, share = (long(I) * k + cus - 1) / cus;   // rows per wavefront of cus / 4 workgroups
+        const bool ok = s.rpw >= 1 && long(s.blocks) * kB1Waves * s.rpw >= I && long(s.blocks - 1) * kB1Waves * s.rpw < I &&
+                        wgs >= 1 && s.rpw <= share;
+        if (!ok && ++bad <= 20)
+          std::printf("cus %d per_cu %d E %d H %d I %d k %d wbytes %d: rpw %d blocks %d\n", cus, per_cu, E, H, I, k, wbytes, s.rpw, s.blocks);
+      }
+    }
+  }""")
