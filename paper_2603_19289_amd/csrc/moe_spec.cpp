@@ -1180,6 +1180,11 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
   if (int rc = c->check_waits()) return rc;
   if (!c->clock_running) { c->clock_running = true; c->t0 = std::chrono::steady_clock::now(); }
 
+  // The copies into this pool go behind the decode kernels that read it.  If that takes an event, it is recorded here,
+  // ahead of the prompt's routing, beside which the first experts are to travel (8192 tokens, 256 experts of 4096
+  // columns: 7.1 ms with the event behind the routing, 5.3 ms with it here).
+  if (int rc = c->copies_behind_readers(layer)) return rc;
+
   // --- true routing of every prompt token, one kernel per micro-batch of at most max_batch tokens
   TimedSpan *sp_route = c->open_span(0, c->compute);
   const bool pair_kernel = route_pair_supported(H, cfg.dtype);   // the fused kernel, asked for the true routing only
@@ -1243,7 +1248,6 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
   std::fill(p.slot_stamp.begin(), p.slot_stamp.end(), -1);
   std::fill(p.where.begin(), p.where.end(), -1);
   p.clock = 0;
-  if (int rc = c->copies_behind_readers(layer)) return rc;
   if (c->ready_recorded[layer]) {
     for (hipStream_t q : c->copy_aux)
       if ((e = hipStreamWaitEvent(q, c->ready[layer], 0)) != hipSuccess) return c->hip_fail(e, "copy queue wait");

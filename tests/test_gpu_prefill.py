@@ -229,3 +229,34 @@ def test_prefill_randomised_configurations():
         wl = small_workload(name=f"pdraw{case}", n_layers=L, hidden=H, n_experts=E, top_k=k, inter=I, dtype=dtype,
                             batch=1, tokens=1, slots=S, seed=5000 + case)
         run_prefill(wl, P=P, max_batch=micro, label=f"draw {case}", copy_engine=int(rng.integers(0, 3)))
+
+
+def test_prefill_after_decode_starts_its_copies_beside_the_routing():
+    """The experts of a prompt travel while its tokens are routed, also into a pool that the decode step just before has
+    read: the copies wait for that step's kernels, not for the prompt's routing.  The layer is shaped so that routing
+    (128 launches of 64 tokens, 256 experts) takes several times as long as issuing it and as the copies: behind the
+    routing they would end with the call's last kernels, beside it they end in its first part."""
+    from paper_2603_19289_amd.engine import engine_for
+    P = 8192
+    wl = small_workload(name="decode_then_prefill", n_layers=1, hidden=4096, n_experts=256, top_k=1, inter=8, dtype="bf16",
+                        slots=512, seed=43)
+    res, ex, _ = build(wl)
+    eng = engine_for(wl, M.MODE_SPECULATIVE, res, ex, max_batch=64, max_prefill_tokens=P, copy_engine=M.COPY_DMA2)
+    r = torch.randn((P, wl.hidden), generator=torch.Generator(device="cuda").manual_seed(9), device="cuda")
+    shares = []
+    try:
+        for _ in range(3):
+            eng.begin_token()
+            eng.layer_step(0, r[:1])
+            torch.cuda.synchronize()
+            start, copied, done = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+            start.record(eng.compute)
+            eng.prefill_layer_step(0, r)
+            copied.record(eng.copy)
+            done.record(eng.compute)
+            torch.cuda.synchronize()
+            shares.append(start.elapsed_time(copied) / start.elapsed_time(done))
+            print(f"[case] copies end after {start.elapsed_time(copied):.2f} of {start.elapsed_time(done):.2f} ms", flush=True)
+    finally:
+        eng.close()
+    assert min(shares) < 0.7, shares
