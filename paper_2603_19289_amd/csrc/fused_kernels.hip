@@ -18,12 +18,14 @@
 #include "expert_mfma.h"
 #include "gateup_b1.h"
 #include "kernels.h"
+#include "launch_rules.h"
 
 namespace moe_spec {
 namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / kWave;
+static_assert(kWaves == kRouteWaves, "the launch rules count wavefronts");
 // Development aid, compiled in with -DMOE_SPEC_STAGE_CLOCK only: workgroup 0 of token 0 notes the
 // constant-rate clock (100 MHz) at the stages of the routing kernel.
 #ifdef MOE_SPEC_STAGE_CLOCK
@@ -539,9 +541,10 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
   }
   STAGE(7);
   if constexpr (PROJ) {
-    // One wavefront per row of the projection, the wavefronts of the token's workgroups taking rows in turn.  q_l is
-    // here anyway: a launch of its own for it (a whole second routing, 14.7 us for 4 tokens of 128 experts) and one
-    // for this product (7.4 us) against 9 us more in this one.
+    // The wavefronts of the token's workgroups take the projection's rows in pairs, in turn; the launcher sizes their
+    // number for that.  q_l is here anyway: 4 tokens of 128 experts of 2048 columns, latent size 512, 15.0 us in this
+    // launch, against 9.1 us for the true routing alone, 14.7 us for a second routing that only yields q_l and 7.4 us
+    // for the product by itself.
     project_rows<WT>(a, b, wg * kWaves + wave, n_wg * kWaves, vec_lds);
     return;
   }
@@ -753,7 +756,6 @@ template <typename WT, int SPLIT, int NCH, int ROWS, bool PROJ>
 hipError_t launch_route_pair_p(const RoutePairArgs &a, hipStream_t st) {
   constexpr int RPW = kWaves / SPLIT * ROWS;
   const size_t lds = size_t(a.H) * sizeof(double);
-  const int n_wg = (a.E + RPW - 1) / RPW;
   static int blocks_per_cu = -1;               // per instantiation
   static size_t checked_lds = 0;
   if (blocks_per_cu < 0 || lds > checked_lds) {
@@ -763,6 +765,7 @@ hipError_t launch_route_pair_p(const RoutePairArgs &a, hipStream_t st) {
     blocks_per_cu = n;
     checked_lds = lds;
   }
+  const int n_wg = routing_workgroups(a.E, RPW, PROJ ? a.proj_rows : 0, a.B, g_compute_units);
   // the workgroups of a token wait for one another: they must fit on the device together
   if (long(n_wg) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
   hipLaunchKernelGGL((route_pair_kernel<WT, SPLIT, NCH, ROWS, PROJ>), dim3(n_wg, a.B), dim3(kBlock), lds, st, a);
@@ -849,9 +852,7 @@ hipError_t launch_route_gateup_mfma_n(const RoutePairArgs &ra, const ExpertArgs 
     blocks_per_cu = n;
     checked_lds = lds;
   }
-  // workgroups per token: about one per compute unit in all (half as many: 2 % slower at 32 tokens, a quarter 16 %;
-  // twice as many 1 %), at least a router row for every wavefront
-  const int n_wg = std::max(1, std::min(g_compute_units / ra.B, (ra.E + kWaves - 1) / kWaves));
+  const int n_wg = beside_experts_workgroups(ra.E, PROJ ? ra.proj_rows : 0, ra.B, g_compute_units);
   if (long(n_wg) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
   constexpr int rows_per_wg = 16 * kMfmaWaves / KSPLIT;
   const int row_blocks = (a.I + rows_per_wg - 1) / rows_per_wg, n_route = n_wg * ra.B;

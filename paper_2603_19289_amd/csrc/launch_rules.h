@@ -6,6 +6,7 @@
 namespace moe_spec {
 
 constexpr int kB1Waves = 4;                    // wavefronts per workgroup of the batch-one gate/up projection
+constexpr int kRouteWaves = 4;                 // and of the routing launches
 
 // How a gate/up launch of its own deals the I rows of each of n experts to wavefronts.  Up to 4096 wavefronts of two
 // rows each are all resident at once (137 registers at NCH = 4): pairs.  Beyond, one row per wavefront until that would
@@ -38,6 +39,24 @@ inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_
   const int wgs = std::max(1, std::max(cus / 4, places - n_route));
   const int rpw = int((long(I) * n + long(kB1Waves) * wgs - 1) / (long(kB1Waves) * wgs));
   return {rpw, (I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
+}
+
+// Workgroups per token of a routing launch beside matrix-core experts, whose rows may be dealt to any number of them:
+// about one per compute unit in all (half as many: 2 % slower at 32 tokens, a quarter 16 %; twice as many 1 %), at least
+// a router row for every wavefront, and two pairs of rows where the estimator's projection rides along (proj_rows, else
+// 0).  Sized by the router alone, the projection is a serial chain where experts are few: a layer step of 8 experts of
+// 4096 columns with a latent size of 1024 takes 236 us at 2 tokens and 293 us at 8 like that, 73 and 126 us like this.
+// One pair instead of two: 4 tokens of 128 experts of 2048 columns 1 % slower, the others within 3 % either way.
+inline int beside_experts_workgroups(int E, int proj_rows, int B, int cus) {
+  const int rows = std::max(E, (proj_rows + 3) / 4);
+  return std::max(1, std::min(cus / B, (rows + kRouteWaves - 1) / kRouteWaves));
+}
+
+// The same for a routing launch of its own: rows_per_wg router rows each, and more workgroups where the projection has
+// more row pairs than those have wavefronts (one token of the layer above: 87 us sized by the router, 50 us like this).
+inline int routing_workgroups(int E, int rows_per_wg, int proj_rows, int B, int cus) {
+  const int for_router = (E + rows_per_wg - 1) / rows_per_wg;
+  return std::max(for_router, std::min(cus / B, ((proj_rows + 1) / 2 + kRouteWaves - 1) / kRouteWaves));
 }
 
 }  // namespace moe_spec

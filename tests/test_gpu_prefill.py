@@ -234,8 +234,9 @@ def test_prefill_randomised_configurations():
 def test_prefill_after_decode_starts_its_copies_beside_the_routing():
     """The experts of a prompt travel while its tokens are routed, also into a pool that the decode step just before has
     read: the copies wait for that step's kernels, not for the prompt's routing.  The layer is shaped so that routing
-    (128 launches of 64 tokens, 256 experts) takes several times as long as issuing it and as the copies: behind the
-    routing they would end with the call's last kernels, beside it they end in its first part."""
+    (128 launches of 64 tokens, 256 experts) takes longer than issuing it and than the copies; behind the routing the
+    copies lengthen the call by a third (7.1 against 5.3 ms).  Compared with the same call after another prefill, which
+    finds the kernels before it ended, whatever hardware queues the process's streams share."""
     from paper_2603_19289_amd.engine import engine_for
     P = 8192
     wl = small_workload(name="decode_then_prefill", n_layers=1, hidden=4096, n_experts=256, top_k=1, inter=8, dtype="bf16",
@@ -243,20 +244,21 @@ def test_prefill_after_decode_starts_its_copies_beside_the_routing():
     res, ex, _ = build(wl)
     eng = engine_for(wl, M.MODE_SPECULATIVE, res, ex, max_batch=64, max_prefill_tokens=P, copy_engine=M.COPY_DMA2)
     r = torch.randn((P, wl.hidden), generator=torch.Generator(device="cuda").manual_seed(9), device="cuda")
-    shares = []
+    took = {"prefill": [], "decode": []}
     try:
-        for _ in range(3):
-            eng.begin_token()
-            eng.layer_step(0, r[:1])
+        eng.prefill_layer_step(0, r)
+        for before in ("prefill", "decode") * 5:
+            if before == "decode":
+                eng.begin_token()
+                eng.layer_step(0, r[:1])
             torch.cuda.synchronize()
-            start, copied, done = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+            start, done = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             start.record(eng.compute)
             eng.prefill_layer_step(0, r)
-            copied.record(eng.copy)
             done.record(eng.compute)
             torch.cuda.synchronize()
-            shares.append(start.elapsed_time(copied) / start.elapsed_time(done))
-            print(f"[case] copies end after {start.elapsed_time(copied):.2f} of {start.elapsed_time(done):.2f} ms", flush=True)
+            took[before].append(start.elapsed_time(done))
     finally:
         eng.close()
-    assert min(shares) < 0.7, shares
+    print("[case] prefill after " + ", after ".join(f"{k}: {min(v):.2f} ms" for k, v in took.items()), flush=True)
+    assert min(took["decode"]) < 1.15 * min(took["prefill"]), took

@@ -35,3 +35,26 @@ def test_gate_up_rows_beside_the_routing_are_dealt_whatever_the_routing_takes(tm
       }
     }
   }""")
+
+
+def test_estimator_projection_gets_workgroups_for_its_rows(tmp_path):
+    # the rows of the projection are dealt in pairs to the wavefronts of a token's workgroups: one pair each (two beside
+    # experts), or as many as it takes when the tokens' workgroups fill the device, whatever the number of experts; every
+    # router row has a place; the launch without a projection is sized by the router alone
+    sweep(tmp_path, r"""
+  for (int cus : {32, 64, 128, 256}) for (int E : {1, 3, 8, 16, 32, 128, 200, 256}) for (int B = 1; B <= 64; ++B) {
+    for (int rows : {0, 8, 64, 72, 256, 512, 1024, 4096, 8192}) {
+      if (B > cus) continue;
+      const int room = std::max(1, cus / B), pairs = (rows + 1) / 2;
+      auto share = [](int n, int wgs) { return (n + kRouteWaves * wgs - 1) / (kRouteWaves * wgs); };   // per wavefront
+      const int beside = beside_experts_workgroups(E, rows, B, cus);
+      bool ok = beside >= 1 && beside <= room && share(pairs, beside) <= std::max(2, share(pairs, room));
+      if (rows == 0) ok = ok && beside == std::max(1, std::min(cus / B, (E + 3) / 4));
+      for (int per_wg : {1, 4, 16}) {
+        const int router = (E + per_wg - 1) / per_wg, own = routing_workgroups(E, per_wg, rows, B, cus);
+        ok = ok && own >= router && own <= std::max(router, room) && share(pairs, own) <= std::max(1, share(pairs, room));
+        if (rows == 0) ok = ok && own == router;
+      }
+      if (!ok && ++bad <= 20) std::printf("cus %d E %d B %d rows %d: %d beside\n", cus, E, B, rows, beside);
+    }
+  }""")
