@@ -1,4 +1,8 @@
 """Glue used by the tests only: build the checker's model from generated inputs."""
+import collections
+import re
+import time
+
 import numpy as np
 
 from oracle import moe_oracle as O
@@ -72,3 +76,28 @@ def make_advance(wl, eps):
     def adv(t, l, r, out):
         return W.advance_residual(wl, r, out, eps[t, l])
     return adv
+
+
+def kernels_launched(call, always):
+    """Runs call() and returns how often each of the library's kernels ran meanwhile, by name with template arguments, as
+    torch's profiler sees them on the device: which path of a dispatch was taken.  always: {part of a name: launches that
+    every path makes}.  The profiler can miss launches close to a session's ends; a session that lacks one of these is
+    repeated."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    for _ in range(4):
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            time.sleep(0.05)
+            call()
+            torch.cuda.synchronize()
+            time.sleep(0.05)
+        found = (re.search(r"moe_spec::\(anonymous namespace\)::(\w+(?:<[^(]*>)?)", e.name) for e in prof.events())
+        counts = collections.Counter(m.group(1) for m in found if m)
+        if all(launches(counts, part) == n for part, n in always.items()):
+            break
+    return counts
+
+
+def launches(counts, part):
+    return sum(n for name, n in counts.items() if part in name)

@@ -9,7 +9,7 @@ import torch
 from oracle import moe_oracle as O
 from paper_2603_19289_amd import moe_spec as M
 from paper_2603_19289_amd import workload as W
-from tests.helpers import build, check_output, make_advance, small_workload
+from tests.helpers import build, check_output, kernels_launched, launches, make_advance, small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -430,40 +430,70 @@ def test_random_call_sequences_leave_a_working_context():
             ref.close()
 
 
-@pytest.mark.parametrize("dtype,hidden,inter,experts,top_k,batch", [
-    ("bf16", 8, 8, 1, 1, 1), ("f32", 264, 72, 6, 2, 1), ("bf16", 520, 200, 9, 3, 1), ("bf16", 2048, 1056, 9, 8, 1),
-    ("bf16", 2056, 40, 200, 16, 1), ("f32", 2048, 24, 70, 5, 1), ("bf16", 4096, 16, 256, 4, 1), ("bf16", 4104, 16, 12, 3, 1),
-    ("bf16", 8, 8, 1, 1, 2), ("bf16", 264, 72, 6, 2, 3), ("bf16", 1032, 200, 9, 3, 17), ("bf16", 2056, 40, 70, 5, 40),
-    ("bf16", 4096, 16, 256, 16, 64), ("bf16", 4104, 16, 12, 3, 5)])
-def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inter, experts, top_k, batch):
-    """Predicted experts that needed no copy share a launch with the routing; with profile = 1 the two are always
-    separate launches.  Same ids, same output bits, whichever ran, at every chunk count of the rows, every count of
-    token tiles (and sizes beyond what the shared launches take).  The second token repeats the first, so that all its
-    experts are in their slots and the first engine takes the shared launch wherever it may."""
-    from paper_2603_19289_amd import moe_spec as M
+def beside_and_separate(wl, kernel, joint_layers, **engine_kw):
+    """Decodes the same token again and again with profile = 0 and with profile = 1, where routing and experts are always
+    separate launches: equal ids, gates, output bits and counters.  From the second token on all experts are in their
+    slots; there the first engine is to make joint_layers[0] joint launches, joint_layers[1] of them of `kernel`, the
+    other one none."""
     from paper_2603_19289_amd.engine import engine_for
-    wl = small_workload(name="beside", n_layers=3, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype=dtype,
-                        batch=batch, tokens=2, slots=experts, seed=41)
-    print(f"[case] beside routing H={hidden} I={inter} E={experts} k={top_k} B={batch} {dtype}", flush=True)
     res, ex, _ = build(wl, "random")
     x0, eps = W.make_inputs(wl)
-    got = []
+    got, joint = [], []
     for profile in (0, 1):
-        eng = engine_for(wl, M.MODE_SPECULATIVE, res, ex, profile=profile)
-        log = []
+        eng = engine_for(wl, M.MODE_SPECULATIVE, res, ex, profile=profile, **engine_kw)
+
+        def token():
+            log = []
+            eng.begin_token()
+            for l in range(wl.n_layers):
+                r = torch.from_numpy(x0[0] + 0.3 * eps[0, l]).cuda()
+                out, ids = eng.layer_step(l, r, want_ids=True)
+                torch.cuda.synchronize()
+                log.append([out.cpu()] + [t.cpu() for _, t in sorted(ids.items())])
+            return log
         try:
-            for t in range(wl.tokens):
-                eng.begin_token()
-                for l in range(wl.n_layers):
-                    r = torch.from_numpy(x0[0] + 0.3 * eps[0, l]).cuda()
-                    out, ids = eng.layer_step(l, r, want_ids=True)
-                    torch.cuda.synchronize()
-                    log.append([out.cpu()] + [ids[n].cpu() for n in ("true_ids", "exec_ids", "next_ids")])
+            log = token() + token()
             stats = {n: eng.stats()[n] for n in ("hits", "predictions", "cache_hits", "cache_misses", "hbm_bytes_algorithmic")}
+            counts = kernels_launched(token, {"_kernel<false" if wl.dtype == "bf16" and wl.batch > 1 else "down_": wl.n_layers})
         finally:
             eng.close()
         got.append((log, stats))
+        joint.append((launches(counts, "route_gateup"), launches(counts, kernel)))
+    assert joint == [joint_layers, (0, 0)], (joint, counts)
     assert got[0][1] == got[1][1]
     for step, (a, b) in enumerate(zip(got[0][0], got[1][0])):
         for x, y in zip(a, b):
             assert torch.equal(x.view(torch.int32), y.view(torch.int32)), step
+
+
+@pytest.mark.parametrize("dtype,hidden,inter,experts,top_k,batch,kernel", [
+    ("bf16", 8, 8, 1, 1, 1, "route_gateup_b1"), ("f32", 264, 72, 6, 2, 1, "route_gateup_b1"),
+    ("bf16", 520, 200, 9, 3, 1, "route_gateup_b1"), ("bf16", 2048, 1056, 9, 8, 1, "route_gateup_b1"),
+    ("bf16", 2056, 40, 200, 16, 1, "route_gateup_b1"), ("f32", 2048, 24, 70, 5, 1, "route_gateup_b1"),
+    ("bf16", 4096, 16, 256, 4, 1, "route_gateup_b1"), ("bf16", 4104, 16, 12, 3, 1, None),
+    ("bf16", 8, 8, 1, 1, 2, "route_gateup_mfma"), ("bf16", 264, 72, 6, 2, 3, "route_gateup_mfma"),
+    ("bf16", 1032, 200, 9, 3, 17, "route_gateup_mfma"), ("bf16", 2056, 40, 70, 5, 40, "route_gateup_mfma"),
+    ("bf16", 4096, 16, 256, 16, 64, "route_gateup_mfma"), ("bf16", 4104, 16, 12, 3, 5, None), ("f32", 264, 72, 6, 2, 3, None)])
+def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inter, experts, top_k, batch, kernel):
+    """Predicted experts that needed no copy share a launch with the routing, at every chunk count of the rows and every
+    count of token tiles; kernel None: sizes beyond what the shared launches take."""
+    wl = small_workload(name="beside", n_layers=3, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype=dtype,
+                        batch=batch, tokens=2, slots=experts, seed=41)
+    print(f"[case] beside routing H={hidden} I={inter} E={experts} k={top_k} B={batch} {dtype}", flush=True)
+    n = wl.n_layers - 1 if kernel else 0                     # layer 0 has no prediction to execute
+    beside_and_separate(wl, kernel or "route_gateup", (n, n))
+
+
+@pytest.mark.parametrize("hidden,experts,m,batch,kernel", [
+    (520, 3, 1, 2, "<1, 4, true>"),          # one token tile, four wavefronts per 16 rows; more projection rows than router rows
+    (72, 40, 9, 16, "<1, 1, true>"),         # latent size 8: most wavefronts have no row of it
+    (264, 9, 3, 17, "<2, 1, true>"), (1032, 5, 3, 20, "<2, 2, true>"), (2056, 128, 1, 32, "<2, 4, true>"),
+    (264, 200, 3, 48, "<3, 1, true>"), (1032, 8, 1, 33, "<3, 2, true>"), (2056, 2, 1, 40, "<3, 4, true>"),
+    (72, 256, 9, 64, "<4, 1, true>"), (1096, 16, 1, 64, "<4, 2, true>"), (4096, 9, 4, 49, "<4, 4, true>")])
+def test_estimator_projection_and_gate_up_beside_the_routing_equal_separate_launches(hidden, experts, m, batch, kernel):
+    """The same with the estimator at every layer: its projection rides in the shared launch too (layers 1 and 2; the last
+    layer predicts nothing)."""
+    wl = small_workload(name="beside_est", n_layers=4, hidden=hidden, n_experts=experts, top_k=2, inter=40, dtype="bf16",
+                        batch=batch, tokens=2, slots=experts, seed=47)
+    print(f"[case] estimator beside routing H={hidden} E={experts} m={m} B={batch}", flush=True)
+    beside_and_separate(wl, f"route_gateup_mfma_kernel{kernel}", (3, 2), estimator=W.make_estimator(wl, m=m, n=2))
