@@ -11,7 +11,7 @@ import torch
 from oracle import moe_oracle as O
 from paper_2603_19289_amd import moe_spec as M
 from paper_2603_19289_amd import workload as W
-from tests.helpers import build, check_output, make_advance, small_workload
+from tests.helpers import build, check_output, kernels_launched, launches, make_advance, oracle_model, small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -21,7 +21,7 @@ def prompt_of(wl, P):
     return x0[0], eps[0]
 
 
-def run_prefill(wl, P, max_batch, label, prebuilt=None, **engine_kw):
+def run_prefill(wl, P, max_batch, label, prebuilt=None, load=None, **engine_kw):
     from paper_2603_19289_amd.engine import engine_for
     print(f"[case] prefill {label} L={wl.n_layers} H={wl.hidden} E={wl.n_experts} k={wl.top_k} I={wl.inter} "
           f"P={P} micro-batch={max_batch} S={wl.slots} {wl.dtype} {engine_kw}", flush=True)
@@ -36,6 +36,8 @@ def run_prefill(wl, P, max_batch, label, prebuilt=None, **engine_kw):
     try:
         for l in range(wl.n_layers):
             want = orc.prefill_layer_step(l, r_np)
+            if load is not None:
+                load[:] = np.bincount(want.true_ids.ravel(), minlength=wl.n_experts)
             r = torch.from_numpy(r_np.astype(np.float32)).to("cuda")
             out, ids, gates = eng.prefill_layer_step(l, r, want_ids=True)
             torch.cuda.synchronize()
@@ -87,10 +89,34 @@ def test_prefill_pool_larger_than_expert_count():
     (128, 128, 64, 1, 9000),      # whole tiles of rows; many experts with about one tile of positions each
 ])
 def test_prefill_tiled_matrix_product(hidden, inter, experts, top_k, P):
-    """Prompts long enough for the tiled kernel in the gate/up or the down launch (or both): positions per expert
+    """Prompts long enough for the tiled kernel in the gate/up and the down launch: positions per expert
     around its 128-position tile, remainders of its 64-column steps and of its row tiles."""
     wl = small_workload(n_layers=1, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype="bf16", slots=2 * experts)
-    run_prefill(wl, P=P, max_batch=64, label="tiles", copy_engine=M.COPY_DMA2)
+    counts = kernels_launched(lambda: run_prefill(wl, P=P, max_batch=64, label="tiles", copy_engine=M.COPY_DMA2),
+                              {"expert_lists": 1, "combine": 1})
+    assert (launches(counts, "expert_tile_kernel<true>"), launches(counts, "expert_tile_kernel<false>")) == (1, 1), counts
+
+
+@pytest.mark.parametrize("hidden,inter,top_k,P,slots,groups", [(520, 264, 1, 9000, 4, 3), (264, 520, 2, 5000, 6, 2),
+                                                               (520, 264, 1, 9000, 12, 1)])
+def test_prefill_tiled_matrix_product_uneven_experts(hidden, inter, top_k, P, slots, groups):
+    """The same kernel with several groups of experts (launch pairs), experts of very different load in a launch and, with
+    top-1 routing, one without a position: expert 5 has expert 0's router row, and of equal logits the lower index wins."""
+    wl = small_workload(n_layers=1, hidden=hidden, n_experts=6, top_k=top_k, inter=inter, dtype="bf16", slots=slots)
+    res, ex, _ = build(wl, "random")
+    row = res["router_w"][0]
+    w = O.decode_weights(row)
+    row[1] = W.to_storage(3 * w[1], "bf16")                # chosen often
+    row[2] = W.to_storage(0.6 * w[0] + 0.6 * w[4], "bf16")  # between two others: seldom the largest logit
+    row[3] = W.to_storage(0.51 * w[0] + 1.53 * w[1], "bf16")
+    row[5] = row[0]
+    model = oracle_model(wl, res, ex)
+    load = np.zeros(6, dtype=int)
+    counts = kernels_launched(lambda: run_prefill(wl, P=P, max_batch=64, label="uneven tiles", prebuilt=(res, model, ex),
+                                                  copy_engine=M.COPY_DMA2, load=load), {"expert_lists": 1, "combine": 1})
+    print("[case] positions per expert", load.tolist(), flush=True)
+    assert top_k > 1 or (load.max() > 10 * load[2] > 10 * load[3] > 0 and load[5] == 0), load
+    assert (launches(counts, "expert_tile_kernel<true>"), launches(counts, "expert_tile_kernel<false>")) == (groups, groups), counts
 
 
 @pytest.mark.parametrize("name,P,layers", [("c2_qwen3_30b_a3b", 150, 2), ("c3_gpt_oss_20b", 70, 1)])
