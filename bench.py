@@ -8,9 +8,10 @@ Qwen3-30B-A3B-shaped workload; on-demand loading is measured beside it on the sa
 After the headline workload two more are timed in the same run, shorter: the batch-32 workload (the
 matrix-core expert path) and the tiny float32 one.
 
-Prints one JSON line: metric, value (tokens/s), ms_per_step (TPOT), both modes' figures, the instrumented
-compute / copy / stall breakdown, `roofline` (dominant kernel, every hot kernel, the layer step), the paper's
-analytic model against the measurement, `cpu_baseline`, and the same for the other workloads of the run.
+Prints one JSON line of at most a few kilobytes: metric, value (tokens/s), ms_per_step (TPOT), both modes' figures,
+the instrumented compute / copy / stall breakdown, `roofline` of the dominant kernel, the paper's analytic model against
+the measurement, prefill, `cpu_baseline`, and both modes' TPOT of the other workloads of the run.  --json-file keeps the
+whole record: every hot kernel, the layer step, per-leg kernel durations, and all of it for the other workloads too.
 """
 import argparse
 import json
@@ -76,6 +77,7 @@ def parse():
     p.add_argument("--kernel-reps", type=int, default=480)
     p.add_argument("--legs-file", default="", help="write the order of the run's legs and their kernel launch counts here "
                                                  "(read by paper_2603_19289_amd.profile_summary to split a kernel trace)")
+    p.add_argument("--json-file", default="", help="write the whole record here (the printed line holds the headline figures)")
     p.add_argument("--per-layer-misses", action="store_true", help="also report cache misses per layer for both modes")
     p.add_argument("--copy-engine", choices=["auto", "kernel", "dma", "dma2"], default="auto",
                    help="auto: each mode gets the engine that is fastest for it (speculative: two DMA queues, "
@@ -99,6 +101,40 @@ def cpu_model():
     except OSError:
         pass
     return platform.processor() or "unknown"
+
+
+def rounded(v, digits=5):
+    """Every float in v to so many significant digits."""
+    if isinstance(v, dict):
+        return {k: rounded(x, digits) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [rounded(x, digits) for x in v]
+    return float(f"{v:.{digits}g}") if isinstance(v, float) else v
+
+
+def headline(record):
+    """What is printed of the whole record: the required keys as they are, the rest cut down to the headline figures, so
+    that the line stays short however many workloads and kernels the run covers."""
+    def pick(d, *keys):
+        return {k: d[k] for k in keys if k in d} if d else d
+    line = {k: v for k, v in record.items() if not isinstance(v, (dict, list))}
+    line["config"] = record["config"]
+    for mode in ("speculative", "on_demand", "prefetch_hint", "speculative_lookahead2"):
+        line[mode] = rounded(pick(record.get(mode), "tpot_ms", "tpot_ms_std", "tokens_per_s", "h2d_gbs_wall", "cache_hit_rate"))
+    line["breakdown_instrumented"] = rounded({
+        mode: pick(b, "copy_ms_per_token", "compute_ms_per_token", "stall_ms_per_token", "overlap_fraction", "hit_rate_recall_at_k")
+        for mode, b in record["breakdown_instrumented"].items()})
+    roof = record["roofline"]
+    line["roofline"] = dict(pick(roof, "bound", "kernel"), **rounded(pick(
+        roof, "achieved", "peak", "unit", "frac", "traffic", "traffic_source", "bytes_per_launch", "us_per_launch", "launches_timed")))
+    line["tpot_model_sec_5_1"] = rounded(pick(record["tpot_model_sec_5_1"], "predicted_reduction", "measured_reduction"))
+    line["prefill"] = rounded(pick(record.get("prefill"), "prompt_tokens", "ms_per_prompt", "ms_per_layer", "prompt_tokens_per_s", "h2d_gbs_wall"))
+    line["cpu_baseline"] = pick(record.get("cpu_baseline"), "value", "unit", "cores", "kind", "cpu_model", "sample")
+    line["other_workloads"] = {name: rounded(
+        {"speculative_tpot_ms": r["speculative"]["tpot_ms"], "on_demand_tpot_ms": r["on_demand"]["tpot_ms"],
+         "tpot_reduction_vs_on_demand": r["tpot_reduction_vs_on_demand"], "roofline_frac": r["roofline"]["frac"]})
+        if "error" not in r else {"error": r["error"][:200]} for name, r in record["other_workloads"].items()}
+    return line
 
 
 class Bench:
@@ -543,7 +579,10 @@ def main():
     for key in ("cpu_baseline", "prefill", "signal_diagnostics"):
         line.setdefault(key, None)
     line["other_workloads"] = legs
-    print(json.dumps(line), flush=True)
+    if args.json_file:
+        with open(args.json_file, "w") as f:
+            json.dump(line, f)
+    print(json.dumps(headline(line)), flush=True)
 
 
 if __name__ == "__main__":

@@ -119,6 +119,32 @@ def test_bench_refuses_more_than_one_gpu(monkeypatch, capsys):
     assert "ONE GPU" in capsys.readouterr().err
 
 
+def test_bench_line_stays_short_however_much_a_run_covers():
+    # the line is read back from the kept end of a run's output: one of 50 KB was cut there
+    import json
+    import bench
+    x = 1234.5678901234567
+    mode = {k: x for k in ("tpot_ms", "tpot_ms_std", "tokens_per_s", "h2d_gb_per_token", "h2d_gbs_wall", "link_frac_wall_nominal",
+                           "expert_transfers_per_token", "cache_hit_rate", "hbm_gb_algorithmic_per_token")}
+    kernels = {f"kernel_number_{i}": {k: x for k in ("us_per_launch", "bytes_per_launch", "gbs", "frac_of_hbm_peak")} for i in range(10)}
+    run = {"config": {k: "c2_qwen3_30b_a3b" for k in ("workload", "layers", "hidden", "experts", "top_k", "inter", "batch", "dtype",
+                                                      "slots_per_layer", "reps", "steps", "warmup", "copy_engine", "expert_bytes")},
+           "speculative": mode, "on_demand": mode, "prefetch_hint": mode, "speculative_lookahead2": mode, "tpot_reduction_vs_on_demand": x,
+           "breakdown_instrumented": {m: dict(mode, copy_ms_per_token=x, stall_ms_per_token=x, note="n" * 100) for m in ("speculative", "on_demand")},
+           "roofline": {"bound": "hbm", "kernel": "k" * 120, "achieved": x, "peak": x, "unit": "GB/s", "frac": x, "traffic": 1 << 40, "traffic_source": "t" * 40,
+                        "bytes_per_launch": 1 << 40, "us_per_launch": x, "launches_timed": 480, "kernels": kernels, "in_token_loop_rocprof": kernels},
+           "tpot_model_sec_5_1": mode, "link": mode, "signal_diagnostics": {"recall": [x] * 100}, "cache_misses_per_layer": [x] * 100,
+           "prefill": {k: x for k in ("prompt_tokens", "ms_per_prompt", "ms_per_layer", "prompt_tokens_per_s", "h2d_gbs_wall")},
+           "cpu_baseline": {"value": x, "unit": "tokens/s", "cores": 16, "kind": "oracle", "cpu_model": "m" * 60, "sample": "s" * 240, "single_thread": mode}}
+    required = {"metric": "m" * 100, "value": x, "unit": "tokens/s", "n_gpus": 1, "steps": 48, "warmup": 4, "ms_per_step": x,
+                "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic"}
+    line = bench.headline(dict(required, **run, other_workloads={f"workload_name_{i}": run if i else {"error": "e" * 5000} for i in range(8)}))
+    assert len(json.dumps(line)) < 5000
+    assert {k: line[k] for k in required} == required and line["config"] == run["config"]
+    assert line["other_workloads"]["workload_name_1"] == {"speculative_tpot_ms": 1234.6, "on_demand_tpot_ms": 1234.6,
+                                                          "tpot_reduction_vs_on_demand": 1234.6, "roofline_frac": 1234.6}
+
+
 def test_workload_pools_fit_what_a_box_can_pin():
     """Every registered workload must be runnable: its host pool stays under the page-locking limit, if need be by
     holding fewer layers' expert blocks than the model has (layers then share blocks, everything else is per layer)."""
