@@ -6,12 +6,12 @@ kernel a leg makes.  rocprofv3 lists every dispatch in order; this script cuts t
 those counts, so that durations (kernel trace) and HBM byte counters (PMC runs) can be reported per leg
 instead of as one average over the whole command.
 
-  kernel trace:  rocprofv3 --kernel-trace --stats --output-format csv -d DIR -o bench -- python3 bench.py --legs-file LEGS
-  HBM traffic :  rocprofv3 --pmc FETCH_SIZE --output-format csv -d DIR_F -o bench -- python3 bench.py ... --calibrate-copy --legs-file LEGS_P
-                 rocprofv3 --pmc WRITE_SIZE --output-format csv -d DIR_W -o bench -- python3 bench.py ... --calibrate-copy --legs-file LEGS_P
+  kernel trace:  rocprofv3 --kernel-trace --stats --output-format csv -d DIR -o bench -- python3 bench.py --legs-file LEGS --json-file RECORD.json
+  HBM traffic :  rocprofv3 --pmc FETCH_SIZE --output-format csv -d DIR_F -o bench -- python3 bench.py ... --calibrate-copy --legs-file LEGS_P --json-file RECORD_P.json
+                 rocprofv3 --pmc WRITE_SIZE --output-format csv -d DIR_W -o bench -- python3 bench.py ... --calibrate-copy --legs-file LEGS_P --json-file RECORD_P.json
 
-  python -m paper_2603_19289_amd.profile_summary --trace DIR --legs LEGS --bench-json LINE.json \\
-         --pmc-fetch DIR_F --pmc-write DIR_W --pmc-legs LEGS_P --pmc-bench-json LINE_P.json --out profiles --tag bench_default
+  python -m paper_2603_19289_amd.profile_summary --trace DIR --legs LEGS --bench-json RECORD.json \\
+         --pmc-fetch DIR_F --pmc-write DIR_W --pmc-legs LEGS_P --pmc-bench-json RECORD_P.json --out profiles --tag bench_default
 
 Writes profiles/<tag>_kernel_trace_by_leg.md, profiles/<tag>_pmc_hbm_traffic.md and merges the figures
 into profiles/kernel_trace_by_leg.json and profiles/hbm_traffic.json, which bench.py reads.
@@ -78,6 +78,30 @@ def cut_by_legs(sequence, legs, symbol):
     return out
 
 
+# What a leg counts (bench.py): launches of any of these, by substrings of kernel names.  With resident predicted experts
+# the gate/up projection shares the routing's launch, so such a launch counts as routing and as gate/up.
+COUNTED = ["route_pair_kernel or route_gateup", "gateup_b1", "down_combine_b1", "stream_read",
+           "expert_mfma_kernel<true or route_gateup_mfma or expert_tile_kernel<true",
+           "expert_mfma_kernel<false or expert_tile_kernel<false", "advance_kernel"]
+# What is reported, each kernel under the first of these that its name contains: a joint launch in a row of its own.
+REPORTED = ["route_gateup_b1", "route_gateup_mfma", "route_pair_kernel", "gateup_b1", "down_combine_b1", "stream_read",
+            "expert_mfma_kernel<true", "expert_mfma_kernel<false", "expert_tile_kernel<true", "expert_tile_kernel<false",
+            "advance_kernel"]
+
+
+def attribute(dispatches, legs):
+    """dispatches: (kernel name, value) in launch order.  Returns {(leg name, reported kernel): values}."""
+    out = {}
+    for symbol in COUNTED:
+        seq = [d for d in dispatches if named(d[0], symbol)]
+        for leg_name, part in cut_by_legs(seq, legs, symbol).items():
+            for reported in REPORTED:
+                values = [v for n, v in part if next(r for r in REPORTED if r in n) == reported]
+                if values:
+                    out[leg_name, reported] = values      # a joint launch comes twice, with the same values
+    return out
+
+
 def category(leg_name):
     parts = leg_name.split("/")
     if " + " in leg_name:
@@ -122,8 +146,6 @@ def main():
     ap.add_argument("--out", default="profiles")
     ap.add_argument("--tag", required=True)
     a = ap.parse_args()
-    symbols = ["route_pair_kernel or route_gateup", "gateup_b1", "down_combine_b1", "stream_read", "expert_mfma_kernel<true or route_gateup_mfma or expert_tile_kernel<true",
-               "expert_mfma_kernel<false or expert_tile_kernel<false", "advance_kernel"]
 
     if a.trace:
         legs = json.load(open(a.legs))
@@ -133,25 +155,20 @@ def main():
         per_wl = collections.defaultdict(lambda: collections.defaultdict(dict))
         md = [f"# rocprofv3 kernel trace of bench.py, durations per leg ({a.tag})\n",
               "Command (run from /tmp with TMPDIR=/tmp on the MI355X box, repository at $R):\n",
-              "    " + (a.trace_command or "rocprofv3 --kernel-trace --stats --output-format csv -d DIR -o bench -- python3 $R/bench.py --legs-file LEGS") + "\n",
+              "    " + (a.trace_command or "rocprofv3 --kernel-trace --stats --output-format csv -d DIR -o bench -- python3 $R/bench.py --legs-file LEGS --json-file RECORD.json") + "\n",
               "Every dispatch of the trace is attributed to the leg of bench.py that launched it (the legs run one after the",
               "other; their launch counts come from --legs-file).  Durations are the trace's End - Start per dispatch.\n"]
         if bench:
             md.append(f"bench.py's own line in this profiled run: speculative TPOT {bench['ms_per_step']:.2f} ms ({bench['value']:.2f} tokens/s), "
                       f"on-demand TPOT {bench['on_demand']['tpot_ms']:.2f} ms.\n")
         md += ["| workload | leg | kernel | launches | mean (us) | median (us) | min (us) | max (us) |", "|---|---|---|---|---|---|---|---|"]
-        for sym in symbols:
-            seq = [(int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in rows if named(r["Kernel_Name"], sym)]
-            if not seq:
-                continue
-            for leg_name, durs in cut_by_legs(seq, legs["legs"], sym).items():
-                if not durs:
-                    continue
-                wl, cat = category(leg_name)
-                cur = per_wl[wl][cat].get(sym)
-                if cur:                                   # several repetitions of one mode: pool them
-                    durs = cur["_durs"] + durs
-                per_wl[wl][cat][sym] = dict(stats_us(durs), _durs=durs)
+        dispatches = [(r["Kernel_Name"], (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3) for r in rows]
+        for (leg_name, sym), durs in attribute(dispatches, legs["legs"]).items():
+            wl, cat = category(leg_name)
+            cur = per_wl[wl][cat].get(sym)
+            if cur:                                       # several repetitions of one mode: pool them
+                durs = cur["_durs"] + durs
+            per_wl[wl][cat][sym] = dict(stats_us(durs), _durs=durs)
         for wl in per_wl:
             for cat in sorted(per_wl[wl]):
                 for sym, s in per_wl[wl][cat].items():
@@ -181,16 +198,11 @@ def main():
             if not cal:
                 raise SystemExit("no calibration copy in the PMC run (bench.py --calibrate-copy)")
             scale[ctr] = CAL_BYTES / cal[-1]              # bytes per count
-            for sym in symbols:
-                seq = [v for n, v in disp if named(n, sym)]
-                if not seq:
-                    continue
-                for leg_name, vals in cut_by_legs(seq, legs["legs"], sym).items():
-                    if vals:
-                        per.setdefault((leg_name, sym), {})[ctr] = (len(vals), statistics.median(vals))
+            for key, vals in attribute(disp, legs["legs"]).items():
+                per.setdefault(key, {})[ctr] = (len(vals), statistics.median(vals))
         md = [f"# rocprofv3 PMC summary: HBM bytes per launch of bench.py's kernels ({a.tag})\n",
               "Commands (one counter per run, run from /tmp with TMPDIR=/tmp, repository at $R):\n",
-              "    " + (a.pmc_command or "rocprofv3 --pmc FETCH_SIZE|WRITE_SIZE --output-format csv -d DIR -o bench -- python3 $R/bench.py ... --calibrate-copy --legs-file LEGS") + "\n",
+              "    " + (a.pmc_command or "rocprofv3 --pmc FETCH_SIZE|WRITE_SIZE --output-format csv -d DIR -o bench -- python3 $R/bench.py ... --calibrate-copy --legs-file LEGS --json-file RECORD.json") + "\n",
               f"Scaling: the last dispatch of each run is a plain device-to-device copy of {CAL_BYTES:,} bytes (read once, written once);",
               f"one FETCH_SIZE count is {scale['FETCH_SIZE']:.2f} bytes and one WRITE_SIZE count {scale['WRITE_SIZE']:.2f} bytes on this box.\n",
               "| workload | leg | kernel | launches | FETCH_SIZE median | WRITE_SIZE median | bytes read | bytes written | algorithmic bytes | traffic / algorithmic |",
