@@ -339,7 +339,8 @@ class Bench:
             "layer_step": {"kernels": step_names, "algorithmic_bytes": step_bytes, "us_back_to_back": step_us,
                            "gbs": step_bytes / step_us / 1e3, "frac_of_hbm_peak": step_bytes / step_us / 1e3 / HBM_PEAK_GBS,
                            "routing_share_of_kernel_time": kern["route_true_and_prediction"]["us_per_launch"] / step_us,
-                           "note": "one routing launch (true routing + prediction) and the expert launches of one cache wave"},
+                           "note": "one routing launch (true routing + prediction) and the expert launches of one cache wave, each by itself; "
+                                   "where predicted experts are in their slots a speculative loop runs routing and gate/up as one launch"},
             "in_token_loop_event_pairs": {m: breakdown[m]["expert_launches_us_per_cache_wave_event_pairs"] for m in breakdown},
             "in_token_loop_rocprof": (self.trace.get("workloads") or {}).get(wl.name),
             "in_token_loop_rocprof_source": os.path.relpath(TRACE_FILE, ROOT) if (self.trace.get("workloads") or {}).get(wl.name) else None}

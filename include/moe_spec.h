@@ -66,7 +66,9 @@ typedef struct {
   int32_t predict_in_on_demand;     /* on-demand mode only: 1 still runs the prediction so that
                                        hit statistics exist; 0 skips it (timing runs) */
   int32_t profile;                  /* 1: bracket copies and kernels with timing events and fill
-                                       copy_ms / compute_ms / stall_ms (adds a sync per token) */
+                                       copy_ms / compute_ms / stall_ms (adds a sync per token).  Routing and
+                                       experts are then always launches of their own; without it, predicted
+                                       experts that needed no copy share the routing's launch */
   int32_t copy_engine;              /* how experts travel host -> device on the copy stream:
                                        0: one hipMemcpyAsync per expert (DMA engine);
                                        1: one gather-copy kernel per request that reads the pinned
@@ -268,6 +270,7 @@ const char *moe_spec_last_error(const moe_spec_ctx *ctx);
  * the prediction for the next layer (both routers and k default-vector rows per token), both on a batch of
  * max_batch tokens,
  * 9 = a kernel that only reads the W_down bytes of the same slots (8 is not used).
+ * The launches that a decode step shares between routing and gate/up are not among them.
  * Writes the mean milliseconds per launch and the weight bytes one launch reads.
  * The slot contents are whatever the cache holds; outputs go to scratch.  Not inside a decode step. */
 int moe_spec_time_kernel(moe_spec_ctx *ctx, int which, int reps, double *ms_per_launch,

@@ -569,9 +569,10 @@ __global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs 
   route_pair_body<WT, SPLIT, NCH, ROWS, PROJ>(a, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, vec_lds, sh);
 }
 
-// The same routing for a launch in which expert workgroups hide its latency: the same sums in the same order, but
-// nothing is kept in registers or asked for early, so that it does not take registers away from them (about 200 in
-// route_pair_body).  Router rows are dealt over the wavefronts of the token's n_wg workgroups, any number of them.
+// The same routing for a launch in which expert workgroups hide its latency: nothing is kept in registers or asked for
+// early, so that it does not take registers away from them (about 200 in route_pair_body).  The double-precision sums are
+// those of route_pair_body in its order, but for the squares of a norm, which it adds in fours from a thread's second
+// group of columns on.  Router rows are dealt over the wavefronts of the token's n_wg workgroups, any number of them.
 template <typename WT, bool PROJ>
 __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const int wg, const int n_wg, const int b,
                                                 const int n_tokens, double *vec_lds, RouteShared &sh) {

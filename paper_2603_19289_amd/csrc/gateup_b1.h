@@ -11,8 +11,9 @@ constexpr int kB1Block = 256;
 static_assert(kB1Waves == kB1Block / kWave, "the launch rules count wavefronts");
 
 // s_l = LN_l(r_l), rounded as the router input is, into LDS [H] by the whole workgroup: the routing of the layer
-// runs beside this workgroup and cannot hand its own copy over in time.  NG = groups of 256 chunks per row.  Split
-// in two so that the weight loads can be issued between the loads of r_l and the waits of the reduction.
+// runs beside this workgroup and cannot hand its own copy over in time.  Both sum the squares in double precision, from
+// a thread's second group of columns on in another order.  NG = groups of 256 chunks per row.  Split in two so that the
+// weight loads can be issued between the loads of r_l and the waits of the reduction.
 template <typename WT, int NG>
 struct InputNorm {
   static constexpr int VN = Packed<WT>::N;

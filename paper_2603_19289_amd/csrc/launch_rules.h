@@ -26,9 +26,12 @@ inline GateupSplit gateup_b1_split(int nch, int I, int n) {
 // first loads came back after 9 us instead of 2.4 and the launch took 20.5 us on 128 experts of 768 x 2048 (50 MB).
 // Up to 64 MB of weights one gate/up workgroup goes on each compute unit that does not route: 2.7 TB/s, at which the
 // routing takes its usual time, 18.6 us together.  Up to 256 MB the workgroups fill the device once, so that none is
-// left over for a second round (32 experts of 2880 x 2880, 133 MB: a token's eight layers 666 -> 628 us).  Beyond,
-// the routing is short beside the stream and the split of the plain launch is the best (470 MB: 688 us for six
-// layers, 700 when filled once).  Two rows per wavefront (pairs) 335 us, this rule 321 us for six layers of the first.
+// left over for a second round.  Beyond, the routing is short beside the stream and the split of the plain launch is as
+// good.  Microseconds per layer step, one workgroup per unit / filled once / plain split, for 8 of 64 experts of 2048
+// columns, 2 of 8 of 4096 and 4 of 32 of 2880: at 24 to 32 MB 20.7 / 20.7 / 20.4, 22.7 / 25.0 / 24.5, 24.4 / 25.6 / 25.7;
+// at 64 MB 30.5 / 28.3 / 29.2, 28.7 / 29.9 / 30.5, 30.9 / 31.2 / 32.4; at 96 MB 37.7 / 34.3 / 36.2, 36.2 / 35.4 / 38.8,
+// 38.0 / 36.5 / 38.0; at 192 MB 67.7 / 57.7 / 59.8, 59.6 / 57.8 / 60.3, 62.7 / 58.0 / 58.4; at 256 MB 84.1 / 72.1 / 72.1,
+// 75.1 / 72.8 / 72.6, 77.6 / 72.1 / 71.8; at 320, 384 MB 102.1 / 87.1 / 86.1, 106.0 / 103.9 / 106.5.
 // Never fewer workgroups than a quarter of the compute units, however many of them the routing takes: with routing that
 // fills the device there would be none.  Never pairs: those end at 67 MB.
 inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_t wbytes, int n_route, int blocks_per_cu,
