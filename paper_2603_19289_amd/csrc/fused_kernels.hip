@@ -14,6 +14,8 @@
 // Who may wait for whom: a workgroup only waits for the other workgroups of its own token, which the
 // launcher checks to fit on the device together (groups are dispatched in order, so the earliest
 // unfinished group always gets the next free compute units).
+#include <type_traits>
+
 #include "device_utils.h"
 #include "expert_mfma.h"
 #include "gateup_b1.h"
@@ -807,19 +809,29 @@ hipError_t launch_route_pair_t(const RoutePairArgs &a, hipStream_t st) {
   return launch_route_pair_s<WT, 4, 1>(a, need4, st);
 }
 
+// Workgroups of the joint batch-one launch that a compute unit holds.
+template <typename WT, int NCH>
+hipError_t route_gateup_b1_per_cu(int H, int *n) {
+  const size_t lds = size_t(H) * sizeof(double);
+  static int blocks_per_cu = -1;               // per instantiation
+  static size_t checked_lds = 0;
+  if (blocks_per_cu < 0 || lds > checked_lds) {
+    int now = 0;
+    hipError_t e = prepare_kernel(route_gateup_b1_kernel<WT, NCH>, lds, &now);
+    if (e != hipSuccess) return e;
+    blocks_per_cu = now;
+    checked_lds = lds;
+  }
+  *n = blocks_per_cu;
+  return hipSuccess;
+}
+
 template <typename WT, int NCH>
 hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
   const size_t lds = size_t(ra.H) * sizeof(double);
   const int n_route = ra.E;                    // one workgroup per router row
-  static int blocks_per_cu = -1;               // per instantiation
-  static size_t checked_lds = 0;
-  if (blocks_per_cu < 0 || lds > checked_lds) {
-    int n = 0;
-    hipError_t e = prepare_kernel(route_gateup_b1_kernel<WT, NCH>, lds, &n);
-    if (e != hipSuccess) return e;
-    blocks_per_cu = n;
-    checked_lds = lds;
-  }
+  int blocks_per_cu = 0;
+  if (hipError_t e = route_gateup_b1_per_cu<WT, NCH>(ra.H, &blocks_per_cu); e != hipSuccess) return e;
   // the routing workgroups wait for one another: they must fit on the device together
   if (long(n_route) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
   const GateupSplit split = beside_routing_split(NCH, a.I, a.H, act.n, sizeof(WT), n_route, blocks_per_cu, g_compute_units);
@@ -828,15 +840,26 @@ hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a
   return hipGetLastError();
 }
 
+// Calls f with the chunks of a weight row per lane (a constant, rounded up to what the kernel is built for).
+template <typename WT, typename F>
+hipError_t with_row_chunks(int H, F f) {
+  const int need = (H + kWave * Packed<WT>::N - 1) / (kWave * Packed<WT>::N);
+  if (need <= 1) return f(std::integral_constant<int, 1>());
+  if (need <= 2) return f(std::integral_constant<int, 2>());
+  if (need <= 4) return f(std::integral_constant<int, 4>());
+  if (need <= 6) return f(std::integral_constant<int, 6>());
+  if (need <= 8) return f(std::integral_constant<int, 8>());
+  return hipErrorInvalidValue;
+}
+
 template <typename WT>
 hipError_t launch_route_gateup_b1_t(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
-  const int need = (a.H + kWave * Packed<WT>::N - 1) / (kWave * Packed<WT>::N);
-  if (need <= 1) return launch_route_gateup_b1_n<WT, 1>(ra, a, act, st);
-  if (need <= 2) return launch_route_gateup_b1_n<WT, 2>(ra, a, act, st);
-  if (need <= 4) return launch_route_gateup_b1_n<WT, 4>(ra, a, act, st);
-  if (need <= 6) return launch_route_gateup_b1_n<WT, 6>(ra, a, act, st);
-  if (need <= 8) return launch_route_gateup_b1_n<WT, 8>(ra, a, act, st);
-  return hipErrorInvalidValue;
+  return with_row_chunks<WT>(a.H, [&](auto nch) { return launch_route_gateup_b1_n<WT, nch()>(ra, a, act, st); });
+}
+
+template <typename WT>
+hipError_t route_gateup_b1_per_cu_t(int H, int *n) {
+  return with_row_chunks<WT>(H, [&](auto nch) { return route_gateup_b1_per_cu<WT, nch()>(H, n); });
 }
 
 template <int NT, int KSPLIT, bool PROJ>
@@ -881,8 +904,14 @@ hipError_t launch_route_gateup_mfma_t(const RoutePairArgs &ra, const ExpertArgs 
 }  // namespace
 
 // Rows of up to 8 chunks per lane: beyond, the LDS that the routing needs would leave the gate/up workgroups too few
-// places.
-bool route_gateup_b1_supported(int H, int dtype) { return H <= kWave * 8 * (dtype == 1 ? 8 : 4); }
+// places.  The routing workgroups, one per expert, have to fit on the device together, which a partition of it may not
+// have room for where the routing by itself, with fewer registers, has (float32 rows of 7 or 8 chunks).
+bool route_gateup_b1_supported(int H, int E, int dtype) {
+  int per_cu = 0;
+  if (H > kWave * 8 * (dtype == 1 ? 8 : 4)) return false;
+  const hipError_t e = dtype == 1 ? route_gateup_b1_per_cu_t<uint16_t>(H, &per_cu) : route_gateup_b1_per_cu_t<float>(H, &per_cu);
+  return e == hipSuccess && long(E) <= long(per_cu) * g_compute_units;
+}
 
 hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,
                                   hipStream_t st) {

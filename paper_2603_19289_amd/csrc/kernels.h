@@ -134,7 +134,7 @@ struct ExpertArgs {
 
 // A batch of one whose executed experts are known before the layer's routing and are resident: the routing of the layer
 // (and the prediction) and the gate/up launch side by side in one launch; `act` in execution-position order.
-bool route_gateup_b1_supported(int H, int dtype);
+bool route_gateup_b1_supported(int H, int E, int dtype);
 hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,
                                   hipStream_t st);
 

@@ -771,9 +771,9 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   // (profile = 1 brackets routing and experts separately.)
   const bool est_beside = use_est && !cfg.diagnostics && route_pair_supported(H, cfg.dtype) && cfg.predict_signal == 0;
   const bool beside_routing =
-      exec_pred && !cfg.profile && c->pending_union.size() <= size_t(S) &&
-      ((fast_b1 && fused_route && route_gateup_b1_supported(H, cfg.dtype)) ||
-       (use_mfma && (fused_route || est_beside) && route_gateup_mfma_supported(H))) && !c->ready_pending[layer];
+      exec_pred && !cfg.profile && c->pending_union.size() <= size_t(S) && !c->ready_pending[layer] &&
+      ((fast_b1 && fused_route && route_gateup_b1_supported(H, E, cfg.dtype)) ||
+       (use_mfma && (fused_route || est_beside) && route_gateup_mfma_supported(H)));
   // The layer's first routing launch, with or without the experts beside it.
   auto launch_first_routing = [&](RoutePairArgs &ra) {
     if (!beside_routing) return launch_route_pair(ra, cfg.dtype, c->compute);

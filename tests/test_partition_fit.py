@@ -1,0 +1,52 @@
+"""The joint launch of routing and gate/up on devices with fewer compute units (a partition of the GPU), on the CPU: a
+program whose own definitions take the place of the runtime's occupancy queries asks the library."""
+import os
+import subprocess
+
+from paper_2603_19289_amd import moe_spec as M
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2603_19289_amd")
+
+PROGRAM = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include <cstdlib>
+#include <dlfcn.h>
+static int cus, per_cu;
+extern "C" hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+extern "C" hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+extern "C" hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = cus; return hipSuccess; }
+extern "C" hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = per_cu; return hipSuccess; }
+int main(int argc, char **argv) {
+  cus = std::atoi(argv[1]); per_cu = std::atoi(argv[2]);
+  void *lib = dlopen(argv[3], RTLD_NOW | RTLD_GLOBAL);
+  if (!lib) { std::puts(dlerror()); return 2; }
+  auto supported = reinterpret_cast<bool (*)(int, int, int)>(dlsym(lib, "_ZN8moe_spec25route_gateup_b1_supportedEiii"));
+  if (!supported) { std::puts(dlerror()); return 2; }
+  for (int i = 4; i + 2 < argc; i += 3) std::printf("%d", supported(std::atoi(argv[i]), std::atoi(argv[i + 1]), std::atoi(argv[i + 2])));
+  return 0;
+}
+"""
+
+
+def test_joint_launch_is_taken_only_where_its_routing_workgroups_fit(tmp_path):
+    src, exe = tmp_path / "ask.cpp", tmp_path / "ask"
+    src.write_text(PROGRAM)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-rdynamic", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}/include", str(src), "-o", str(exe), "-ldl"], check=True)
+    M.lib()                                                  # built, or the failure is about the build
+
+    def ask(cus, per_cu, *shapes):
+        args = [str(v) for shape in shapes for v in shape]
+        done = subprocess.run([str(exe), str(cus), str(per_cu), os.path.join(PKG, "libmoe_spec.so")] + args, capture_output=True,
+                              text=True, timeout=60, env=dict(os.environ, LD_LIBRARY_PATH=f"{rocm}/lib"))
+        assert done.returncode == 0, done.stdout + done.stderr
+        return done.stdout
+
+    # (hidden, experts, dtype 1 = bf16): the whole device takes every number of experts, at the sizes the kernel is built for
+    assert ask(256, 2, (2048, 256, 1), (4096, 256, 1), (4104, 8, 1), (2048, 256, 0), (2056, 8, 0)) == "11010"
+    # 64 and 32 units: as many experts as workgroups fit, and not one more
+    assert ask(64, 2, (2048, 128, 1), (2048, 129, 1), (2048, 128, 0), (2048, 192, 0)) == "1010"
+    assert ask(32, 2, (2048, 64, 1), (512, 65, 1), (1024, 64, 0), (2048, 96, 0)) == "1010"
+    assert ask(32, 3, (1024, 96, 0), (1024, 97, 0)) == "10"
