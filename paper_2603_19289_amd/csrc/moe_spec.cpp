@@ -24,6 +24,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "kernels.h"
@@ -198,6 +199,7 @@ struct moe_spec_ctx {
   std::vector<int> pending_union;               // sorted union of predicted ids (host copy)
   std::vector<int> pending_ids;                 // the predicted ids [B,k] in position order (host copy)
   ActiveList pending_wave0{};                   // slots of its first wave (already requested)
+  bool step_begun = false;                      // a step for next_layer has launched kernels and did not come to its end
   std::vector<int> look_ids[3];                 // lookahead = 2: ids predicted for layer l two layers earlier, at [l % 3]
 
   // statistics
@@ -693,6 +695,7 @@ int moe_spec_begin_token(moe_spec_ctx *c) {
   c->next_layer = 0;
   c->batch = 0;
   c->have_pending = false;
+  c->step_begun = false;
   c->pending_union.clear();
   for (auto &v : c->look_ids) v.clear();
   c->st.tokens += 1;
@@ -724,6 +727,8 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   hipError_t e;
 
   if (int rc = c->check_waits()) return rc;
+  const bool again = c->step_begun;             // a step that failed is called once more
+  c->step_begun = true;
   c->step_seq += 1;
   TimedSpan *sp_route = c->open_span(0, c->compute);
 
@@ -771,7 +776,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   // (profile = 1 brackets routing and experts separately.)
   const bool est_beside = use_est && !cfg.diagnostics && route_pair_supported(H, cfg.dtype) && cfg.predict_signal == 0;
   const bool beside_routing =
-      exec_pred && !cfg.profile && c->pending_union.size() <= size_t(S) && !c->ready_pending[layer] &&
+      exec_pred && !again && !cfg.profile && c->pending_union.size() <= size_t(S) && !c->ready_pending[layer] &&
       ((fast_b1 && fused_route && route_gateup_b1_supported(H, E, cfg.dtype)) ||
        (use_mfma && (fused_route || est_beside) && route_gateup_mfma_supported(H)));
   // The layer's first routing launch, with or without the experts beside it.
@@ -1028,7 +1033,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   for (size_t w0 = 0, wave = 0; w0 < exec_union.size(); w0 += S, ++wave) {
     ActiveList act{};
     int copies = 0;
-    if (exec_pred && wave == 0) {
+    if (exec_pred && wave == 0 && !again) {
       act = c->pending_wave0;                   // requested one step earlier; its copies may still be in flight
     } else {
       std::vector<int> req(exec_union.begin() + w0, exec_union.begin() + std::min(exec_union.size(), w0 + S));
@@ -1076,18 +1081,21 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     c->close_span(sp_comb, c->compute);
   }
 
-  // --- prefetch the first wave of the predicted experts of layer l+1
-  c->have_pending = do_pred;
+  // --- prefetch the first wave of the predicted experts of layer l+1.  What the context carries over to that layer is
+  // replaced only when nothing can fail any more: a step that fails (an expert never registered) may be called again,
+  // and executes the prediction made for its own layer then, after asking for its experts anew (further cache waves may
+  // have taken their slots).
+  std::vector<int> next_union, next_ids;
+  ActiveList next_wave0{};
   if (do_pred && prefetching) {
     int rc = c->wait_ids(c->mb_next, batch * k);
     if (rc) return rc;
     if ((rc = c->check_ids(c->mb_next->ids, batch * k))) return rc;
-    c->pending_union = moe_spec_ctx::sorted_union(c->mb_next->ids, batch * k);
-    c->pending_ids.assign(c->mb_next->ids, c->mb_next->ids + batch * k);
-    std::vector<int> req(c->pending_union.begin(),
-                         c->pending_union.begin() + std::min<size_t>(c->pending_union.size(), S));
+    next_union = moe_spec_ctx::sorted_union(c->mb_next->ids, batch * k);
+    next_ids.assign(c->mb_next->ids, c->mb_next->ids + batch * k);
+    std::vector<int> req(next_union.begin(), next_union.begin() + std::min<size_t>(next_union.size(), S));
     int copies = 0;
-    rc = c->request(layer + 1, req, &c->pending_wave0, &copies);
+    rc = c->request(layer + 1, req, &next_wave0, &copies);
     if (rc) return rc;
   }
   if (score_look) {
@@ -1117,6 +1125,13 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     if ((rc = c->request(layer + 2, uni, &hinted_slots, &copies))) return rc;
   }
 
+  c->step_begun = false;
+  c->have_pending = do_pred;
+  if (do_pred && prefetching) {
+    c->pending_union = std::move(next_union);
+    c->pending_ids = std::move(next_ids);
+    c->pending_wave0 = next_wave0;
+  }
   c->batch = batch;
   c->next_layer = layer + 1;
   if (last) c->token_open = false;
@@ -1434,6 +1449,7 @@ int moe_spec_reset(moe_spec_ctx *c) {
   c->clock_running = false;
   c->token_open = false;
   c->have_pending = false;
+  c->step_begun = false;
   c->next_layer = 0;
   c->pending_union.clear();
   return MOE_SPEC_OK;

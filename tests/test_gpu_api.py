@@ -497,3 +497,53 @@ def test_estimator_projection_and_gate_up_beside_the_routing_equal_separate_laun
                         batch=batch, tokens=2, slots=experts, seed=47)
     print(f"[case] estimator beside routing H={hidden} E={experts} m={m} B={batch}", flush=True)
     beside_and_separate(wl, f"route_gateup_mfma_kernel{kernel}", (3, 2), estimator=W.make_estimator(wl, m=m, n=2))
+
+
+@pytest.mark.parametrize("dtype,batch,slots", [("bf16", 1, 8), ("f32", 1, 3), ("bf16", 5, 3), ("bf16", 3, 8), ("f32", 3, 4)])
+@pytest.mark.parametrize("mode", ["MODE_SPECULATIVE", "MODE_PREFETCH_HINT"])
+def test_a_step_that_failed_for_an_unregistered_expert_can_be_called_again(dtype, batch, slots, mode, monkeypatch):
+    """The prefetch for the next layer fails when its experts are not registered yet.  Registered afterwards, the same
+    step is called again and executes what it would have executed, with every expert in its slots, with copies and with
+    several cache waves."""
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(name="again", n_layers=4, hidden=264, n_experts=8, top_k=2, inter=72, dtype=dtype, batch=batch,
+                        tokens=1, slots=slots, seed=61)
+    res, ex, _ = build(wl, "random")
+    x0, eps = W.make_inputs(wl)
+    r = [torch.from_numpy(x0[0] + 0.3 * eps[0, l]).cuda() for l in range(wl.n_layers)]
+    register = M.moe_spec_load_host_experts
+    held_back = []
+
+    def later(ctx, layer, *rest):
+        if layer == 0:
+            register(ctx, layer, *rest)
+        else:
+            held_back.append((ctx, layer) + rest)
+
+    def token(eng):
+        log = []
+        eng.begin_token()
+        for l in range(wl.n_layers):
+            if held_back:
+                with pytest.raises(M.MoeSpecError) as ei:
+                    eng.layer_step(l, r[l])
+                assert ei.value.code == M.ESTATE and "never registered" in str(ei.value)
+                register(*held_back.pop(0))
+            out, ids = eng.layer_step(l, r[l], want_ids=True)
+            torch.cuda.synchronize()
+            log.append([out.cpu()] + [t.cpu() for _, t in sorted(ids.items())])
+        return log
+
+    plain = engine_for(wl, getattr(M, mode), res, ex)
+    with monkeypatch.context() as m:
+        m.setattr(M, "moe_spec_load_host_experts", later)
+        eng = engine_for(wl, getattr(M, mode), res, ex)
+    try:
+        assert len(held_back) == wl.n_layers - 1
+        for _ in range(2):
+            for step, (a, b) in enumerate(zip(token(eng), token(plain))):
+                for x, y in zip(a, b):
+                    assert torch.equal(x.view(torch.int32), y.view(torch.int32)), step
+    finally:
+        eng.close()
+        plain.close()
