@@ -209,11 +209,19 @@ __global__ __launch_bounds__(kBlock) void down_combine_b1_kernel(const ExpertArg
 
 // ---------------------------------------------------------------------------------------------
 // Matrix-core kernels for decode batches of two and more (bf16 weights) and for prefill
-template <bool GATEUP, int NT, int KSPLIT>
-__global__ __launch_bounds__(kBlock) void expert_mfma_kernel(const ExpertArgs a, const ActiveList act,
+template <bool GATEUP, int NT, int KSPLIT, bool STREAM>
+__global__ __launch_bounds__(kBlock) void expert_mfma_kernel(const ExpertArgs a, const TokenLists lists,
                                                              const uint16_t *act_q, uint16_t *hq_out) {
   __shared__ ExpertMfmaShared<GATEUP, NT, KSPLIT> sh;
-  expert_mfma_body<GATEUP, NT, KSPLIT>(a, act, act_q, hq_out, blockIdx.x, blockIdx.y, blockIdx.z, sh);
+  expert_mfma_body<GATEUP, NT, KSPLIT>(a, DecodeTokens<STREAM>{lists, int(blockIdx.y)}, act_q, hq_out, blockIdx.x, sh);
+}
+
+template <bool GATEUP, int NT, int KSPLIT>
+__global__ __launch_bounds__(kBlock) void expert_mfma_lists_kernel(const ExpertArgs a, const ActiveList act,
+                                                                   const uint16_t *act_q, uint16_t *hq_out) {
+  __shared__ ExpertMfmaShared<GATEUP, NT, KSPLIT> sh;
+  expert_mfma_body<GATEUP, NT, KSPLIT>(a, PrefillTokens{act, int(blockIdx.y), int(blockIdx.z)}, act_q, hq_out,
+                                       blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -577,23 +585,49 @@ void launch_down_combine_b1(const ExpertArgs &a, const ActiveList &act, hipStrea
   else launch_down_combine_b1_n<WT, 4, 4>(a, act, st);
 }
 
-// Tiles of 16 positions that an expert may need in one launch (or one plane of 64).
-int mfma_token_tiles(const ExpertArgs &a) {
-  return ((a.pos_list ? std::min(a.list_tokens, kMaxBatch) : a.B) + 15) / 16;
-}
-
-template <bool GATEUP, int KSPLIT>
-hipError_t launch_expert_mfma_k(const ExpertArgs &a, const ActiveList &act, const uint16_t *act_q, uint16_t *hq,
+template <bool GATEUP, int NT, bool STREAM>
+hipError_t launch_expert_mfma_n(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq,
                                 hipStream_t st) {
   const int rows = GATEUP ? a.I : a.H;
+  const int positions = int(lists.expert[lists.n] & 0xffff);
+  return with_ksplit(GATEUP ? gateup_ksplit(a.H, (a.B + 15) / 16) : down_ksplit(a.I, rows, lists.n, positions), [&](auto ksplit) {
+    const int rows_per_wg = 16 * kWaves / ksplit();
+    const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg, lists.n), block(kBlock);
+    hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, NT, ksplit(), STREAM>), grid, block, 0, st, a, lists, act_q, hq);
+    return hipGetLastError();
+  });
+}
+
+template <bool GATEUP, bool STREAM>
+hipError_t launch_expert_mfma_s(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq,
+                                hipStream_t st) {
+  switch (decode_tiles(lists.most)) {
+    case 1: return launch_expert_mfma_n<GATEUP, 1, STREAM>(a, lists, act_q, hq, st);
+    case 2: return launch_expert_mfma_n<GATEUP, 2, STREAM>(a, lists, act_q, hq, st);
+    default: return launch_expert_mfma_n<GATEUP, 4, STREAM>(a, lists, act_q, hq, st);
+  }
+}
+
+template <bool GATEUP>
+hipError_t launch_expert_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq,
+                              hipStream_t st) {
+  return whole_lines(GATEUP ? a.H : a.I) ? launch_expert_mfma_s<GATEUP, true>(a, lists, act_q, hq, st)
+                                         : launch_expert_mfma_s<GATEUP, false>(a, lists, act_q, hq, st);
+}
+
+// The same over position lists on the device (prefill), 64 positions per grid plane.
+template <bool GATEUP, int KSPLIT>
+hipError_t launch_expert_mfma_lists_k(const ExpertArgs &a, const ActiveList &act, const uint16_t *act_q, uint16_t *hq,
+                                      hipStream_t st) {
+  const int rows = GATEUP ? a.I : a.H;
   const int rows_per_wg = 16 * kWaves / KSPLIT;
-  const int planes = a.pos_list ? (a.list_tokens + kMaxBatch - 1) / kMaxBatch : 1;
+  const int planes = (a.list_tokens + kMaxBatch - 1) / kMaxBatch;
   const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg, act.n, planes), block(kBlock);
-  switch (mfma_token_tiles(a)) {
-    case 1: hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, 1, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
-    case 2: hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, 2, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
-    case 3: hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, 3, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
-    default: hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, 4, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
+  switch ((std::min(a.list_tokens, kMaxBatch) + 15) / 16) {
+    case 1: hipLaunchKernelGGL((expert_mfma_lists_kernel<GATEUP, 1, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
+    case 2: hipLaunchKernelGGL((expert_mfma_lists_kernel<GATEUP, 2, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
+    case 3: hipLaunchKernelGGL((expert_mfma_lists_kernel<GATEUP, 3, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
+    default: hipLaunchKernelGGL((expert_mfma_lists_kernel<GATEUP, 4, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
   }
   return hipGetLastError();
 }
@@ -623,21 +657,19 @@ bool tiles_pay(const ExpertArgs &a, int n_experts, bool gateup, int cus) {
 }
 
 template <bool GATEUP>
-hipError_t launch_expert_mfma(const ExpertArgs &a, const ActiveList &act, const uint16_t *act_q, uint16_t *hq,
-                              hipStream_t st) {
-  if (a.pos_list) {
-    int cus = 0;
-    if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
-    if (tiles_pay(a, act.n, GATEUP, cus)) {
-      const int wgs = (cus + 7) / 8 * 8;                 // one per compute unit: 97 KB of LDS
-      hipLaunchKernelGGL((expert_tile_kernel<GATEUP>), dim3(wgs), dim3(kTileBlock), 0, st, a, act, act_q, hq);
-      return hipGetLastError();
-    }
+hipError_t launch_expert_mfma_lists(const ExpertArgs &a, const ActiveList &act, const uint16_t *act_q, uint16_t *hq,
+                                    hipStream_t st) {
+  int cus = 0;
+  if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
+  if (tiles_pay(a, act.n, GATEUP, cus)) {
+    const int wgs = (cus + 7) / 8 * 8;                   // one per compute unit: 97 KB of LDS
+    hipLaunchKernelGGL((expert_tile_kernel<GATEUP>), dim3(wgs), dim3(kTileBlock), 0, st, a, act, act_q, hq);
+    return hipGetLastError();
   }
-  const int ksplit = mfma_ksplit(GATEUP ? a.H : a.I, mfma_token_tiles(a));
-  if (ksplit == 4) return launch_expert_mfma_k<GATEUP, 4>(a, act, act_q, hq, st);
-  if (ksplit == 2) return launch_expert_mfma_k<GATEUP, 2>(a, act, act_q, hq, st);
-  return launch_expert_mfma_k<GATEUP, 1>(a, act, act_q, hq, st);
+  const int ksplit = gateup_ksplit(GATEUP ? a.H : a.I, (std::min(a.list_tokens, kMaxBatch) + 15) / 16);
+  if (ksplit == 4) return launch_expert_mfma_lists_k<GATEUP, 4>(a, act, act_q, hq, st);
+  if (ksplit == 2) return launch_expert_mfma_lists_k<GATEUP, 2>(a, act, act_q, hq, st);
+  return launch_expert_mfma_lists_k<GATEUP, 1>(a, act, act_q, hq, st);
 }
 
 template <typename K>
@@ -676,15 +708,22 @@ hipError_t launch_down(const ExpertArgs &a, const ActiveList &act, int dtype, hi
 
 // bf16 weights, batch >= kMfmaMinBatch: s_q is s_l as bf16 [B,H]; hq (bf16 [B,k,I]) is written by the gate/up
 // launch and read by the down launch.
-hipError_t launch_gateup_mfma(const ExpertArgs &a, const ActiveList &act, const uint16_t *s_q, uint16_t *hq,
+hipError_t launch_gateup_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *s_q, uint16_t *hq,
                               hipStream_t st) {
-  if (act.n <= 0) return hipSuccess;
-  return launch_expert_mfma<true>(a, act, s_q, hq, st);
+  return lists.n <= 0 ? hipSuccess : launch_expert_mfma<true>(a, lists, s_q, hq, st);
 }
 
-hipError_t launch_down_mfma(const ExpertArgs &a, const ActiveList &act, const uint16_t *hq, hipStream_t st) {
-  if (act.n <= 0) return hipSuccess;
-  return launch_expert_mfma<false>(a, act, hq, nullptr, st);
+hipError_t launch_down_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *hq, hipStream_t st) {
+  return lists.n <= 0 ? hipSuccess : launch_expert_mfma<false>(a, lists, hq, nullptr, st);
+}
+
+hipError_t launch_gateup_prefill(const ExpertArgs &a, const ActiveList &act, const uint16_t *s_q, uint16_t *hq,
+                                 hipStream_t st) {
+  return act.n <= 0 ? hipSuccess : launch_expert_mfma_lists<true>(a, act, s_q, hq, st);
+}
+
+hipError_t launch_down_prefill(const ExpertArgs &a, const ActiveList &act, const uint16_t *hq, hipStream_t st) {
+  return act.n <= 0 ? hipSuccess : launch_expert_mfma_lists<false>(a, act, hq, nullptr, st);
 }
 
 hipError_t launch_expert_lists(const int32_t *ids, int tokens, int k, int E, int32_t *pos, int32_t *count,

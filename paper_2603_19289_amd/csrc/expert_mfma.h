@@ -1,8 +1,13 @@
 // The expert FFN of a batch on the matrix cores, as a device function: expert_kernels.hip launches it by itself,
 // fused_kernels.hip beside the routing of the same layer.
 #pragma once
+#include <type_traits>
+
 #include "device_utils.h"
 #include "kernels.h"
+#ifdef MOE_DEV
+#include <cstdlib>
+#endif
 
 namespace moe_spec {
 
@@ -40,11 +45,17 @@ __device__ __forceinline__ void gather_tokens(const int32_t *ids, int n_ids, int
 // Matrix-core kernels for decode batches of two and more (bf16 weights) and for prefill: the
 // expert FFN as 16x16x32 bf16 MFMA tiles.  The launches stay HBM-bound, but one weight fragment
 // meets up to 16 tokens per instruction, where the general kernels above fetch every token's
-// activations from LDS for every weight chunk and are LDS-bound from a few tokens on.  A operand = 16 weight rows, B operand = up to 16 tokens routed to the expert, K walks
-// the reduction dimension 64 columns per step: lane (m, g) = (lane % 16, lane / 16) loads the 32
-// contiguous bytes at column k0 + 16 g of row m (so four lanes cover one 128-byte line) and
-// feeds the first 8 columns to one MFMA and the next 8 to a second one; the B operand is read
-// with the same column assignment, which is all that the contraction needs.
+// activations from LDS for every weight chunk and are LDS-bound from a few tokens on.
+// A operand = 16 weight rows, B operand = up to 16 tokens routed to the expert; K walks the reduction 128 columns per
+// step.  HBM decides how the weights are read: a load that takes 64 bytes of each of 16 rows, as the operand wants them,
+// streams at 5.5 to 5.8 TB/s however it is split (read-only kernel, 700 and 300 MB), one that takes 256 bytes of each of
+// four rows at 6.6 to 6.8, past the caches.  So lane (r, c) = (lane % 4, lane / 4) loads chunk c of 16 bytes of rows
+// r, 4 + r, 8 + r and 12 + r, and the four registers are turned in place (rows_to_lanes) until lane (m, g) =
+// (lane % 16, lane / 16) holds chunks 4 g .. 4 g + 3 of row m: 48 moves for 4 KB, a seventh of the time these take to
+// arrive.  The B operand is read with the same column assignment, which is all that the contraction needs.
+// Gate/up and down of 21 experts of 2880 x 2880, 12 positions of each most: 117.5 -> 101.5 us (6.9 TB/s) and
+// 64.4 -> 54.0; 48 experts of 768 x 2048, 32 tokens: 56.0 -> 47.7 and 31.1 -> 28.2; 8 of 14336 x 4096, 64 tokens: 349 ->
+// 352 and 232 -> 201.
 // Accumulator layout: lane holds token column lane % 16, rows 4 (lane / 16) .. +3.
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -56,132 +67,177 @@ __device__ __forceinline__ bf16x8_t load_bf16x8(const uint16_t *p, bool valid) {
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
-// One step of the reduction for one wavefront: the weight fragments of its 16 rows and the token
-// fragments of up to NT tiles, each the 2 x 16 bytes a lane feeds to two MFMAs.
+// One step of the reduction for one wavefront, 128 columns: 16 weight rows in four loads, tokens of up to NT tiles.
 template <bool GATEUP, int NT>
 struct MfmaStep {
-  bf16x8_t w0[2], w1[2];       // rows of W_gate (or W_down), rows of W_up
-  bf16x8_t x[NT][2];
+  uint4 w0[4], w1[4];          // rows of W_gate (or W_down), rows of W_up
+  bf16x8_t x[NT][4];
 };
+
+// Lane bit (SHIFT / 4's bit 2 or 3) against the choice between two registers: afterwards a holds what both registers
+// had in the lanes with the bit clear, b what they had in the others.
+template <int SHIFT, int HIGH, int LOW>
+__device__ __forceinline__ void swap_lanes(uint32_t &a, uint32_t &b) {
+  const uint32_t from_a = a;
+  a = __builtin_amdgcn_update_dpp(a, b, 0x110 + SHIFT, 0xf, HIGH, false);          // row_shr
+  b = __builtin_amdgcn_update_dpp(b, from_a, 0x100 + SHIFT, 0xf, LOW, false);      // row_shl
+}
+
+// w[i], lane (r, c) = (lane % 4, lane / 4): chunk c of row 4 i + r  ->  w[s], lane (m, g): chunk 4 g + s of row m.
+__device__ __forceinline__ void rows_to_lanes(uint4 (&w)[4]) {
+#define MOE_SWAP(f)                                                              \
+  swap_lanes<4, 0xa, 0x5>(w[0].f, w[1].f); swap_lanes<4, 0xa, 0x5>(w[2].f, w[3].f); \
+  swap_lanes<8, 0xc, 0x3>(w[0].f, w[2].f); swap_lanes<8, 0xc, 0x3>(w[1].f, w[3].f);
+  MOE_SWAP(x) MOE_SWAP(y) MOE_SWAP(z) MOE_SWAP(w)
+#undef MOE_SWAP
+}
+
+template <bool STREAM>
+__device__ __forceinline__ uint4 load_weights(const char *p) {
+  return STREAM ? load_stream<uint4>(p) : *reinterpret_cast<const uint4 *>(p);
+}
 
 // GATEUP: hq[f, row] = bf16(silu(W_gate[row,:] . s_b) * (W_up[row,:] . s_b)),  act_q = s_l as bf16 [tokens, K]
 // else  : y[f, row]  = W_down[row,:] . hq[f,:],                                  act_q = hq [tokens*k, K]
-// The positions f = b*k + j routed to the expert come either from the [B,k] id table of a decode
-// batch (B <= 64, one grid plane) or, with a.pos_list, from per-expert lists over any number of
-// tokens, 64 positions per plane.  Weights are read with ordinary loads: a lane's
-// two 16-byte loads of a step take alternate quarters of the same 128-byte lines, and the planes
-// of an expert share its weights through the caches; streaming loads measured 8-10 % slower here.
 template <bool GATEUP, int NT, int KSPLIT>
 struct ExpertMfmaShared {
-  int list[kMaxBatch];
-  int n_list;
+  int list[kMaxBatch];         // prefill
   // partial accumulators of the wavefronts that share a tile: [wave][token tile][gate | up][register][lane]
   float partial[KSPLIT > 1 ? kMfmaWaves : 1][NT][GATEUP ? 2 : 1][4][kWave];
 };
 
-// One workgroup: row block bx, expert by of the active list, plane bz of 64 positions.
-template <bool GATEUP, int NT, int KSPLIT>
-__device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const ActiveList &act, const uint16_t *act_q,
-                                                 uint16_t *hq_out, const int bx, const int by, const int bz,
+// The positions f = b*k + j routed to an expert: in a decode batch from the host's lists (no search, so the first
+// weights are on their way at once), in prefill from
+// per-expert lists on the device over any number of tokens, 64 positions per grid plane.
+// STREAM: weights, read once, bypass the caches (nontemporal).  Not where two steps share a line of a row, and not in
+// prefill, where the planes of an expert share its weights through the caches.
+template <bool STREAM>
+struct DecodeTokens {
+  const TokenLists &lists;
+  int by;
+  static constexpr bool kStream = STREAM, kEarly = true;
+  __device__ __forceinline__ int slot() const { return int(lists.expert[by] >> 16); }
+  __device__ __forceinline__ int count(const ExpertArgs &, int *, int) const {
+    return int(lists.expert[by + 1] & 0xffff) - int(lists.expert[by] & 0xffff);
+  }
+  __device__ __forceinline__ int position(const int *, int i) const { return lists.pos[(lists.expert[by] & 0xffff) + i]; }
+  __device__ __forceinline__ static int f_of(int p) { return p & 1023; }
+  __device__ __forceinline__ static int token_of(int p, int) { return p >> 10; }
+};
+struct PrefillTokens {
+  const ActiveList &act;
+  int by, bz;
+  static constexpr bool kStream = false, kEarly = false;
+  __device__ __forceinline__ int slot() const { return act.slot[by]; }
+  __device__ __forceinline__ int count(const ExpertArgs &a, int *list, int tid) const {
+    const int e = act.expert[by], first = bz * kMaxBatch;
+    const int n = min(kMaxBatch, a.pos_count[e] - first);
+    if (n > 0) {                               // the same for the whole workgroup
+      if (tid < n) list[tid] = a.pos_list[size_t(e) * a.list_stride + first + tid];
+      __syncthreads();
+    }
+    return n;
+  }
+  __device__ __forceinline__ int position(const int *list, int i) const { return list[i]; }
+  __device__ __forceinline__ static int f_of(int p) { return p; }
+  __device__ __forceinline__ static int token_of(int p, int k) { return p / k; }
+};
+
+// One workgroup: row block bx of the expert that tok names.
+template <bool GATEUP, int NT, int KSPLIT, typename Tokens>
+__device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Tokens &tok, const uint16_t *act_q,
+                                                 uint16_t *hq_out, const int bx,
                                                  ExpertMfmaShared<GATEUP, NT, KSPLIT> &sh) {
-  int (&list)[kMaxBatch] = sh.list;
   auto &partial = sh.partial;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int m = lane & 15, g = lane >> 4;
   const int K = GATEUP ? a.H : a.I;            // reduction length
   const int R = GATEUP ? a.I : a.H;            // output rows
 
-  const int e = act.expert[by];
-  const uint16_t *wbase = reinterpret_cast<const uint16_t *>(a.pool + size_t(act.slot[by]) * a.slot_bytes);
+  const uint16_t *wbase = reinterpret_cast<const uint16_t *>(a.pool + size_t(tok.slot()) * a.slot_bytes);
   // KSPLIT wavefronts share 16 output rows: they split the reduction dimension into equal parts
-  // (whole 64-column steps) and add their partial tiles in LDS.  Many short chains of dependent
-  // loads that start at different columns keep HBM busier than few long ones that walk their rows
-  // in step: a read-only probe of this access pattern reaches 6.2 TB/s with four wavefronts per 16
-  // rows against 4.6 TB/s with one.  Short reductions are not split: the launcher picks KSPLIT.
+  // (of whole 64 columns) and add their partial tiles in LDS: many short chains of dependent loads
+  // keep HBM busier than few long ones.  Short reductions are not split: the launcher picks KSPLIT.
   const int row_base = (bx * (kMfmaWaves / KSPLIT) + wave / KSPLIT) * 16;
   const int part = wave % KSPLIT;
   const bool rows_inside = row_base < R;       // a workgroup's last tiles may lie past the matrix
   const int k_part = (K + KSPLIT * 64 - 1) / (KSPLIT * 64) * 64;
   const int k_begin = part * k_part, k_end = rows_inside ? min(K, k_begin + k_part) : k_begin;
-  const int my_row = min(row_base + m, R - 1);
-  const uint16_t *p0 = wbase + (GATEUP ? size_t(0) : size_t(2) * a.I * a.H) + size_t(my_row) * K;
-  const uint16_t *p1 = p0 + size_t(a.I) * a.H;             // W_up row (GATEUP only)
+  // base and column in scalar registers, a lane's rows as byte offsets (an expert block is smaller than 4 GB)
+  const char *p0 = reinterpret_cast<const char *>(wbase + (GATEUP ? size_t(0) : size_t(2) * a.I * a.H));
+  const char *p1 = p0 + size_t(2) * a.I * a.H;             // W_up (GATEUP only)
+  uint32_t woff[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) woff[i] = (uint32_t(min(row_base + 4 * i + (lane & 3), R - 1)) * uint32_t(K) + 8 * (lane >> 2)) * 2;
 
   // columns past the wavefront's part load nothing and contribute zeros, so the staged loop
   // below may run one step beyond the end
   auto fetch_w = [&](int k0, MfmaStep<GATEUP, NT> &st) {
-    const int kk = k0 + 16 * g;
-    const bool v0 = kk < k_end, v1 = kk + 8 < k_end;
-    st.w0[0] = load_bf16x8(p0 + kk, v0);
-    st.w0[1] = load_bf16x8(p0 + kk + 8, v1);
-    if (GATEUP) { st.w1[0] = load_bf16x8(p1 + kk, v0); st.w1[1] = load_bf16x8(p1 + kk + 8, v1); }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { st.w0[i] = make_uint4(0u, 0u, 0u, 0u); if (GATEUP) st.w1[i] = make_uint4(0u, 0u, 0u, 0u); }
+    if (k0 + 8 * (lane >> 2) < k_end) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        st.w0[i] = load_weights<Tokens::kStream>(p0 + size_t(k0) * 2 + woff[i]);
+        if (GATEUP) st.w1[i] = load_weights<Tokens::kStream>(p1 + size_t(k0) * 2 + woff[i]);
+      }
+    }
   };
   MfmaStep<GATEUP, NT> even, odd;              // the loads of one step are in flight during the other's MFMAs
-  // down projection with up to two token tiles: the first weights are on their way while the token list is
-  // built (measured: 6 % faster there; 7 % slower in the gate/up kernel, which has twice the weight registers
-  // per step, and 20 % slower with four token tiles, as in prefill)
-  constexpr bool kEarlyWeights = !GATEUP && NT <= 2;
+  constexpr bool kEarlyWeights = Tokens::kEarly || (!GATEUP && NT <= 2);
   if (kEarlyWeights) fetch_w(k_begin, even);
 
-  int n;
-  if (a.pos_list) {
-    const int first = bz * kMaxBatch;
-    n = min(kMaxBatch, a.pos_count[e] - first);
-    if (n <= 0) return;                        // the same for the whole workgroup
-    if (tid < n) list[tid] = a.pos_list[size_t(e) * a.list_stride + first + tid];
-    __syncthreads();
-  } else {
-    gather_tokens(a.exec_ids, a.B * a.k, e, list, &sh.n_list, tid);
-    n = sh.n_list;
-  }
-  if (n == 0) return;                          // the same for the whole workgroup
+  const int n = tok.count(a, sh.list, tid);
+  if (n <= 0) return;                          // the same for the whole workgroup
   if (KSPLIT == 1 && !rows_inside) return;     // nothing to share, nobody waits for this wavefront
   const int ntiles = (n + 15) / 16;
 
   const uint16_t *bp[NT];
   bool bvalid[NT];
+  int fpos[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int idx = t * 16 + m;
     bvalid[t] = idx < n;
-    const int f = bvalid[t] ? list[idx] : 0;
-    bp[t] = act_q + size_t(GATEUP ? f / a.k : f) * K;
+    const int p = bvalid[t] ? tok.position(sh.list, idx) : 0;
+    fpos[t] = Tokens::f_of(p);
+    bp[t] = act_q + size_t(GATEUP ? Tokens::token_of(p, a.k) : fpos[t]) * K;
   }
   f32x4_t acc0[NT], acc1[NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) { acc0[t] = f32x4_t{0.f, 0.f, 0.f, 0.f}; acc1[t] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+  for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   auto fetch_x = [&](int k0, MfmaStep<GATEUP, NT> &st) {
-    const int kk = k0 + 16 * g;
-    const bool v0 = kk < k_end, v1 = kk + 8 < k_end;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       if (t < ntiles) {
-        st.x[t][0] = load_bf16x8(bp[t] + kk, v0 && bvalid[t]);
-        st.x[t][1] = load_bf16x8(bp[t] + kk + 8, v1 && bvalid[t]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) st.x[t][c] = load_bf16x8(bp[t] + k0 + 32 * g + 8 * c, k0 + 32 * g + 8 * c < k_end && bvalid[t]);
       }
     }
   };
-  auto fetch = [&](int k0, MfmaStep<GATEUP, NT> &st) { fetch_w(k0, st); fetch_x(k0, st); };
-  auto multiply = [&](const MfmaStep<GATEUP, NT> &st) {
+  auto multiply = [&](MfmaStep<GATEUP, NT> &st) {
+    rows_to_lanes(st.w0);
+    if (GATEUP) rows_to_lanes(st.w1);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       if (t < ntiles) {
-        acc0[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(st.w0[0], st.x[t][0], acc0[t], 0, 0, 0);
-        acc0[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(st.w0[1], st.x[t][1], acc0[t], 0, 0, 0);
-        if (GATEUP) {
-          acc1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(st.w1[0], st.x[t][0], acc1[t], 0, 0, 0);
-          acc1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(st.w1[1], st.x[t][1], acc1[t], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          acc0[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.w0[c]), st.x[t][c], acc0[t], 0, 0, 0);
+          if (GATEUP)
+            acc1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.w1[c]), st.x[t][c], acc1[t], 0, 0, 0);
         }
       }
     }
   };
-  if (kEarlyWeights) fetch_x(k_begin, even);
-  else fetch(k_begin, even);
-  for (int k0 = k_begin; k0 < k_end; k0 += 128) {
-    fetch(k0 + 64, odd);
+  if (!kEarlyWeights) fetch_w(k_begin, even);
+  for (int k0 = k_begin; k0 < k_end; k0 += 256) {
+    fetch_x(k0, even);
+    fetch_w(k0 + 128, odd);
     multiply(even);
-    fetch(k0 + 128, even);
+    fetch_x(k0 + 128, odd);
+    fetch_w(k0 + 256, even);
     multiply(odd);
   }
 
@@ -223,7 +279,7 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Acti
           }
         }
       }
-      const int f = list[t * 16 + m];
+      const int f = fpos[t];
       if (GATEUP) {
         uint16_t q[4];
 #pragma unroll
@@ -242,15 +298,42 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Acti
   }
 }
 
-// Wavefronts per 16-row tile by the length of the reduction: each should still walk at least eight
-// 64-column steps, below that the shared start-up (token lists, partial sums) outweighs what the extra
-// parallelism wins.  With a single tile of tokens there is less to start up and two steps are enough: down
-// projection of about 30 experts of 2048 x 768, 4 tokens, 21.2 / 18.9 / 18.1 us with 1 / 2 / 4 wavefronts (with
-// 32 tokens, two tiles, 27.5 / 28.6 / 31.7 us).
-inline int mfma_ksplit(int K, int token_tiles) {
+// Wavefronts per 16-row tile.  gateup_ksplit: each should still walk eight steps of 64 columns, below that the shared
+// start-up (partial sums) outweighs what the extra parallelism wins; in batches of a single tile of tokens two are enough
+// (16 experts of 1024 columns, 64 tokens, 1 / 2 / 4 wavefronts: 15.2 / 13.5 / 14.9 us; 12 of them, 8 tokens: 13.6 / 12.3 /
+// 10.3).  By the tokens of the batch, not of an expert, so that a launch beside the routing and one of its own add in the
+// same order.  Prefill splits both its products like that.
+inline int gateup_ksplit(int K, int token_tiles) {
   const int steps = (K + 63) / 64;
   if (steps >= 32 || (token_tiles == 1 && steps >= 8)) return 4;
   return steps >= 16 ? 2 : 1;
 }
+
+// Down projection of a decode batch: as many wavefronts as leave each two whole steps of 128 columns, unless its experts
+// have eight positions or more on average and there are two workgroups per compute unit without a split: then the
+// activations weigh as much as the weights, and the four wavefronts of a workgroup share them if they walk the same
+// columns.  Microseconds with 1 / 2 / 4 wavefronts: 30 experts of 768 columns x 2048 rows at 1 position each 18.2 / 18.0 /
+// 19.5, 48 of them at 5 27.4 / 28.2 / 29.9, 21 of 2880 x 2880 at 1.5 60.9 / 58.1 / 54.1, 8 of 14336 x 4096 at 4 148 / 155 /
+// 153, at 8 164 / 177 / 182, at 16 201 / 238 / 249, 5 of them at 1.6 130 / 103 / 90.6, 16 of 2048 x 2048 at 16 31 / 35 / 37,
+// 16 of 1024 x 1024 at 16 (256 workgroups without a split) 10.7 / 9.1 / 9.0.
+inline int down_ksplit(int K, int rows, int experts, int positions) {
+  if (positions >= 8 * experts && long(experts) * ((rows + 63) / 64) >= 512) return 1;
+  return K >= 1024 ? 4 : K >= 512 ? 2 : 1;
+}
+
+template <int V> using int_c = std::integral_constant<int, V>;
+
+// Calls f with the wavefronts per 16-row tile as a constant.
+template <typename F>
+hipError_t with_ksplit(int ksplit, F f) {
+  if (ksplit == 4) return f(int_c<4>());
+  if (ksplit == 2) return f(int_c<2>());
+  return f(int_c<1>());
+}
+
+// Decode batches: tiles of 16 positions of the expert that has most (1, 2 or 4), and whether two steps of a row never
+// share a line, so that the weights may bypass the caches.
+inline int decode_tiles(int most) { return most <= 16 ? 1 : most <= 32 ? 2 : 4; }
+inline bool whole_lines(int K) { return K % 64 == 0; }
 
 }  // namespace moe_spec

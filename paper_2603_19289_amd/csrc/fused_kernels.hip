@@ -722,9 +722,9 @@ __global__ __launch_bounds__(kBlock) void norm_rows_kernel(const ExpertArgs a, u
 // those with the estimator's projection 16.5 + 31 / 4.6 + 37 us.  One router row and two default-vector rows in flight
 // per wavefront instead of two and four: 56 us for the second.
 template <int NT, int KSPLIT, bool PROJ>
-__global__ __launch_bounds__(kBlock, NT <= 2 ? 4 : 2)
-void route_gateup_mfma_kernel(const RoutePairArgs ra, const ExpertArgs a, const ActiveList act, const uint16_t *s_q,
-                              uint16_t *hq, const int n_wg, const int n_route, const int row_blocks) {
+__global__ __launch_bounds__(kBlock, NT <= 1 ? 3 : NT == 4 && KSPLIT == 1 ? 1 : 2)
+void route_gateup_mfma_kernel(const RoutePairArgs ra, const ExpertArgs a, const TokenLists lists, const uint16_t *s_q,
+                              uint16_t *hq, const int n_wg, const int n_route, const int row_blocks, const int stream) {
   extern __shared__ __align__(16) unsigned char beside_lds[];
   if (int(blockIdx.x) < n_route) {
     RouteShared &sh = *reinterpret_cast<RouteShared *>(beside_lds);
@@ -733,8 +733,9 @@ void route_gateup_mfma_kernel(const RoutePairArgs ra, const ExpertArgs a, const 
     return;
   }
   const int i = blockIdx.x - n_route;
-  expert_mfma_body<true, NT, KSPLIT>(a, act, s_q, hq, i % row_blocks, i / row_blocks, 0,
-                                     *reinterpret_cast<ExpertMfmaShared<true, NT, KSPLIT> *>(beside_lds));
+  ExpertMfmaShared<true, NT, KSPLIT> &sh = *reinterpret_cast<ExpertMfmaShared<true, NT, KSPLIT> *>(beside_lds);
+  if (stream) expert_mfma_body<true, NT, KSPLIT>(a, DecodeTokens<true>{lists, i / row_blocks}, s_q, hq, i % row_blocks, sh);
+  else expert_mfma_body<true, NT, KSPLIT>(a, DecodeTokens<false>{lists, i / row_blocks}, s_q, hq, i % row_blocks, sh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -863,7 +864,7 @@ hipError_t route_gateup_b1_per_cu_t(int H, int *n) {
 }
 
 template <int NT, int KSPLIT, bool PROJ>
-hipError_t launch_route_gateup_mfma_n(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act,
+hipError_t launch_route_gateup_mfma_n(const RoutePairArgs &ra, const ExpertArgs &a, const TokenLists &lists,
                                       const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
   const size_t route_lds = (sizeof(RouteShared) + 15) / 16 * 16 + size_t(ra.H) * sizeof(double);
   const size_t lds = std::max(route_lds, sizeof(ExpertMfmaShared<true, NT, KSPLIT>));
@@ -880,25 +881,17 @@ hipError_t launch_route_gateup_mfma_n(const RoutePairArgs &ra, const ExpertArgs 
   if (long(n_wg) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
   constexpr int rows_per_wg = 16 * kMfmaWaves / KSPLIT;
   const int row_blocks = (a.I + rows_per_wg - 1) / rows_per_wg, n_route = n_wg * ra.B;
-  hipLaunchKernelGGL((route_gateup_mfma_kernel<NT, KSPLIT, PROJ>), dim3(n_route + row_blocks * act.n), dim3(kBlock), lds,
-                     st, ra, a, act, s_q, hq, n_wg, n_route, row_blocks);
+  hipLaunchKernelGGL((route_gateup_mfma_kernel<NT, KSPLIT, PROJ>), dim3(n_route + row_blocks * lists.n), dim3(kBlock), lds,
+                     st, ra, a, lists, s_q, hq, n_wg, n_route, row_blocks, int(whole_lines(a.H)));
   return hipGetLastError();
 }
 
-template <int NT, int KSPLIT>
-hipError_t launch_route_gateup_mfma_k(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act,
+template <int NT, bool PROJ>
+hipError_t launch_route_gateup_mfma_t(const RoutePairArgs &ra, const ExpertArgs &a, const TokenLists &lists,
                                       const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
-  return ra.proj ? launch_route_gateup_mfma_n<NT, KSPLIT, true>(ra, a, act, s_q, hq, st)
-                 : launch_route_gateup_mfma_n<NT, KSPLIT, false>(ra, a, act, s_q, hq, st);
-}
-
-template <int NT>
-hipError_t launch_route_gateup_mfma_t(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act,
-                                      const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
-  const int ksplit = mfma_ksplit(a.H, NT);
-  if (ksplit == 4) return launch_route_gateup_mfma_k<NT, 4>(ra, a, act, s_q, hq, st);
-  if (ksplit == 2) return launch_route_gateup_mfma_k<NT, 2>(ra, a, act, s_q, hq, st);
-  return launch_route_gateup_mfma_k<NT, 1>(ra, a, act, s_q, hq, st);
+  return with_ksplit(gateup_ksplit(a.H, (a.B + 15) / 16), [&](auto ksplit) {
+    return launch_route_gateup_mfma_n<NT, ksplit(), PROJ>(ra, a, lists, s_q, hq, st);
+  });
 }
 
 }  // namespace
@@ -920,17 +913,24 @@ hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, 
 
 bool route_gateup_mfma_supported(int H) { return H <= 4096; }   // beyond, LDS for two workgroups per compute unit only
 
-hipError_t launch_route_gateup_mfma(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, uint16_t *s_q,
+hipError_t launch_route_gateup_mfma(const RoutePairArgs &ra, const ExpertArgs &a, const TokenLists &lists, uint16_t *s_q,
                                     uint16_t *hq, hipStream_t st) {
   const size_t lds = size_t(a.H) * sizeof(float);
   if (a.H <= 2048) hipLaunchKernelGGL(norm_rows_kernel<1>, dim3(a.B), dim3(kBlock), lds, st, a, s_q);
   else hipLaunchKernelGGL(norm_rows_kernel<2>, dim3(a.B), dim3(kBlock), lds, st, a, s_q);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  switch ((a.B + 15) / 16) {
-    case 1: return launch_route_gateup_mfma_t<1>(ra, a, act, s_q, hq, st);
-    case 2: return launch_route_gateup_mfma_t<2>(ra, a, act, s_q, hq, st);
-    case 3: return launch_route_gateup_mfma_t<3>(ra, a, act, s_q, hq, st);
-    default: return launch_route_gateup_mfma_t<4>(ra, a, act, s_q, hq, st);
+  if (ra.proj) {                               // a token tile count of its own for every sixteen tokens
+    switch ((a.B + 15) / 16) {
+      case 1: return launch_route_gateup_mfma_t<1, true>(ra, a, lists, s_q, hq, st);
+      case 2: return launch_route_gateup_mfma_t<2, true>(ra, a, lists, s_q, hq, st);
+      case 3: return launch_route_gateup_mfma_t<3, true>(ra, a, lists, s_q, hq, st);
+      default: return launch_route_gateup_mfma_t<4, true>(ra, a, lists, s_q, hq, st);
+    }
+  }
+  switch (decode_tiles(lists.most)) {
+    case 1: return launch_route_gateup_mfma_t<1, false>(ra, a, lists, s_q, hq, st);
+    case 2: return launch_route_gateup_mfma_t<2, false>(ra, a, lists, s_q, hq, st);
+    default: return launch_route_gateup_mfma_t<4, false>(ra, a, lists, s_q, hq, st);
   }
 }
 

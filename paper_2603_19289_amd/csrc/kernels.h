@@ -112,6 +112,15 @@ struct ActiveList {           // experts executed by one launch and where they l
   int16_t slot[kMaxExperts];
 };
 
+// The token positions of each expert of a matrix-core launch of a decode batch, sorted by the host (which knows the ids
+// of every step it launches experts for) and handed over as a kernel argument.
+struct TokenLists {
+  uint32_t expert[kMaxExperts + 1];   // slot << 16 | index of the expert's first entry in pos; [n]: one past the last
+  uint16_t pos[kMaxBatch * kMaxTopK]; // token << 10 | position f = token * k + j, grouped by expert
+  int32_t n;                          // experts
+  int32_t most;                       // positions of the expert that has most
+};
+
 struct ExpertArgs {
   const char *pool;           // first slot of the layer's pool
   size_t slot_bytes;          // distance between slots (expert block bytes)
@@ -125,8 +134,7 @@ struct ExpertArgs {
   const float *gain;          // [H]: the residual and its norm's gain, where s_l is formed beside the routing
   float eps;
   int B, k, H, I, bf16, E;
-  // matrix-core kernels over more than one decode batch (prefill): positions grouped by expert as
-  // written by launch_expert_lists for list_tokens tokens; null: the [B,k] table exec_ids is searched
+  // prefill: positions grouped by expert as written by launch_expert_lists for list_tokens tokens
   const int32_t *pos_list;    // [E, list_stride]
   const int32_t *pos_count;   // [E]
   int list_stride, list_tokens;   // E is read with them: positions per expert on average
@@ -138,9 +146,9 @@ bool route_gateup_b1_supported(int H, int E, int dtype);
 hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,
                                   hipStream_t st);
 
-// The same for bf16 batches on the matrix cores (s_q, hq as for launch_gateup_mfma, s_q written here); `act` as there.
+// The same for bf16 batches on the matrix cores (s_q, hq as for launch_gateup_mfma, s_q written here).
 bool route_gateup_mfma_supported(int H);
-hipError_t launch_route_gateup_mfma(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, uint16_t *s_q,
+hipError_t launch_route_gateup_mfma(const RoutePairArgs &ra, const ExpertArgs &a, const TokenLists &lists, uint16_t *s_q,
                                     uint16_t *hq, hipStream_t st);
 
 // Host-to-device gather copy: each entry moves one expert block from the pinned pool to a slot.
@@ -171,9 +179,12 @@ hipError_t launch_down(const ExpertArgs &a, const ActiveList &act, int dtype, hi
 hipError_t launch_combine(const ExpertArgs &a, hipStream_t st);
 // reads n16 16-byte units of every active slot, starting first16 units into the slot, and nothing else
 hipError_t launch_stream_read(const ExpertArgs &a, const ActiveList &act, size_t first16, size_t n16, hipStream_t st);
-hipError_t launch_gateup_mfma(const ExpertArgs &a, const ActiveList &act, const uint16_t *s_q, uint16_t *hq,
+hipError_t launch_gateup_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *s_q, uint16_t *hq,
                               hipStream_t st);
-hipError_t launch_down_mfma(const ExpertArgs &a, const ActiveList &act, const uint16_t *hq, hipStream_t st);
+hipError_t launch_down_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *hq, hipStream_t st);
+hipError_t launch_gateup_prefill(const ExpertArgs &a, const ActiveList &act, const uint16_t *s_q, uint16_t *hq,
+                                 hipStream_t st);     // with a.pos_list
+hipError_t launch_down_prefill(const ExpertArgs &a, const ActiveList &act, const uint16_t *hq, hipStream_t st);
 hipError_t launch_expert_lists(const int32_t *ids, int tokens, int k, int E, int32_t *pos, int32_t *count,
                                hipStream_t st);      // pos [E, tokens], count [E]
 constexpr int kMfmaMinBatch = 2;      // bf16 decode batches from here on use the matrix-core expert kernels

@@ -478,6 +478,27 @@ struct moe_spec_ctx {
     return at<unsigned long long>(lay.zslots) + (size_t(which) * 2 + parity) * cfg.max_batch * cfg.n_experts;
   }
 
+  // The positions of the active experts, by expert, for the matrix-core launches (ids [n_ids], inside [0, E)).
+  void token_lists(const ActiveList &act, const std::vector<int> &ids, TokenLists *out) const {
+    int at[kMaxExperts];                         // index of an expert in act, or -1
+    std::fill(at, at + cfg.n_experts, -1);
+    for (int i = 0; i < act.n; ++i) at[act.expert[i]] = i;
+    int count[kMaxExperts] = {};
+    for (int id : ids) if (at[id] >= 0) count[at[id]] += 1;
+    out->n = act.n;
+    out->most = 0;
+    int first = 0, next[kMaxExperts];
+    for (int i = 0; i < act.n; ++i) {
+      out->expert[i] = uint32_t(act.slot[i]) << 16 | uint32_t(first);
+      next[i] = first;
+      first += count[i];
+      out->most = std::max(out->most, count[i]);
+    }
+    out->expert[act.n] = uint32_t(first);
+    for (int f = 0; f < int(ids.size()); ++f)
+      if (const int i = at[ids[f]]; i >= 0) out->pos[next[i]++] = uint16_t(f / cfg.top_k << 10 | f);
+  }
+
   static std::vector<int> sorted_union(const int32_t *ids, int n) {
     std::vector<int> u(ids, ids + n);
     std::sort(u.begin(), u.end());
@@ -760,6 +781,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   xa.bf16 = cfg.dtype == MOE_SPEC_BF16;
   const bool fast_b1 = batch == 1 && b1_supported(H, cfg.dtype) && !cfg.accumulate_defaults;
   const bool use_mfma = cfg.dtype == MOE_SPEC_BF16 && batch >= kMfmaMinBatch;
+  TokenLists lists;                             // matrix-core batches
   ActiveList by_pos{};                          // batch 1: the slots in position order (the k experts are one cache wave)
   auto slots_by_position = [&](const std::vector<int> &ids) {
     by_pos.n = k;
@@ -788,8 +810,8 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       return launch_route_gateup_b1(ra, xa, by_pos, cfg.dtype, c->compute);
     }
     ra.s_out_q = nullptr;                       // written for the expert workgroups before the launch
-    xa.exec_ids = c->at<int32_t>(c->lay.pend_ids[layer & 1]);
-    return launch_route_gateup_mfma(ra, xa, c->pending_wave0, c->at<uint16_t>(c->lay.s_q), c->at<uint16_t>(c->lay.h),
+    c->token_lists(c->pending_wave0, c->pending_ids, &lists);
+    return launch_route_gateup_mfma(ra, xa, lists, c->at<uint16_t>(c->lay.s_q), c->at<uint16_t>(c->lay.h),
                                     c->compute);
   };
   if (fused_route) {
@@ -1058,9 +1080,10 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       c->close_span(sp_gu, c->compute);
     } else if (use_mfma) {
       uint16_t *hq = c->at<uint16_t>(c->lay.h);
-      if (!beside_routing && (e = launch_gateup_mfma(xa, act, c->at<uint16_t>(c->lay.s_q), hq, c->compute)) != hipSuccess)
+      if (!beside_routing) c->token_lists(act, exec_ids_host, &lists);
+      if (!beside_routing && (e = launch_gateup_mfma(xa, lists, c->at<uint16_t>(c->lay.s_q), hq, c->compute)) != hipSuccess)
         return c->hip_fail(e, "gate/up MFMA kernel");
-      if ((e = launch_down_mfma(xa, act, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");
+      if ((e = launch_down_mfma(xa, lists, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");
       c->close_span(sp_gu, c->compute);
     } else {
       if ((e = launch_gateup(xa, act, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");
@@ -1328,9 +1351,9 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
         xa.list_stride = P;
         xa.list_tokens = P;
         xa.E = E;
-        if ((e = launch_gateup_mfma(xa, act, sq_all, hq, c->compute)) != hipSuccess)
+        if ((e = launch_gateup_prefill(xa, act, sq_all, hq, c->compute)) != hipSuccess)
           return c->hip_fail(e, "gate/up MFMA kernel");
-        if ((e = launch_down_mfma(xa, act, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");
+        if ((e = launch_down_prefill(xa, act, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");
       } else {
         if ((e = launch_gateup(xa, act, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");
         if ((e = launch_down(xa, act, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "down kernel");
@@ -1515,18 +1538,13 @@ int moe_spec_time_kernel(moe_spec_ctx *c, int which, int reps, double *ms_per_la
   const int n_act = std::min({cfg.slots_per_layer, E, Bm * k});
   ActiveList act_m{};
   ExpertArgs xm = xa;
-  std::vector<int32_t> tab;                                        // outlives the launches that read its device copy
+  TokenLists lists;
   if (which == 4 || which == 5) {
-    tab.resize(size_t(Bm) * k);
-    for (size_t f = 0; f < tab.size(); ++f) tab[f] = int32_t(f % n_act);
+    std::vector<int> tab(size_t(Bm) * k);
+    for (size_t f = 0; f < tab.size(); ++f) tab[f] = int(f % n_act);
     act_m.n = n_act;
     for (int j = 0; j < n_act; ++j) { act_m.expert[j] = int16_t(j); act_m.slot[j] = int16_t(j); }
-    // on the compute stream, like the launches that follow (the stream does not synchronise with the null stream)
-    if ((e = hipMemcpyAsync(c->arena + c->lay.pend_ids[0], tab.data(), tab.size() * 4, hipMemcpyHostToDevice, c->compute)) != hipSuccess) {
-      (void)hipEventDestroy(t0); (void)hipEventDestroy(t1);
-      return c->hip_fail(e, "upload ids");
-    }
-    xm.exec_ids = c->at<int32_t>(c->lay.pend_ids[0]);
+    c->token_lists(act_m, tab, &lists);
     xm.B = Bm;
   }
   hipError_t le = hipSuccess;
@@ -1573,8 +1591,8 @@ int moe_spec_time_kernel(moe_spec_ctx *c, int which, int reps, double *ms_per_la
 #endif
         le = launch_route_pair(pa, cfg.dtype, c->compute);
       }
-      else if (which == 4) { xm.pool = xa.pool; le = launch_gateup_mfma(xm, act_m, c->at<uint16_t>(c->lay.s_q), c->at<uint16_t>(c->lay.h), c->compute); }
-      else if (which == 5) { xm.pool = xa.pool; le = launch_down_mfma(xm, act_m, c->at<uint16_t>(c->lay.h), c->compute); }
+      else if (which == 4) { xm.pool = xa.pool; le = launch_gateup_mfma(xm, lists, c->at<uint16_t>(c->lay.s_q), c->at<uint16_t>(c->lay.h), c->compute); }
+      else if (which == 5) { xm.pool = xa.pool; le = launch_down_mfma(xm, lists, c->at<uint16_t>(c->lay.h), c->compute); }
       else { ra.w = c->router_w[l]; ra.gain = static_cast<const float *>(c->gain[l]); c->prep_route(ra); le = launch_route(ra, cfg.dtype, c->compute); }
     }
     if (pass == 1 && le == hipSuccess) le = hipEventRecord(t1, c->compute);

@@ -101,6 +101,21 @@ def test_matrix_core_path_batches_of_16_and_more(mode, B, S):
     run_teacher_forced(wl, MODES[mode])
 
 
+@pytest.mark.parametrize("hidden,inter,experts,top_k,batch", [
+    (128, 120, 4, 2, 2),         # one whole 128-column step, one that ends inside; rows that share lines
+    (136, 1016, 2, 1, 16),       # two wavefronts per tile, the last chunk of the second one partly outside
+    (512, 1024, 4, 2, 17),       # rows of whole lines; parts of exactly one and two steps
+    (1096, 520, 2, 2, 33),       # more than 32 positions of an expert; parts of whole 64 columns, the last one short
+    (64, 2056, 2, 1, 28),        # half a step; four parts of which the last is nearly empty
+    (2048, 128, 16, 4, 32),      # eight positions per expert and 512 workgroups: the down projection is not split
+    (2048, 24, 1, 1, 64)])       # every position on one expert; a reduction of less than half a step
+def test_matrix_core_path_at_the_edges_of_its_splits(hidden, inter, experts, top_k, batch):
+    wl = small_workload(name="mfma_edges", n_layers=2, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter,
+                        dtype="bf16", batch=batch, tokens=2, slots=experts, seed=23)
+    run_teacher_forced(wl, O.MODE_SPECULATIVE)
+    run_teacher_forced(wl, O.MODE_ON_DEMAND)
+
+
 @pytest.mark.parametrize("mode", list(MODES))
 def test_edge_shapes(mode):
     # every expert selected; pool exactly k; one expert; one layer (no prediction at all)
