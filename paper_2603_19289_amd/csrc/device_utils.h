@@ -133,6 +133,37 @@ __device__ __forceinline__ T wave_sum(T v) {
   return (readlane(v, 0) + readlane(v, 16)) + (readlane(v, 32) + readlane(v, 48));
 }
 
+// A double as an unsigned integer that orders the same way (the sign bit flipped for positive values, all
+// bits for negative ones); a number is never 0.  -0.0 must not get here.
+__device__ __forceinline__ unsigned long long sortable(double v) {
+  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(v));
+  return u ^ ((u >> 63) ? ~0ull : 0x8000000000000000ull);
+}
+__device__ __forceinline__ double unsortable(unsigned long long s) {
+  const unsigned long long u = s ^ ((s >> 63) ? 0x8000000000000000ull : ~0ull);
+  return __longlong_as_double(static_cast<long long>(u));
+}
+__device__ __forceinline__ unsigned long long readlane(unsigned long long v, int src_lane) {
+  const unsigned int lo = __builtin_amdgcn_readlane(static_cast<unsigned int>(v), src_lane);
+  const unsigned int hi = __builtin_amdgcn_readlane(static_cast<unsigned int>(v >> 32), src_lane);
+  return (static_cast<unsigned long long>(hi) << 32) | lo;
+}
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_move(unsigned long long v) {
+  const unsigned int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xf, 0xf, true);
+  const unsigned int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), CTRL, 0xf, 0xf, true);
+  return (static_cast<unsigned long long>(hi) << 32) | lo;
+}
+// Largest of the 64 lanes' values, the same in every lane.
+__device__ __forceinline__ unsigned long long wave_max(unsigned long long v) {
+  auto larger = [](unsigned long long a, unsigned long long b) { return a > b ? a : b; };
+  v = larger(v, dpp_move<0xB1>(v));
+  v = larger(v, dpp_move<0x4E>(v));
+  v = larger(v, dpp_move<0x141>(v));
+  v = larger(v, dpp_move<0x140>(v));
+  return larger(larger(readlane(v, 0), readlane(v, 16)), larger(readlane(v, 32), readlane(v, 48)));
+}
+
 // ---- Hand-over slots: "the data is the flag".  A slot of global memory holds all ones (a NaN pattern no
 // result can have) until its producer overwrites it with one relaxed device-scope atomic store; consumers read
 // it with relaxed device-scope atomic loads until it no longer holds that pattern.  Each slot is a single

@@ -66,22 +66,6 @@ __device__ __forceinline__ double block_sum(double v, double *red, int lane, int
   return tot;
 }
 
-// A double as an unsigned integer that orders the same way (the sign bit flipped for positive values, all
-// bits for negative ones).  -0.0 never gets here: logits are published as v + 0.0.
-__device__ __forceinline__ unsigned long long sortable(double v) {
-  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(v));
-  return u ^ ((u >> 63) ? ~0ull : 0x8000000000000000ull);
-}
-__device__ __forceinline__ double unsortable(unsigned long long s) {
-  const unsigned long long u = s ^ ((s >> 63) ? 0x8000000000000000ull : ~0ull);
-  return __longlong_as_double(static_cast<long long>(u));
-}
-__device__ __forceinline__ unsigned long long readlane(unsigned long long v, int src_lane) {
-  const unsigned int lo = __builtin_amdgcn_readlane(static_cast<unsigned int>(v), src_lane);
-  const unsigned int hi = __builtin_amdgcn_readlane(static_cast<unsigned int>(v >> 32), src_lane);
-  return (static_cast<unsigned long long>(hi) << 32) | lo;
-}
-
 // Top-k of one token's E logits, read from their slots as they arrive: larger logit first, equal logits by
 // lower index.  Every wavefront holds all candidates in registers as order-preserving integers (element
 // i = r*64 + lane, R per lane) and counts, for each of its candidates, how many candidates broadcast from

@@ -103,6 +103,20 @@ struct RoutePairArgs {
   unsigned long long *stage_clock;        // development builds only (MOE_SPEC_STAGE_CLOCK): [12] stage times, or null
 };
 bool route_pair_supported(int H, int dtype);
+
+// The true routing of a whole prompt in one launch.
+struct RoutePromptArgs {
+  const float *r;             // [P,H]
+  const void *w;              // [E,H]
+  const float *gain;          // [H]
+  float *s_out;               // [P,H] s_l, or null
+  uint16_t *s_out_q;          // [P,H] the same as bf16 bit patterns, or null
+  int32_t *ids;  float *gates;                  // [P,k]
+  int32_t *user_ids;  float *user_gates;        // optional copies for the caller
+  int P, H, E, k;
+  float eps;
+};
+hipError_t launch_route_prompt(const RoutePromptArgs &a, int dtype, hipStream_t st);
 hipError_t launch_route_pair(const RoutePairArgs &a, int dtype, hipStream_t st);
 
 // Expert kernels read weights from the device slots of one layer.

@@ -288,3 +288,38 @@ def test_prefill_after_decode_starts_its_copies_beside_the_routing():
         eng.close()
     print("[case] prefill after " + ", after ".join(f"{k}: {min(v):.2f} ms" for k, v in took.items()), flush=True)
     assert min(took["decode"]) < 1.15 * min(took["prefill"]), took
+
+
+@pytest.mark.parametrize("dtype,hidden,experts,top_k,P", [
+    ("bf16", 8, 1, 1, 1), ("bf16", 40, 16, 16, 15), ("f32", 72, 17, 4, 16), ("bf16", 136, 33, 8, 17), ("f32", 1032, 64, 16, 33),
+    ("bf16", 264, 65, 3, 31), ("f32", 40, 129, 16, 20), ("bf16", 2056, 128, 8, 18), ("bf16", 72, 256, 16, 47), ("bf16", 8192, 9, 2, 16)])
+def test_prefill_routing_at_the_edges_of_its_tiles(dtype, hidden, experts, top_k, P):
+    """The routing of a prompt at every number of router tiles, with row counts around 16, reductions that end inside
+    a 32-column step, and token counts around its 16-token tile; two experts with the same router row, of whose equal logits
+    the lower index wins."""
+    wl = small_workload(n_layers=1, hidden=hidden, n_experts=experts, top_k=top_k, inter=8, dtype=dtype, slots=experts)
+    res, ex, _ = build(wl, "random")
+    if experts > 1:
+        res["router_w"][0][experts - 1] = res["router_w"][0][0]
+    run_prefill(wl, P=P, max_batch=16, label="routing", prebuilt=(res, oracle_model(wl, res, ex), ex))
+
+
+@pytest.mark.parametrize("experts", [9, 70])
+def test_prefill_non_finite_inputs_keep_expert_ids_in_range(experts):
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(n_layers=1, hidden=128, n_experts=experts, top_k=4, inter=64, dtype="bf16", slots=8)
+    res, ex, _ = build(wl, "random")
+    eng = engine_for(wl, M.MODE_ON_DEMAND, res, ex, max_batch=16, max_prefill_tokens=20)
+    try:
+        r = torch.from_numpy(prompt_of(wl, 20)[0]).cuda()
+        clean, clean_ids, _ = eng.prefill_layer_step(0, r, want_ids=True)
+        bad = r.clone()
+        bad[3, 5], bad[17, 0] = float("nan"), float("inf")
+        out, ids, gates = eng.prefill_layer_step(0, bad, want_ids=True)
+        torch.cuda.synchronize()
+        assert ((ids >= 0) & (ids < experts)).all() and all(len(set(row)) == wl.top_k for row in ids.tolist())
+        rest = [b for b in range(20) if b not in (3, 17)]
+        assert torch.isnan(out[[3, 17]]).all() and torch.isnan(gates[[3, 17]]).all()
+        assert torch.equal(ids[rest], clean_ids[rest]) and torch.equal(out[rest], clean[rest])
+    finally:
+        eng.close()
