@@ -152,6 +152,7 @@ struct ExpertArgs {
   const int32_t *pos_list;    // [E, list_stride]
   const int32_t *pos_count;   // [E]
   int list_stride, list_tokens;   // E is read with them: positions per expert on average
+  int row_first, row_end;     // output rows of this launch, or 0, 0: all of them; a part goes to the tiled kernel
 };
 
 // A batch of one whose executed experts are known before the layer's routing and are resident: the routing of the layer

@@ -62,4 +62,19 @@ inline int routing_workgroups(int E, int rows_per_wg, int proj_rows, int B, int 
   return std::max(for_router, std::min(cus / B, ((proj_rows + 1) / 2 + kRouteWaves - 1) / kRouteWaves));
 }
 
+// The last experts of a prompt's layer: nothing travels beside their kernels any more, so these end the call.  Whether
+// the experts of the last group are run one by one as they arrive, and the last one in pieces, by what the kernels of an
+// expert are estimated to take (600 TFLOP/s, what the tiled kernel reaches on a whole expert) beside its transfer (57
+// GB/s): only if a copy takes longer than its kernels, otherwise the kernels are the bottleneck and whole groups fill the
+// device better, and only if there is more than the overhead of a launch pair and of a transfer (some 10 us each).
+struct TailSplit {
+  bool by_expert, pieces;
+};
+inline TailSplit prefill_tail(double positions, int H, int I, int group, std::size_t expert_bytes) {
+  const double kernels_us = 6.0 * positions * H * I / 600e6, copy_us = double(expert_bytes) / 57e3;
+  if (kernels_us > copy_us) return {false, false};
+  const bool pieces = kernels_us >= 300.0;
+  return {pieces || (kernels_us >= 15.0 && kernels_us * (group - 1) >= 100.0), pieces};
+}
+
 }  // namespace moe_spec

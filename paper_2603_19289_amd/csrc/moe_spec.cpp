@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "kernels.h"
+#include "launch_rules.h"
 
 using namespace moe_spec;
 
@@ -173,6 +174,7 @@ struct moe_spec_ctx {
   std::vector<hipStream_t> copy_aux;             // owned; further DMA queues of copy_engine 2
   std::vector<hipEvent_t> aux_done;
   hipEvent_t pf_ready[2] = {nullptr, nullptr}, pf_done[2] = {nullptr, nullptr};   // prefill: one pair per half pool
+  hipEvent_t pf_tail[2] = {nullptr, nullptr};    // and one per copy queue
 
   std::vector<const void *> router_w, gain, dvecs;
   struct { const void *proj, *layer_emb, *ffn_in, *ffn_out, *head; const float *ln_gain, *ln_bias; float ln_eps; bool set; } est{};
@@ -579,6 +581,7 @@ int moe_spec_create(const moe_spec_config *cfg, moe_spec_ctx **out) {
   for (int h = 0; h < 2 && cfg->max_prefill_tokens > 0; ++h) {
     if ((e = hipEventCreateWithFlags(&c->pf_ready[h], hipEventDisableTiming)) != hipSuccess) return bail(e, "event");
     if ((e = hipEventCreateWithFlags(&c->pf_done[h], hipEventDisableTiming)) != hipSuccess) return bail(e, "event");
+    if ((e = hipEventCreateWithFlags(&c->pf_tail[h], hipEventDisableTiming)) != hipSuccess) return bail(e, "event");
   }
   if (cfg->copy_engine == MOE_SPEC_COPY_DMA2) {
     for (int q = 1; q < kDmaQueues; ++q) {
@@ -629,6 +632,7 @@ void moe_spec_destroy(moe_spec_ctx *c) {
   for (int h = 0; h < 2; ++h) {
     if (c->pf_ready[h]) (void)hipEventDestroy(c->pf_ready[h]);
     if (c->pf_done[h]) (void)hipEventDestroy(c->pf_done[h]);
+    if (c->pf_tail[h]) (void)hipEventDestroy(c->pf_tail[h]);
   }
   for (auto ev : c->ready) if (ev) (void)hipEventDestroy(ev);
   for (auto ev : c->done) if (ev) (void)hipEventDestroy(ev);
@@ -1262,6 +1266,107 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
       if ((e = hipStreamWaitEvent(q, c->ready[layer], 0)) != hipSuccess) return c->hip_fail(e, "copy queue wait");
   }
 
+  // The kernels of the experts in act.  bf16: the matrix-core kernels take all tokens of every expert in one launch, gate/up
+  // and down apart and, for the last expert of a long prompt, a part of their output rows at a time (row_end 0: all of
+  // them); float32: the general kernels, one launch pair per micro-batch.
+  auto args_of = [&](int t0, int nb) {
+    ExpertArgs xa{};
+    xa.pool = c->pool_base(layer);
+    xa.slot_bytes = c->slot_stride;
+    xa.s = s_all + size_t(t0) * H;
+    xa.exec_ids = ids_all + size_t(t0) * k;
+    xa.exec_gates = gates_all + size_t(t0) * k;
+    xa.h = c->at<float>(c->lay.h);                     // [nb,k,I], reused by every micro-batch
+    xa.y = y_all + size_t(t0) * k * H;
+    xa.out = out + size_t(t0) * H;
+    xa.B = nb; xa.k = k; xa.H = H; xa.I = I;
+    xa.bf16 = cfg.dtype == MOE_SPEC_BF16;
+    return xa;
+  };
+  auto run_product = [&](const ActiveList &act, bool gateup, int row_first, int row_end) {
+    ExpertArgs xa = args_of(0, std::min(MB, P));
+    uint16_t *hq = c->at<uint16_t>(c->lay.pf_hq);      // [P,k,I]
+    xa.pos_list = c->at<int32_t>(c->lay.pf_pos);
+    xa.pos_count = c->at<int32_t>(c->lay.pf_count);
+    xa.list_stride = P;
+    xa.list_tokens = P;
+    xa.E = E;
+    xa.row_first = row_first;
+    xa.row_end = row_end;
+    const hipError_t le = gateup ? launch_gateup_prefill(xa, act, sq_all, hq, c->compute) : launch_down_prefill(xa, act, hq, c->compute);
+    return le == hipSuccess ? MOE_SPEC_OK : c->hip_fail(le, gateup ? "gate/up MFMA kernel" : "down MFMA kernel");
+  };
+  auto accumulate = [&](const ActiveList &act, int from, int to) {
+    for (int u0 = from; cfg.accumulate_defaults && u0 < to; u0 += MB) {      // per micro-batch: the kernel indexes positions from 0
+      const hipError_t le = launch_accumulate_defaults(args_of(u0, std::min(MB, to - u0)), act,
+                                                       c->at<double>(c->lay.dacc_sum) + size_t(layer) * E * H,
+                                                       c->at<unsigned long long>(c->lay.dacc_cnt) + size_t(layer) * E, c->compute);
+      if (le != hipSuccess) return c->hip_fail(le, "default-vector accumulation");
+    }
+    return int(MOE_SPEC_OK);
+  };
+  auto run_experts = [&](const ActiveList &act) {
+    int rc = MOE_SPEC_OK;
+    if (all_at_once) {
+      if ((rc = run_product(act, true, 0, 0)) || (rc = run_product(act, false, 0, 0))) return rc;
+      return accumulate(act, 0, P);
+    }
+    for (int t0 = 0; t0 < P && !rc; t0 += MB) {
+      const int nb = std::min(MB, P - t0);
+      const ExpertArgs xa = args_of(t0, nb);
+      hipError_t le = launch_gateup(xa, act, cfg.dtype, c->compute);
+      if (le != hipSuccess) return c->hip_fail(le, "gate/up kernel");
+      if ((le = launch_down(xa, act, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(le, "down kernel");
+      rc = accumulate(act, t0, t0 + nb);
+    }
+    return rc;
+  };
+  // What lies behind the last transfer ends the call: the experts of the last group may run one by one as they arrive, each
+  // behind an event of the queue that carried it, and the last one in four pieces: the gate and up rows of the first half of
+  // its hidden units, of the second half, W_down's first half of rows, the second half.  32768 tokens of 8 experts of 14336
+  // x 4096: 4.5 ms of kernels behind the last transfer before, 1.2 now.
+  const TailSplit tail = all_at_once && cfg.copy_engine != MOE_SPEC_COPY_KERNEL
+                             ? prefill_tail(double(P) * k / E, H, I, (E - 1) % group + 1, c->expert_bytes) : TailSplit{false, false};
+  auto run_tail = [&](const ActiveList &act) {
+    for (int x = 0; x < act.n; ++x) {
+      ActiveList one{};
+      one.n = 1;
+      one.expert[0] = act.expert[x];
+      one.slot[0] = act.slot[x];
+      const size_t q = size_t(x) % (1 + c->copy_aux.size());
+      const hipStream_t queue = q == 0 ? c->copy : c->copy_aux[q - 1];
+      const char *src = c->host_expert[size_t(layer) * E + act.expert[x]];
+      char *dst = c->pool_base(layer) + size_t(act.slot[x]) * c->slot_stride;
+      hipError_t le = hipSuccess;
+      auto copy = [&](size_t from, size_t bytes) {
+        if (le == hipSuccess && bytes) le = hipMemcpyAsync(dst + from, src + from, bytes, hipMemcpyHostToDevice, queue);
+      };
+      auto arrived = [&]() {                           // what was queued so far, before the next launch
+        if (le == hipSuccess) le = hipEventRecord(c->pf_tail[q], queue);
+        if (le == hipSuccess) le = hipStreamWaitEvent(c->compute, c->pf_tail[q], 0);
+        return le == hipSuccess ? MOE_SPEC_OK : c->hip_fail(le, "host-to-device expert copy");
+      };
+      int rc = MOE_SPEC_OK;
+      if (x + 1 < act.n || !tail.pieces) {
+        copy(0, c->expert_bytes);
+        if ((rc = arrived()) || (rc = run_experts(one))) return rc;
+        continue;
+      }
+      const size_t matrix = c->expert_bytes / 3;
+      for (const bool gateup : {true, false}) {
+        const int rows = gateup ? I : H, half = std::min(rows, (rows / 2 + 255) / 256 * 256);   // whole tiles of rows
+        const size_t row = matrix / size_t(rows);
+        for (int r0 = 0, r1 = half; r0 < rows; r0 = r1, r1 = rows) {
+          if (gateup) copy(size_t(r0) * row, size_t(r1 - r0) * row);
+          copy((gateup ? 1 : 2) * matrix + size_t(r0) * row, size_t(r1 - r0) * row);
+          if ((rc = arrived()) || (rc = run_product(one, gateup, r0, r1))) return rc;
+        }
+      }
+      if ((rc = accumulate(one, 0, P))) return rc;
+    }
+    return int(MOE_SPEC_OK);
+  };
+
   // --- stream every expert through the two halves of the pool
   for (int e0 = 0, g = 0; e0 < E; e0 += group, ++g) {
     const int half = g % halves, n_here = std::min(group, E - e0);
@@ -1274,71 +1379,40 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
       int rc = c->copy_queues_wait(c->pf_done[half]);
       if (rc) return rc;
     }
+    ActiveList act{};
+    for (int x = 0; x < n_here; ++x) {
+      act.expert[x] = int16_t(e0 + x);
+      act.slot[x] = int16_t(half * group + x);         // < halves * group <= S
+    }
+    act.n = n_here;
+    c->st.cache_misses += n_here;
+    c->st.h2d_bytes += int64_t(n_here) * int64_t(c->expert_bytes);
+    c->st.hbm_bytes_algorithmic += int64_t(n_here) * int64_t(c->expert_bytes);
     TimedSpan *sp_copy = c->open_span(1, c->copy);
     CopyList cl{};
     cl.n16 = uint32_t(c->expert_bytes / 16);
-    ActiveList act{};
+    if (tail.by_expert && e0 + group >= E) {
+      TimedSpan *sp_exec = c->open_span(0, c->compute);
+      int rc = run_tail(act);
+      if (rc || (rc = c->copy_join(cl))) return rc;
+      c->close_span(sp_copy, c->copy);
+      c->close_span(sp_exec, c->compute);
+      break;
+    }
     for (int x = 0; x < n_here; ++x) {
-      const int slot = half * group + x;               // < halves * group <= S
-      int rc = c->copy_expert(cl, x, c->pool_base(layer) + size_t(slot) * c->slot_stride,
+      int rc = c->copy_expert(cl, x, c->pool_base(layer) + size_t(act.slot[x]) * c->slot_stride,
                               c->host_expert[size_t(layer) * E + e0 + x]);
       if (rc) return rc;
-      act.expert[x] = int16_t(e0 + x);
-      act.slot[x] = int16_t(slot);
     }
-    act.n = n_here;
     if (int rc = c->copy_join(cl)) return rc;
     c->close_span(sp_copy, c->copy);
     if ((e = hipEventRecord(c->pf_ready[half], c->copy)) != hipSuccess) return c->hip_fail(e, "record ready event");
-    c->st.cache_misses += n_here;
-    c->st.h2d_bytes += int64_t(n_here) * int64_t(c->expert_bytes);
 
     TimedSpan *sp_stall = c->open_span(2, c->compute);
     if ((e = hipStreamWaitEvent(c->compute, c->pf_ready[half], 0)) != hipSuccess) return c->hip_fail(e, "compute stream wait");
     c->close_span(sp_stall, c->compute);
     TimedSpan *sp_exec = c->open_span(0, c->compute);
-    // bf16: the matrix-core kernels take all tokens of every expert in one launch, 64 per grid plane;
-    // float32: the general kernels, one launch pair per micro-batch
-    for (int t0 = 0; t0 < P; t0 += all_at_once ? P : MB) {
-      const int nb = all_at_once ? std::min(MB, P) : std::min(MB, P - t0);
-      ExpertArgs xa{};
-      xa.pool = c->pool_base(layer);
-      xa.slot_bytes = c->slot_stride;
-      xa.s = s_all + size_t(t0) * H;
-      xa.exec_ids = ids_all + size_t(t0) * k;
-      xa.exec_gates = gates_all + size_t(t0) * k;
-      xa.h = c->at<float>(c->lay.h);                   // [nb,k,I], reused by every micro-batch
-      xa.y = y_all + size_t(t0) * k * H;
-      xa.out = out + size_t(t0) * H;
-      xa.B = nb; xa.k = k; xa.H = H; xa.I = I;
-      xa.bf16 = cfg.dtype == MOE_SPEC_BF16;
-      if (all_at_once) {
-        uint16_t *hq = c->at<uint16_t>(c->lay.pf_hq);  // [P,k,I]
-        xa.pos_list = c->at<int32_t>(c->lay.pf_pos);
-        xa.pos_count = c->at<int32_t>(c->lay.pf_count);
-        xa.list_stride = P;
-        xa.list_tokens = P;
-        xa.E = E;
-        if ((e = launch_gateup_prefill(xa, act, sq_all, hq, c->compute)) != hipSuccess)
-          return c->hip_fail(e, "gate/up MFMA kernel");
-        if ((e = launch_down_prefill(xa, act, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");
-      } else {
-        if ((e = launch_gateup(xa, act, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");
-        if ((e = launch_down(xa, act, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "down kernel");
-      }
-      if (cfg.accumulate_defaults)
-        for (int u0 = t0; u0 < (all_at_once ? P : t0 + nb); u0 += MB) {
-          ExpertArgs ya = xa;                          // per micro-batch: the kernel indexes positions from 0
-          ya.exec_ids = ids_all + size_t(u0) * k;
-          ya.y = y_all + size_t(u0) * k * H;
-          ya.B = std::min(MB, P - u0);
-          if ((e = launch_accumulate_defaults(ya, act, c->at<double>(c->lay.dacc_sum) + size_t(layer) * E * H,
-                                              c->at<unsigned long long>(c->lay.dacc_cnt) + size_t(layer) * E,
-                                              c->compute)) != hipSuccess)
-            return c->hip_fail(e, "default-vector accumulation");
-        }
-      c->st.hbm_bytes_algorithmic += int64_t(n_here) * int64_t(c->expert_bytes);
-    }
+    if (int rc = run_experts(act)) return rc;
     c->close_span(sp_exec, c->compute);
     if ((e = hipEventRecord(c->pf_done[half], c->compute)) != hipSuccess) return c->hip_fail(e, "record done event");
   }

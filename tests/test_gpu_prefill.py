@@ -323,3 +323,28 @@ def test_prefill_non_finite_inputs_keep_expert_ids_in_range(experts):
         assert torch.equal(ids[rest], clean_ids[rest]) and torch.equal(out[rest], clean[rest])
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("slots,engine,pairs", [(6, M.COPY_DMA2, 4), (4, M.COPY_DMA, 3)])
+def test_prefill_tail_in_pieces_equals_whole_groups(slots, engine, pairs):
+    """Kernels of 0.3 ms per expert: the last group runs expert by expert and the last expert in halves of its rows, which
+    end inside a tile.  Bit for bit what the copy kernel's whole groups give: a tile's sums do not depend on its launch."""
+    from paper_2603_19289_amd.engine import engine_for
+    P = 7400
+    wl = small_workload(n_layers=1, hidden=2056, n_experts=3, top_k=1, inter=6008, dtype="bf16", slots=slots)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    pool = torch.empty((1, 3, 3 * wl.hidden * wl.inter), dtype=torch.bfloat16, pin_memory=True)
+    pool.copy_(0.02 * torch.randn(pool.shape, generator=g, device="cuda"))
+    r = torch.randn((P, wl.hidden), generator=g, device="cuda")
+    got = []
+    for e in (engine, M.COPY_KERNEL):
+        eng = engine_for(wl, M.MODE_ON_DEMAND, W.make_resident(wl), pool, max_batch=64, max_prefill_tokens=P, copy_engine=e)
+        try:
+            counts = kernels_launched(lambda: got.append(eng.prefill_layer_step(0, r)[0]), {"expert_lists": 1, "combine": 1})
+            assert torch.isfinite(got[-1]).all() and got[-1].square().mean() > 0.01
+        finally:
+            eng.close()
+        whole = (3 + slots // 2 - 1) // (slots // 2)
+        expected = pairs if e == engine else whole
+        assert [launches(counts, f"expert_tile_kernel<{b}>") for b in ("true", "false")] == [expected] * 2, counts
+    assert torch.equal(got[0], got[-1])

@@ -58,3 +58,15 @@ def test_estimator_projection_gets_workgroups_for_its_rows(tmp_path):
       if (!ok && ++bad <= 20) std::printf("cus %d E %d B %d rows %d: %d beside\n", cus, E, B, rows, beside);
     }
   }""")
+
+
+def test_prefill_tail_is_split_only_where_copies_are_the_bottleneck(tmp_path):
+    sweep(tmp_path, r"""
+  for (double pos : {1.0, 100.0, 2500.0, 30000.0, 500000.0}) for (int H : {8, 1024, 4096, 8192}) for (int I : {8, 768, 14336, 32768})
+    for (int group : {1, 2, 8, 128}) {
+      const std::size_t bytes = std::size_t(6) * H * I;
+      const TailSplit t = prefill_tail(pos, H, I, group, bytes);
+      const double kernels = 6.0 * pos * H * I / 600e6;
+      const bool ok = (!t.pieces || t.by_expert) && (kernels <= bytes / 57e3 || !t.by_expert) && (kernels >= 15.0 || !t.by_expert);
+      if (!ok && ++bad <= 20) std::printf("pos %g H %d I %d group %d\n", pos, H, I, group);
+    }""")
