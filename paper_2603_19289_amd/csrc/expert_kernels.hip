@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kBlock) void down_kernel(const ExpertArgs a, const 
 template <typename WT, int NCH>
 __global__ __launch_bounds__(kBlock) void gateup_b1_kernel(const ExpertArgs a, const ActiveList act,
                                                            const int rpw) {
-  gateup_b1_body<WT, NCH, false>(a, act, blockIdx.y, blockIdx.x, rpw, nullptr, nullptr);
+  gateup_b1_body<WT, NCH, false>(a, act, blockIdx.y, blockIdx.x, rpw, 0, a.I, nullptr, nullptr);
 }
 
 template <typename WT, int NCH>

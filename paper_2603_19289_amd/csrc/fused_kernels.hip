@@ -667,16 +667,22 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
 template <typename WT, int NCH>
 __global__ __launch_bounds__(kBlock, 2)
 void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const ActiveList act, const int n_route,
-                            const int blocks, const int rpw) {
+                            const SharedSplit split) {
   extern __shared__ double vec_lds[];
   __shared__ RouteShared sh;
-  if (int(blockIdx.x) < n_route) {
+  int i = int(blockIdx.x) - n_route, blocks = split.stream.blocks, rpw = split.stream.rpw, first = 0, last = split.first_tail;
+  if (i < 0) {
     route_pair_body<WT, kWaves, (NCH + 3) / 4, 1, false>(ra, blockIdx.x, n_route, 0, 1, vec_lds, sh);
-    return;
+    i = int(blockIdx.x) - 1;
+    blocks = split.tail_blocks;
+    if (i < 0 || i >= blocks * act.n) return;
+    rpw = split.tail_rpw;
+    first = last;
+    last = a.I;
+    __syncthreads();                           // the routing's last readers of the shared memory are done
   }
-  const int i = blockIdx.x - n_route;
   float *s_lds = reinterpret_cast<float *>(vec_lds);
-  gateup_b1_body<WT, NCH, true>(a, act, i / blocks, i % blocks, rpw, s_lds, sh.red);
+  gateup_b1_body<WT, NCH, true>(a, act, i / blocks, i % blocks, rpw, first, last, s_lds, sh.red);
 }
 
 // s_l = LN_l(r_l) as bf16, one workgroup per token: what the expert workgroups of the launch below read.
@@ -820,8 +826,9 @@ hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a
   // the routing workgroups wait for one another: they must fit on the device together
   if (long(n_route) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
   const GateupSplit split = beside_routing_split(NCH, a.I, a.H, act.n, sizeof(WT), n_route, blocks_per_cu, g_compute_units);
-  hipLaunchKernelGGL((route_gateup_b1_kernel<WT, NCH>), dim3(n_route + split.blocks * act.n), dim3(kBlock), lds, st, ra,
-                     a, act, n_route, split.blocks, split.rpw);
+  const SharedSplit shared = share_with_routing(split, a.I, a.H, act.n, sizeof(WT), n_route, g_compute_units);
+  hipLaunchKernelGGL((route_gateup_b1_kernel<WT, NCH>), dim3(n_route + shared.stream.blocks * act.n), dim3(kBlock), lds, st,
+                     ra, a, act, n_route, shared);
   return hipGetLastError();
 }
 

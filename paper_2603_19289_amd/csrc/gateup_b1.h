@@ -70,19 +70,19 @@ struct InputNorm {
 };
 
 // hq[pos, row] for the one token of the batch, stored in the weight dtype for the down kernel.
-// `act` is in execution-position order.  Each lane keeps its NCH chunks of s_l in registers; a wavefront owns
+// `act` is in execution-position order; rows [first, last) of the expert.  Each lane keeps its NCH chunks of s_l in registers; a wavefront owns
 // `rpw` consecutive rows and keeps the 2*NCH 16-byte loads of the next row in flight while it reduces the
 // current one.  NORM: s_l is formed here from a.r (LDS s_lds, red), else read from a.s.
 template <typename WT, int NCH, bool NORM>
 __device__ __forceinline__ void gateup_b1_body(const ExpertArgs &a, const ActiveList &act, int pos, int block, int rpw,
-                                               float *s_lds, double *red) {
+                                               int first, int last, float *s_lds, double *red) {
   using R = Packed<WT>;
   constexpr int VN = R::N;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int H = a.H, I = a.I;
-  const int row0 = (block * kB1Waves + wave) * rpw;
-  if (!NORM && row0 >= I) return;
-  const int row_end = min(row0 + rpw, I);
+  const int row0 = first + (block * kB1Waves + wave) * rpw;
+  if (!NORM && row0 >= last) return;
+  const int row_end = min(row0 + rpw, last);
   const WT *wg = reinterpret_cast<const WT *>(a.pool + size_t(act.slot[pos]) * a.slot_bytes);
   const WT *wu = wg + size_t(I) * H;
   WT *hq = reinterpret_cast<WT *>(a.h) + size_t(pos) * I;
@@ -98,11 +98,11 @@ __device__ __forceinline__ void gateup_b1_body(const ExpertArgs &a, const Active
     if (!live[ch]) col[ch] = 0;                // dead lanes re-read column 0 and multiply by zero
   }
   typename R::Raw rg[NCH], ru[NCH];
-  const size_t first = size_t(NORM ? min(row0, I - 1) : row0) * H;
+  const size_t at0 = size_t(NORM ? min(row0, I - 1) : row0) * H;
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
-    rg[ch] = load_stream<typename R::Raw>(wg + first + col[ch]);
-    ru[ch] = load_stream<typename R::Raw>(wu + first + col[ch]);
+    rg[ch] = load_stream<typename R::Raw>(wg + at0 + col[ch]);
+    ru[ch] = load_stream<typename R::Raw>(wu + at0 + col[ch]);
   }
   if (NORM) norm.finish(a, s_lds, red, tid);
   const float *s = NORM ? s_lds : a.s;

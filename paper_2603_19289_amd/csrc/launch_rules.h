@@ -44,6 +44,38 @@ inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_
   return {rpw, (I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
 }
 
+// The same with the routing workgroups taking rows too once they have routed (all but the first, which finishes the
+// prediction): the last I - first_tail rows of every expert, tail_rpw per wavefront, in tail_blocks workgroups.  They come
+// free after about 6 us in which another workgroup streams 130 KB.  Worth it where routing takes half of the device or
+// more and the others are left with 320 KB and more each (the routing, 12 us, is over well before them then), for rows of up
+// to 4 KB: longer ones make the vector that these workgroups have to form a second time cost more than they win.
+// Microseconds per pass without / with: 8 of 128 experts of 768 x 2048 (393 KB each) 611 / 578, 8 of 200 of 480 x 2048 (493)
+// 334 / 299, 8 of 128 of 1600 x 1024 (410) 367 / 324; not taken: 8 of 64 of 960 x 2048 (328) 323 / 315, 8 of 128 of 640 x
+// 2880 (461) 370 / 375, 4 of 100 of 800 x 3000 (246) 578 / 614, 4 of 32 of 768 x 4096 (225) 565 / 619, 6 of 60 of 1200 x 1544
+// (227) 583 / 583, 8 of 128 of 520 x 1024 (133) 475 / 478.
+struct SharedSplit {
+  GateupSplit stream;                          // of rows [0, first_tail)
+  int first_tail, tail_rpw, tail_blocks;       // tail_blocks 0: none
+};
+inline SharedSplit share_with_routing(const GateupSplit &s, int I, int H, int n, std::size_t wbytes, int n_route, int cus) {
+  const SharedSplit none{s, I, 0, 0};
+  const std::size_t row = std::size_t(2) * H * wbytes, bytes = row * I * n;
+  const int helpers = (n_route - 1) / n;       // workgroups per expert
+  if (s.rpw < 1 || helpers < 1 || H * wbytes > 4096 || 2 * n_route < cus || bytes > std::size_t(64) << 20 ||
+      bytes < std::size_t(320 << 10) * s.blocks * n)
+    return none;
+  const double lead = 130e3 / double(row), stream_wgs = double(s.blocks) * n, tail_wgs = double(helpers) * n;
+  const double rows_each = (double(I) * n + tail_wgs * lead) / (stream_wgs + tail_wgs);
+  const int tail_rpw = int((rows_each - lead) / kB1Waves);
+  if (tail_rpw < 1) return none;
+  SharedSplit out{s, I, tail_rpw, std::min(helpers, I / 2 / (kB1Waves * tail_rpw))};
+  if (out.tail_blocks < 1) return none;
+  out.first_tail = I - out.tail_blocks * kB1Waves * tail_rpw;
+  out.stream.rpw = (out.first_tail + kB1Waves * s.blocks - 1) / (kB1Waves * s.blocks);
+  out.stream.blocks = (out.first_tail + kB1Waves * out.stream.rpw - 1) / (kB1Waves * out.stream.rpw);
+  return out;
+}
+
 // Workgroups per token of a routing launch beside matrix-core experts, whose rows may be dealt to any number of them:
 // about one per compute unit in all (half as many: 2 % slower at 32 tokens, a quarter 16 %; twice as many 1 %), at least
 // a router row for every wavefront, and two pairs of rows where the estimator's projection rides along (proj_rows, else

@@ -484,6 +484,37 @@ def test_gate_up_beside_the_routing_equals_separate_launches(dtype, hidden, inte
     beside_and_separate(wl, kernel or "route_gateup", (n, n))
 
 
+@pytest.mark.parametrize("hidden,inter,experts,top_k", [(1024, 344, 200, 16), (1016, 352, 256, 16)])
+def test_rows_taken_by_the_routing_workgroups_equal_separate_launches(hidden, inter, experts, top_k):
+    """Batch one with so many experts that their routing workgroups take gate/up rows afterwards: bit for bit the launches of
+    their own (profile = 1), over two tokens of resident experts."""
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(name="shared_rows", n_layers=3, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype="bf16",
+                        batch=1, tokens=1, slots=experts)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    pool = torch.empty((experts, 3 * hidden * inter), dtype=torch.bfloat16, pin_memory=True)
+    pool.copy_(0.02 * torch.randn(pool.shape, generator=g, device="cuda"))
+    r = torch.randn((2, wl.n_layers, 1, hidden), generator=g, device="cuda")
+    got = []
+    for profile in (0, 1):
+        eng = engine_for(wl, M.MODE_SPECULATIVE, W.make_resident(wl), [pool] * wl.n_layers, profile=profile)
+
+        def tokens(log):
+            for t in range(2):
+                eng.begin_token()
+                for l in range(wl.n_layers):
+                    log.append(eng.layer_step(l, r[t, l])[0])
+        try:
+            tokens([])
+            log = []
+            counts = kernels_launched(lambda: (log.clear(), tokens(log)), {"down_": 2 * wl.n_layers})
+            assert launches(counts, "route_gateup_b1") == (0 if profile else 2 * (wl.n_layers - 1)), counts
+            got.append(log)
+        finally:
+            eng.close()
+    assert all(torch.equal(a, b) for a, b in zip(*got)) and all(torch.isfinite(a).all() and a.abs().max() > 0 for a in got[0])
+
+
 @pytest.mark.parametrize("hidden,experts,m,batch,kernel", [
     (520, 3, 1, 2, "<1, 4, true>"),          # one token tile, four wavefronts per 16 rows; more projection rows than router rows
     (72, 40, 9, 16, "<1, 1, true>"),         # latent size 8: most wavefronts have no row of it

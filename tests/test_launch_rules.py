@@ -70,3 +70,24 @@ def test_prefill_tail_is_split_only_where_copies_are_the_bottleneck(tmp_path):
       const bool ok = (!t.pieces || t.by_expert) && (kernels <= bytes / 57e3 || !t.by_expert) && (kernels >= 15.0 || !t.by_expert);
       if (!ok && ++bad <= 20) std::printf("pos %g H %d I %d group %d\n", pos, H, I, group);
     }""")
+
+
+def test_rows_shared_with_the_routing_workgroups_are_dealt_once(tmp_path):
+    # stream and tail together hold every row of an expert exactly once, no workgroup starts past its rows, and the first
+    # routing workgroup is left out
+    sweep(tmp_path, r"""
+  int shared = 0;
+  for (int cus : {32, 64, 128, 256}) for (int per_cu : {1, 2, 4}) for (int E = 1; E <= 256; ++E) {
+    if (long(E) > long(per_cu) * cus) continue;
+    for (int H : {8, 512, 1024, 2048, 2880}) for (int I : {8, 328, 480, 768, 1600, 14336}) for (int k : {1, 2, 8, 16}) for (int wbytes : {2, 4}) {
+      const int nch = (H + 64 * (16 / wbytes) - 1) / (64 * (16 / wbytes));
+      const GateupSplit base = beside_routing_split(nch, I, H, k, wbytes, E, per_cu, cus);
+      const SharedSplit s = share_with_routing(base, I, H, k, wbytes, E, cus);
+      const long stream = long(s.stream.blocks) * kB1Waves * s.stream.rpw;
+      const bool ok = s.stream.rpw >= 1 && stream >= s.first_tail && stream - kB1Waves * s.stream.rpw < s.first_tail &&
+                      s.first_tail + long(s.tail_blocks) * kB1Waves * s.tail_rpw == I && s.tail_blocks * k <= E - 1 + (s.tail_blocks == 0);
+      shared += s.tail_blocks > 0;
+      if (!ok && ++bad <= 20) std::printf("cus %d E %d H %d I %d k %d wbytes %d\n", cus, E, H, I, k, wbytes);
+    }
+  }
+  if (shared == 0) ++bad;""")
