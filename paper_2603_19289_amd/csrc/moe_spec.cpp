@@ -296,15 +296,15 @@ struct moe_spec_ctx {
     return MOE_SPEC_OK;
   }
 
-  // One expert block host -> device by the configured engine; `index` counts the blocks of the
+  // One expert block host -> device by the configured engine (the copy kernel on kernel_stream); `index` counts the blocks of the
   // current group (it picks the queue).  copy_join ends the group: afterwards everything issued is
   // ordered before whatever is recorded next on the copy stream.
-  int copy_expert(CopyList &cl, int index, char *dst, const char *src) {
+  int copy_expert(CopyList &cl, int index, char *dst, const char *src, hipStream_t kernel_stream) {
     if (cfg.copy_engine == MOE_SPEC_COPY_KERNEL) {
       cl.src[cl.n] = src;
       cl.dst[cl.n] = dst;
       if (++cl.n == kCopyListMax) {
-        hipError_t c = launch_gather_copy(cl, copy);
+        hipError_t c = launch_gather_copy(cl, kernel_stream);
         if (c != hipSuccess) return hip_fail(c, "host-to-device gather copy");
         cl.n = 0;
       }
@@ -320,9 +320,9 @@ struct moe_spec_ctx {
     }
     return MOE_SPEC_OK;
   }
-  int copy_join(CopyList &cl) {
+  int copy_join(CopyList &cl, hipStream_t kernel_stream) {
     if (cl.n > 0) {
-      hipError_t c = launch_gather_copy(cl, copy);
+      hipError_t c = launch_gather_copy(cl, kernel_stream);
       if (c != hipSuccess) return hip_fail(c, "host-to-device gather copy");
       cl.n = 0;
     }
@@ -369,7 +369,12 @@ struct moe_spec_ctx {
   // Cache request for at most S experts (ascending ids): hits are stamped, each miss takes the
   // least recently used slot that holds no requested expert and is copied in on the copy stream.
   // Fills act with (expert, slot) of every requested expert.  Returns the number of copies issued.
-  int request(int layer, const std::vector<int> &experts, ActiveList *act, int *n_copies) {
+  // blocking: kernels that read these experts are launched next and the compute stream has nothing to do meanwhile, so the
+  // copy kernel runs on it, unless copies into this pool still travel on the copy stream: in order behind the slots' readers
+  // and before the kernels, without an event there and back.  4 layers x 4 tokens on demand, experts of 1.6 MB: 940 -> 790
+  // us.  Not where the routing launch goes on to a prediction, which the first copies run beside (prefetch as a hint, the
+  // same layers: 892 -> 932 us).
+  int request(int layer, const std::vector<int> &experts, ActiveList *act, int *n_copies, bool blocking) {
     Pool &p = pools[layer];
     const int S = cfg.slots_per_layer;
     std::vector<char> in_q(cfg.n_experts, 0);
@@ -377,6 +382,8 @@ struct moe_spec_ctx {
     act->n = 0;
     int copies = 0;
     TimedSpan *span = nullptr;
+    const bool in_order = blocking && cfg.copy_engine == MOE_SPEC_COPY_KERNEL && !cfg.profile && !ready_pending[layer];
+    const hipStream_t kernel_stream = in_order ? compute : copy;
     CopyList cl{};
     cl.n16 = uint32_t(expert_bytes / 16);
     for (int e : experts)                        // refuse before any state changes
@@ -396,7 +403,9 @@ struct moe_spec_ctx {
       }
       if (victim < 0) return fail(MOE_SPEC_ESTATE, "no evictable slot (request larger than the pool)");
       const char *src = host_expert[size_t(layer) * cfg.n_experts + e];
-      if (copies == 0) {
+      if (copies == 0 && in_order) {
+        read_step[layer] = step_seq;             // what is queued on the copy stream later goes behind this step
+      } else if (copies == 0) {
         if (int rc = copies_behind_readers(layer)) return rc;
         if (ready_recorded[layer]) {
           // further queues: also behind the previous request on this pool (its slots may be reused
@@ -413,15 +422,15 @@ struct moe_spec_ctx {
       p.slot_stamp[victim] = int(p.clock);
       p.where[e] = victim;
       char *dst = pool_base(layer) + size_t(victim) * slot_stride;
-      if (int rc = copy_expert(cl, copies, dst, src)) return rc;
+      if (int rc = copy_expert(cl, copies, dst, src, kernel_stream)) return rc;
       copies += 1;
       st.cache_misses += 1;
       st.h2d_bytes += int64_t(expert_bytes);
     }
     if (copies > 0) {                            // the request is complete when every queue is
-      if (int rc = copy_join(cl)) return rc;
+      if (int rc = copy_join(cl, kernel_stream)) return rc;
     }
-    if (copies > 0) {
+    if (copies > 0 && !in_order) {
       close_span(span, copy);
       hipError_t r = hipEventRecord(ready[layer], copy);
       if (r != hipSuccess) return hip_fail(r, "record ready event");
@@ -1063,7 +1072,8 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       act = c->pending_wave0;                   // requested one step earlier; its copies may still be in flight
     } else {
       std::vector<int> req(exec_union.begin() + w0, exec_union.begin() + std::min(exec_union.size(), w0 + S));
-      int rc = c->request(layer, req, &act, &copies);
+      // With a prediction behind the true routing in the same launch, the first copies start beside it.
+      int rc = c->request(layer, req, &act, &copies, wave > 0 || !do_pred);
       if (rc) return rc;
     }
     if (c->ready_pending[layer]) {
@@ -1122,7 +1132,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     next_ids.assign(c->mb_next->ids, c->mb_next->ids + batch * k);
     std::vector<int> req(next_union.begin(), next_union.begin() + std::min<size_t>(next_union.size(), S));
     int copies = 0;
-    rc = c->request(layer + 1, req, &next_wave0, &copies);
+    rc = c->request(layer + 1, req, &next_wave0, &copies, false);
     if (rc) return rc;
   }
   if (score_look) {
@@ -1149,7 +1159,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     uni.resize(std::min<size_t>(uni.size(), S));
     ActiveList hinted_slots{};
     int copies = 0;
-    if ((rc = c->request(layer + 2, uni, &hinted_slots, &copies))) return rc;
+    if ((rc = c->request(layer + 2, uni, &hinted_slots, &copies, false))) return rc;
   }
 
   c->step_begun = false;
@@ -1394,17 +1404,17 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
     if (tail.by_expert && e0 + group >= E) {
       TimedSpan *sp_exec = c->open_span(0, c->compute);
       int rc = run_tail(act);
-      if (rc || (rc = c->copy_join(cl))) return rc;
+      if (rc || (rc = c->copy_join(cl, c->copy))) return rc;
       c->close_span(sp_copy, c->copy);
       c->close_span(sp_exec, c->compute);
       break;
     }
     for (int x = 0; x < n_here; ++x) {
       int rc = c->copy_expert(cl, x, c->pool_base(layer) + size_t(act.slot[x]) * c->slot_stride,
-                              c->host_expert[size_t(layer) * E + e0 + x]);
+                              c->host_expert[size_t(layer) * E + e0 + x], c->copy);
       if (rc) return rc;
     }
-    if (int rc = c->copy_join(cl)) return rc;
+    if (int rc = c->copy_join(cl, c->copy)) return rc;
     c->close_span(sp_copy, c->copy);
     if ((e = hipEventRecord(c->pf_ready[half], c->copy)) != hipSuccess) return c->hip_fail(e, "record ready event");
 
