@@ -73,7 +73,8 @@ typedef struct {
                                        0: one hipMemcpyAsync per expert (DMA engine);
                                        1: one gather-copy kernel per request that reads the pinned
                                           pool directly (a few workgroups; keeps the link busier but
-                                          slows kernels that run beside it);
+                                          slows kernels that run beside it).  A blocking load that nothing
+                                          runs beside goes on compute_stream, in order with its kernels;
                                        2: experts dealt alternately to two DMA queues (copy_stream and one
                                           stream the library creates), so that one transfer's set-up hides
                                           behind the other's data */

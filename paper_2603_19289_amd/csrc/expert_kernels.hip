@@ -776,7 +776,7 @@ hipError_t launch_stream_read(const ExpertArgs &a, const ActiveList &act, size_t
 }
 
 hipError_t launch_combine(const ExpertArgs &a, hipStream_t st) {
-  const int v = a.B > kMaxBatch ? 4 : 1;
+  const int v = a.B > kMaxBatch && reinterpret_cast<uintptr_t>(a.out) % 16 == 0 ? 4 : 1;   // the caller's rows
   const dim3 grid((a.H + kBlock * v - 1) / (kBlock * v), a.B), block(kBlock);
   if (v == 4) hipLaunchKernelGGL(combine_kernel<4>, grid, block, 0, st, a);
   else hipLaunchKernelGGL(combine_kernel<1>, grid, block, 0, st, a);

@@ -708,9 +708,10 @@ __global__ __launch_bounds__(kBlock) void norm_rows_kernel(const ExpertArgs a, u
 // The routing of a layer and the matrix-core gate/up projection of its experts, predicted one layer earlier, in one
 // launch.  The first n_route workgroups route, n_wg per token (dispatched first: a token's are resident together).
 // Measured, routing + gate/up as two launches against this one and the norm before it: 8 tokens of 32 experts of
-// 2880 x 2880 16 + 124 / 4.7 + 120 us, 32 tokens of 128 experts of 768 x 2048 19 + 47 / 4.7 + 53.7 us, 4 tokens of
-// those with the estimator's projection 16.5 + 31 / 4.6 + 37 us.  One router row and two default-vector rows in flight
-// per wavefront instead of two and four: 56 us for the second.
+// 2880 x 2880 15.5 + 114 / 4.7 + 106 us, 32 tokens of 128 experts of 768 x 2048 20 + 42 / 4.2 + 47 to 51 us, 4 tokens of
+// those with the estimator's projection 13 + 32 / 4 + 32 us.  One router row and two default-vector rows in flight
+// per wavefront instead of two and four: 4 % slower for the second.  Three wavefronts per SIMD with one token tile: the
+// gate/up body holds 151 registers.
 template <int NT, int KSPLIT, bool PROJ>
 __global__ __launch_bounds__(kBlock, NT <= 1 ? 3 : NT == 4 && KSPLIT == 1 ? 1 : 2)
 void route_gateup_mfma_kernel(const RoutePairArgs ra, const ExpertArgs a, const TokenLists lists, const uint16_t *s_q,
