@@ -49,10 +49,12 @@ __device__ __forceinline__ void gather_tokens(const int32_t *ids, int n_ids, int
 // A operand = 16 weight rows, B operand = up to 16 tokens routed to the expert; K walks the reduction 128 columns per
 // step.  HBM decides how the weights are read: a load that takes 64 bytes of each of 16 rows, as the operand wants them,
 // streams at 5.5 to 5.8 TB/s however it is split (read-only kernel, 700 and 300 MB), one that takes 256 bytes of each of
-// four rows at 6.6 to 6.8, past the caches.  So lane (r, c) = (lane % 4, lane / 4) loads chunk c of 16 bytes of rows
+// four rows at 6.6 to 6.8, past the caches.  So lane (r, p) = (lane % 4, lane / 4) loads one chunk of 16 bytes of rows
 // r, 4 + r, 8 + r and 12 + r, and the four registers are turned in place (rows_to_lanes) until lane (m, g) =
-// (lane % 16, lane / 16) holds chunks 4 g .. 4 g + 3 of row m: 48 moves for 4 KB, a seventh of the time these take to
-// arrive.  The B operand is read with the same column assignment, which is all that the contraction needs.
+// (lane % 16, lane / 16) holds what lanes p = 4 g .. 4 g + 3 loaded of row m: 48 moves for 4 KB, a seventh of the time
+// these take to arrive.  Place p takes the chunk at column chunk_column(p), so that a row's sum adds 64 columns after 64
+// columns, the even chunks of each 64 and then the odd ones, however wide a step is.  The B operand is read with the same
+// column assignment.
 // Gate/up and down of 21 experts of 2880 x 2880, 12 positions of each most: 117.5 -> 101.5 us (6.9 TB/s) and
 // 64.4 -> 54.0; 48 experts of 768 x 2048, 32 tokens: 56.0 -> 47.7 and 31.1 -> 28.2; 8 of 14336 x 4096, 64 tokens: 349 ->
 // 352 and 232 -> 201.
@@ -83,7 +85,7 @@ __device__ __forceinline__ void swap_lanes(uint32_t &a, uint32_t &b) {
   b = __builtin_amdgcn_update_dpp(b, from_a, 0x100 + SHIFT, 0xf, LOW, false);      // row_shl
 }
 
-// w[i], lane (r, c) = (lane % 4, lane / 4): chunk c of row 4 i + r  ->  w[s], lane (m, g): chunk 4 g + s of row m.
+// w[i], lane (r, p) = (lane % 4, lane / 4): chunk p of row 4 i + r  ->  w[s], lane (m, g): chunk 4 g + s of row m.
 __device__ __forceinline__ void rows_to_lanes(uint4 (&w)[4]) {
 #define MOE_SWAP(f)                                                              \
   swap_lanes<4, 0xa, 0x5>(w[0].f, w[1].f); swap_lanes<4, 0xa, 0x5>(w[2].f, w[3].f); \
@@ -91,6 +93,10 @@ __device__ __forceinline__ void rows_to_lanes(uint4 (&w)[4]) {
   MOE_SWAP(x) MOE_SWAP(y) MOE_SWAP(z) MOE_SWAP(w)
 #undef MOE_SWAP
 }
+
+// Column, within a step of 128, of the chunk of 8 at place p = 0 .. 15: lane group g gets chunks 2 g and 2 g + 1 of the
+// first 64 columns, then of the second.
+__device__ __forceinline__ int chunk_column(int p) { return 16 * (p >> 2) + 64 * ((p >> 1) & 1) + 8 * (p & 1); }
 
 template <bool STREAM>
 __device__ __forceinline__ uint4 load_weights(const char *p) {
@@ -166,16 +172,17 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Toke
   // base and column in scalar registers, a lane's rows as byte offsets (an expert block is smaller than 4 GB)
   const char *p0 = reinterpret_cast<const char *>(wbase + (GATEUP ? size_t(0) : size_t(2) * a.I * a.H));
   const char *p1 = p0 + size_t(2) * a.I * a.H;             // W_up (GATEUP only)
+  const int w_col = chunk_column(lane >> 2), x_col = chunk_column(4 * g);
   uint32_t woff[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) woff[i] = (uint32_t(min(row_base + 4 * i + (lane & 3), R - 1)) * uint32_t(K) + 8 * (lane >> 2)) * 2;
+  for (int i = 0; i < 4; ++i) woff[i] = (uint32_t(min(row_base + 4 * i + (lane & 3), R - 1)) * uint32_t(K) + w_col) * 2;
 
   // columns past the wavefront's part load nothing and contribute zeros, so the staged loop
   // below may run one step beyond the end
   auto fetch_w = [&](int k0, MfmaStep<GATEUP, NT> &st) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) { st.w0[i] = make_uint4(0u, 0u, 0u, 0u); if (GATEUP) st.w1[i] = make_uint4(0u, 0u, 0u, 0u); }
-    if (k0 + 8 * (lane >> 2) < k_end) {
+    if (k0 + w_col < k_end) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         st.w0[i] = load_weights<Tokens::kStream>(p0 + size_t(k0) * 2 + woff[i]);
@@ -212,7 +219,10 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Toke
     for (int t = 0; t < NT; ++t) {
       if (t < ntiles) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) st.x[t][c] = load_bf16x8(bp[t] + k0 + 32 * g + 8 * c, k0 + 32 * g + 8 * c < k_end && bvalid[t]);
+        for (int c = 0; c < 4; ++c) {
+          const int col = k0 + x_col + chunk_column(c);
+          st.x[t][c] = load_bf16x8(bp[t] + col, col < k_end && bvalid[t]);
+        }
       }
     }
   };

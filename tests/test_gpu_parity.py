@@ -116,6 +116,64 @@ def test_matrix_core_path_at_the_edges_of_its_splits(hidden, inter, experts, top
     run_teacher_forced(wl, O.MODE_ON_DEMAND)
 
 
+def sums_of(hidden, inter, batch, gate_rows, down_rows, experts=1, slots=None, prefill=False):
+    """Outputs [batch,H] of one layer of equal experts, float64: s_l is all ones, a hidden unit is silu(gate row . 1), an
+    output is the down row . h."""
+    from paper_2603_19289_amd import moe_spec as M
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(name="sums", n_layers=1, hidden=hidden, n_experts=experts, top_k=1, inter=inter, dtype="bf16", batch=batch,
+                        tokens=1, slots=slots or experts)
+    up = torch.zeros(inter, hidden)
+    up[:, 0] = 1.0
+    block = torch.cat([t.to(torch.bfloat16).reshape(-1) for t in (gate_rows, up, down_rows)])
+    pool = torch.empty((1, experts, block.numel()), dtype=torch.bfloat16, pin_memory=True)
+    pool.copy_(block)
+    res = W.make_resident(wl)
+    res["rms_gain"] = np.ones_like(res["rms_gain"])
+    eng = engine_for(wl, M.MODE_ON_DEMAND, res, pool, max_batch=min(batch, 64), max_prefill_tokens=batch if prefill else 0)
+    try:
+        r = torch.ones((batch, hidden), device="cuda")
+        if prefill:
+            out = eng.prefill_layer_step(0, r)[0]
+        else:
+            eng.begin_token()
+            out = eng.layer_step(0, r)[0]
+        torch.cuda.synchronize()
+        return out.double().cpu()
+    finally:
+        eng.close()
+
+
+BIG = 2.0 ** 60                  # a sum that holds it has no room for numbers near one
+
+
+@pytest.mark.parametrize("columns,batch,prefill", [
+    (128, 2, False),             # one wavefront per tile
+    (1160, 2, False),            # four, whose parts end inside a step
+    (1160, 17, False), (2056, 40, False), (264, 64, False),
+    (1160, 5, True), (264, 70, True)])
+def test_matrix_core_sums_add_64_columns_after_64_columns(columns, batch, prefill):
+    """The order in which a matrix-core launch adds, seen through cancellation: of every 64 columns the even chunks of eight
+    are added first, then the odd ones: +BIG and -BIG in two even chunks are gone when a one in an odd chunk is added."""
+    print(f"[case] order of sums K={columns} B={batch} prefill={prefill}", flush=True)
+    rows = 64
+    patterns = torch.zeros(rows, columns)
+    for i in range(rows):
+        piece = 64 * (i % (columns // 64))
+        pair = [16 * (i // 3 % 4) + i % 8, 16 * ((i // 3 + 1 + i % 3) % 4) + (i + 3) % 8]       # in two even chunks
+        for col, v in zip(pair + [8 + 16 * (i // 2 % 4) + i // 4 % 8], (BIG, -BIG, 1.0)):
+            patterns[i, piece + col] = v
+    silu1 = 1.0 / (1.0 + np.exp(-1.0))
+    # gate/up: hidden unit i sums pattern i; the outputs pick the hidden units out
+    out = sums_of(columns, rows, batch, patterns, torch.eye(rows).repeat(-(-columns // rows), 1)[:columns], prefill=prefill)
+    assert (out[:, :rows] - silu1).abs().max() < 4e-3, out[0, :rows]
+    # down: all hidden units alike, output i sums pattern i
+    ones = torch.zeros(columns, rows)
+    ones[:, 0] = 1.0
+    out = sums_of(rows, columns, batch, ones, patterns, prefill=prefill)
+    assert (out - silu1).abs().max() < 4e-3, out[0]
+
+
 @pytest.mark.parametrize("mode", list(MODES))
 def test_edge_shapes(mode):
     # every expert selected; pool exactly k; one expert; one layer (no prediction at all)
