@@ -11,6 +11,7 @@
 #include "expert_mfma.h"
 #include "gateup_b1.h"
 #include "kernels.h"
+#include "launch_rules.h"
 
 namespace moe_spec {
 namespace {
@@ -209,19 +210,19 @@ __global__ __launch_bounds__(kBlock) void down_combine_b1_kernel(const ExpertArg
 
 // ---------------------------------------------------------------------------------------------
 // Matrix-core kernels for decode batches of two and more (bf16 weights) and for prefill
-template <bool GATEUP, int NT, int KSPLIT, bool STREAM>
+template <bool GATEUP, int NT, int KSPLIT, int CHAINS, bool STREAM>
 __global__ __launch_bounds__(kBlock) void expert_mfma_kernel(const ExpertArgs a, const TokenLists lists,
                                                              const uint16_t *act_q, uint16_t *hq_out) {
   __shared__ ExpertMfmaShared<GATEUP, NT, KSPLIT> sh;
-  expert_mfma_body<GATEUP, NT, KSPLIT>(a, DecodeTokens<STREAM>{lists, int(blockIdx.y)}, act_q, hq_out, blockIdx.x, sh);
+  expert_mfma_body<GATEUP, NT, KSPLIT, CHAINS>(a, DecodeTokens<STREAM>{lists, int(blockIdx.y)}, act_q, hq_out, blockIdx.x, sh);
 }
 
 template <bool GATEUP, int NT, int KSPLIT>
 __global__ __launch_bounds__(kBlock) void expert_mfma_lists_kernel(const ExpertArgs a, const ActiveList act,
                                                                    const uint16_t *act_q, uint16_t *hq_out) {
   __shared__ ExpertMfmaShared<GATEUP, NT, KSPLIT> sh;
-  expert_mfma_body<GATEUP, NT, KSPLIT>(a, PrefillTokens{act, int(blockIdx.y), int(blockIdx.z)}, act_q, hq_out,
-                                       blockIdx.x, sh);
+  expert_mfma_body<GATEUP, NT, KSPLIT, kOneChain>(a, PrefillTokens{act, int(blockIdx.y), int(blockIdx.z)}, act_q, hq_out,
+                                                  blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -602,17 +603,34 @@ void launch_down_combine_b1(const ExpertArgs &a, const ActiveList &act, hipStrea
   else launch_down_combine_b1_n<WT, 4, 4>(a, act, st);
 }
 
+// Compute units of the current device.
+hipError_t compute_units(int *n) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  return e != hipSuccess ? e : hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev);
+}
+
 template <bool GATEUP, int NT, bool STREAM>
 hipError_t launch_expert_mfma_n(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq,
                                 hipStream_t st) {
-  const int rows = GATEUP ? a.I : a.H;
-  const int positions = int(lists.expert[lists.n] & 0xffff);
-  return with_ksplit(GATEUP ? gateup_ksplit(a.H, (a.B + 15) / 16) : down_ksplit(a.I, rows, lists.n, positions), [&](auto ksplit) {
+  const int rows = GATEUP ? a.I : a.H, tiles = (a.B + 15) / 16, positions = int(lists.expert[lists.n] & 0xffff);
+  auto launch = [&](auto ksplit, auto chains) {
     const int rows_per_wg = 16 * kWaves / ksplit();
     const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg, lists.n), block(kBlock);
-    hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, NT, ksplit(), STREAM>), grid, block, 0, st, a, lists, act_q, hq);
+    hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, NT, ksplit(), chains(), STREAM>), grid, block, 0, st, a, lists, act_q, hq);
     return hipGetLastError();
-  });
+  };
+  if constexpr (GATEUP) {
+    return with_ksplit(gateup_ksplit(a.H, tiles), [&](auto ksplit) { return launch(ksplit, int_c<kOneChain>()); });
+  } else {
+    int cus = 0;
+    if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
+    return with_ksplit(down_ksplit(a.I, tiles, rows, lists.n, positions, cus), [&](auto ksplit) {
+      if constexpr (ksplit() == 4) return launch(ksplit, int_c<kOneChain>());
+      else if constexpr (ksplit() == 2) return launch(ksplit, int_c<kTwoChains>());
+      else return a.I < 1024 ? launch(ksplit, int_c<kTwoChains>()) : launch(ksplit, int_c<kFourParts>());
+    });
+  }
 }
 
 template <bool GATEUP, bool STREAM>
@@ -647,13 +665,6 @@ hipError_t launch_expert_mfma_lists_k(const ExpertArgs &a, const ActiveList &act
     default: hipLaunchKernelGGL((expert_mfma_lists_kernel<GATEUP, 4, KSPLIT>), grid, block, 0, st, a, act, act_q, hq); break;
   }
   return hipGetLastError();
-}
-
-// Compute units of the current device.
-hipError_t compute_units(int *n) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  return e != hipSuccess ? e : hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev);
 }
 
 // Prefill: the tiled kernel, or position lists through expert_mfma_kernel?  A tile takes about 1.5 us per 64

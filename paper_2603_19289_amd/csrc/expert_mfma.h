@@ -149,8 +149,12 @@ struct PrefillTokens {
   __device__ __forceinline__ static int token_of(int p, int k) { return p / k; }
 };
 
+// How a wavefront sums its part of a row: in one chain, in two (of every 64 columns alternately), or, where it has the whole
+// row, in a chain for each of four equal parts: the sum that four wavefronts come to.
+constexpr int kOneChain = 1, kTwoChains = 2, kFourParts = 4;
+
 // One workgroup: row block bx of the expert that tok names.
-template <bool GATEUP, int NT, int KSPLIT, typename Tokens>
+template <bool GATEUP, int NT, int KSPLIT, int CHAINS, typename Tokens>
 __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Tokens &tok, const uint16_t *act_q,
                                                  uint16_t *hq_out, const int bx,
                                                  ExpertMfmaShared<GATEUP, NT, KSPLIT> &sh) {
@@ -161,14 +165,17 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Toke
   const int R = GATEUP ? a.I : a.H;            // output rows
 
   const uint16_t *wbase = reinterpret_cast<const uint16_t *>(a.pool + size_t(tok.slot()) * a.slot_bytes);
+  static_assert(CHAINS == kOneChain || !GATEUP, "the second accumulator is W_up's");
+  static_assert(CHAINS != kFourParts || KSPLIT == 1, "four parts of the whole row");
   // KSPLIT wavefronts share 16 output rows: they split the reduction dimension into equal parts
   // (of whole 64 columns) and add their partial tiles in LDS: many short chains of dependent loads
   // keep HBM busier than few long ones.  Short reductions are not split: the launcher picks KSPLIT.
   const int row_base = (bx * (kMfmaWaves / KSPLIT) + wave / KSPLIT) * 16;
   const int part = wave % KSPLIT;
   const bool rows_inside = row_base < R;       // a workgroup's last tiles may lie past the matrix
-  const int k_part = (K + KSPLIT * 64 - 1) / (KSPLIT * 64) * 64;
-  const int k_begin = part * k_part, k_end = rows_inside ? min(K, k_begin + k_part) : k_begin;
+  constexpr int kParts = CHAINS == kFourParts ? 4 : KSPLIT;
+  const int k_part = (K + kParts * 64 - 1) / (kParts * 64) * 64;
+  const int k_begin = part * k_part, k_end = rows_inside ? min(K, k_begin + kParts / KSPLIT * k_part) : k_begin;
   // base and column in scalar registers, a lane's rows as byte offsets (an expert block is smaller than 4 GB)
   const char *p0 = reinterpret_cast<const char *>(wbase + (GATEUP ? size_t(0) : size_t(2) * a.I * a.H));
   const char *p1 = p0 + size_t(2) * a.I * a.H;             // W_up (GATEUP only)
@@ -213,6 +220,7 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Toke
   f32x4_t acc0[NT], acc1[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  int chain_end = k_part;                      // kFourParts: acc1 is the sum of the chains that have ended
 
   auto fetch_x = [&](int k0, MfmaStep<GATEUP, NT> &st) {
 #pragma unroll
@@ -226,17 +234,29 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Toke
       }
     }
   };
-  auto multiply = [&](MfmaStep<GATEUP, NT> &st) {
+  auto multiply = [&](int k0, MfmaStep<GATEUP, NT> &st) {
     rows_to_lanes(st.w0);
     if (GATEUP) rows_to_lanes(st.w1);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      if (t < ntiles) {
+    for (int half = 0; half < 2; ++half) {                 // 64 columns each
+      if (CHAINS == kFourParts && k0 + 64 * half == chain_end) {
+        chain_end += k_part;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          acc0[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.w0[c]), st.x[t][c], acc0[t], 0, 0, 0);
-          if (GATEUP)
-            acc1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.w1[c]), st.x[t][c], acc1[t], 0, 0, 0);
+        for (int t = 0; t < NT; ++t) {
+          acc1[t] += acc0[t];
+          acc0[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (t < ntiles) {
+#pragma unroll
+          for (int c = 2 * half; c < 2 * half + 2; ++c) {
+            f32x4_t &acc = CHAINS == kTwoChains && half == 1 ? acc1[t] : acc0[t];
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.w0[c]), st.x[t][c], acc, 0, 0, 0);
+            if (GATEUP)
+              acc1[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, st.w1[c]), st.x[t][c], acc1[t], 0, 0, 0);
+          }
         }
       }
     }
@@ -245,12 +265,16 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Toke
   for (int k0 = k_begin; k0 < k_end; k0 += 256) {
     fetch_x(k0, even);
     fetch_w(k0 + 128, odd);
-    multiply(even);
+    multiply(k0, even);
     fetch_x(k0 + 128, odd);
     fetch_w(k0 + 256, even);
-    multiply(odd);
+    multiply(k0 + 128, odd);
   }
 
+  if (CHAINS != kOneChain) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] + acc0[t];
+  }
   if (KSPLIT > 1) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
@@ -306,29 +330,6 @@ __device__ __forceinline__ void expert_mfma_body(const ExpertArgs &a, const Toke
       }
     }
   }
-}
-
-// Wavefronts per 16-row tile.  gateup_ksplit: each should still walk eight steps of 64 columns, below that the shared
-// start-up (partial sums) outweighs what the extra parallelism wins; in batches of a single tile of tokens two are enough
-// (16 experts of 1024 columns, 64 tokens, 1 / 2 / 4 wavefronts: 15.2 / 13.5 / 14.9 us; 12 of them, 8 tokens: 13.6 / 12.3 /
-// 10.3).  By the tokens of the batch, not of an expert, so that a launch beside the routing and one of its own add in the
-// same order.  Prefill splits both its products like that.
-inline int gateup_ksplit(int K, int token_tiles) {
-  const int steps = (K + 63) / 64;
-  if (steps >= 32 || (token_tiles == 1 && steps >= 8)) return 4;
-  return steps >= 16 ? 2 : 1;
-}
-
-// Down projection of a decode batch: as many wavefronts as leave each two whole steps of 128 columns, unless its experts
-// have eight positions or more on average and there are two workgroups per compute unit without a split: then the
-// activations weigh as much as the weights, and the four wavefronts of a workgroup share them if they walk the same
-// columns.  Microseconds with 1 / 2 / 4 wavefronts: 30 experts of 768 columns x 2048 rows at 1 position each 18.2 / 18.0 /
-// 19.5, 48 of them at 5 27.4 / 28.2 / 29.9, 21 of 2880 x 2880 at 1.5 60.9 / 58.1 / 54.1, 8 of 14336 x 4096 at 4 148 / 155 /
-// 153, at 8 164 / 177 / 182, at 16 201 / 238 / 249, 5 of them at 1.6 130 / 103 / 90.6, 16 of 2048 x 2048 at 16 31 / 35 / 37,
-// 16 of 1024 x 1024 at 16 (256 workgroups without a split) 10.7 / 9.1 / 9.0.
-inline int down_ksplit(int K, int rows, int experts, int positions) {
-  if (positions >= 8 * experts && long(experts) * ((rows + 63) / 64) >= 512) return 1;
-  return K >= 1024 ? 4 : K >= 512 ? 2 : 1;
 }
 
 template <int V> using int_c = std::integral_constant<int, V>;

@@ -725,8 +725,8 @@ void route_gateup_mfma_kernel(const RoutePairArgs ra, const ExpertArgs a, const 
   }
   const int i = blockIdx.x - n_route;
   ExpertMfmaShared<true, NT, KSPLIT> &sh = *reinterpret_cast<ExpertMfmaShared<true, NT, KSPLIT> *>(beside_lds);
-  if (stream) expert_mfma_body<true, NT, KSPLIT>(a, DecodeTokens<true>{lists, i / row_blocks}, s_q, hq, i % row_blocks, sh);
-  else expert_mfma_body<true, NT, KSPLIT>(a, DecodeTokens<false>{lists, i / row_blocks}, s_q, hq, i % row_blocks, sh);
+  if (stream) expert_mfma_body<true, NT, KSPLIT, kOneChain>(a, DecodeTokens<true>{lists, i / row_blocks}, s_q, hq, i % row_blocks, sh);
+  else expert_mfma_body<true, NT, KSPLIT, kOneChain>(a, DecodeTokens<false>{lists, i / row_blocks}, s_q, hq, i % row_blocks, sh);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -94,6 +94,33 @@ inline int routing_workgroups(int E, int rows_per_wg, int proj_rows, int B, int 
   return std::max(for_router, std::min(cus / B, ((proj_rows + 1) / 2 + kRouteWaves - 1) / kRouteWaves));
 }
 
+// Wavefronts per 16-row tile of the matrix-core kernels.  Each sums its part of a row in a float32 chain of its own, so the
+// rules of what a row's sum consists of go by the length of the reduction and the tokens of the batch or prompt alone: a
+// result does not depend on how many experts a launch has, on the slots they are in or on what runs beside it.
+// Gate/up, and both products of a prompt: each should still walk eight steps of 64 columns, below that the shared start-up
+// (partial sums) outweighs what the extra parallelism wins; in batches of a single tile of tokens two are enough (16 experts
+// of 1024 columns, 64 tokens, 1 / 2 / 4 wavefronts: 15.2 / 13.5 / 14.9 us; 12 of them, 8 tokens: 13.6 / 12.3 / 10.3).
+inline int gateup_ksplit(int K, int token_tiles) {
+  const int steps = (K + 63) / 64;
+  if (steps >= 32 || (token_tiles == 1 && steps >= 8)) return 4;
+  return steps >= 16 ? 2 : 1;
+}
+
+// Down projection of a decode batch: as many as leave each two whole steps of 128 columns.  Below 1024 columns a wavefront
+// has two chains, so that a sum of 512 columns, or 449 in batches of a single tile, has four of them however it is split: a
+// chain of 456 columns is 1.5 times as far from 64 bits.
+// From 1024 columns on one wavefront takes the four parts one after another, with the same sum, if the experts have eight
+// positions or more on average and there are two workgroups per compute unit without a split: then the activations weigh as
+// much as the weights, and the four wavefronts of a workgroup share them if they walk the same columns.  Microseconds with 1
+// / 2 / 4 wavefronts: 30 experts of 768 columns x 2048 rows at 1 position each 18.2 / 18.0 / 19.5, 48 of them at 5 27.4 / 28.2
+// / 29.9, 21 of 2880 x 2880 at 1.5 60.9 / 58.1 / 54.1, 8 of 14336 x 4096 at 4 148 / 155 / 153, at 8 164 / 177 / 182, at 16 201
+// / 238 / 249, 5 of them at 1.6 130 / 103 / 90.6, 16 of 2048 x 2048 at 16 31 / 35 / 37, 16 of 1024 x 1024 at 16 (256
+// workgroups without a split) 10.7 / 9.1 / 9.0.
+inline int down_ksplit(int K, int token_tiles, int rows, int experts, int positions, int cus) {
+  if (K < 1024) return K >= 512 || (token_tiles == 1 && K > 448) ? 2 : 1;
+  return positions >= 8 * experts && long(experts) * ((rows + 63) / 64) >= 2l * cus ? 1 : 4;
+}
+
 // The last experts of a prompt's layer: nothing travels beside their kernels any more, so these end the call.  Whether
 // the experts of the last group are run one by one as they arrive, and the last one in pieces, by what the kernels of an
 // expert are estimated to take (600 TFLOP/s, what the tiled kernel reaches on a whole expert) beside its transfer (57

@@ -7,7 +7,7 @@ import torch
 
 from oracle import moe_oracle as O
 from paper_2603_19289_amd import workload as W
-from tests.helpers import build, check_output, make_advance, small_workload
+from tests.helpers import build, check_output, kernels_launched, make_advance, small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -116,28 +116,34 @@ def test_matrix_core_path_at_the_edges_of_its_splits(hidden, inter, experts, top
     run_teacher_forced(wl, O.MODE_ON_DEMAND)
 
 
-def sums_of(hidden, inter, batch, gate_rows, down_rows, experts=1, slots=None, prefill=False):
+def sums_of(hidden, inter, batch, gate_rows, down_rows, experts=1, prefill=False, call=lambda f: f()):
     """Outputs [batch,H] of one layer of equal experts, float64: s_l is all ones, a hidden unit is silu(gate row . 1), an
-    output is the down row . h."""
+    output is the down row . h.  With several experts s_l has random signs behind its first column, so that they are used."""
     from paper_2603_19289_amd import moe_spec as M
     from paper_2603_19289_amd.engine import engine_for
     wl = small_workload(name="sums", n_layers=1, hidden=hidden, n_experts=experts, top_k=1, inter=inter, dtype="bf16", batch=batch,
-                        tokens=1, slots=slots or experts)
+                        tokens=1, slots=experts)
     up = torch.zeros(inter, hidden)
     up[:, 0] = 1.0
     block = torch.cat([t.to(torch.bfloat16).reshape(-1) for t in (gate_rows, up, down_rows)])
     pool = torch.empty((1, experts, block.numel()), dtype=torch.bfloat16, pin_memory=True)
     pool.copy_(block)
+    r = torch.ones((batch, hidden))
+    if experts > 1:
+        r[:, 1:] = torch.randint(0, 2, (batch, hidden - 1), generator=torch.Generator().manual_seed(3)) * 2.0 - 1.0
     res = W.make_resident(wl)
     res["rms_gain"] = np.ones_like(res["rms_gain"])
     eng = engine_for(wl, M.MODE_ON_DEMAND, res, pool, max_batch=min(batch, 64), max_prefill_tokens=batch if prefill else 0)
     try:
-        r = torch.ones((batch, hidden), device="cuda")
-        if prefill:
-            out = eng.prefill_layer_step(0, r)[0]
-        else:
-            eng.begin_token()
-            out = eng.layer_step(0, r)[0]
+        r, out = r.cuda(), torch.zeros((batch, hidden), device="cuda")
+
+        def step():
+            if prefill:
+                eng.prefill_layer_step(0, r, out)
+            else:
+                eng.begin_token()
+                eng.layer_step(0, r, out)
+        call(step)
         torch.cuda.synchronize()
         return out.double().cpu()
     finally:
@@ -173,6 +179,50 @@ def test_matrix_core_sums_add_64_columns_after_64_columns(columns, batch, prefil
     out = sums_of(rows, columns, batch, ones, patterns, prefill=prefill)
     assert (out - silu1).abs().max() < 4e-3, out[0]
 
+
+
+@pytest.mark.parametrize("hidden,inter,experts,batch,waves", [(4096, 2056, 8, 64, 1), (8192, 1096, 4, 64, 1),
+                                                              (72, 1096, 1, 2, 4), (72, 2056, 1, 40, 4)])
+def test_long_down_projection_sums_in_four_parts_whatever_the_wavefronts(hidden, inter, experts, batch, waves):
+    """From 1024 columns on the sum of a down projection is that of four parts, whether four wavefronts have one each or one
+    has all: visible where +BIG and -BIG meet inside a part behind a one in the part before."""
+    print(f"[case] parts of sums H={hidden} I={inter} E={experts} B={batch}", flush=True)
+    part = -(-inter // 256) * 64
+    patterns = torch.zeros(hidden, inter)
+    for i in range(hidden):
+        second = part * (1 + i % max(1, (inter - 1) // part))
+        room = min(part, inter - second)
+        patterns[i, i % part + second - part] = 1.0
+        patterns[i, second + i % min(8, room)] = BIG
+        patterns[i, second + room - 1 - i % min(8, room // 2)] -= BIG
+    gate = torch.zeros(inter, hidden)
+    gate[:, 0] = 1.0
+    counts = {}
+    out = sums_of(hidden, inter, batch, gate, patterns, experts=experts,
+                  call=lambda step: counts.update(kernels_launched(step, {"expert_mfma_kernel<false": 1, "combine": 1})))
+    assert [n.split(", ")[2] for n in counts if "expert_mfma_kernel<false" in n] == [str(waves)], counts
+    silu1 = 1.0 / (1.0 + np.exp(-1.0))
+    assert (out - silu1).abs().max() < 4e-3, out[0]
+
+
+@pytest.mark.parametrize("inter", [456, 520, 712, 1032])
+def test_sums_do_not_depend_on_the_slots(inter):
+    """A batch whose experts run in one cache wave or in three adds in the same order: bit for bit the same outputs."""
+    from paper_2603_19289_amd import moe_spec as M
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(name="slots", n_layers=1, hidden=4096, n_experts=8, top_k=2, inter=inter, dtype="bf16", batch=64, tokens=1)
+    res, ex, _ = build(wl, "random")
+    r = torch.from_numpy(W.make_inputs(wl)[0][0]).cuda()
+    got = []
+    for slots in (8, 3):
+        eng = engine_for(wl.with_(slots=slots), M.MODE_ON_DEMAND, res, ex)
+        try:
+            eng.begin_token()
+            got.append(eng.layer_step(0, r)[0])
+            assert eng.stats()["cache_waves"] == -(-8 // slots)
+        finally:
+            eng.close()
+    assert torch.equal(*got) and got[0].abs().max() > 0
 
 @pytest.mark.parametrize("mode", list(MODES))
 def test_edge_shapes(mode):
