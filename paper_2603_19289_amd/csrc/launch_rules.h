@@ -121,6 +121,17 @@ inline int down_ksplit(int K, int token_tiles, int rows, int experts, int positi
   return positions >= 8 * experts && long(experts) * ((rows + 63) / 64) >= 2l * cus ? 1 : 4;
 }
 
+// Whether the copies of a step's second and further cache waves go on the compute stream although a prefetch for the next
+// layer is queued on the copy stream right behind them and takes half of the link meanwhile.  They save an event there and
+// back (some 15 us a wave) and the prefetch runs beside the kernels of the waves, but the last wave ends later, and nothing
+// travels beside its kernels and the next routing.  Microseconds per layer step on the copy stream / on the compute stream,
+// experts of 50 MB: 28 experts in 8 slots 24141 / 24030, 28 in 24 6768 / 6726, 16 in 6 13222 / 13107, but 28 in 16 19301 /
+// 19616, 28 in 14 22666 / 22877, 16 in 10 10009 / 10061; of 9.4 MB the same six 4759 / 4680, 1445 / 1416, 2555 / 2532, 3975 /
+// 4021, 4558 / 4569, 1969 / 1960; of 3.1 MB 1643 / 1580, 460 / 445, 1004 / 971, 1334 / 1338, 1530 / 1527, 785 / 771.
+inline bool waves_in_order(int experts, int slots, std::size_t expert_bytes) {
+  return experts > 2 * slots || 4 * (experts - slots) <= slots || expert_bytes <= std::size_t(4) << 20;
+}
+
 // The last experts of a prompt's layer: nothing travels beside their kernels any more, so these end the call.  Whether
 // the experts of the last group are run one by one as they arrive, and the last one in pieces, by what the kernels of an
 // expert are estimated to take (600 TFLOP/s, what the tiled kernel reaches on a whole expert) beside its transfer (57

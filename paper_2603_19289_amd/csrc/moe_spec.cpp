@@ -1073,7 +1073,8 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     } else {
       std::vector<int> req(exec_union.begin() + w0, exec_union.begin() + std::min(exec_union.size(), w0 + S));
       // With a prediction behind the true routing in the same launch, the first copies start beside it.
-      int rc = c->request(layer, req, &act, &copies, wave > 0 || !do_pred);
+      const bool in_order = !do_pred || (wave > 0 && (!prefetching || waves_in_order(int(exec_union.size()), S, c->expert_bytes)));
+      int rc = c->request(layer, req, &act, &copies, in_order);
       if (rc) return rc;
     }
     if (c->ready_pending[layer]) {

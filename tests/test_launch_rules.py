@@ -91,3 +91,14 @@ def test_rows_shared_with_the_routing_workgroups_are_dealt_once(tmp_path):
     }
   }
   if (shared == 0) ++bad;""")
+
+
+def test_cache_waves_stay_behind_a_prefetch_where_it_would_slow_them_down(tmp_path):
+    # (experts of a step, slots, bytes of an expert): measured slower on the compute stream, and faster
+    sweep(tmp_path, r"""
+  const std::size_t MB = 1000000;
+  const struct { int experts, slots; std::size_t bytes; bool in_order; } cases[] = {
+    {28, 16, 50 * MB, false}, {28, 14, 50 * MB, false}, {16, 10, 50 * MB, false}, {28, 16, 28 * MB, false}, {28, 16, 9 * MB, false},
+    {28, 8, 50 * MB, true}, {28, 24, 50 * MB, true}, {16, 6, 50 * MB, true}, {28, 8, 6 * MB, true}, {28, 14, 3 * MB, true}, {16, 10, MB, true}};
+  for (const auto &c : cases)
+    if (waves_in_order(c.experts, c.slots, c.bytes) != c.in_order) { ++bad; std::printf("%d %d %zu\n", c.experts, c.slots, c.bytes); }""")
