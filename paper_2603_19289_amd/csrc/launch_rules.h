@@ -132,6 +132,17 @@ inline bool waves_in_order(int experts, int slots, std::size_t expert_bytes) {
   return experts > 2 * slots || 4 * (experts - slots) <= slots || expert_bytes <= std::size_t(4) << 20;
 }
 
+// Whether a prompt is routed by the launches of a decode step, one for each micro-batch of up to max_batch tokens, or all at
+// once by the kernel for prompts, whose workgroups take 16 tokens each: with few of them most of the device is idle and the
+// launch takes what one workgroup takes, by experts and columns.  Microseconds, launches of a decode step / prompt kernel:
+// 128 experts, 2048 columns: 1 token in 1 launch 8 / 69, 64 in 1 12 / 73, 128 in 2 24 / 73, 200 in 4 42 / 73, 64 in 8 93 / 73,
+// 600 in 10 116 / 81; 8, 1024: 64 in 1 6 / 17, 128 in 2 17 / 17, 200 in 4 31 / 16; 16, 8192: 64 in 1 20 / 82, 200 in 4 71 /
+// 100, 600 in 10 184 / 102; 256, 8192: 64 in 1 201 / 443, 64 in 8 269 / 440, 128 in 2 401 / 441, 200 in 4 643 / 442.
+inline bool routed_like_decode(int P, int max_batch, int E, int H) {
+  const int launches = (P + max_batch - 1) / max_batch;
+  return P <= 128 && (launches <= 2 || 20.0 * launches < 2e-4 * E * H);
+}
+
 // The last experts of a prompt's layer: nothing travels beside their kernels any more, so these end the call.  Whether
 // the experts of the last group are run one by one as they arrive, and the last one in pieces, by what the kernels of an
 // expert are estimated to take (600 TFLOP/s, what the tiled kernel reaches on a whole expert) beside its transfer (57

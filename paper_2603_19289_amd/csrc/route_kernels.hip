@@ -371,6 +371,8 @@ hipError_t launch_route(const RouteArgs &a, int dtype, hipStream_t st) {
 // One launch instead of one per max_batch tokens, each of which took 8 to 22 us and 2.6 us of the host, which queues the
 // experts' copies behind them: 32768 tokens, 8 experts, 4096 columns 4.2 ms and more -> 0.37 ms; 512 tokens,
 // 128 experts, 2048 columns (32 workgroups: a chain of 128 matrix instructions per 32 columns) 112 -> 89 us.
+namespace {
+
 constexpr int kPromptTokens = 16;
 typedef __attribute__((ext_vector_type(4))) double f64x4_t;
 
@@ -545,6 +547,8 @@ hipError_t launch_route_prompt_t(const RoutePromptArgs &a, hipStream_t st) {
   else hipLaunchKernelGGL((route_prompt_kernel<WT, 16>), grid, block, 0, st, a);
   return hipGetLastError();
 }
+
+}  // namespace
 
 hipError_t launch_route_prompt(const RoutePromptArgs &a, int dtype, hipStream_t st) {
   return dtype == 1 ? launch_route_prompt_t<uint16_t>(a, st) : launch_route_prompt_t<float>(a, st);

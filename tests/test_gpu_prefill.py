@@ -304,6 +304,20 @@ def test_prefill_routing_at_the_edges_of_its_tiles(dtype, hidden, experts, top_k
     run_prefill(wl, P=P, max_batch=16, label="routing", prebuilt=(res, oracle_model(wl, res, ex), ex))
 
 
+@pytest.mark.parametrize("dtype,hidden,experts,top_k,P,max_batch,launches_like_decode", [
+    ("bf16", 40, 16, 16, 15, 4, 0), ("f32", 72, 17, 4, 16, 4, 0), ("bf16", 136, 33, 8, 17, 4, 0), ("f32", 1032, 64, 16, 33, 16, 0),
+    ("bf16", 264, 65, 3, 31, 8, 0), ("f32", 40, 129, 16, 20, 1, 0), ("bf16", 2056, 128, 8, 18, 4, 0), ("bf16", 72, 256, 16, 47, 16, 0),
+    ("bf16", 8192, 9, 2, 16, 4, 0), ("bf16", 2056, 128, 8, 18, 18, 1), ("f32", 264, 12, 3, 40, 39, 2), ("bf16", 264, 12, 3, 128, 64, 2),
+    ("f32", 264, 12, 3, 129, 64, 0), ("bf16", 8192, 64, 2, 10, 4, 3)])
+def test_prefill_routing_by_the_prompt_kernel_and_by_decode_launches(dtype, hidden, experts, top_k, P, max_batch, launches_like_decode):
+    """Prompts of up to two micro-batches, and of more where the routers are large, are routed by the launches of a decode
+    step, all others by the kernel for prompts; both against the checker, at the edges of the latter's tiles."""
+    wl = small_workload(n_layers=1, hidden=hidden, n_experts=experts, top_k=top_k, inter=8, dtype=dtype, slots=experts)
+    counts = kernels_launched(lambda: run_prefill(wl, P=P, max_batch=max_batch, label="routing"), {"combine": 1})
+    assert launches(counts, "route_pair_kernel") == launches_like_decode, counts
+    assert launches(counts, "route_prompt_kernel") == (launches_like_decode == 0), counts
+
+
 @pytest.mark.parametrize("experts", [9, 70])
 def test_prefill_non_finite_inputs_keep_expert_ids_in_range(experts):
     from paper_2603_19289_amd.engine import engine_for

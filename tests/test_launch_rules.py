@@ -102,3 +102,14 @@ def test_cache_waves_stay_behind_a_prefetch_where_it_would_slow_them_down(tmp_pa
     {28, 8, 50 * MB, true}, {28, 24, 50 * MB, true}, {16, 6, 50 * MB, true}, {28, 8, 6 * MB, true}, {28, 14, 3 * MB, true}, {16, 10, MB, true}};
   for (const auto &c : cases)
     if (waves_in_order(c.experts, c.slots, c.bytes) != c.in_order) { ++bad; std::printf("%d %d %zu\n", c.experts, c.slots, c.bytes); }""")
+
+
+def test_short_prompts_are_routed_by_the_launches_of_a_decode_step(tmp_path):
+    # (tokens, largest batch, experts, columns): measured faster that way, and slower
+    sweep(tmp_path, r"""
+  const struct { int P, max_batch, E, H; bool decode; } cases[] = {
+    {1, 64, 8, 1024, true}, {64, 64, 128, 2048, true}, {128, 64, 128, 2048, true}, {1, 1, 256, 8192, true}, {64, 8, 256, 8192, true},
+    {16, 1, 256, 8192, true}, {200, 64, 256, 8192, false}, {600, 64, 128, 2048, false}, {64, 8, 128, 2048, false},
+    {16, 1, 128, 2048, false}, {200, 64, 8, 1024, false}, {32768, 64, 8, 4096, false}};
+  for (const auto &c : cases)
+    if (routed_like_decode(c.P, c.max_batch, c.E, c.H) != c.decode) { ++bad; std::printf("%d %d %d %d\n", c.P, c.max_batch, c.E, c.H); }""")
