@@ -1425,7 +1425,7 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
     act.n = n_here;
     c->st.cache_misses += n_here;
     c->st.h2d_bytes += int64_t(n_here) * int64_t(c->expert_bytes);
-    c->st.hbm_bytes_algorithmic += int64_t(n_here) * int64_t(c->expert_bytes);
+    c->st.hbm_bytes_algorithmic += int64_t(n_here) * int64_t(c->expert_bytes) * (all_at_once ? 1 : (P + MB - 1) / MB);
     TimedSpan *sp_copy = c->open_span(1, c->copy);
     CopyList cl{};
     cl.n16 = uint32_t(c->expert_bytes / 16);

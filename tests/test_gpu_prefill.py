@@ -318,6 +318,20 @@ def test_prefill_routing_by_the_prompt_kernel_and_by_decode_launches(dtype, hidd
     assert launches(counts, "route_prompt_kernel") == (launches_like_decode == 0), counts
 
 
+@pytest.mark.parametrize("dtype,P,max_batch,passes", [("f32", 37, 16, 3), ("f32", 16, 16, 1), ("bf16", 37, 16, 1)])
+def test_prefill_counts_the_weight_bytes_its_kernels_read(dtype, P, max_batch, passes):
+    """float32 experts are launched, and read, once for each micro-batch; bf16 experts and the router once per prompt."""
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(n_layers=1, hidden=72, n_experts=6, top_k=2, inter=40, dtype=dtype, slots=4)
+    eng = engine_for(wl, M.MODE_ON_DEMAND, *build(wl, "random")[:2], max_batch=max_batch, max_prefill_tokens=P)
+    try:
+        eng.prefill_layer_step(0, torch.from_numpy(prompt_of(wl, P)[0]).cuda())
+        size = 4 if dtype == "f32" else 2
+        assert eng.stats()["hbm_bytes_algorithmic"] == 6 * 72 * size + passes * 6 * 3 * 72 * 40 * size
+    finally:
+        eng.close()
+
+
 @pytest.mark.parametrize("experts", [9, 70])
 def test_prefill_non_finite_inputs_keep_expert_ids_in_range(experts):
     from paper_2603_19289_amd.engine import engine_for
