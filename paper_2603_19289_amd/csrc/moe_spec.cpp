@@ -1381,13 +1381,21 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
       };
       auto arrived = [&]() {                           // what was queued so far, before the next launch
         if (le == hipSuccess) le = hipEventRecord(c->pf_tail[q], queue);
+        TimedSpan *sp_stall = c->open_span(2, c->compute);
         if (le == hipSuccess) le = hipStreamWaitEvent(c->compute, c->pf_tail[q], 0);
+        c->close_span(sp_stall, c->compute);
         return le == hipSuccess ? MOE_SPEC_OK : c->hip_fail(le, "host-to-device expert copy");
+      };
+      auto timed = [&](auto launch) {
+        TimedSpan *sp_exec = c->open_span(0, c->compute);
+        const int rc = launch();
+        c->close_span(sp_exec, c->compute);
+        return rc;
       };
       int rc = MOE_SPEC_OK;
       if (x + 1 < act.n || !tail.pieces) {
         copy(0, c->expert_bytes);
-        if ((rc = arrived()) || (rc = run_experts(one))) return rc;
+        if ((rc = arrived()) || (rc = timed([&] { return run_experts(one); }))) return rc;
         continue;
       }
       const size_t matrix = c->expert_bytes / 3;
@@ -1397,10 +1405,10 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
         for (int r0 = 0, r1 = half; r0 < rows; r0 = r1, r1 = rows) {
           if (gateup) copy(size_t(r0) * row, size_t(r1 - r0) * row);
           copy((gateup ? 1 : 2) * matrix + size_t(r0) * row, size_t(r1 - r0) * row);
-          if ((rc = arrived()) || (rc = run_product(one, gateup, r0, r1))) return rc;
+          if ((rc = arrived()) || (rc = timed([&] { return run_product(one, gateup, r0, r1); }))) return rc;
         }
       }
-      if ((rc = accumulate(one, 0, P))) return rc;
+      if (cfg.accumulate_defaults && (rc = timed([&] { return accumulate(one, 0, P); }))) return rc;
     }
     return int(MOE_SPEC_OK);
   };
@@ -1430,11 +1438,9 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
     CopyList cl{};
     cl.n16 = uint32_t(c->expert_bytes / 16);
     if (tail.by_expert && e0 + group >= E) {
-      TimedSpan *sp_exec = c->open_span(0, c->compute);
       int rc = run_tail(act);
       if (rc || (rc = c->copy_join(cl, c->copy))) return rc;
       c->close_span(sp_copy, c->copy);
-      c->close_span(sp_exec, c->compute);
       break;
     }
     for (int x = 0; x < n_here; ++x) {

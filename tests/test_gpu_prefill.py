@@ -376,3 +376,37 @@ def test_prefill_tail_in_pieces_equals_whole_groups(slots, engine, pairs):
         expected = pairs if e == engine else whole
         assert [launches(counts, f"expert_tile_kernel<{b}>") for b in ("true", "false")] == [expected] * 2, counts
     assert torch.equal(got[0], got[-1])
+
+
+def tail_inputs(hidden, inter, experts, top_k, P):
+    """A layer of `experts` random experts and a prompt, everything from one seed: (workload, pool, residuals)."""
+    wl = small_workload(n_layers=1, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype="bf16", slots=2 * experts)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    pool = torch.empty((1, experts, 3 * hidden * inter), dtype=torch.bfloat16, pin_memory=True)
+    pool.copy_(0.02 * torch.randn(pool.shape, generator=g, device="cuda"))
+    return wl, pool, torch.randn((P, hidden), generator=g, device="cuda")
+
+
+@pytest.mark.parametrize("hidden,inter,experts,top_k,P", [(2056, 6008, 3, 1, 7400), (520, 1032, 8, 2, 16000)])
+def test_prefill_profile_separates_the_tail_s_kernels_from_their_waits(hidden, inter, experts, top_k, P):
+    """The last group's experts one by one, with and without the last one in pieces: transfers take longer than kernels, so
+    the compute stream mostly waits, and its two figures together fit into the call."""
+    from paper_2603_19289_amd.engine import engine_for
+    wl, pool, r = tail_inputs(hidden, inter, experts, top_k, P)
+    eng = engine_for(wl, M.MODE_ON_DEMAND, W.make_resident(wl), pool, max_batch=64, max_prefill_tokens=P, copy_engine=M.COPY_DMA2,
+                     profile=1)
+    try:
+        eng.prefill_layer_step(0, r)
+        eng.reset()
+        start, done = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record(eng.compute)
+        eng.prefill_layer_step(0, r)
+        done.record(eng.compute)
+        st = eng.stats()
+        took = start.elapsed_time(done)
+        print(f"[case] profile of the tail: {took:.2f} ms, copies {st['copy_ms']:.2f}, kernels {st['compute_ms']:.2f}, "
+              f"stalls {st['stall_ms']:.2f}", flush=True)
+        assert st["stall_ms"] > 0.2 * st["copy_ms"] and st["compute_ms"] + st["stall_ms"] < 1.05 * took
+        assert st["compute_ms"] < 0.8 * took
+    finally:
+        eng.close()
