@@ -88,7 +88,8 @@ typedef struct {
                                        behind the default vectors, Sec. 3.1); costs L*E*H doubles of arena
                                        and disables the fused batch-1 down+combine kernel */
   int32_t max_prefill_tokens;       /* 0 <= P_max <= 32768: most prompt tokens one moe_spec_prefill_layer_step takes;
-                                       0: no prefill path.  Costs about P_max*(k+2)*H floats of arena */
+                                       0: no prefill path.  Costs about P_max*(k+1)*H floats of arena; with bf16 weights
+                                       P_max*k*H floats, P_max*(H + k*I) bf16 values and P_max*E words */
   int32_t wait_spin_limit;          /* kernels that wait for another workgroup's result poll at most this
                                        often before they give up and the call after reports MOE_SPEC_EHIP;
                                        0: the default (about two seconds).  Tests force tiny values */

@@ -5,9 +5,6 @@
 
 #include "device_utils.h"
 #include "kernels.h"
-#ifdef MOE_DEV
-#include <cstdlib>
-#endif
 
 namespace moe_spec {
 

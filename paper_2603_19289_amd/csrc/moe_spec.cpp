@@ -148,8 +148,8 @@ ArenaLayout layout_of(const moe_spec_config *c) {
   a.est_v = take(B * size_t(c->est_latent) * 8);
   a.tr_end = off;
   const size_t P = size_t(c->max_prefill_tokens);
-  a.pf_s = take(P * H * 4);
-  a.pf_sq = take(P * H * 2);
+  a.pf_s = take(c->dtype == MOE_SPEC_F32 ? P * H * 4 : 0);
+  a.pf_sq = take(c->dtype == MOE_SPEC_BF16 ? P * H * 2 : 0);
   a.pf_ids = take(P * k * 4);
   a.pf_gates = take(P * k * 4);
   a.pf_y = take(P * k * H * 4);
@@ -1227,8 +1227,9 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
   const size_t wbytes = cfg.dtype == MOE_SPEC_BF16 ? 2 : 4;
   const float *r = static_cast<const float *>(r_dev);
   float *out = static_cast<float *>(out_dev);
-  float *s_all = c->at<float>(c->lay.pf_s);
-  uint16_t *sq_all = c->at<uint16_t>(c->lay.pf_sq);
+  const bool bf16 = cfg.dtype == MOE_SPEC_BF16;
+  float *s_all = bf16 ? nullptr : c->at<float>(c->lay.pf_s);                 // s_l in the form that the experts read
+  uint16_t *sq_all = bf16 ? c->at<uint16_t>(c->lay.pf_sq) : nullptr;
   int32_t *ids_all = c->at<int32_t>(c->lay.pf_ids);
   float *gates_all = c->at<float>(c->lay.pf_gates);
   float *y_all = c->at<float>(c->lay.pf_y);
@@ -1255,8 +1256,8 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
       pa.z_pred_next = c->zslot_set(1, c->route_parity ^ 1);
       pa.arm_count = cfg.max_batch * E;
       c->route_parity ^= 1;
-      pa.s_out = s_all + size_t(t0) * H;
-      pa.s_out_q = cfg.dtype == MOE_SPEC_BF16 ? sq_all + size_t(t0) * H : nullptr;
+      pa.s_out = bf16 ? c->at<float>(c->lay.s_buf) : s_all + size_t(t0) * H;   // decode scratch of one micro-batch
+      pa.s_out_q = bf16 ? sq_all + size_t(t0) * H : nullptr;
       pa.true_ids = ids_all + size_t(t0) * k;
       pa.true_gates = gates_all + size_t(t0) * k;
       pa.diag = c->at<LayerDiag>(c->lay.diag) + layer;
@@ -1265,7 +1266,7 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
       pa.status = c->wait_status_dev;
       pa.B = std::min(MB, P - t0); pa.H = H; pa.E = E; pa.k = k;
       pa.eps = cfg.rms_eps;
-      pa.bf16 = cfg.dtype == MOE_SPEC_BF16;
+      pa.bf16 = bf16;
       pa.spin_limit = c->spin_limit;
       if ((e = launch_route_pair(pa, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "routing kernel");
       c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes;
@@ -1275,8 +1276,8 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
     pa.r = r;
     pa.w = c->router_w[layer];
     pa.gain = static_cast<const float *>(c->gain[layer]);
-    if (cfg.dtype == MOE_SPEC_BF16) pa.s_out_q = sq_all;
-    else pa.s_out = s_all;
+    pa.s_out = s_all;
+    pa.s_out_q = sq_all;
     pa.ids = ids_all;
     pa.gates = gates_all;
     pa.user_ids = true_ids;
@@ -1286,7 +1287,7 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
     if ((e = launch_route_prompt(pa, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "routing kernel");
     c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes;
   }
-  const bool all_at_once = cfg.dtype == MOE_SPEC_BF16;   // matrix-core kernels over per-expert position lists
+  const bool all_at_once = bf16;                         // matrix-core kernels over per-expert position lists
   if (all_at_once &&
       (e = launch_expert_lists(ids_all, P, k, E, c->at<int32_t>(c->lay.pf_pos), c->at<int32_t>(c->lay.pf_count),
                                c->compute)) != hipSuccess)
@@ -1311,14 +1312,14 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
     ExpertArgs xa{};
     xa.pool = c->pool_base(layer);
     xa.slot_bytes = c->slot_stride;
-    xa.s = s_all + size_t(t0) * H;
+    xa.s = bf16 ? nullptr : s_all + size_t(t0) * H;
     xa.exec_ids = ids_all + size_t(t0) * k;
     xa.exec_gates = gates_all + size_t(t0) * k;
     xa.h = c->at<float>(c->lay.h);                     // [nb,k,I], reused by every micro-batch
     xa.y = y_all + size_t(t0) * k * H;
     xa.out = out + size_t(t0) * H;
     xa.B = nb; xa.k = k; xa.H = H; xa.I = I;
-    xa.bf16 = cfg.dtype == MOE_SPEC_BF16;
+    xa.bf16 = bf16;
     return xa;
   };
   auto run_product = [&](const ActiveList &act, bool gateup, int row_first, int row_end) {

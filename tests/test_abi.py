@@ -110,6 +110,17 @@ def test_invalid_prefill_capacity_is_rejected():
     assert M.moe_spec_arena_bytes(cfg) > small           # the prefill buffers are part of the arena
 
 
+@pytest.mark.parametrize("dtype,P,H,I,E,k", [(M.F32, 100, 256, 512, 8, 2), (M.BF16, 100, 256, 512, 8, 2), (M.BF16, 32768, 4096, 14336, 8, 2)])
+def test_prefill_buffers_hold_the_normalised_rows_once(dtype, P, H, I, E, k):
+    """s_l of a prompt is kept in the one form that its kernels read; beside it the outputs, ids and gates of every position
+    and, with bf16 weights, the SwiGLU products and the position lists."""
+    sizes = dict(hidden=H, inter=I, n_experts=E, top_k=k, dtype=dtype, slots_per_layer=k, n_layers=1)
+    grown = M.moe_spec_arena_bytes(good_config(max_prefill_tokens=P, **sizes)) - M.moe_spec_arena_bytes(good_config(**sizes))
+    want = P * k * (4 * H + 4 + 4) + (P * H * 4 if dtype == M.F32 else P * H * 2 + P * k * I * 2 + (E * P + E) * 4)
+    assert want <= grown <= want + 8 * 256
+
+
+
 def test_bench_refuses_more_than_one_gpu(monkeypatch, capsys):
     import bench
     monkeypatch.setattr("sys.argv", ["bench.py", "--gpus", "2"])
