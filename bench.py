@@ -37,8 +37,9 @@ K_GATEUP, K_DOWN, K_ROUTE_OLD, K_READ_GU, K_MFMA_GU, K_MFMA_DOWN, K_ROUTE_TRUE, 
 # kernels a launch may run under, by substrings of their names: with resident predicted experts the gate/up projection
 # shares the routing's launch
 ROUTE_SYM = "route_pair_kernel or route_gateup"
-MFMA_DOWN_SYM = "expert_mfma_kernel<false or expert_tile_kernel<false"
-MFMA_GU_SYM = "expert_mfma_kernel<true or route_gateup_mfma or expert_tile_kernel<true"
+MFMA_DOWN_SYM = "expert_mfma_kernel<false or expert_mfma_lists_kernel<false or expert_tile_kernel<false"
+MFMA_GU_SYM = "expert_mfma_kernel<true or expert_mfma_lists_kernel<true or route_gateup_mfma or expert_tile_kernel<true"
+ROUTE_PROMPT_SYM = "route_prompt_kernel"
 KERNEL_NAMES = {K_GATEUP: ("expert_gateup_gemv", "gateup_b1"), K_DOWN: ("expert_down_combine_gemv", "down_combine_b1"),
                 K_READ_GU: ("pure_read_of_the_gateup_bytes", "stream_read"), K_READ_DOWN: ("pure_read_of_the_down_bytes", "stream_read"),
                 K_MFMA_GU: ("expert_gateup_mfma", MFMA_GU_SYM), K_MFMA_DOWN: ("expert_down_mfma", MFMA_DOWN_SYM),
@@ -174,6 +175,7 @@ class Bench:
         back, and (headline only) prefill, hint mode, diagnostics and the CPU checker.  Returns (result, pool)."""
         import numpy as np
         from paper_2603_19289_amd.engine import engine_for
+        from paper_2603_19289_amd.profile_summary import prompt_launches
         args, torch, M, W, dev = self.args, self.torch, self.M, self.W, self.dev
         B, L, H = wl.batch, wl.n_layers, wl.hidden
         T = K + Wm
@@ -403,10 +405,11 @@ class Bench:
                         eng.prefill_layer_step(l, r, pout, sync_input=False)
                         if l + 1 < L:
                             r = eng.advance(r, pout, pe[l], wl.res_a, wl.res_b, pbuf[l & 1])
-            group = min(max(wl.slots // 2, 1), wl.n_experts)          # experts per launch pair of the prefill step
-            n_pairs = 3 * L * ((wl.n_experts + group - 1) // group)
-            self.leg(f"{wl.name}/prefill", dict({"advance_kernel": 3 * (L - 1)},    # a prompt's routing is a kernel of its own
-                                                **({m: n_pairs for m in MFMA} if wl.dtype == "bf16" else {})))
+            like_decode, pairs = prompt_launches(P, min(64, P), wl.n_experts, wl.top_k, H, wl.inter, wl.slots, wl.dtype == "bf16",
+                                                 name != "kernel")
+            self.leg(f"{wl.name}/prefill", dict({"advance_kernel": 3 * (L - 1), ROUTE_SYM: 3 * L * like_decode,
+                                                 ROUTE_PROMPT_SYM: 3 * L * (like_decode == 0)},
+                                                **({m: 3 * L * pairs for m in MFMA} if wl.dtype == "bf16" else {})))
             prompt_pass()
             torch.cuda.synchronize()
             before = eng.stats()

@@ -231,10 +231,10 @@ __global__ __launch_bounds__(kBlock) void expert_mfma_lists_kernel(const ExpertA
 // of W_up, so that both factors of the SwiGLU product meet in one lane; down: 256 rows of W_down), and
 // walks the reduction 64 columns at a time through two LDS buffers: the next 64 columns travel to
 // registers while the current ones are multiplied.  A wavefront multiplies 64 positions with 64 weight
-// rows.  expert_mfma_kernel, which feeds every MFMA from global memory, re-reads each weight row once
+// rows.  expert_mfma_lists_kernel, which feeds every MFMA from global memory, re-reads each weight row once
 // per 64 positions and stops where the caches do.
 // Sums: every 512 columns the accumulators are added to a second set and start again from zero, so that
-// no float32 chain is longer than those of expert_mfma_kernel (one chain of 4096 columns moved half as
+// no float32 chain is longer than those of the other kernels from 2048 columns on (one chain of 4096 columns moved half as
 // many SwiGLU values more to the neighbouring bf16 value).
 // The tiles of all experts of the launch form one list that one workgroup per compute unit walks:
 // positions per expert are known on the device only.
@@ -667,11 +667,11 @@ hipError_t launch_expert_mfma_lists_k(const ExpertArgs &a, const ActiveList &act
   return hipGetLastError();
 }
 
-// Prefill: the tiled kernel, or position lists through expert_mfma_kernel?  A tile takes about 1.5 us per 64
+// Prefill: the tiled kernel, or position lists through expert_mfma_lists_kernel?  A tile takes about 1.5 us per 64
 // columns however many of its positions are real (one workgroup per compute unit, the loads of one step in
 // flight), the other kernel's time goes with the positions (about 170 TFLOP/s once its weights are read): tiles
 // pay once a round of them holds about a quarter of the device's worth of real positions, taking the experts as
-// equally loaded.  Measured, expert_mfma_kernel against tiles: gate/up of 8 experts 768 x 2048 with 128
+// equally loaded.  Measured, expert_mfma_lists_kernel against tiles: gate/up of 8 experts 768 x 2048 with 128
 // positions each 50 / 58 us, with 256 87 / 58 us; down (2048 x 768) with 64 24 / 28, with 128 38 / 30; one expert
 // 14336 x 4096 with 64 positions 120 / 101, with 128 201 / 101, its down with 256 259 / 341, with 8192 7784 / 1428
 // (gate/up 9492 / 2618 us, 735 TFLOP/s).

@@ -81,12 +81,26 @@ def cut_by_legs(sequence, legs, symbol):
 # What a leg counts (bench.py): launches of any of these, by substrings of kernel names.  With resident predicted experts
 # the gate/up projection shares the routing's launch, so such a launch counts as routing and as gate/up.
 COUNTED = ["route_pair_kernel or route_gateup", "gateup_b1", "down_combine_b1", "stream_read",
-           "expert_mfma_kernel<true or route_gateup_mfma or expert_tile_kernel<true",
-           "expert_mfma_kernel<false or expert_tile_kernel<false", "advance_kernel"]
+           "expert_mfma_kernel<true or expert_mfma_lists_kernel<true or route_gateup_mfma or expert_tile_kernel<true",
+           "expert_mfma_kernel<false or expert_mfma_lists_kernel<false or expert_tile_kernel<false", "route_prompt_kernel",
+           "advance_kernel"]
 # What is reported, each kernel under the first of these that its name contains: a joint launch in a row of its own.
 REPORTED = ["route_gateup_b1", "route_gateup_mfma", "route_pair_kernel", "gateup_b1", "down_combine_b1", "stream_read",
-            "expert_mfma_kernel<true", "expert_mfma_kernel<false", "expert_tile_kernel<true", "expert_tile_kernel<false",
-            "advance_kernel"]
+            "expert_mfma_kernel<true", "expert_mfma_kernel<false", "expert_mfma_lists_kernel<true", "expert_mfma_lists_kernel<false",
+            "expert_tile_kernel<true", "expert_tile_kernel<false", "route_prompt_kernel", "advance_kernel"]
+
+
+def prompt_launches(P, max_batch, experts, top_k, hidden, inter, slots, bf16, dma):
+    """What one moe_spec_prefill_layer_step launches, by the rules of csrc/launch_rules.h (routed_like_decode, prefill_tail):
+    (routing launches of a decode step, 0: one of the prompt kernel; pairs of expert launches of a bf16 layer)."""
+    launches = -(-P // max_batch)
+    like_decode = P <= 128 and (launches <= 2 or 20.0 * launches < 2e-4 * experts * hidden)
+    group = min(max(slots // 2, 1), experts)
+    groups, last = -(-experts // group), (experts - 1) % group + 1
+    kernels_us, copy_us = 6.0 * (P * top_k / experts) * hidden * inter / 600e6, 6.0 * hidden * inter / 57e3
+    pieces = kernels_us <= copy_us and kernels_us >= 300.0
+    by_expert = pieces or (kernels_us <= copy_us and kernels_us >= 15.0 and kernels_us * (last - 1) >= 100.0)
+    return launches if like_decode else 0, groups - 1 + last + pieces if bf16 and dma and by_expert else groups
 
 
 def attribute(dispatches, legs):
