@@ -578,3 +578,35 @@ def test_a_step_that_failed_for_an_unregistered_expert_can_be_called_again(dtype
     finally:
         eng.close()
         plain.close()
+
+
+@pytest.mark.parametrize("mode,lookahead,batch,slots,dtype", [
+    ("MODE_ON_DEMAND", 0, 1, 2, "f32"), ("MODE_ON_DEMAND", 0, 3, 4, "bf16"), ("MODE_SPECULATIVE", 0, 3, 2, "f32"),
+    ("MODE_SPECULATIVE", 0, 8, 5, "bf16"), ("MODE_PREFETCH_HINT", 0, 1, 3, "bf16"), ("MODE_PREFETCH_HINT", 0, 8, 3, "bf16"),
+    ("MODE_PREFETCH_HINT", 2, 3, 5, "bf16"), ("MODE_SPECULATIVE", 2, 5, 3, "bf16")])
+def test_copies_in_order_with_the_kernels_and_beside_them_give_the_same_outputs(mode, lookahead, batch, slots, dtype):
+    """Copies that the next kernels wait for run on the compute stream, unless earlier ones into that pool still travel on the
+    copy stream, and prefetches follow them there: slots given away again while copies and their readers are under way.  The
+    same steps with every copy on the copy stream (profile = 1) and with two DMA queues are bit for bit the same; experts of
+    2 to 4 MB travel longer than the kernels of a layer take."""
+    from paper_2603_19289_amd.engine import engine_for
+    wl = small_workload(name="in_order", n_layers=4, hidden=264, n_experts=8, top_k=2, inter=2568, dtype=dtype, batch=batch, tokens=6,
+                        slots=slots, seed=53)
+    res, ex, _ = build(wl, "random")
+    x0, eps = W.make_inputs(wl)
+    r = [[torch.from_numpy(x0[t] + 0.3 * eps[t, l]).cuda() for l in range(wl.n_layers)] for t in range(wl.tokens)]
+    got = []
+    for kw in (dict(copy_engine=M.COPY_KERNEL), dict(copy_engine=M.COPY_KERNEL, profile=1), dict(copy_engine=M.COPY_DMA2)):
+        eng = engine_for(wl, getattr(M, mode), res, ex, predict_in_on_demand=0, lookahead=lookahead, **kw)
+        outs = [[torch.zeros_like(v) for v in row] for row in r]
+        try:
+            for t in range(wl.tokens):                 # no wait for the GPU in between
+                eng.begin_token()
+                for l in range(wl.n_layers):
+                    eng.layer_step(l, r[t][l], outs[t][l])
+            assert eng.stats()["cache_misses"] > wl.n_layers * wl.top_k * 2
+            got.append(torch.stack([torch.stack(row) for row in outs]).cpu())
+        finally:
+            eng.close()
+    assert torch.isfinite(got[0]).all() and (got[0].abs().amax(dim=(2, 3)) > 0).all()
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])

@@ -410,3 +410,35 @@ def test_prefill_profile_separates_the_tail_s_kernels_from_their_waits(hidden, i
         assert st["stall_ms"] > 0 and st["compute_ms"] > 0 and st["compute_ms"] + st["stall_ms"] < 1.05 * took
     finally:
         eng.close()
+
+
+@pytest.mark.parametrize("hidden,inter,experts,top_k,P,kernels", [
+    (520, 1032, 8, 2, 16000, {"expert_tile_kernel<true>": 8, "expert_tile_kernel<false>": 8}),
+    # one expert by itself has too few row tiles for the tiled kernel, the whole group has enough
+    (2048, 512, 8, 2, 6000, {"expert_mfma_lists_kernel<true": 8, "expert_tile_kernel<false>": 8}),
+    (2056, 6008, 3, 1, 7400, {"expert_tile_kernel<true>": 4, "expert_tile_kernel<false>": 4})])
+def test_prefill_tail_expert_by_expert_equals_whole_groups(hidden, inter, experts, top_k, P, kernels):
+    """The last group's experts one by one as they arrive, the last one whole or in pieces, against the copy kernel's whole
+    group: outputs, and the running means of every expert's outputs, which the tail adds up one expert at a time."""
+    from paper_2603_19289_amd.engine import engine_for
+    wl, pool, r = tail_inputs(hidden, inter, experts, top_k, P)
+    got = []
+    for e, expected in ((M.COPY_DMA2, kernels), (M.COPY_KERNEL, {"expert_tile_kernel<true>": 1, "expert_tile_kernel<false>": 1})):
+        eng = engine_for(wl, M.MODE_ON_DEMAND, W.make_resident(wl), pool, max_batch=64, max_prefill_tokens=P, copy_engine=e,
+                         accumulate_defaults=1)
+        try:
+            out = torch.zeros_like(r)
+
+            def prompt():                              # again where the profiler missed a launch: from empty sums
+                eng.reset()
+                eng.prefill_layer_step(0, r, out)
+            counts = kernels_launched(prompt, {"expert_lists": 1, "combine": 1})
+            assert all(launches(counts, name) == n for name, n in expected.items()), counts
+            mean, n = eng.read_default_vectors(0)
+            got.append((out.cpu().numpy(), mean.cpu().numpy(), n))
+        finally:
+            eng.close()
+    (out, mean, n), (want, want_mean, want_n) = got
+    assert n == want_n and sum(n) == P * top_k and min(n) > 0
+    check_output(out, want, "bf16", "outputs", terms=top_k * inter)
+    check_output(mean, want_mean, "bf16", "means")

@@ -113,3 +113,14 @@ def test_short_prompts_are_routed_by_the_launches_of_a_decode_step(tmp_path):
     {16, 1, 128, 2048, false}, {200, 64, 8, 1024, false}, {32768, 64, 8, 4096, false}};
   for (const auto &c : cases)
     if (routed_like_decode(c.P, c.max_batch, c.E, c.H) != c.decode) { ++bad; std::printf("%d %d %d %d\n", c.P, c.max_batch, c.E, c.H); }""")
+
+
+def test_routing_workgroups_take_rows_at_the_sizes_of_the_gpu_test(tmp_path):
+    # 16 of 200 experts of 344 x 1024 and 16 of 256 of 352 x 1016, bf16, on the whole device
+    sweep(tmp_path, r"""
+  const int sizes[][3] = {{1024, 344, 200}, {1016, 352, 256}};
+  for (const auto &v : sizes) for (int per_cu : {2, 3, 4}) {
+    const int nch = (v[0] + 511) / 512;
+    const SharedSplit s = share_with_routing(beside_routing_split(nch, v[1], v[0], 16, 2, v[2], per_cu, 256), v[1], v[0], 16, 2, v[2], 256);
+    if (s.tail_blocks < 1) { ++bad; std::printf("%d %d %d\n", v[0], v[1], v[2]); }
+  }""")
