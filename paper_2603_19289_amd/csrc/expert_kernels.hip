@@ -626,9 +626,11 @@ hipError_t launch_expert_mfma_n(const ExpertArgs &a, const TokenLists &lists, co
     int cus = 0;
     if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
     return with_ksplit(down_ksplit(a.I, tiles, rows, lists.n, positions, cus), [&](auto ksplit) {
-      if constexpr (ksplit() == 4) return launch(ksplit, int_c<kOneChain>());
-      else if constexpr (ksplit() == 2) return launch(ksplit, int_c<kTwoChains>());
-      else return a.I < 1024 ? launch(ksplit, int_c<kTwoChains>()) : launch(ksplit, int_c<kFourParts>());
+      if constexpr (ksplit() == 1)
+        if (a.I >= 1024) return launch(ksplit, int_c<kFourParts>());
+      if constexpr (ksplit() == 2 && NT == 1)
+        if (tiles == 1) return launch(ksplit, int_c<kTwoChains>());
+      return launch(ksplit, int_c<kOneChain>());
     });
   }
 }

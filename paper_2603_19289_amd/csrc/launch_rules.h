@@ -106,9 +106,9 @@ inline int gateup_ksplit(int K, int token_tiles) {
   return steps >= 16 ? 2 : 1;
 }
 
-// Down projection of a decode batch: as many as leave each two whole steps of 128 columns.  Below 1024 columns a wavefront
-// has two chains, so that a sum of 512 columns, or 449 in batches of a single tile, has four of them however it is split: a
-// chain of 456 columns is 1.5 times as far from 64 bits.
+// Down projection of a decode batch: as many as leave each two whole steps of 128 columns.  In batches of a single tile two
+// wavefronts have two chains each, so that a sum of 449 columns and more has four of them: in one chain of 456 columns it is
+// 1.5 times as far from 64 bits.  With two tiles of tokens the second accumulators would cost a wavefront per SIMD.
 // From 1024 columns on one wavefront takes the four parts one after another, with the same sum, if the experts have eight
 // positions or more on average and there are two workgroups per compute unit without a split: then the activations weigh as
 // much as the weights, and the four wavefronts of a workgroup share them if they walk the same columns.  Microseconds with 1
