@@ -911,7 +911,9 @@ hipError_t launch_route_gateup_mfma(const RoutePairArgs &ra, const ExpertArgs &a
   if (a.H <= 2048) hipLaunchKernelGGL(norm_rows_kernel<1>, dim3(a.B), dim3(kBlock), lds, st, a, s_q);
   else hipLaunchKernelGGL(norm_rows_kernel<2>, dim3(a.B), dim3(kBlock), lds, st, a, s_q);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-  if (ra.proj) {                               // a token tile count of its own for every sixteen tokens
+  if (ra.proj) {
+    // The estimator's launch is built for the tiles of the batch, not for those of the fullest expert: with 17 tokens and
+    // more it may hold more registers than its experts need.  Tiles by the expert were not measured here.
     switch ((a.B + 15) / 16) {
       case 1: return launch_route_gateup_mfma_t<1, true>(ra, a, lists, s_q, hq, st);
       case 2: return launch_route_gateup_mfma_t<2, true>(ra, a, lists, s_q, hq, st);

@@ -45,14 +45,17 @@ inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_
 }
 
 // The same with the routing workgroups taking rows too once they have routed (all but the first, which finishes the
-// prediction): the last I - first_tail rows of every expert, tail_rpw per wavefront, in tail_blocks workgroups.  They come
-// free after about 6 us in which another workgroup streams 130 KB.  Worth it where routing takes half of the device or
-// more and the others are left with 320 KB and more each (the routing, 12 us, is over well before them then), for rows of up
-// to 4 KB: longer ones make the vector that these workgroups have to form a second time cost more than they win.
-// Microseconds per pass without / with: 8 of 128 experts of 768 x 2048 (393 KB each) 611 / 578, 8 of 200 of 480 x 2048 (493)
-// 334 / 299, 8 of 128 of 1600 x 1024 (410) 367 / 324; not taken: 8 of 64 of 960 x 2048 (328) 323 / 315, 8 of 128 of 640 x
-// 2880 (461) 370 / 375, 4 of 100 of 800 x 3000 (246) 578 / 614, 4 of 32 of 768 x 4096 (225) 565 / 619, 6 of 60 of 1200 x 1544
-// (227) 583 / 583, 8 of 128 of 520 x 1024 (133) 475 / 478.
+// prediction): the last I - first_tail rows of every expert, at most half of them, tail_rpw per wavefront, in tail_blocks
+// workgroups.  They come free after about 6 us in which another workgroup streams 130 KB.  Taken where all of this holds: one
+// gate/up workgroup per compute unit beside the routing (up to 64 MB of weights, see above); routing on half of the device or
+// more; 320 KB and more for each of the other workgroups (the routing, 12 us, is over well before them then); rows of up to 4
+// KB.  Microseconds per pass without / with: 8 of 128 experts of 768 x 2048 (393 KB each) 611 / 578, 8 of 200 of 480 x 2048
+// (493) 334 / 299, 8 of 128 of 1600 x 1024 (410) 367 / 324; not taken: 8 of 64 of 960 x 2048 (328) 323 / 315, 8 of 128 of 640
+// x 2880 (461) 370 / 375, 4 of 100 of 800 x 3000 (246) 578 / 614, 4 of 32 of 768 x 4096 (225) 565 / 619, 6 of 60 of 1200 x
+// 1544 (227) 583 / 583, 8 of 128 of 520 x 1024 (133) 475 / 478.  The limits are those of the shapes that gained: the first of
+// them stands on two of them (half of 256 units, 4 KB), and none was moved as far as it would go.  The limit on routing
+// workgroups leaves out a gain of 2.5 % (64 experts), the one on rows rests on a loss of 1.3 % (2880 columns: the vector that
+// these workgroups form a second time is longer) and on shapes that the bytes per workgroup exclude as well.
 struct SharedSplit {
   GateupSplit stream;                          // of rows [0, first_tail)
   int first_tail, tail_rpw, tail_blocks;       // tail_blocks 0: none
