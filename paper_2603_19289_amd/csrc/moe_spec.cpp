@@ -1244,8 +1244,10 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
 
   // --- true routing of every prompt token
   TimedSpan *sp_route = c->open_span(0, c->compute);
+  bool routed = false;
   if (routed_like_decode(P, MB, E, H) && route_pair_supported(H, cfg.dtype)) {
-    for (int t0 = 0; t0 < P; t0 += MB) {
+    routed = true;
+    for (int t0 = 0; t0 < P && routed; t0 += MB) {
       RoutePairArgs pa{};
       pa.r = r + size_t(t0) * H;
       pa.w_true = c->router_w[layer];
@@ -1268,10 +1270,18 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
       pa.eps = cfg.rms_eps;
       pa.bf16 = bf16;
       pa.spin_limit = c->spin_limit;
-      if ((e = launch_route_pair(pa, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "routing kernel");
-      c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes;
+      e = launch_route_pair(pa, cfg.dtype, c->compute);
+      if (e == hipErrorLaunchOutOfResources) {         // not launched: the workgroups of a token do not fit on the device
+        c->route_parity ^= 1;
+        routed = false;
+      } else if (e != hipSuccess) {
+        return c->hip_fail(e, "routing kernel");
+      } else {
+        c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes;
+      }
     }
-  } else {
+  }
+  if (!routed) {                                       // needs no two workgroups on the device together
     RoutePromptArgs pa{};
     pa.r = r;
     pa.w = c->router_w[layer];
