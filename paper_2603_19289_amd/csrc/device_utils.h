@@ -133,6 +133,16 @@ __device__ __forceinline__ T wave_sum(T v) {
   return (readlane(v, 0) + readlane(v, 16)) + (readlane(v, 32) + readlane(v, 48));
 }
 
+// What lane and lane ^ 16, or lane ^ 32, hold, added up, in both.
+__device__ __forceinline__ int add_lanes_16_apart(int v) {
+  const auto both = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return int(both[0]) + int(both[1]);
+}
+__device__ __forceinline__ int add_lanes_32_apart(int v) {
+  const auto both = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return int(both[0]) + int(both[1]);
+}
+
 // A double as an unsigned integer that orders the same way (the sign bit flipped for positive values, all
 // bits for negative ones); a number is never 0.  -0.0 must not get here.
 __device__ __forceinline__ unsigned long long sortable(double v) {

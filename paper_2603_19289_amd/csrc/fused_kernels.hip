@@ -41,23 +41,25 @@ static_assert(kWaves == kRouteWaves, "the launch rules count wavefronts");
 
 struct SelectShared {
   unsigned long long keys[kMaxExperts];   // the token's logits as order-preserving integers
-  int cnt[kWaves][kMaxExperts];   // partial rank counts of the four wavefronts
+  uint32_t high[kMaxExperts + 64];        // their high words, in parts (select_ids)
+  int cnt[kWaves][kMaxExperts];           // partial rank counts of the four wavefronts, where high words are not enough
+  unsigned int filled[kMaxTopK];          // candidates that count as this rank by their high words
   double top_z[kMaxTopK];
-  double top_e[kMaxTopK];
+  double top_e[kWaves][kMaxTopK];         // exp(z_j - z_0), 0 beyond k; every wavefront has its own
   int top_i[kMaxTopK];
   int hits;
 };
 
 struct RouteShared {
-  double red[kWaves];
+  double red[2][kWaves];                  // one per norm
   double part[kWaves];
   SelectShared sel;
 };
 
-// Sum over the workgroup, the same value in every thread; red[] may be reused after the call.
+// Sum over the workgroup, the same value in every thread.  red[] is written before the barrier and read behind it: a
+// second sum takes another array.
 __device__ __forceinline__ double block_sum(double v, double *red, int lane, int wave) {
   v = wave_sum(v);
-  __syncthreads();
   if (lane == 0) red[wave] = v;
   __syncthreads();
   double tot = 0.0;
@@ -66,41 +68,16 @@ __device__ __forceinline__ double block_sum(double v, double *red, int lane, int
   return tot;
 }
 
-// Top-k of one token's E logits, read from their slots as they arrive: larger logit first, equal logits by
-// lower index.  Every wavefront holds all candidates in registers as order-preserving integers (element
-// i = r*64 + lane, R per lane) and counts, for each of its candidates, how many candidates broadcast from
-// source lanes [16 wave, 16 wave + 16) rank before it; the four partial counts of a candidate add up to
-// its position in the sorted order.  Fills sel.top_i / sel.top_z (by descending logit), the same in every
-// workgroup that calls it.
+// Ranks by whole logits: larger logit first, equal logits by lower index.  Every wavefront holds all candidates in
+// registers (element i = r*64 + lane, R per lane) and counts, for each of its candidates, how many candidates broadcast
+// from source lanes [16 wave, 16 wave + 16) rank before it; the four partial counts of a candidate add up to its position.
 template <int R>
-__device__ void select_ids(const RoutePairArgs &a, int stage, const unsigned long long *slots, int E, int k,
-                           SelectShared &sel, int tid, int32_t *post) {
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
+__device__ void rank_whole(int E, int k, SelectShared &sel, int lane, int wave) {
   constexpr int kSrcPerWave = kWave / kWaves;
-  // thread i waits for logit i (one look at every slot per workgroup, not one per wavefront) and shares it
-  // through LDS; then every wavefront holds all candidates in registers
-  static_assert(kMaxExperts == kBlock, "one thread per candidate");
-  unsigned long long mine = 0ull;                // padding ranks below every logit, minus infinity included
-  // A logit needs more than a microsecond to get from its producer to here, so the first look comes 0.4 us after
-  // this workgroup's own logits went out.  Fewer polls in flight across the device let the stores themselves get
-  // through sooner: both routings 12.9 -> 11.7 us on 128 experts (8 to 25 units of 64 cycles measure alike,
-  // 45 units 12.7 us).
-  __builtin_amdgcn_s_sleep(16);
-  if (tid < E) {
-    const double zi = __longlong_as_double(static_cast<long long>(await64(slots + tid, a.spin_limit, a.status)));
-    // a logit that is not a number (an empty slot after a wait that ran out) sorts as minus infinity: the
-    // order stays total whatever the input, so the k ids are distinct and inside [0, E)
-    mine = sortable(zi == zi ? zi : -INFINITY);
-  }
-  sel.keys[tid] = mine;
-  __syncthreads();
   unsigned long long key[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) key[r] = sel.keys[r * kWave + lane];
-  STAGE(stage);
   int cnt[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) cnt[r] = 0;
+  for (int r = 0; r < R; ++r) { key[r] = sel.keys[r * kWave + lane]; cnt[r] = 0; }
   for (int j = wave * kSrcPerWave; j < (wave + 1) * kSrcPerWave; ++j) {
     const bool after = lane > j;                 // same register: the source has the lower index
 #pragma unroll
@@ -118,7 +95,6 @@ __device__ void select_ids(const RoutePairArgs &a, int stage, const unsigned lon
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) sel.cnt[wave][r * kWave + lane] = cnt[r];
-  if (tid == 0) sel.hits = 0;
   __syncthreads();
   if (wave == 0) {
 #pragma unroll
@@ -127,14 +103,72 @@ __device__ void select_ids(const RoutePairArgs &a, int stage, const unsigned lon
       const int rk = (sel.cnt[0][i] + sel.cnt[1][i]) + (sel.cnt[2][i] + sel.cnt[3][i]);
       if (i < E && rk < k) { sel.top_z[rk] = unsortable(key[r]); sel.top_i[rk] = i; }
     }
-    // still in wavefront 0, whose own LDS writes it reads back in order: the ids go out to the host, if it waits
-    // for them, and the numerators of the k gates are formed, before the other wavefronts are let go
-    if (lane < k) {
-      if (post) post[lane] = sel.top_i[lane];
-      sel.top_e[lane] = exp(sel.top_z[lane] - sel.top_z[0]);
+  }
+  __syncthreads();
+}
+
+// Top-k of one token's E logits, read from their slots as they arrive: larger logit first, equal logits by lower index.
+// Fills sel.top_i / sel.top_z (by descending logit) and sel.top_e, the same in every workgroup that calls it.
+// A chain of dependent steps of one wavefront per SIMD, so instructions count: candidates are ranked by the high words of
+// their keys (sign, exponent, 20 bits), one compare instead of a 64-bit one with its ties, read from LDS as broadcasts of
+// four, and the lanes that share a candidate sit in one wavefront, which needs no barrier to add them up.  If two of the
+// first k have the same high word, some rank is taken twice and another not at all (or one too many is below k): then all
+// wavefronts see that and rank whole keys.  64 / 128 / 256 experts: 645 / 1370 / 3015 -> 360 / 595 / 1615 ns a selection.
+template <int R>
+__device__ void select_ids(const RoutePairArgs &a, int stage, const unsigned long long *slots, int E, int k,
+                           SelectShared &sel, int tid, int32_t *post) {
+  const int lane = tid & (kWave - 1), wave = tid / kWave;
+  constexpr int kParts = kWaves / R;             // lanes that share a candidate
+  constexpr int kCands = kWave / kParts;         // candidates of a wavefront
+  constexpr int kSrc = R * kWave / kParts;       // sources of a lane
+  // thread i waits for logit i (one look at every slot per workgroup, not one per wavefront) and shares it
+  // through LDS
+  static_assert(kMaxExperts == kBlock, "one thread per candidate");
+  unsigned long long mine = 0ull;                // padding ranks below every logit, minus infinity included
+  // A logit needs more than a microsecond to get from its producer to here, so the first look comes 0.4 us after
+  // this workgroup's own logits went out.  Fewer polls in flight across the device let the stores themselves get
+  // through sooner: both routings 12.9 -> 11.7 us on 128 experts (8 to 25 units of 64 cycles measure alike,
+  // 45 units 12.7 us).
+  __builtin_amdgcn_s_sleep(16);
+  if (tid < E) {
+    const double zi = __longlong_as_double(static_cast<long long>(await64(slots + tid, a.spin_limit, a.status)));
+    // a logit that is not a number (an empty slot after a wait that ran out) sorts as minus infinity: the
+    // order stays total whatever the input, so the k ids are distinct and inside [0, E)
+    mine = sortable(zi == zi ? zi : -INFINITY);
+  }
+  sel.keys[tid] = mine;
+  if (tid < R * kWave) sel.high[tid + tid / kSrc * 4] = uint32_t(mine >> 32);    // parts 16 bytes apart: on other banks
+  if (tid < kMaxTopK) sel.filled[tid] = 0u;
+  if (tid == 0) sel.hits = 0;
+  __syncthreads();
+  STAGE(stage);
+  {
+    const int c = wave * kCands + lane % kCands, part = lane / kCands;
+    const unsigned long long key = sel.keys[c];
+    const uint32_t high = uint32_t(key >> 32);
+    const uint4 *src = reinterpret_cast<const uint4 *>(sel.high + part * (kSrc + 4));
+    int n[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < kSrc / 4; ++j) {
+      const uint4 s = src[j];
+      n[0] += s.x > high ? 1 : 0;
+      n[1] += s.y > high ? 1 : 0;
+      n[2] += s.z > high ? 1 : 0;
+      n[3] += s.w > high ? 1 : 0;
+    }
+    int rk = (n[0] + n[1]) + (n[2] + n[3]);
+    if (kParts >= 4) rk = add_lanes_16_apart(rk);
+    if (kParts >= 2) rk = add_lanes_32_apart(rk);
+    if (part == 0 && rk < k) {
+      sel.top_z[rk] = unsortable(key);
+      sel.top_i[rk] = c;
+      atomicAdd(&sel.filled[rk], 1u);
     }
   }
   __syncthreads();
+  if (__ballot(lane < k && sel.filled[lane < k ? lane : 0] != 1u)) rank_whole<R>(E, k, sel, lane, wave);
+  if (wave == 0 && lane < k && post) post[lane] = sel.top_i[lane];   // the host, if it waits for the ids, goes first
+  if (lane < kMaxTopK) sel.top_e[wave][lane] = lane < k ? exp(sel.top_z[lane] - sel.top_z[0]) : 0.0;
 }
 
 __device__ __forceinline__ void select_ids_any(const RoutePairArgs &a, int stage, const unsigned long long *slots,
@@ -144,12 +178,11 @@ __device__ __forceinline__ void select_ids_any(const RoutePairArgs &a, int stage
   else select_ids<4>(a, stage, slots, E, k, sel, tid, post);
 }
 
-// Softmax over the k selected logits: select_ids left sel.top_e[j] = exp(z_j - z_0); returns their sum (the same
-// in every thread), so that gate j is top_e[j] / sum.
-__device__ __forceinline__ double select_gates(int k, SelectShared &sel, int tid) {
-  (void)tid;
+// Softmax over the k selected logits: top_e[wave] holds the numerators; returns their sum (the same in every thread).
+__device__ __forceinline__ double select_gates(int k, const SelectShared &sel, int tid) {
+  const double *e = sel.top_e[tid / kWave];
   double denom = 0.0;
-  for (int q = 0; q < k; ++q) denom += sel.top_e[q];
+  for (int q = 0; q < k; q += 4) denom = (((denom + e[q]) + e[q + 1]) + e[q + 2]) + e[q + 3];
   return denom;
 }
 
@@ -231,7 +264,7 @@ __device__ __forceinline__ void report_true(const RoutePairArgs &a, int b, Selec
   const int k = a.k;
   if (tid < k) {
     const int id = sel.top_i[tid];
-    const double g64 = sel.top_e[tid] / denom;
+    const double g64 = sel.top_e[0][tid] / denom;
     const float g = static_cast<float>(g64);
     const size_t o = size_t(b) * k + tid;
     if (a.mb_true) a.mb_true->ids[o] = id;     // the host waits for every word it armed
@@ -259,7 +292,7 @@ __device__ __forceinline__ void report_true(const RoutePairArgs &a, int b, Selec
 __device__ __forceinline__ void report_next(const RoutePairArgs &a, int b, SelectShared &sel, double denom, int tid) {
   if (tid < a.k) {
     const int id = sel.top_i[tid];
-    const float g = static_cast<float>(sel.top_e[tid] / denom);
+    const float g = static_cast<float>(sel.top_e[0][tid] / denom);
     const size_t o = size_t(b) * a.k + tid;
     a.next_ids[o] = id;
     a.next_gates[o] = g;
@@ -294,6 +327,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int H = a.H, E = a.E, k = a.k;
   const int G = H / VN;                        // column groups (H is a multiple of 8)
+  const double inv_h = 1.0 / double(H);
 #define V(c, x) vec_lds[(x) * G + (c) / VN]
   const int row = wg * RPW + wave / SPLIT * ROWS, part = wave % SPLIT;   // this wavefront's (first) row
   const bool pred = PROJ || a.w_next != nullptr;
@@ -349,8 +383,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
         ss += double(f.x) * double(f.x) + double(f.y) * double(f.y) + double(f.z) * double(f.z) + double(f.w) * double(f.w);
       }
     }
-    const double tot = block_sum(ss, sh.red, lane, wave);
-    const double inv = 1.0 / sqrt(tot / double(H) + double(a.eps));
+    const double inv = rsqrt(block_sum(ss, sh.red[0], lane, wave) * inv_h + double(a.eps));
     for (int c = c0; c < H; c += kBlock * VN) {
 #pragma unroll
       for (int x = 0; x < VN; ++x) {
@@ -485,7 +518,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           if (j0 + q < k) {
-            const double g = sh.sel.top_e[j0 + q] * inv_denom;
+            const double g = sh.sel.top_e[wave][j0 + q] * inv_denom;
             float dvf[VN];
             P::unpack(dr[q], dvf);
 #pragma unroll
@@ -513,8 +546,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
       }
     }
     STAGE(6);
-    const double tot = block_sum(ss, sh.red, lane, wave);
-    const double inv = 1.0 / sqrt(tot / double(H) + double(a.eps));
+    const double inv = rsqrt(block_sum(ss, sh.red[1], lane, wave) * inv_h + double(a.eps));
     for (int c = c0; c < H; c += kBlock * VN) {
 #pragma unroll
       for (int x = 0; x < VN; ++x) {
@@ -567,6 +599,7 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
   constexpr int VN = P::N;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int H = a.H, E = a.E, k = a.k, G = H / VN;
+  const double inv_h = 1.0 / double(H);
 #define V(c, x) vec_lds[(x) * G + (c) / VN]
   const bool pred = PROJ || a.w_next != nullptr;
   const float *rrow = a.r + size_t(b) * H;
@@ -575,9 +608,8 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
     arm64(a.z_true_next + i);
     arm64(a.z_pred_next + i);
   }
-  auto finish_norm = [&](double ss, bool write) {      // V holds x * gain
-    const double tot = block_sum(ss, sh.red, lane, wave);
-    const double inv = 1.0 / sqrt(tot / double(H) + double(a.eps));
+  auto finish_norm = [&](double ss, double *red, bool write) {      // V holds x * gain
+    const double inv = rsqrt(block_sum(ss, red, lane, wave) * inv_h + double(a.eps));
     for (int c = c0; c < H; c += kBlock * VN) {
 #pragma unroll
       for (int x = 0; x < VN; ++x) {
@@ -603,7 +635,7 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
       ss += r * r;
     }
   }
-  finish_norm(ss, wg == 0);
+  finish_norm(ss, sh.red[0], wg == 0);
   auto publish_rows = [&](const void *router, unsigned long long *slots) {
     rows_dot<WT, false>(static_cast<const WT *>(router), E, H, first, stride, vec_lds, [&](int r, double sum) {
       if (lane == 0) publish64(slots + size_t(b) * E + r, sum);
@@ -632,7 +664,7 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (j0 + q < k) {
-          const double g = sh.sel.top_e[j0 + q] * inv_denom;
+          const double g = sh.sel.top_e[wave][j0 + q] * inv_denom;
           float dvf[VN];
           P::unpack(dr[q], dvf);
 #pragma unroll
@@ -647,7 +679,7 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
       ss += ux * ux;
     }
   }
-  finish_norm(ss, false);
+  finish_norm(ss, sh.red[1], false);
   if constexpr (PROJ) {
     project_rows<WT>(a, b, first, stride, vec_lds);
     return;
@@ -682,7 +714,7 @@ void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const Ac
     __syncthreads();                           // the routing's last readers of the shared memory are done
   }
   float *s_lds = reinterpret_cast<float *>(vec_lds);
-  gateup_b1_body<WT, NCH, true>(a, act, i / blocks, i % blocks, rpw, first, last, s_lds, sh.red);
+  gateup_b1_body<WT, NCH, true>(a, act, i / blocks, i % blocks, rpw, first, last, s_lds, sh.red[0]);
 }
 
 // s_l = LN_l(r_l) as bf16, one workgroup per token: what the expert workgroups of the launch below read.

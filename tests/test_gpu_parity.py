@@ -7,7 +7,7 @@ import torch
 
 from oracle import moe_oracle as O
 from paper_2603_19289_amd import workload as W
-from tests.helpers import build, check_output, kernels_launched, make_advance, small_workload
+from tests.helpers import build, check_output, kernels_launched, make_advance, oracle_model, small_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -320,6 +320,23 @@ def test_two_layer_lookahead(mode, dtype, B, S, engine):
     wl = small_workload(name="lookahead", n_layers=6, hidden=264, n_experts=12, top_k=3, inter=200, dtype=dtype,
                         batch=B, tokens=5, slots=S, seed=19)
     run_teacher_forced(wl, MODES[mode], oracle_kw=dict(lookahead=2), lookahead=2, copy_engine=getattr(M, engine))
+
+
+@pytest.mark.parametrize("n_experts", [2, 8, 64, 65, 128, 200, 256])
+@pytest.mark.parametrize("batch", [1, 3])
+def test_logits_that_agree_in_their_high_words(n_experts, batch):
+    """Candidates are ranked by the upper 32 bits of their logits first.  Here pairs and triples of experts share these, a
+    triple in which two logits are equal among them, inside the selected k and across its end: ids and gates are the checker's."""
+    wl = small_workload(name="near ties", n_layers=4, hidden=264, n_experts=n_experts, top_k=min(n_experts, 7), inter=8, dtype="f32",
+                        batch=batch, tokens=3, slots=n_experts, seed=11)
+    res, ex, _ = build(wl, "random")
+    w = res["router_w"]
+    for e in range(1, n_experts):
+        if e % 5 in (1, 2):
+            w[:, e] = w[:, e - 1] * np.float32(1 + 2.0 ** -22)
+        elif e % 5 == 3:
+            w[:, e] = w[:, e - 1]
+    run_teacher_forced(wl, O.MODE_SPECULATIVE, prebuilt=(res, oracle_model(wl, res, ex), ex))
 
 
 def test_crafted_ties_pick_the_lower_index():
