@@ -696,6 +696,11 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
 // The routing of a layer and the gate/up projection of its experts, which were predicted one layer earlier, in one
 // launch for a batch of one.  The first n_route workgroups route (they are dispatched first, so they are resident
 // together), the others stream expert rows; these form s_l themselves.  NCH: chunks of a weight row per lane.
+// A compute unit streams up to 28 GB/s from memory however many loads it has in flight, so each one that routes instead is
+// missed: two router rows per workgroup.  8 of 128 experts of 768 x 2048, a layer step, 1 / 2 / 4 rows per workgroup:
+// 23.9 / 22.3 / 22.4 us, with the dot instructions of row_sums 24.5 / 21.2 / 21.6 (128 / 64 / 32 workgroups; 4 of 32
+// of 2880 x 2880 and 2 of 8 of 14336 x 4096 within 1 % of one another).
+constexpr int kJointSplit = 2, kJointRows = kWaves / kJointSplit;   // wavefronts of a router row, rows of a workgroup
 template <typename WT, int NCH>
 __global__ __launch_bounds__(kBlock, 2)
 void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const ActiveList act, const int n_route,
@@ -704,7 +709,7 @@ void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const Ac
   __shared__ RouteShared sh;
   int i = int(blockIdx.x) - n_route, blocks = split.stream.blocks, rpw = split.stream.rpw, first = 0, last = split.first_tail;
   if (i < 0) {
-    route_pair_body<WT, kWaves, (NCH + 3) / 4, 1, false>(ra, blockIdx.x, n_route, 0, 1, vec_lds, sh);
+    route_pair_body<WT, kJointSplit, (NCH + kJointSplit - 1) / kJointSplit, 1, false>(ra, blockIdx.x, n_route, 0, 1, vec_lds, sh);
     i = int(blockIdx.x) - 1;
     blocks = split.tail_blocks;
     if (i < 0 || i >= blocks * act.n) return;
@@ -853,7 +858,7 @@ hipError_t route_gateup_b1_per_cu(int H, int *n) {
 template <typename WT, int NCH>
 hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
   const size_t lds = size_t(ra.H) * sizeof(double);
-  const int n_route = ra.E;                    // one workgroup per router row
+  const int n_route = (ra.E + kJointRows - 1) / kJointRows;
   int blocks_per_cu = 0;
   if (hipError_t e = route_gateup_b1_per_cu<WT, NCH>(ra.H, &blocks_per_cu); e != hipSuccess) return e;
   // the routing workgroups wait for one another: they must fit on the device together

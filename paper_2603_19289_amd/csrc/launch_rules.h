@@ -22,16 +22,16 @@ inline GateupSplit gateup_b1_split(int nch, int I, int n) {
 }
 
 // How the gate/up rows are dealt to wavefronts beside the routing.  The routing is a chain of dependent memory accesses
-// (11 us alone) and every one of them queues behind the weight loads in flight: with all rows asked for at once its
-// first loads came back after 9 us instead of 2.4 and the launch took 20.5 us on 128 experts of 768 x 2048 (50 MB).
-// Up to 64 MB of weights one gate/up workgroup goes on each compute unit that does not route: 2.7 TB/s, at which the
-// routing takes its usual time, 18.6 us together.  Up to 256 MB the workgroups fill the device once, so that none is
-// left over for a second round.  Beyond, the routing is short beside the stream and the split of the plain launch is as
-// good.  Microseconds per layer step, one workgroup per unit / filled once / plain split, for 8 of 64 experts of 2048
-// columns, 2 of 8 of 4096 and 4 of 32 of 2880: at 24 to 32 MB 20.7 / 20.7 / 20.4, 22.7 / 25.0 / 24.5, 24.4 / 25.6 / 25.7;
-// at 64 MB 30.5 / 28.3 / 29.2, 28.7 / 29.9 / 30.5, 30.9 / 31.2 / 32.4; at 96 MB 37.7 / 34.3 / 36.2, 36.2 / 35.4 / 38.8,
-// 38.0 / 36.5 / 38.0; at 192 MB 67.7 / 57.7 / 59.8, 59.6 / 57.8 / 60.3, 62.7 / 58.0 / 58.4; at 256 MB 84.1 / 72.1 / 72.1,
-// 75.1 / 72.8 / 72.6, 77.6 / 72.1 / 71.8; at 320, 384 MB 102.1 / 87.1 / 86.1, 106.0 / 103.9 / 106.5.
+// (9 us alone) and every one of them queues behind the weight loads in flight, above all those of its own compute unit.  Up
+// to 64 MB of weights one gate/up workgroup goes on each compute unit that does not route: 128 experts of 768 x 2048 (50 MB,
+// 64 routing workgroups) 3.9 TB/s, the prediction posted after 10.7 us, 14.5 us together; with a quarter more workgroups 13.5
+// and 16.  Up to 256 MB the workgroups fill the device once, so that none is left over for a second round.  Beyond, the
+// routing is short beside the stream and the split of the plain launch is as good.  Microseconds per layer step, one
+// workgroup per unit / filled once, for 8 of 64 experts of 2048 columns, 2 of 8 of 4096 and 4 of 32 of 2880: at 24 MB 19.0 /
+// 19.8, 22.3 / 23.7, 22.6 / 23.9; at 40 20.8 / 22.5, 25.0 / 26.7, 23.9 / 25.3; at 63 26.5 / 26.2, 26.6 / 28.3, 26.4 / 28.3;
+// at 80 28.3 / 27.0, 29.2 / 31.0, 31.9 / 32.0; at 112 35.8 / 32.6, 35.4 / 35.2, 36.0 / 34.1; at 160 48.3 / 44.2, 44.8 /
+// 44.4, 50.0 / 47.2; at 224 65.0 / 59.2, 59.7 / 59.7, 63.9 / 60.5.  Filled once / plain split, before the two rows per
+// routing workgroup: at 256 MB 72.1 / 72.1, 72.8 / 72.6, 72.1 / 71.8; at 320, 384 MB 87.1 / 86.1, 103.9 / 106.5.
 // Never fewer workgroups than a quarter of the compute units, however many of them the routing takes: with routing that
 // fills the device there would be none.  Never pairs: those end at 67 MB.
 inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_t wbytes, int n_route, int blocks_per_cu,
@@ -56,6 +56,8 @@ inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_
 // them stands on two of them (half of 256 units, 4 KB), and none was moved as far as it would go.  The limit on routing
 // workgroups leaves out a gain of 2.5 % (64 experts), the one on rows rests on a loss of 1.3 % (2880 columns: the vector that
 // these workgroups form a second time is longer) and on shapes that the bytes per workgroup exclude as well.
+// All of this with one router row per routing workgroup.  With two of them it takes 255 experts on a whole device to get here
+// (8 of 256 of 480 x 2048 366 / 366, and 383 with one row per workgroup and the rows shared); a partition gets here with fewer.
 struct SharedSplit {
   GateupSplit stream;                          // of rows [0, first_tail)
   int first_tail, tail_rpw, tail_blocks;       // tail_blocks 0: none
