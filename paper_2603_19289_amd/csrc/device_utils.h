@@ -191,6 +191,12 @@ __device__ __forceinline__ void publish64(unsigned long long *slot, double v) {
                      __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The same for a value that is worked on further: one that is not a number stays one.
+__device__ __forceinline__ void publish_value64(unsigned long long *slot, double v) {
+  const unsigned long long u = v == v ? static_cast<unsigned long long>(__double_as_longlong(v)) : 0x7ff8000000000000ull;
+  __hip_atomic_store(slot, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ void arm64(unsigned long long *slot) {
   __hip_atomic_store(slot, kEmpty64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -221,6 +227,27 @@ __device__ __forceinline__ unsigned long long await64(const unsigned long long *
     else v = v3;
   }
   return v;
+}
+
+// Waits (boundedly) until slots[at(0)] .. slots[at(N - 1)] hold values.  Every look is at all of them, without a condition,
+// so that they are in flight together (under a condition each load is waited for by itself).
+template <int N, typename At>
+__device__ __forceinline__ void await_all64(const unsigned long long *slots, At at, unsigned int limit, unsigned int *status,
+                                            double (&v)[N]) {
+  for (unsigned int spins = 0;; ++spins) {
+    unsigned long long u[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) u[i] = peek64(slots + at(i));
+    bool missing = false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      missing |= u[i] == kEmpty64;
+      v[i] = __longlong_as_double(static_cast<long long>(u[i]));
+    }
+    if (!missing) break;
+    if (spins >= limit) { raise_status(status); break; }
+    __builtin_amdgcn_s_sleep(3);
+  }
 }
 
 // In-register rank sort of one token's logits.  Every wavefront holds all candidates in

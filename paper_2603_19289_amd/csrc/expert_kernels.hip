@@ -610,46 +610,21 @@ hipError_t compute_units(int *n) {
   return e != hipSuccess ? e : hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev);
 }
 
-template <bool GATEUP, int NT, bool STREAM>
-hipError_t launch_expert_mfma_n(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq,
-                                hipStream_t st) {
-  const int rows = GATEUP ? a.I : a.H, tiles = (a.B + 15) / 16, positions = int(lists.expert[lists.n] & 0xffff);
-  auto launch = [&](auto ksplit, auto chains) {
-    const int rows_per_wg = 16 * kWaves / ksplit();
-    const dim3 grid((rows + rows_per_wg - 1) / rows_per_wg, lists.n), block(kBlock);
-    hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, NT, ksplit(), chains(), STREAM>), grid, block, 0, st, a, lists, act_q, hq);
-    return hipGetLastError();
-  };
-  if constexpr (GATEUP) {
-    return with_ksplit(gateup_ksplit(a.H, tiles), [&](auto ksplit) { return launch(ksplit, int_c<kOneChain>()); });
-  } else {
-    int cus = 0;
-    if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
-    return with_ksplit(down_ksplit(a.I, tiles, rows, lists.n, positions, cus), [&](auto ksplit) {
-      if constexpr (ksplit() == 1)
-        if (a.I >= 1024) return launch(ksplit, int_c<kFourParts>());
-      if constexpr (ksplit() == 2 && NT == 1)
-        if (tiles == 1) return launch(ksplit, int_c<kTwoChains>());
-      return launch(ksplit, int_c<kOneChain>());
-    });
-  }
+template <bool GATEUP, int NT, int KSPLIT, int CHAINS>
+hipError_t launch_expert_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq, hipStream_t st) {
+  constexpr int rows_per_wg = 16 * kWaves / KSPLIT;
+  const dim3 grid(((GATEUP ? a.I : a.H) + rows_per_wg - 1) / rows_per_wg, lists.n), block(kBlock);
+  if (whole_lines(GATEUP ? a.H : a.I))
+    hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, NT, KSPLIT, CHAINS, true>), grid, block, 0, st, a, lists, act_q, hq);
+  else
+    hipLaunchKernelGGL((expert_mfma_kernel<GATEUP, NT, KSPLIT, CHAINS, false>), grid, block, 0, st, a, lists, act_q, hq);
+  return hipGetLastError();
 }
 
-template <bool GATEUP, bool STREAM>
-hipError_t launch_expert_mfma_s(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq,
-                                hipStream_t st) {
-  switch (decode_tiles(lists.most)) {
-    case 1: return launch_expert_mfma_n<GATEUP, 1, STREAM>(a, lists, act_q, hq, st);
-    case 2: return launch_expert_mfma_n<GATEUP, 2, STREAM>(a, lists, act_q, hq, st);
-    default: return launch_expert_mfma_n<GATEUP, 4, STREAM>(a, lists, act_q, hq, st);
-  }
-}
-
-template <bool GATEUP>
-hipError_t launch_expert_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *act_q, uint16_t *hq,
-                              hipStream_t st) {
-  return whole_lines(GATEUP ? a.H : a.I) ? launch_expert_mfma_s<GATEUP, true>(a, lists, act_q, hq, st)
-                                         : launch_expert_mfma_s<GATEUP, false>(a, lists, act_q, hq, st);
+template <int NT>
+hipError_t launch_gateup_mfma_t(const ExpertArgs &a, const TokenLists &lists, const uint16_t *s_q, uint16_t *hq, hipStream_t st) {
+  return with_ksplit(gateup_ksplit(a.H, (a.B + 15) / 16),
+                     [&](auto ksplit) { return launch_expert_mfma<true, NT, ksplit(), kOneChain>(a, lists, s_q, hq, st); });
 }
 
 // The same over position lists on the device (prefill), 64 positions per grid plane.
@@ -740,11 +715,21 @@ hipError_t launch_down(const ExpertArgs &a, const ActiveList &act, int dtype, hi
 // launch and read by the down launch.
 hipError_t launch_gateup_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *s_q, uint16_t *hq,
                               hipStream_t st) {
-  return lists.n <= 0 ? hipSuccess : launch_expert_mfma<true>(a, lists, s_q, hq, st);
+  if (lists.n <= 0) return hipSuccess;
+  switch (decode_tiles(lists.most)) {
+    case 1: return launch_gateup_mfma_t<1>(a, lists, s_q, hq, st);
+    case 2: return launch_gateup_mfma_t<2>(a, lists, s_q, hq, st);
+    default: return launch_gateup_mfma_t<4>(a, lists, s_q, hq, st);
+  }
 }
 
 hipError_t launch_down_mfma(const ExpertArgs &a, const TokenLists &lists, const uint16_t *hq, hipStream_t st) {
-  return lists.n <= 0 ? hipSuccess : launch_expert_mfma<false>(a, lists, hq, nullptr, st);
+  if (lists.n <= 0) return hipSuccess;
+  int cus = 0;
+  if (hipError_t e = compute_units(&cus); e != hipSuccess) return e;
+  return with_down_form(a, lists, cus, [&](auto nt, auto ksplit, auto chains) {
+    return launch_expert_mfma<false, nt(), ksplit(), chains()>(a, lists, hq, nullptr, st);
+  });
 }
 
 hipError_t launch_gateup_prefill(const ExpertArgs &a, const ActiveList &act, const uint16_t *s_q, uint16_t *hq,

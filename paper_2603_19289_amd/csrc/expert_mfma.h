@@ -5,6 +5,7 @@
 
 #include "device_utils.h"
 #include "kernels.h"
+#include "launch_rules.h"
 
 namespace moe_spec {
 
@@ -343,5 +344,25 @@ hipError_t with_ksplit(int ksplit, F f) {
 // share a line, so that the weights may bypass the caches.
 inline int decode_tiles(int most) { return most <= 16 ? 1 : most <= 32 ? 2 : 4; }
 inline bool whole_lines(int K) { return K % 64 == 0; }
+
+// Calls f with the tiles, wavefronts per tile and chains of the down projection of a decode batch, as constants.
+template <typename F>
+hipError_t with_down_form(const ExpertArgs &a, const TokenLists &lists, int cus, F f) {
+  const int tiles = (a.B + 15) / 16, positions = int(lists.expert[lists.n] & 0xffff);
+  auto of_tiles = [&](auto nt) {
+    return with_ksplit(down_ksplit(a.I, tiles, a.H, lists.n, positions, cus), [&](auto ksplit) {
+      if constexpr (ksplit() == 1)
+        if (a.I >= 1024) return f(nt, ksplit, int_c<kFourParts>());
+      if constexpr (ksplit() == 2 && nt() == 1)
+        if (tiles == 1) return f(nt, ksplit, int_c<kTwoChains>());
+      return f(nt, ksplit, int_c<kOneChain>());
+    });
+  };
+  switch (decode_tiles(lists.most)) {
+    case 1: return of_tiles(int_c<1>());
+    case 2: return of_tiles(int_c<2>());
+    default: return of_tiles(int_c<4>());
+  }
+}
 
 }  // namespace moe_spec

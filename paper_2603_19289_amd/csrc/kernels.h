@@ -82,6 +82,8 @@ struct RoutePairArgs {
   const void *proj_add;                   // [proj_rows]
   double *proj_out;                       // [B,proj_rows]
   int proj_rows;
+  unsigned long long *est_t, *est_v;      // and the hand-over slots of launch_estimator, which this launch arms
+  int est_t_count, est_v_count;
   unsigned long long *z_true, *z_pred;    // [B,E] logit slots of this launch, armed
   unsigned long long *z_true_next, *z_pred_next;   // the other set, armed by this launch
   int arm_count;                          // slots per set (largest batch * E)
@@ -187,6 +189,24 @@ struct GemvArgs {
   int B, rows, cols, silu;
 };
 hipError_t launch_gemv64(const GemvArgs &a, int dtype, hipStream_t st);
+
+// The estimator from its feed-forward on, in one launch: t = silu(ffn_in u), v = u + ffn_out t, LayerNorm, head, top-k.
+// The prediction is reported as a routing launch does: next_*, mb_next, z_pred and the sets of slots to arm are read from
+// the routing arguments, and H, w_* are not.
+struct EstimatorArgs {
+  const double *u;            // [B, dm] the projection, of the launch before
+  const void *ffn_in, *ffn_out, *head;         // [F, dm], [dm, F], [E, dm]
+  const float *ln_gain, *ln_bias;
+  unsigned long long *t, *v;  // [B, F], [B, dm] hand-over slots, armed by the launch before
+  int dm, F;
+  float ln_eps;
+};
+bool estimator_supported(int dm, int F, int B, int dtype);      // sizes, and whether its workgroups fit on the device together
+hipError_t launch_estimator(const EstimatorArgs &e, const RoutePairArgs &ra, int dtype, hipStream_t st);
+// The same beside the down projection of a bf16 batch on the matrix cores (launch_down_mfma); hipErrorLaunchOutOfResources,
+// and nothing launched, where that does not fit.
+hipError_t launch_down_estimator(const EstimatorArgs &e, const RoutePairArgs &ra, const ExpertArgs &a, const TokenLists &lists,
+                                 const uint16_t *hq, hipStream_t st);
 
 hipError_t launch_route(const RouteArgs &a, int dtype, hipStream_t st);
 hipError_t launch_gateup(const ExpertArgs &a, const ActiveList &act, int dtype, hipStream_t st);

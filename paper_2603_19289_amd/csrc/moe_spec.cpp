@@ -810,6 +810,10 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
   // 38 us per layer (experts of 1.6 MB) to 1.1 ms (50 MB), both copy engines, differ by less than 2 % either way (medians).
   // (profile = 1 brackets routing and experts separately.)
   const bool est_beside = use_est && !cfg.diagnostics && route_pair_supported(H, cfg.dtype) && cfg.predict_signal == 0;
+  const bool est_whole = est_beside && estimator_supported(cfg.est_latent, cfg.est_ffn, batch, cfg.dtype);
+  EstimatorArgs est_args{};
+  RoutePairArgs est_report{};
+  bool est_with_down = false;                   // the estimator goes on beside the down projection
   const bool beside_routing =
       exec_pred && !again && !cfg.profile && c->pending_union.size() <= size_t(S) && !c->ready_pending[layer] &&
       ((fast_b1 && fused_route && route_gateup_b1_supported(H, E, cfg.dtype)) ||
@@ -951,6 +955,12 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       ta.proj_add = static_cast<const char *>(c->est.layer_emb) + size_t(layer) * cfg.est_latent * wbytes;
       ta.proj_out = c->at<double>(c->lay.est_u);
       ta.proj_rows = cfg.est_latent;
+      if (est_whole) {
+        ta.est_t = c->at<unsigned long long>(c->lay.est_t);
+        ta.est_v = c->at<unsigned long long>(c->lay.est_v);
+        ta.est_t_count = batch * cfg.est_ffn;
+        ta.est_v_count = batch * cfg.est_latent;
+      }
     }
     if ((e = launch_first_routing(ta)) != hipSuccess) return c->hip_fail(e, "routing kernel");
   } else {
@@ -982,6 +992,34 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     pa.spec = cfg.predict_signal == 1 ? 2 : 1;
     pa.from_normalized = cfg.q_from_normalized;
     if (use_est) {
+      c->st.hbm_bytes_algorithmic += (int64_t(cfg.est_latent) * H + 2 * int64_t(cfg.est_ffn) * cfg.est_latent +
+                                      int64_t(E) * cfg.est_latent + cfg.est_latent) * wbytes + int64_t(batch) * k * H * wbytes;
+    }
+    if (est_whole) {
+      // The projection was part of the routing launch; one launch takes it from there.  Where the experts ran beside that
+      // launch it runs beside their down projection: nothing else would, and with copies pending the experts wait for them,
+      // which the next layer's copies must not.
+      est_args.u = c->at<double>(c->lay.est_u);
+      est_args.ffn_in = c->est.ffn_in; est_args.ffn_out = c->est.ffn_out; est_args.head = c->est.head;
+      est_args.ln_gain = c->est.ln_gain; est_args.ln_bias = c->est.ln_bias; est_args.ln_eps = c->est.ln_eps;
+      est_args.t = c->at<unsigned long long>(c->lay.est_t);
+      est_args.v = c->at<unsigned long long>(c->lay.est_v);
+      est_args.dm = cfg.est_latent; est_args.F = cfg.est_ffn;
+      est_report.z_pred = c->zslot_set(1, c->route_parity);
+      est_report.z_true_next = c->zslot_set(0, c->route_parity ^ 1);
+      est_report.z_pred_next = c->zslot_set(1, c->route_parity ^ 1);
+      est_report.arm_count = cfg.max_batch * E;
+      c->route_parity ^= 1;
+      est_report.next_ids = pa.ids_out; est_report.next_gates = pa.gates_out;
+      est_report.user_next_ids = pa.user_ids; est_report.user_next_gates = pa.user_gates;
+      est_report.mb_next = pa.mailbox;
+      est_report.status = c->wait_status_dev;
+      est_report.spin_limit = c->spin_limit;
+      est_report.B = batch; est_report.H = H; est_report.E = E; est_report.k = k;
+      est_with_down = beside_routing && use_mfma;
+      if (!est_with_down && (e = launch_estimator(est_args, est_report, cfg.dtype, c->compute)) != hipSuccess)
+        return c->hip_fail(e, "estimator");
+    } else if (use_est) {
       // The routing launch only produces the predicting signal; the estimator's four steps turn it
       // into logits, and its last step (the routing kernel in LayerNorm mode) selects and hands over.
       const int dm = cfg.est_latent, F = cfg.est_ffn;
@@ -1022,8 +1060,6 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       ha.vec_out = nullptr;
       c->prep_route(ha);
       if ((e = launch_route(ha, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "estimator head");
-      c->st.hbm_bytes_algorithmic += (int64_t(dm) * H + 2 * int64_t(F) * dm + int64_t(E) * dm + dm) * wbytes +
-                                     int64_t(batch) * k * H * wbytes;
     } else {
       c->prep_route(pa);
       if ((e = launch_route(pa, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "prediction kernel");
@@ -1098,7 +1134,15 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       if (!beside_routing) c->token_lists(act, exec_ids_host, &lists);
       if (!beside_routing && (e = launch_gateup_mfma(xa, lists, c->at<uint16_t>(c->lay.s_q), hq, c->compute)) != hipSuccess)
         return c->hip_fail(e, "gate/up MFMA kernel");
-      if ((e = launch_down_mfma(xa, lists, hq, c->compute)) != hipSuccess) return c->hip_fail(e, "down MFMA kernel");
+      if (est_with_down) {
+        e = launch_down_estimator(est_args, est_report, xa, lists, hq, c->compute);
+        if (e != hipSuccess && e != hipErrorLaunchOutOfResources) return c->hip_fail(e, "down MFMA kernel with the estimator");
+        est_with_down = e == hipSuccess;
+        if (!est_with_down && (e = launch_estimator(est_args, est_report, cfg.dtype, c->compute)) != hipSuccess)
+          return c->hip_fail(e, "estimator");
+      }
+      if (!est_with_down && (e = launch_down_mfma(xa, lists, hq, c->compute)) != hipSuccess)
+        return c->hip_fail(e, "down MFMA kernel");
       c->close_span(sp_gu, c->compute);
     } else {
       if ((e = launch_gateup(xa, act, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");

@@ -309,6 +309,25 @@ def test_estimator_projection_beside_the_routing(dtype, B, hidden, experts, m):
                        estimator=est, estimator_layers=[0, 1, 2])
 
 
+@pytest.mark.parametrize("dtype,B,hidden,experts,m,n,inter,kernel", [
+    ("bf16", 2, 264, 3, 33, 2, 1032, "down_estimator_kernel"),       # latent size 8: one row per wavefront of a few workgroups
+    ("bf16", 64, 256, 20, 4, 2, 24, "down_estimator_kernel"),       # 16 groups of four tokens
+    ("bf16", 5, 2048, 4, 1, 2, 264, "down_estimator_kernel"),       # 4096 values: a token per group, two steps per row
+    ("bf16", 18, 1024, 8, 1, 2, 1032, "down_estimator_kernel"),     # two tokens per group; two tiles of tokens
+    ("bf16", 7, 264, 6, 1, 3, 40, "down_estimator_kernel"),         # rows that are no multiple of 64 chunks, the last group of three
+    ("bf16", 1, 264, 128, 3, 2, 40, "estimator_kernel<unsigned short>"), ("f32", 3, 1040, 12, 2, 3, 24, "estimator_kernel<float>"),
+    ("bf16", 3, 2056, 3, 1, 2, 24, "gemv64_kernel")])                # 4112 values: the separate launches
+def test_estimator_in_one_launch(dtype, B, hidden, experts, m, n, inter, kernel):
+    # from the feed-forward on the estimator is one launch, beside the down projection where the experts ran beside the routing
+    wl = small_workload(name="estimator_launch", n_layers=4, hidden=hidden, n_experts=experts, top_k=2, inter=inter,
+                        dtype=dtype, batch=B, tokens=3, slots=experts, seed=59)
+    est = W.make_estimator(wl, m=m, n=n)
+    counts = kernels_launched(lambda: run_teacher_forced(
+        wl, O.MODE_SPECULATIVE, oracle_kw=dict(estimator=O.Estimator(**est), estimator_layers=[0, 1, 2, 3]),
+        estimator=est, estimator_layers=[0, 1, 2, 3]), {})
+    assert any(name.startswith(kernel) for name in counts), counts
+
+
 @pytest.mark.parametrize("mode", ["speculative", "prefetch_hint"])
 @pytest.mark.parametrize("dtype,B,S,engine", [("bf16", 1, 4, "COPY_DMA2"), ("f32", 3, 5, "COPY_KERNEL"), ("bf16", 20, 6, "COPY_DMA"),
                                              ("bf16", 1, 3, "COPY_DMA2")])

@@ -124,3 +124,18 @@ def test_routing_workgroups_take_rows_at_the_sizes_of_the_gpu_test(tmp_path):
     const SharedSplit s = share_with_routing(beside_routing_split(nch, v[1], v[0], 16, 2, v[2], per_cu, 256), v[1], v[0], 16, 2, v[2], 256);
     if (s.tail_blocks < 1) { ++bad; std::printf("%d %d %d\n", v[0], v[1], v[2]); }
   }""")
+
+
+def test_estimator_groups_cover_the_batch_and_fit_on_the_device(tmp_path):
+    sweep(tmp_path, r"""
+  int taken = 0;
+  for (int cus : {32, 64, 128, 256}) for (int dm : {8, 88, 512, 2048, 2056, 4096, 8192}) for (int F : {8, 176, 1024, 4096, 4104, 65536})
+    for (int B = 1; B <= 64; ++B) {
+      const EstimatorSplit s = estimator_split(dm, F, B, cus);
+      if (s.wgs == 0) { if (std::max(dm, F) <= 4096 && B * 4 <= cus) ++bad; continue; }
+      ++taken;
+      const bool ok = s.tokens >= 1 && s.tokens <= 2 && s.tokens * std::max(dm, F) <= 4096 && s.groups * s.tokens >= B &&
+                      (s.groups - 1) * s.tokens < B && s.wgs >= 4 && s.wgs * s.groups <= cus;
+      if (!ok && ++bad <= 20) std::printf("cus %d dm %d F %d B %d: %d %d %d\n", cus, dm, F, B, s.tokens, s.groups, s.wgs);
+    }
+  if (!taken) ++bad;""")
