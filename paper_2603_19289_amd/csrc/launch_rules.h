@@ -142,6 +142,43 @@ inline int down_ksplit(int K, int token_tiles, int rows, int experts, int positi
   return positions >= 8 * experts && long(experts) * ((rows + 63) / 64) >= 2l * cus ? 1 : 4;
 }
 
+// How a request's n blocks are dealt to the two DMA queues: the second one takes `second` whole blocks and the first `cut`
+// bytes of one more (0: none).  A half each, in turn, as long as the queues are equally fast.  They are not where something
+// else uses the engine behind one of them: the driver clears freed device memory with it, some 16 GB/s, and meanwhile a 9.4
+// MB block takes 300 us on the second queue instead of 172, both queues still fill the link together, and the first one
+// waits for the second at the end of every request (47 ms instead of 37 for 32 layer steps of 128 experts of 768 x 2048 with
+// 16 slots, for 1.3 s after an engine of 22 GB was given back).  So the second queue's share follows how much later than the
+// first it was done in an earlier request.  Left at a half until a share of less than 0.38 or more than 0.62 is indicated,
+// so that the odd block of ordinary requests (0.43 of seven, done earlier) moves nothing.
+constexpr double kEvenShare = 0.5;
+struct QueueDeal {
+  int second;
+  std::size_t cut;
+};
+inline QueueDeal deal_to_queues(int n, std::size_t block, double share) {
+  if (share == kEvenShare || n < 2) return {n / 2, 0};
+  const double blocks = share * n;
+  QueueDeal deal{int(blocks), std::size_t((blocks - int(blocks)) * double(block)) & ~std::size_t(4095)};
+  if (deal.cut < block / 8) deal.cut = 0;                 // what a transfer costs beside its bytes is some 10 us
+  if (deal.cut > block - block / 8) { deal.cut = 0; deal.second += 1; }
+  return deal;
+}
+// taken: the part of the request's bytes that the second queue had; late_us: how much later than the first it was done.
+// What is left when one queue is done travels at 30 to 55 GB/s, and some two thirds of it belong to the other queue.  Half of
+// the way there each time: a request's blocks are few and their times scatter.  first_sign: the even share was indicated to
+// be wrong by the request measured before as well (a single one is an accident of the link).
+inline double next_queue_share(double share, double taken, double late_us, double bytes, bool *first_sign) {
+  const double to = std::min(0.9, std::max(0.1, taken - late_us * 20e3 / bytes));
+  if (share == kEvenShare) {
+    const bool wrong = to < 0.38 || to > 0.62, again = *first_sign;
+    *first_sign = wrong;
+    return wrong && again ? to : kEvenShare;
+  }
+  const double next = 0.5 * (share + to);
+  *first_sign = false;
+  return next > 0.46 && next < 0.54 ? kEvenShare : next;
+}
+
 // Whether the copies of a step's second and further cache waves go on the compute stream although a prefetch for the next
 // layer is queued on the copy stream right behind them and takes half of the link meanwhile.  They save an event there and
 // back (some 15 us a wave) and the prefetch runs beside the kernels of the waves, but the last wave ends later, and nothing

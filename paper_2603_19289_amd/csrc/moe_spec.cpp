@@ -173,6 +173,12 @@ struct moe_spec_ctx {
   hipStream_t compute = nullptr, copy = nullptr;
   std::vector<hipStream_t> copy_aux;             // owned; further DMA queues of copy_engine 2
   std::vector<hipEvent_t> aux_done;
+  double second_share = kEvenShare;              // copy_engine 2: the second queue's share of a request's bytes
+  hipEvent_t queue_end[2] = {nullptr, nullptr};  // when the queues were done with the request that is being measured
+  bool measuring = false;
+  double measured_share = 0.0, measured_bytes = 0.0;
+  int since_measured = 0;                        // requests
+  bool uneven_sign = false;                      // the last one measured spoke against even shares
   hipEvent_t pf_ready[2] = {nullptr, nullptr}, pf_done[2] = {nullptr, nullptr};   // prefill: one pair per half pool
   hipEvent_t pf_tail[2] = {nullptr, nullptr};    // and one per copy queue
 
@@ -297,9 +303,9 @@ struct moe_spec_ctx {
   }
 
   // One expert block host -> device by the configured engine (the copy kernel on kernel_stream); `index` counts the blocks of the
-  // current group (it picks the queue).  copy_join ends the group: afterwards everything issued is
+  // current group of n (it picks the queue).  copy_join ends the group: afterwards everything issued is
   // ordered before whatever is recorded next on the copy stream.
-  int copy_expert(CopyList &cl, int index, char *dst, const char *src, hipStream_t kernel_stream) {
+  int copy_expert(CopyList &cl, int index, int n, double share, char *dst, const char *src, hipStream_t kernel_stream) {
     if (cfg.copy_engine == MOE_SPEC_COPY_KERNEL) {
       cl.src[cl.n] = src;
       cl.dst[cl.n] = dst;
@@ -308,17 +314,47 @@ struct moe_spec_ctx {
         if (c != hipSuccess) return hip_fail(c, "host-to-device gather copy");
         cl.n = 0;
       }
-    } else if (cfg.copy_engine == MOE_SPEC_COPY_DMA2) {
-      // whole experts, dealt round-robin over the queues (cutting every expert into one part per
-      // queue moved no more bytes per second and made the timing erratic)
-      const size_t q = size_t(index) % (1 + copy_aux.size());
-      hipError_t c = hipMemcpyAsync(dst, src, expert_bytes, hipMemcpyHostToDevice, q == 0 ? copy : copy_aux[q - 1]);
-      if (c != hipSuccess) return hip_fail(c, "host-to-device expert copy");
-    } else {
-      hipError_t c = hipMemcpyAsync(dst, src, expert_bytes, hipMemcpyHostToDevice, copy);
-      if (c != hipSuccess) return hip_fail(c, "host-to-device expert copy");
+      return MOE_SPEC_OK;
     }
-    return MOE_SPEC_OK;
+    // whole experts, dealt in turn over the queues (cutting every expert into one part per queue moved no more bytes per
+    // second and made the timing erratic), or by their shares, one expert cut
+    std::size_t second = 0;                      // bytes for the second queue
+    if (!copy_aux.empty()) {
+      const QueueDeal deal = deal_to_queues(n, expert_bytes, share);
+      const int whole = n - (deal.cut > 0);
+      if (share == kEvenShare) second = index % 2 ? expert_bytes : 0;
+      else if (index >= whole) second = deal.cut;
+      else second = (index + 1) * deal.second / whole > index * deal.second / whole ? expert_bytes : 0;
+    }
+    hipError_t c = hipSuccess;
+    if (second > 0) c = hipMemcpyAsync(dst, src, second, hipMemcpyHostToDevice, copy_aux[0]);
+    if (c == hipSuccess && second < expert_bytes)
+      c = hipMemcpyAsync(dst + second, src + second, expert_bytes - second, hipMemcpyHostToDevice, copy);
+    return c == hipSuccess ? MOE_SPEC_OK : hip_fail(c, "host-to-device expert copy");
+  }
+  // The second queue's share after the measured request, once both queues are done with it.
+  void follow_queues() {
+    if (!measuring) return;
+    if (hipEventQuery(queue_end[0]) != hipSuccess || hipEventQuery(queue_end[1]) != hipSuccess) {
+      (void)hipGetLastError();                   // not ready
+      return;
+    }
+    measuring = false;
+    float late_ms = 0.f;
+    if (hipEventElapsedTime(&late_ms, queue_end[0], queue_end[1]) == hipSuccess)
+      second_share = next_queue_share(second_share, measured_share, 1e3 * double(late_ms), measured_bytes, &uneven_sign);
+  }
+  // Notes when the queues are done with a request of n blocks: every eighth one while they are even (the two events are 0.3 %
+  // of such a request), of 8 MB and more (below, what a transfer costs beside its bytes weighs as much).
+  void measure_queues(int n) {
+    const double bytes = double(n) * double(expert_bytes);
+    if (copy_aux.empty() || measuring || n < 2 || bytes < 8e6) return;
+    if (second_share == kEvenShare && !uneven_sign && ++since_measured < 8) return;
+    since_measured = 0;
+    const QueueDeal deal = deal_to_queues(n, expert_bytes, second_share);
+    measured_bytes = bytes;
+    measured_share = (double(deal.second) * double(expert_bytes) + double(deal.cut)) / bytes;
+    measuring = hipEventRecord(queue_end[0], copy) == hipSuccess && hipEventRecord(queue_end[1], copy_aux[0]) == hipSuccess;
   }
   int copy_join(CopyList &cl, hipStream_t kernel_stream) {
     if (cl.n > 0) {
@@ -389,6 +425,9 @@ struct moe_spec_ctx {
     for (int e : experts)                        // refuse before any state changes
       if (p.where[e] < 0 && !host_expert[size_t(layer) * cfg.n_experts + e])
         return fail(MOE_SPEC_ESTATE, "expert %d of layer %d was never registered", e, layer);
+    follow_queues();
+    int missing = 0;
+    for (int e : experts) missing += p.where[e] < 0;
     p.clock += 1;
     for (int e : experts) {
       if (p.where[e] >= 0) { p.slot_stamp[p.where[e]] = int(p.clock); st.cache_hits += 1; }
@@ -422,12 +461,13 @@ struct moe_spec_ctx {
       p.slot_stamp[victim] = int(p.clock);
       p.where[e] = victim;
       char *dst = pool_base(layer) + size_t(victim) * slot_stride;
-      if (int rc = copy_expert(cl, copies, dst, src, kernel_stream)) return rc;
+      if (int rc = copy_expert(cl, copies, missing, second_share, dst, src, kernel_stream)) return rc;
       copies += 1;
       st.cache_misses += 1;
       st.h2d_bytes += int64_t(expert_bytes);
     }
     if (copies > 0) {                            // the request is complete when every queue is
+      measure_queues(copies);
       if (int rc = copy_join(cl, kernel_stream)) return rc;
     }
     if (copies > 0 && !in_order) {
@@ -601,6 +641,8 @@ int moe_spec_create(const moe_spec_config *cfg, moe_spec_ctx **out) {
       if ((e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return bail(e, "event");
       c->aux_done.push_back(ev);
     }
+    for (hipEvent_t &end : c->queue_end)
+      if ((e = hipEventCreate(&end)) != hipSuccess) return bail(e, "event");
   }
   void *mb = nullptr;
   // fine-grained (coherent) pinned memory: device stores become visible to the spinning host
@@ -638,6 +680,7 @@ void moe_spec_destroy(moe_spec_ctx *c) {
   }
   for (hipStream_t q : c->copy_aux) (void)hipStreamDestroy(q);
   for (hipEvent_t ev : c->aux_done) (void)hipEventDestroy(ev);
+  for (hipEvent_t ev : c->queue_end) if (ev) (void)hipEventDestroy(ev);
   for (int h = 0; h < 2; ++h) {
     if (c->pf_ready[h]) (void)hipEventDestroy(c->pf_ready[h]);
     if (c->pf_done[h]) (void)hipEventDestroy(c->pf_done[h]);
@@ -1499,7 +1542,7 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
       break;
     }
     for (int x = 0; x < n_here; ++x) {
-      int rc = c->copy_expert(cl, x, c->pool_base(layer) + size_t(act.slot[x]) * c->slot_stride,
+      int rc = c->copy_expert(cl, x, n_here, kEvenShare, c->pool_base(layer) + size_t(act.slot[x]) * c->slot_stride,
                               c->host_expert[size_t(layer) * E + e0 + x], c->copy);
       if (rc) return rc;
     }

@@ -139,3 +139,41 @@ def test_estimator_groups_cover_the_batch_and_fit_on_the_device(tmp_path):
       if (!ok && ++bad <= 20) std::printf("cus %d dm %d F %d B %d: %d %d %d\n", cus, dm, F, B, s.tokens, s.groups, s.wgs);
     }
   if (!taken) ++bad;""")
+
+
+def test_blocks_are_dealt_to_the_copy_queues_once_and_their_shares_settle(tmp_path):
+    # every byte of a request goes to one queue; two queues of unequal speeds come to be done together, whatever the number of
+    # blocks, and go back to even shares when the speeds are equal again; equal queues are left alone, odd blocks or not
+    sweep(tmp_path, r"""
+  for (int n = 1; n <= 256; ++n) for (std::size_t block : {std::size_t(3) * 8 * 8 * 2, std::size_t(9437184), std::size_t(352321536)})
+    for (double share : {0.1, 0.29, 0.37, 0.5, 0.61, 0.9}) {
+      const QueueDeal d = deal_to_queues(n, block, share);
+      const bool ok = d.second >= 0 && d.second + (d.cut > 0) <= n && d.cut < block &&
+                      (n < 2 || share == kEvenShare || block < 65536 || std::abs(d.second + double(d.cut) / block - share * n) <= 0.126);
+      if (!ok && ++bad <= 20) std::printf("n %d block %zu share %g: %d %zu\n", n, block, share, d.second, d.cut);
+    }
+  const double block = 9437184, link = 57e3;               // bytes per us
+  for (double slow : {1.0, 0.55, 0.7}) for (int which : {0, 1}) for (int n : {2, 3, 7, 8, 16}) {
+    double share = kEvenShare, late = 0, length = 0;
+    bool sign = false;
+    for (int step = 0; step < 60; ++step) {
+      const double factor = step < 40 ? slow : 1.0;
+      const QueueDeal d = deal_to_queues(n, std::size_t(block), share);
+      double left[2] = {n * block - (d.second * block + d.cut), d.second * block + d.cut};
+      const double taken = left[1] / (n * block), own[2] = {55e3 * (which == 0 ? factor : 1.0), 55e3 * (which == 1 ? factor : 1.0)};
+      double at[2] = {0, 0}, t = 0;                          // both: the link shared by speed; one: its own speed
+      while (left[0] > 1 || left[1] > 1) {
+        const bool both = left[0] > 1 && left[1] > 1;
+        double v[2], go = 1e30;
+        for (int q = 0; q < 2; ++q) v[q] = both ? std::min(own[q], link * own[q] / (own[0] + own[1])) : own[q];
+        for (int q = 0; q < 2; ++q) if (left[q] > 1) go = std::min(go, left[q] / v[q]);
+        t += go;
+        for (int q = 0; q < 2; ++q) if (left[q] > 1) { left[q] -= v[q] * go; if (left[q] <= 1) at[q] = t; }
+      }
+      late = at[1] - at[0]; length = t;
+      share = next_queue_share(share, taken, late, n * block, &sign);
+      if (slow == 1.0 && share != kEvenShare) { ++bad; std::printf("even n %d: %g\n", n, share); break; }
+      if (step == 39 && slow < 0.6 && n >= 7 && std::abs(late) > 0.25 * length) { ++bad; std::printf("slow %g queue %d n %d: %g of %g\n", slow, which, n, late, length); }
+    }
+    if (share != kEvenShare) { ++bad; std::printf("not even again: slow %g queue %d n %d: %g\n", slow, which, n, share); }
+  }""")
