@@ -146,15 +146,36 @@ __global__ __launch_bounds__(kBlock) void down_kernel(const ExpertArgs a, const 
 // Batch-1 kernels: no token lists, no staging barrier in the gate/up kernel, combine fused into
 // the down kernel.  These are the kernels of the headline workload.
 
-template <typename WT, int NCH>
-__global__ __launch_bounds__(kBlock) void gateup_b1_kernel(const ExpertArgs a, const ActiveList act,
-                                                           const int rpw) {
-  gateup_b1_body<WT, NCH, false>(a, act, blockIdx.y, blockIdx.x, rpw, 0, a.I, nullptr, nullptr);
+// The slots of a launch that was queued behind the routing without waiting for its ids (BY_ROUTING): a lane for each of the k
+// positions, or "absent" if an expert is in none; the host, which learns the same ids meanwhile, copies it and launches again.
+__device__ __forceinline__ bool routed_slots(const ExpertArgs &a, int lane, int *slot) {
+  *slot = a.slots[lane < a.k ? lane : 0];
+  return __ballot(*slot < 0) == 0;
 }
 
-template <typename WT, int NCH>
+template <typename WT, int NCH, bool BY_ROUTING>
+__global__ __launch_bounds__(kBlock) void gateup_b1_kernel(const ExpertArgs a, const ActiveList act,
+                                                           const int rpw) {
+  int slot = 0;
+  if (BY_ROUTING) {
+    if (!routed_slots(a, threadIdx.x & (kWave - 1), &slot)) return;
+    slot = __builtin_amdgcn_readlane(slot, blockIdx.y);
+  } else {
+    slot = act.slot[blockIdx.y];
+  }
+  gateup_b1_body<WT, NCH, false>(a, slot, blockIdx.y, blockIdx.x, rpw, 0, a.I, nullptr, nullptr);
+}
+
+template <typename WT, int NCH, bool BY_ROUTING>
 __global__ __launch_bounds__(kBlock) void gateup_b1_pair_kernel(const ExpertArgs a, const ActiveList act) {
-  gateup_b1_pair_body<WT, NCH>(a, act, blockIdx.y, blockIdx.x);
+  int slot = 0;
+  if (BY_ROUTING) {
+    if (!routed_slots(a, threadIdx.x & (kWave - 1), &slot)) return;
+    slot = __builtin_amdgcn_readlane(slot, blockIdx.y);
+  } else {
+    slot = act.slot[blockIdx.y];
+  }
+  gateup_b1_pair_body<WT, NCH>(a, slot, blockIdx.y, blockIdx.x);
 }
 
 // O[row] = sum_j gate_j * (W_down_{e_j}[row,:] . hq[j,:]) for the one token of the batch: the down
@@ -164,13 +185,19 @@ __global__ __launch_bounds__(kBlock) void gateup_b1_pair_kernel(const ExpertArgs
 // whatever I is; each lane folds the gate of its chunk's expert into its partial sum, one
 // reduction per wavefront remains, and the SPLIT partial sums meet in LDS.  `act` is in
 // execution-position order.
-template <typename WT, int SPLIT, int UNROLL>
+template <typename WT, int SPLIT, int UNROLL, bool BY_ROUTING>
 __global__ __launch_bounds__(kBlock) void down_combine_b1_kernel(const ExpertArgs a, const ActiveList act,
                                                                  const float inv_chunks) {
   using R = Packed<WT>;
   constexpr int VN = R::N;
   __shared__ float part_sum[kWaves];
+  __shared__ int slots[BY_ROUTING ? kWaves : 1][kWave];      // every wavefront has its own
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  if (BY_ROUTING) {
+    int slot;
+    if (!routed_slots(a, lane, &slot)) return;
+    slots[wave][lane] = slot;
+  }
   const int H = a.H, I = a.I, k = a.k;
   const int row = blockIdx.x * (kWaves / SPLIT) + wave / SPLIT;
   const int part = wave % SPLIT;
@@ -187,7 +214,8 @@ __global__ __launch_bounds__(kBlock) void down_combine_b1_kernel(const ExpertArg
       j -= (j * chunks > t);
       j += ((j + 1) * chunks <= t);
       const int c = (t - j * chunks) * VN;
-      const char *base = a.pool + size_t(act.slot[j]) * a.slot_bytes + down_off;
+      const int slot = BY_ROUTING ? slots[BY_ROUTING ? wave : 0][j] : act.slot[j];
+      const char *base = a.pool + size_t(slot) * a.slot_bytes + down_off;
       const typename R::Raw w = load_stream<typename R::Raw>(base + size_t(c) * sizeof(WT));
       const typename R::Raw hh = *reinterpret_cast<const typename R::Raw *>(hq + size_t(j) * I + c);
       acc += a.exec_gates[j] * dot_chunk(w, hh, 0.f);
@@ -561,8 +589,10 @@ template <typename WT, int NCH>
 void launch_gateup_b1_n(const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
   const GateupSplit split = gateup_b1_split(NCH, a.I, act.n);
   const dim3 grid(split.blocks, act.n), block(kBlock);
-  if (split.rpw == 0) hipLaunchKernelGGL((gateup_b1_pair_kernel<WT, NCH>), grid, block, 0, st, a, act);
-  else hipLaunchKernelGGL((gateup_b1_kernel<WT, NCH>), grid, block, 0, st, a, act, split.rpw);
+  if (split.rpw == 0 && a.slots) hipLaunchKernelGGL((gateup_b1_pair_kernel<WT, NCH, true>), grid, block, 0, st, a, act);
+  else if (split.rpw == 0) hipLaunchKernelGGL((gateup_b1_pair_kernel<WT, NCH, false>), grid, block, 0, st, a, act);
+  else if (a.slots) hipLaunchKernelGGL((gateup_b1_kernel<WT, NCH, true>), grid, block, 0, st, a, act, split.rpw);
+  else hipLaunchKernelGGL((gateup_b1_kernel<WT, NCH, false>), grid, block, 0, st, a, act, split.rpw);
 }
 
 // Returns false when H needs more register chunks than the batch-1 kernel is built for.
@@ -584,7 +614,8 @@ template <typename WT, int SPLIT, int UNROLL>
 void launch_down_combine_b1_n(const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
   const dim3 grid((a.H + kWaves / SPLIT - 1) / (kWaves / SPLIT)), block(kBlock);
   const float inv_chunks = 1.0f / float(a.I / Packed<WT>::N);
-  hipLaunchKernelGGL((down_combine_b1_kernel<WT, SPLIT, UNROLL>), grid, block, 0, st, a, act, inv_chunks);
+  if (a.slots) hipLaunchKernelGGL((down_combine_b1_kernel<WT, SPLIT, UNROLL, true>), grid, block, 0, st, a, act, inv_chunks);
+  else hipLaunchKernelGGL((down_combine_b1_kernel<WT, SPLIT, UNROLL, false>), grid, block, 0, st, a, act, inv_chunks);
 }
 
 // The loop of a wavefront is unrolled UNROLL times, so that many loads per lane are in flight

@@ -116,7 +116,8 @@ __device__ __forceinline__ void project_rows(const RoutePairArgs &a, int b, int 
 // slower with the branch in it).
 template <typename WT, int SPLIT, int NCH, int ROWS, bool PROJ>
 __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const int wg, const int n_wg, const int b,
-                                                const int n_tokens, double *vec_lds, RouteShared &sh) {
+                                                const int n_tokens, double *vec_lds, RouteShared &sh,
+                                                const SlotTable *resident = nullptr) {
   static_assert(ROWS == 1 || SPLIT == 1, "several rows per wavefront only with one wavefront per row");
   // The router input being built, double precision, H values.  Threads own groups of VN consecutive columns (in
   // the norms: group tid, tid + 256, ...; in the products: the groups of the wavefront's chunks); column x of
@@ -285,7 +286,7 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
     }
   }
   const double denom = select_gates(k, sh.sel, tid);
-  if (wg == reporter) report_true(a, b, sh.sel, denom, tid);
+  if (wg == reporter) report_true(a, b, sh.sel, denom, tid, resident);
   STAGE(5);
   if (!pred) return;
 
@@ -386,10 +387,10 @@ __device__ __forceinline__ void route_pair_body(const RoutePairArgs &a, const in
 }
 
 template <typename WT, int SPLIT, int NCH, int ROWS, bool PROJ>
-__global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs a) {
+__global__ __launch_bounds__(kBlock) void route_pair_kernel(const RoutePairArgs a, const SlotTable resident) {
   extern __shared__ double vec_lds[];
   __shared__ RouteShared sh;
-  route_pair_body<WT, SPLIT, NCH, ROWS, PROJ>(a, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, vec_lds, sh);
+  route_pair_body<WT, SPLIT, NCH, ROWS, PROJ>(a, blockIdx.x, gridDim.x, blockIdx.y, gridDim.y, vec_lds, sh, &resident);
 }
 
 // The same routing for a launch in which expert workgroups hide its latency: nothing is kept in registers or asked for
@@ -453,7 +454,7 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
 
   select_ids_any(a, 3, a.z_true + size_t(b) * E, E, k, sh.sel, tid);
   const double denom = select_gates(k, sh.sel, tid);
-  if (wg == reporter) report_true(a, b, sh.sel, denom, tid);
+  if (wg == reporter) report_true(a, b, sh.sel, denom, tid, nullptr);
   if (!pred) return;
 
   const WT *dv = static_cast<const WT *>(a.dvec);
@@ -525,7 +526,7 @@ void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const Ac
     __syncthreads();                           // the routing's last readers of the shared memory are done
   }
   float *s_lds = reinterpret_cast<float *>(vec_lds);
-  gateup_b1_body<WT, NCH, true>(a, act, i / blocks, i % blocks, rpw, first, last, s_lds, sh.red[0]);
+  gateup_b1_body<WT, NCH, true>(a, act.slot[i / blocks], i / blocks, i % blocks, rpw, first, last, s_lds, sh.red[0]);
 }
 
 // s_l = LN_l(r_l) as bf16, one workgroup per token: what the expert workgroups of the launch below read.
@@ -606,7 +607,8 @@ hipError_t launch_route_pair_p(const RoutePairArgs &a, hipStream_t st) {
   const int n_wg = routing_workgroups(a.E, RPW, PROJ ? a.proj_rows : 0, a.B, g_compute_units);
   // the workgroups of a token wait for one another: they must fit on the device together
   if (long(n_wg) > long(blocks_per_cu) * g_compute_units) return hipErrorLaunchOutOfResources;
-  hipLaunchKernelGGL((route_pair_kernel<WT, SPLIT, NCH, ROWS, PROJ>), dim3(n_wg, a.B), dim3(kBlock), lds, st, a);
+  hipLaunchKernelGGL((route_pair_kernel<WT, SPLIT, NCH, ROWS, PROJ>), dim3(n_wg, a.B), dim3(kBlock), lds, st, a,
+                     a.slots_out ? *a.resident : SlotTable());
   return hipGetLastError();
 }
 

@@ -112,12 +112,12 @@ __device__ __forceinline__ void store_product(const ExpertArgs &a, WT *at, float
 }
 
 // hq[pos, row] for the one token of the batch, stored in the weight dtype for the down kernel.
-// `act` is in execution-position order; rows [first, last) of the expert.  Each lane keeps its NCH chunks of s_l in registers; a wavefront owns
+// slot is that of the expert at execution position pos; rows [first, last) of the expert.  Each lane keeps its NCH chunks of s_l in registers; a wavefront owns
 // `rpw` consecutive rows and keeps the 2*NCH 16-byte loads of the next row in flight while it reduces the
 // current one (two rows: no faster, a compute unit has as many requests on their way as it can).  NORM: s_l is formed here from
 // a.r (LDS s_lds, red), else read from a.s.
 template <typename WT, int NCH, bool NORM>
-__device__ __forceinline__ void gateup_b1_body(const ExpertArgs &a, const ActiveList &act, int pos, int block, int rpw,
+__device__ __forceinline__ void gateup_b1_body(const ExpertArgs &a, int slot, int pos, int block, int rpw,
                                                int first, int last, float *s_lds, double *red) {
   using R = Packed<WT>;
   constexpr int VN = R::N;
@@ -126,7 +126,7 @@ __device__ __forceinline__ void gateup_b1_body(const ExpertArgs &a, const Active
   const int row0 = first + (block * kB1Waves + wave) * rpw;
   if (!NORM && row0 >= last) return;
   const int row_end = min(row0 + rpw, last);
-  const WT *wg = reinterpret_cast<const WT *>(a.pool + size_t(act.slot[pos]) * a.slot_bytes);
+  const WT *wg = reinterpret_cast<const WT *>(a.pool + size_t(slot) * a.slot_bytes);
   const WT *wu = wg + size_t(I) * H;
   WT *hq = reinterpret_cast<WT *>(a.h) + size_t(pos) * I;
   InputNorm<WT, (NCH + 3) / 4> norm;
@@ -170,14 +170,14 @@ __device__ __forceinline__ void gateup_b1_body(const ExpertArgs &a, const Active
 // Small launches (all wavefronts resident at once): a wavefront owns two consecutive rows and
 // issues the 4*NCH 16-byte loads of both before it reduces anything.
 template <typename WT, int NCH>
-__device__ __forceinline__ void gateup_b1_pair_body(const ExpertArgs &a, const ActiveList &act, int pos, int block) {
+__device__ __forceinline__ void gateup_b1_pair_body(const ExpertArgs &a, int slot, int pos, int block) {
   using R = Packed<WT>;
   constexpr int VN = R::N;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int H = a.H, I = a.I;
   const int row0 = (block * kB1Waves + wave) * 2;
   if (row0 >= I) return;
-  const WT *wg = reinterpret_cast<const WT *>(a.pool + size_t(act.slot[pos]) * a.slot_bytes);
+  const WT *wg = reinterpret_cast<const WT *>(a.pool + size_t(slot) * a.slot_bytes);
   const WT *wu = wg + size_t(I) * H;
   WT *hq = reinterpret_cast<WT *>(a.h) + size_t(pos) * I;
 

@@ -68,6 +68,11 @@ struct RouteArgs {
   int bf16, spec, from_normalized, tok_tile;
 };
 
+// Where the experts of a layer are, or -1: what the host knows before the layer's routing does.
+struct SlotTable {
+  int16_t slot[kMaxExperts];
+};
+
 // True routing of layer l and the prediction for layer l+1 in one launch (route_pair_kernel).  Logits
 // travel between the workgroups of a token through 8-byte slots that hold all ones until written; the
 // two sets of slots are used by alternate launches, and a launch re-arms the other set.
@@ -92,6 +97,8 @@ struct RoutePairArgs {
   int32_t *true_ids;  float *true_gates;  // [B,k]
   double *true_gates64;                   // [B,k] the same gates unrounded, or null
   int32_t *next_ids;  float *next_gates;  // [B,k] the prediction carried to layer l+1
+  const SlotTable *resident;              // host memory, and
+  int32_t *slots_out;                     // [k]: a batch of one also reports the slots of its true experts; or null
   const int32_t *cmp_ids;                 // [B,k] prediction to score against this routing, or null
   LayerDiag *diag;
   int32_t *user_true_ids;  float *user_true_gates;   // optional copies for the caller
@@ -143,6 +150,8 @@ struct ExpertArgs {
   const float *s;             // [B,H] router input s_l
   const int32_t *exec_ids;    // [B,k]
   const float *exec_gates;    // [B,k]
+  const int32_t *slots;       // a batch of one whose host does not wait for the ids: [k] slots as the routing reported them
+                              // (any of them -1: nothing is done), or null: those of the launch's list
   float *h;                   // [B,k,I] SwiGLU products
   float *y;                   // [B,k,H] un-gated expert outputs
   float *out;                 // [B,H]

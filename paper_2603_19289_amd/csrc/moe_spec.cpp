@@ -190,6 +190,7 @@ struct moe_spec_ctx {
   std::vector<hipEvent_t> ready, done;
   std::vector<char> done_recorded, ready_recorded;
   std::vector<char> ready_pending;              // copies into this pool that the compute stream has not waited for yet
+  std::vector<int> hit_run;                     // steps in a row (2 at most) whose true experts were all in this pool
   std::vector<uint64_t> read_step;              // routing step whose expert kernels last read this pool; 0: none
   uint64_t step_seq = 0;                        // decode layer steps launched (their routing launches)
   uint64_t seen_seq = 0;                        // latest of them whose expert ids the host has seen
@@ -612,6 +613,7 @@ int moe_spec_create(const moe_spec_config *cfg, moe_spec_ctx **out) {
   c->ready_recorded.assign(L, 0);
   c->ready_pending.assign(L, 0);
   c->read_step.assign(L, 0);
+  c->hit_run.assign(L, 0);
 
   auto bail = [&](hipError_t err, const char *what) {
     g_create_error = std::string(what) + ": " + hipGetErrorString(err);
@@ -861,6 +863,13 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       exec_pred && !again && !cfg.profile && c->pending_union.size() <= size_t(S) && !c->ready_pending[layer] &&
       ((fast_b1 && fused_route && route_gateup_b1_supported(H, E, cfg.dtype)) ||
        (use_mfma && (fused_route || est_beside) && route_gateup_mfma_supported(H)));
+  // True experts that are expected to be in their slots, as those of the last two steps were, do not wait for the host
+  // either: the routing reports their slots and the expert launches are queued right behind it; if one of them is absent after
+  // all, they do nothing and the ordinary way is taken.  Only where the launch ends with the true routing: with a prediction
+  // behind it the ids are here before it ends.  Batch 1, 8 of 128 experts of 768 x 2048, a layer step: 28.9 -> 23.2 us.
+  const bool behind_routing = !exec_pred && !do_pred && !again && fused_route && fast_b1 && !cfg.profile && cfg.lookahead != 2 &&
+                              !c->ready_pending[layer] && c->hit_run[layer] >= 2;
+  SlotTable resident;
   // The layer's first routing launch, with or without the experts beside it.
   auto launch_first_routing = [&](RoutePairArgs &ra) {
     if (!beside_routing) return launch_route_pair(ra, cfg.dtype, c->compute);
@@ -912,7 +921,21 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     pa.bf16 = cfg.dtype == MOE_SPEC_BF16;
     pa.from_normalized = cfg.q_from_normalized;
     pa.spin_limit = c->spin_limit;
+    if (behind_routing) {
+      for (int x = 0; x < E; ++x) resident.slot[x] = int16_t(c->pools[layer].where[x]);
+      pa.resident = &resident;
+      pa.slots_out = c->at<int32_t>(c->lay.la_ids);          // scratch of the lookahead, which is off
+    }
     if ((e = launch_first_routing(pa)) != hipSuccess) return c->hip_fail(e, "routing kernel");
+    if (behind_routing) {
+      ExpertArgs ba = xa;
+      ba.exec_gates = pa.true_gates;
+      ba.slots = pa.slots_out;
+      by_pos.n = k;                                          // how many; which, the routing says
+      c->read_step[layer] = c->step_seq;
+      if ((e = launch_gateup_b1(ba, by_pos, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");
+      if ((e = launch_down_combine_b1(ba, by_pos, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "down kernel");
+    }
     c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes;
     if (do_pred) c->st.hbm_bytes_algorithmic += int64_t(E) * H * wbytes + int64_t(batch) * k * H * wbytes;
     if (look2) {
@@ -1155,6 +1178,7 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
       const bool in_order = !do_pred || (wave > 0 && (!prefetching || waves_in_order(int(exec_union.size()), S, c->expert_bytes)));
       int rc = c->request(layer, req, &act, &copies, in_order);
       if (rc) return rc;
+      if (!exec_pred && wave == 0) c->hit_run[layer] = copies ? 0 : std::min(2, c->hit_run[layer] + 1);
     }
     if (c->ready_pending[layer]) {
       TimedSpan *sp_stall = c->open_span(2, c->compute);
@@ -1165,7 +1189,9 @@ int layer_step_impl(moe_spec_ctx *c, int layer, const void *r_dev, int batch, vo
     c->st.cache_waves += 1;
     TimedSpan *sp_exec = c->open_span(0, c->compute);
     TimedSpan *sp_gu = c->open_span(3, c->compute);
-    if (fast_b1) {
+    if (behind_routing && copies == 0) {
+      // launched behind the routing
+    } else if (fast_b1) {
       if (!beside_routing) {
         slots_by_position(exec_ids_host);
         if ((e = launch_gateup_b1(xa, by_pos, cfg.dtype, c->compute)) != hipSuccess) return c->hip_fail(e, "gate/up kernel");
@@ -1397,6 +1423,7 @@ int moe_spec_prefill_layer_step(moe_spec_ctx *c, int layer, const void *r_dev, i
   std::fill(p.slot_stamp.begin(), p.slot_stamp.end(), -1);
   std::fill(p.where.begin(), p.where.end(), -1);
   p.clock = 0;
+  c->hit_run[layer] = 0;
   if (c->ready_recorded[layer]) {
     for (hipStream_t q : c->copy_aux)
       if ((e = hipStreamWaitEvent(q, c->ready[layer], 0)) != hipSuccess) return c->hip_fail(e, "copy queue wait");
@@ -1659,6 +1686,7 @@ int moe_spec_reset(moe_spec_ctx *c) {
   c->step_begun = false;
   c->next_layer = 0;
   c->pending_union.clear();
+  std::fill(c->hit_run.begin(), c->hit_run.end(), 0);
   return MOE_SPEC_OK;
 }
 

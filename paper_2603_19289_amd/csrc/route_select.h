@@ -170,7 +170,8 @@ __device__ __forceinline__ double select_gates(int k, const SelectShared &sel, i
 }
 
 // The true routing of token b, written out by the workgroup that reports it.
-__device__ __forceinline__ void report_true(const RoutePairArgs &a, int b, SelectShared &sel, double denom, int tid) {
+__device__ __forceinline__ void report_true(const RoutePairArgs &a, int b, SelectShared &sel, double denom, int tid,
+                                            const SlotTable *resident) {
   const int k = a.k;
   if (tid < k) {
     const int id = sel.top_i[tid];
@@ -179,6 +180,7 @@ __device__ __forceinline__ void report_true(const RoutePairArgs &a, int b, Selec
     const size_t o = size_t(b) * k + tid;
     if (a.mb_true) a.mb_true->ids[o] = id;     // the host waits for every word it armed
     a.true_ids[o] = id;
+    if (resident && a.slots_out) a.slots_out[o] = resident->slot[id];
     a.true_gates[o] = g;
     if (a.true_gates64) a.true_gates64[o] = g64;
     if (a.user_true_ids) a.user_true_ids[o] = id;
