@@ -309,22 +309,22 @@ def test_estimator_projection_beside_the_routing(dtype, B, hidden, experts, m):
                        estimator=est, estimator_layers=[0, 1, 2])
 
 
+@pytest.mark.parametrize("mode", ["on_demand", "prefetch_hint"])
 @pytest.mark.parametrize("dtype,hidden,inter,experts,top_k,slots", [
     ("bf16", 8, 8, 1, 1, 1),              # one expert, smaller than a wavefront's load
     ("bf16", 264, 1024, 5, 2, 3),         # down rows of four batches of a wavefront; every step in its slots or not, by chance
     ("bf16", 1032, 768, 4, 4, 4),         # of twelve, by two wavefronts
     ("bf16", 2056, 200, 7, 3, 6),         # more chunks than pairs of rows take; ragged rows of both products
     ("f32", 520, 72, 6, 2, 5), ("f32", 2048, 264, 3, 2, 3), ("bf16", 136, 72, 40, 16, 40)])
-def test_experts_queued_behind_the_routing(dtype, hidden, inter, experts, top_k, slots):
-    """Loading on demand, batch one, where nothing is predicted (the last layer): once it found its experts in their slots for
-    two steps, they are launched behind the routing and find their slots on the device; in steps where one is absent after
-    all, nothing is executed twice or missed."""
+def test_experts_queued_behind_the_routing(mode, dtype, hidden, inter, experts, top_k, slots):
+    """True experts, batch one: once a layer found them in their slots for two steps they are launched behind the routing and
+    find their slots on the device; in steps where one is absent after all, nothing is executed twice or missed."""
     wl = small_workload(name="behind routing", n_layers=2, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype=dtype,
                         batch=1, tokens=30, slots=slots, seed=67)
-    counts = kernels_launched(lambda: run_teacher_forced(wl, O.MODE_ON_DEMAND), {})
+    counts = kernels_launched(lambda: run_teacher_forced(wl, MODES[mode]), {})
     queued = sum(n for name, n in counts.items() if name.startswith("down_combine_b1_kernel") and name.endswith("true>"))
     waited = sum(n for name, n in counts.items() if name.startswith("down_combine_b1_kernel") and name.endswith("false>"))
-    assert queued > 0 and waited >= 32 and queued + waited >= 60, counts      # layer 0 and the first two steps of layer 1 wait
+    assert queued > 0 and waited >= 4 and queued + waited >= 60, counts       # the first two steps of a layer wait
 
 
 @pytest.mark.parametrize("dtype,B,hidden,experts,m,n,inter,kernel", [
