@@ -103,9 +103,30 @@ def prompt_launches(P, max_batch, experts, top_k, hidden, inter, slots, bf16, dm
     return launches if like_decode else 0, groups - 1 + last + pieces if bf16 and dma and by_expert else groups
 
 
+def without_void(dispatches):
+    """The dispatches without the batch-one expert launches that were queued behind a routing launch (last template argument
+    true) and found an expert absent: they end at once, and the same layer's experts are launched again before the next
+    routing.  No leg counts them."""
+    kinds = ("gateup_b1", "down_combine_b1")
+    out, queued = [], []                                 # queued: places in out, since the last routing launch
+    for name, value in dispatches:
+        kind = next((k for k in kinds if k in name and "route_" not in name), None)
+        if "route_" in name:
+            queued = []
+        elif kind and name.endswith("true>") or kind and ", true>(" in name:
+            queued.append((len(out), kind))
+        elif kind:
+            for at, k in queued:
+                if k == kind:
+                    out[at] = None
+        out.append((name, value))
+    return [d for d in out if d]
+
+
 def attribute(dispatches, legs):
     """dispatches: (kernel name, value) in launch order.  Returns {(leg name, reported kernel): values}."""
     out = {}
+    dispatches = without_void(dispatches)
     for symbol in COUNTED:
         seq = [d for d in dispatches if named(d[0], symbol)]
         for leg_name, part in cut_by_legs(seq, legs, symbol).items():

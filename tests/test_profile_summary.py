@@ -98,3 +98,13 @@ int main() {
     want = [tuple(map(int, line.split())) for line in done.stdout.splitlines()]
     got = [tuple(map(int, P.prompt_launches(*c[:7], c[7] == 1, c[8] == 1))) for c in cases]
     assert got == want and any(w[0] for w in want) and not all(w[0] for w in want)
+
+
+def test_launches_queued_in_vain_are_not_counted():
+    gateup, down = GATEUP.replace("4>", "4, {}>"), DOWN[:-1] + ", {}>"
+    step = [(ROUTE, 6.0)]
+    queued, again = [(gateup.format("true"), 10.0), (down.format("true"), 6.0)], [(gateup.format("false"), 10.5), (down.format("false"), 6.5)]
+    void = [(n, 1.5) for n, _ in queued]
+    assert P.without_void(step + queued + step + void + again + step + again) == step + queued + step + again + step + again
+    signature = [(n + "(moe_spec::ExpertArgs)", v) for n, v in step + void + again]
+    assert P.without_void(signature) == [signature[0]] + signature[3:]
