@@ -144,7 +144,7 @@ inline int down_ksplit(int K, int token_tiles, int rows, int experts, int positi
 
 // How a request's n blocks are dealt to the two DMA queues: the second one takes `second` whole blocks and the first `cut`
 // bytes of one more (0: none).  A half each, in turn, as long as the queues are equally fast.  They are not where something
-// else uses the engine behind one of them: the driver clears freed device memory with it, some 16 GB/s, and meanwhile a 9.4
+// else uses the engine behind one of them: the GPU driver clears freed device memory with it, some 16 GB/s, and meanwhile a 9.4
 // MB block takes 300 us on the second queue instead of 172, both queues still fill the link together, and the first one
 // waits for the second at the end of every request (47 ms instead of 37 for 32 layer steps of 128 experts of 768 x 2048 with
 // 16 slots, for 1.3 s after an engine of 22 GB was given back).  So the second queue's share follows how much later than the

@@ -11,6 +11,8 @@
 // step needs no event between those kernels and the copies (an event recorded behind a kernel holds the next
 // one up by 5.6 us).  Where the host has not seen that (further cache waves of a step), done(l) is recorded
 // when a copy needs it and every copy into pool l waits for it: a slot is never overwritten while it is read.
+// Experts of a batch of one that are expected in their slots are queued behind the routing before the host has its ids
+// (behind_routing); if one is absent they read no slot.
 #include "../../include/moe_spec.h"
 
 #include <hip/hip_runtime.h>

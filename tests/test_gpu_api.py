@@ -289,6 +289,32 @@ def test_non_finite_inputs_keep_expert_ids_in_range(dtype, B):
             eng.close()
 
 
+@pytest.mark.parametrize("batch", [1, 3])
+def test_a_wait_of_the_estimator_that_runs_out_is_reported(batch):
+    # as below for the launch that carries the estimator on (three waits in a row): with one poll allowed every kernel still
+    # runs to its end and ids stay in range; whether a waiter gave up is up to timing, and if one did, a call says so
+    wl = small_workload(n_layers=3, hidden=512, n_experts=24, top_k=4, inter=64, dtype="bf16", slots=24, tokens=3, batch=batch, seed=79)
+    res, ex, _ = build(wl, "random")
+    x0, eps = W.make_inputs(wl)
+    eng = _engine(wl, M.MODE_SPECULATIVE, res, ex, wait_spin_limit=1, estimator=W.make_estimator(wl, m=2, n=2))
+    try:
+        try:
+            for t in range(wl.tokens):
+                eng.begin_token()
+                for l in range(wl.n_layers):
+                    _, ids = eng.layer_step(l, torch.from_numpy(x0[t] + 0.3 * eps[t, l]).cuda(), want_ids=True)
+                    torch.cuda.synchronize()
+                    got = ids["exec_ids"].cpu().numpy()
+                    assert ((got >= 0) & (got < wl.n_experts)).all()
+            eng.stats()
+        except M.MoeSpecError as err:
+            assert err.code == M.EHIP and "bounded wait" in str(err)
+        eng.reset()
+        assert eng.stats()["tokens"] == 0
+    finally:
+        eng.close()
+
+
 def test_a_wait_that_runs_out_is_reported_and_reset_recovers():
     # The fused kernels wait, boundedly, for results of other workgroups of the same launch.  With the bound
     # forced down to one poll from the host, waiters give up early: every kernel still runs to its end, ids

@@ -363,7 +363,7 @@ def test_two_layer_lookahead(mode, dtype, B, S, engine):
 @pytest.mark.parametrize("batch", [1, 3])
 def test_logits_that_agree_in_their_high_words(n_experts, batch):
     """Candidates are ranked by the upper 32 bits of their logits first.  Here pairs and triples of experts share these, a
-    triple in which two logits are equal among them, inside the selected k and across its end: ids and gates are the checker's."""
+    triple in which two logits are equal among them, inside the selected k and across its end: ids and gates are the oracle's."""
     wl = small_workload(name="near ties", n_layers=4, hidden=264, n_experts=n_experts, top_k=min(n_experts, 7), inter=8, dtype="f32",
                         batch=batch, tokens=3, slots=n_experts, seed=11)
     res, ex, _ = build(wl, "random")
