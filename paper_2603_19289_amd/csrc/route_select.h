@@ -1,6 +1,8 @@
 // Selection of experts from logits that arrive in hand-over slots, and the reports of a routing launch, as device functions:
 // for the launches that route a layer (fused_kernels.hip) and for the estimator's (estimator_kernels.hip).
 #pragma once
+#include <cstddef>
+
 #include "device_utils.h"
 #include "kernels.h"
 #include "launch_rules.h"
@@ -24,7 +26,7 @@ static_assert(kWaves == kRouteWaves, "the launch rules count wavefronts");
 
 struct SelectShared {
   unsigned long long keys[kMaxExperts];   // the token's logits as order-preserving integers
-  uint32_t high[kMaxExperts + 64];        // their high words, in parts (select_ids)
+  alignas(16) uint32_t high[kMaxExperts + 64];   // their high words, in parts (select_ids)
   int cnt[kWaves][kMaxExperts];           // partial rank counts of the four wavefronts, where high words are not enough
   unsigned int filled[kMaxTopK];          // candidates that count as this rank by their high words
   double top_z[kMaxTopK];
@@ -32,6 +34,7 @@ struct SelectShared {
   int top_i[kMaxTopK];
   int hits;
 };
+static_assert(alignof(SelectShared) % 16 == 0 && offsetof(SelectShared, high) % 16 == 0, "high is read 16 bytes at a time");
 
 struct RouteShared {
   double red[2][kWaves];                  // one per norm
