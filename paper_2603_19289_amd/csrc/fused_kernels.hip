@@ -507,7 +507,6 @@ __device__ __forceinline__ void route_lean_body(const RoutePairArgs &a, const in
 // missed: two router rows per workgroup.  8 of 128 experts of 768 x 2048, a layer step, 1 / 2 / 4 rows per workgroup:
 // 23.9 / 22.3 / 22.4 us, with the dot instructions of row_sums 24.5 / 21.2 / 21.6 (128 / 64 / 32 workgroups; 4 of 32
 // of 2880 x 2880 and 2 of 8 of 14336 x 4096 within 1 % of one another).
-constexpr int kJointSplit = 2, kJointRows = kWaves / kJointSplit;   // wavefronts of a router row, rows of a workgroup
 template <typename WT, int NCH>
 __global__ __launch_bounds__(kBlock, 2)
 void route_gateup_b1_kernel(const RoutePairArgs ra, const ExpertArgs a, const ActiveList act, const int n_route,
@@ -666,7 +665,7 @@ hipError_t route_gateup_b1_per_cu(int H, int *n) {
 template <typename WT, int NCH>
 hipError_t launch_route_gateup_b1_n(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, hipStream_t st) {
   const size_t lds = size_t(ra.H) * sizeof(double);
-  const int n_route = (ra.E + kJointRows - 1) / kJointRows;
+  const int n_route = joint_routing_workgroups(ra.E);
   int blocks_per_cu = 0;
   if (hipError_t e = route_gateup_b1_per_cu<WT, NCH>(ra.H, &blocks_per_cu); e != hipSuccess) return e;
   // the routing workgroups wait for one another: they must fit on the device together
@@ -734,13 +733,12 @@ hipError_t launch_route_gateup_mfma_t(const RoutePairArgs &ra, const ExpertArgs 
 }  // namespace
 
 // Rows of up to 8 chunks per lane: beyond, the LDS that the routing needs would leave the gate/up workgroups too few
-// places.  The routing workgroups, one per expert, have to fit on the device together, which a partition of it may not
-// have room for where the routing by itself, with fewer registers, has (float32 rows of 7 or 8 chunks).
+// places.  The routing workgroups have to fit on the device together, which a small partition of it may not have room for.
 bool route_gateup_b1_supported(int H, int E, int dtype) {
   int per_cu = 0;
   if (H > kWave * 8 * (dtype == 1 ? 8 : 4)) return false;
   const hipError_t e = dtype == 1 ? route_gateup_b1_per_cu_t<uint16_t>(H, &per_cu) : route_gateup_b1_per_cu_t<float>(H, &per_cu);
-  return e == hipSuccess && long(E) <= long(per_cu) * g_compute_units;
+  return e == hipSuccess && long(joint_routing_workgroups(E)) <= long(per_cu) * g_compute_units;
 }
 
 hipError_t launch_route_gateup_b1(const RoutePairArgs &ra, const ExpertArgs &a, const ActiveList &act, int dtype,

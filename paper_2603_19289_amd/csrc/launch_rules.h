@@ -21,6 +21,13 @@ inline GateupSplit gateup_b1_split(int nch, int I, int n) {
   return {rpw, (I + kB1Waves * rpw - 1) / (kB1Waves * rpw)};
 }
 
+// Workgroups that route in the joint batch-one launch: kJointSplit wavefronts share a router row.
+constexpr int kJointSplit = 2;
+inline int joint_routing_workgroups(int E) {
+  constexpr int rows = kRouteWaves / kJointSplit;
+  return (E + rows - 1) / rows;
+}
+
 // How the gate/up rows are dealt to wavefronts beside the routing.  The routing is a chain of dependent memory accesses
 // (9 us alone) and every one of them queues behind the weight loads in flight, above all those of its own compute unit.  Up
 // to 64 MB of weights one gate/up workgroup goes on each compute unit that does not route: 128 experts of 768 x 2048 (50 MB,

@@ -46,10 +46,12 @@ def test_joint_launch_is_taken_only_where_its_routing_workgroups_fit(tmp_path):
 
     # (hidden, experts, dtype 1 = bf16): the whole device takes every number of experts, at the sizes the kernel is built for
     assert ask(256, 2, (2048, 256, 1), (4096, 256, 1), (4104, 8, 1), (2048, 256, 0), (2056, 8, 0)) == "11010"
-    # 64 and 32 units: as many experts as workgroups fit, and not one more
-    assert ask(64, 2, (2048, 128, 1), (2048, 129, 1), (2048, 128, 0), (2048, 192, 0)) == "1010"
-    assert ask(32, 2, (2048, 64, 1), (512, 65, 1), (1024, 64, 0), (2048, 96, 0)) == "1010"
-    assert ask(32, 3, (1024, 96, 0), (1024, 97, 0)) == "10"
+    # 64 and 32 units: as many experts as two per workgroup that fits, and not one more
+    assert ask(64, 2, (2048, 256, 1), (2048, 256, 0)) == "11"
+    assert ask(64, 1, (2048, 128, 1), (2048, 129, 1), (1024, 127, 0), (2048, 192, 0)) == "1010"
+    assert ask(32, 2, (2048, 128, 1), (512, 129, 1), (1024, 128, 0), (2048, 192, 0)) == "1010"
+    assert ask(32, 3, (1024, 192, 0), (1024, 193, 0)) == "10"
+
 
 
 ROUTING = r"""
