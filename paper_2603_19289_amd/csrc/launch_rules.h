@@ -56,15 +56,16 @@ inline GateupSplit beside_routing_split(int nch, int I, int H, int n, std::size_
 // workgroups.  They come free after about 6 us in which another workgroup streams 130 KB.  Taken where all of this holds: one
 // gate/up workgroup per compute unit beside the routing (up to 64 MB of weights, see above); routing on half of the device or
 // more; 320 KB and more for each of the other workgroups (the routing, 12 us, is over well before them then); rows of up to 4
-// KB.  Microseconds per pass without / with: 8 of 128 experts of 768 x 2048 (393 KB each) 611 / 578, 8 of 200 of 480 x 2048
-// (493) 334 / 299, 8 of 128 of 1600 x 1024 (410) 367 / 324; not taken: 8 of 64 of 960 x 2048 (328) 323 / 315, 8 of 128 of 640
-// x 2880 (461) 370 / 375, 4 of 100 of 800 x 3000 (246) 578 / 614, 4 of 32 of 768 x 4096 (225) 565 / 619, 6 of 60 of 1200 x
-// 1544 (227) 583 / 583, 8 of 128 of 520 x 1024 (133) 475 / 478.  The limits are those of the shapes that gained: the first of
-// them stands on two of them (half of 256 units, 4 KB), and none was moved as far as it would go.  The limit on routing
-// workgroups leaves out a gain of 2.5 % (64 experts), the one on rows rests on a loss of 1.3 % (2880 columns: the vector that
-// these workgroups form a second time is longer) and on shapes that the bytes per workgroup exclude as well.
-// All of this with one router row per routing workgroup.  With two of them it takes 255 experts on a whole device to get here
-// (8 of 256 of 480 x 2048 366 / 366, and 383 with one row per workgroup and the rows shared); a partition gets here with fewer.
+// KB.  Two router rows per routing workgroup: on a whole device that is 255 and 256 experts, on a partition of it fewer.
+// Microseconds per layer step, 8 of 256 experts, without / with: 1024 columns, 40 MB 27.3 / 24.7, 48 MB 30.3 / 26.4, 63 MB
+// 37.5 / 32.8; 2048 columns, 40 MB 24.6 / 24.6 (again: 23.9 / 24.4), 44 MB 25.5 / 24.9, 48 MB 26.4 / 25.7, 63 MB 33.2 / 31.4;
+// 1536 columns, 47 MB 29.2 / 27.4; 16 of 256 of 704 x 1016 29.2 / 26.7; 8 of 255 of 704 x 2048 25.1 / 24.8.  Not taken: fewer
+// bytes, 1024 columns 36 MB 26.0 / 23.7 and 2048 columns 36 MB 24.1 / 23.8; fewer routing workgroups, 128 experts of 2048
+// columns 40 MB 21.5 / 22.1, 48 MB 22.6 / 23.1, 63 MB 29.2 / 28.9 and of 1024 columns 48 MB 24.2 / 24.4, 63 MB 31.7 / 30.2,
+// 200 experts of 2048 columns 44 MB 24.4 / 24.7, 63 MB 31.2 / 31.2 and of 1024 columns 48 MB 28.2 / 26.8.  So the limit on
+// routing workgroups rests on rows of 4 KB, and leaves out gains of up to 8 % at rows of 2 KB; the one on bytes per workgroup
+// rests on rows of 4 KB as well.  The limit on rows was drawn with one router row per workgroup (8 of 128 of 640 x 2880 370
+// without, 375 us a pass with).
 struct SharedSplit {
   GateupSplit stream;                          // of rows [0, first_tail)
   int first_tail, tail_rpw, tail_blocks;       // tail_blocks 0: none

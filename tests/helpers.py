@@ -27,6 +27,11 @@ L2_TOL = {"f32": 1e-5, "bf16": 2e-2}
 ELEM_TOL = {"f32": 1e-5, "bf16": 1e-2}
 
 
+# (hidden, inter, experts, top_k), bf16, batch one: layers whose routing workgroups take gate/up rows once they have routed,
+# on a whole device (the launch rules are asked whether that is so)
+SHARED_ROWS = [(1016, 704, 256, 16), (2048, 360, 255, 16), (504, 1416, 256, 16)]
+
+
 def elem_tol(dtype, terms=None):
     if dtype != "bf16" or not terms:
         return ELEM_TOL[dtype]

@@ -3,6 +3,8 @@ takes and over the compute-unit counts of a whole device and of its partitions."
 import os
 import subprocess
 
+from tests.helpers import SHARED_ROWS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -22,11 +24,12 @@ def test_gate_up_rows_beside_the_routing_are_dealt_whatever_the_routing_takes(tm
     # left with more than its share of a quarter of the device, also where the routing takes every place
     sweep(tmp_path, r"""
   for (int cus : {32, 64, 128, 256}) for (int per_cu : {1, 2, 4, 8}) for (int E = 1; E <= 256; ++E) {
-    if (long(E) > long(per_cu) * cus) continue;               // refused by the launcher
+    const int n_route = joint_routing_workgroups(E);
+    if (long(n_route) > long(per_cu) * cus) continue;         // refused by the launcher
     for (int H : {8, 512, 1024, 2048, 2880, 4096}) for (int I : {8, 768, 2880, 14336, 32768}) for (int k : {1, 2, 8, 16}) {
       for (int wbytes : {2, 4}) {
         const int nch = (H + 64 * (16 / wbytes) - 1) / (64 * (16 / wbytes));
-        const GateupSplit s = beside_routing_split(nch, I, H, k, wbytes, E, per_cu, cus);
+        const GateupSplit s = beside_routing_split(nch, I, H, k, wbytes, n_route, per_cu, cus);
         const long wgs = long(s.blocks) * k, share = (long(I) * k + cus - 1) / cus;   // rows per wavefront of cus / 4 workgroups
         const bool ok = s.rpw >= 1 && long(s.blocks) * kB1Waves * s.rpw >= I && long(s.blocks - 1) * kB1Waves * s.rpw < I &&
                         wgs >= 1 && s.rpw <= share;
@@ -74,23 +77,27 @@ def test_prefill_tail_is_split_only_where_copies_are_the_bottleneck(tmp_path):
 
 def test_rows_shared_with_the_routing_workgroups_are_dealt_once(tmp_path):
     # stream and tail together hold every row of an expert exactly once, no workgroup starts past its rows, and the first
-    # routing workgroup is left out
+    # routing workgroup is left out; the whole device and its partitions get there
     sweep(tmp_path, r"""
-  int shared = 0;
-  for (int cus : {32, 64, 128, 256}) for (int per_cu : {1, 2, 4}) for (int E = 1; E <= 256; ++E) {
-    if (long(E) > long(per_cu) * cus) continue;
-    for (int H : {8, 512, 1024, 2048, 2880}) for (int I : {8, 328, 480, 768, 1600, 14336}) for (int k : {1, 2, 8, 16}) for (int wbytes : {2, 4}) {
-      const int nch = (H + 64 * (16 / wbytes) - 1) / (64 * (16 / wbytes));
-      const GateupSplit base = beside_routing_split(nch, I, H, k, wbytes, E, per_cu, cus);
-      const SharedSplit s = share_with_routing(base, I, H, k, wbytes, E, cus);
-      const long stream = long(s.stream.blocks) * kB1Waves * s.stream.rpw;
-      const bool ok = s.stream.rpw >= 1 && stream >= s.first_tail && stream - kB1Waves * s.stream.rpw < s.first_tail &&
-                      s.first_tail + long(s.tail_blocks) * kB1Waves * s.tail_rpw == I && s.tail_blocks * k <= E - 1 + (s.tail_blocks == 0);
-      shared += s.tail_blocks > 0;
-      if (!ok && ++bad <= 20) std::printf("cus %d E %d H %d I %d k %d wbytes %d\n", cus, E, H, I, k, wbytes);
+  for (int cus : {32, 64, 128, 256}) {
+    int shared = 0;
+    for (int per_cu : {1, 2, 4}) for (int E = 1; E <= 256; ++E) {
+      const int n_route = joint_routing_workgroups(E);
+      if (2 * n_route < E || 2 * n_route > E + 1) ++bad;      // two router rows each
+      if (long(n_route) > long(per_cu) * cus) continue;
+      for (int H : {8, 512, 1016, 1024, 2048, 2880}) for (int I : {8, 328, 480, 704, 768, 1600, 14336}) for (int k : {1, 2, 8, 16}) for (int wbytes : {2, 4}) {
+        const int nch = (H + 64 * (16 / wbytes) - 1) / (64 * (16 / wbytes));
+        const GateupSplit base = beside_routing_split(nch, I, H, k, wbytes, n_route, per_cu, cus);
+        const SharedSplit s = share_with_routing(base, I, H, k, wbytes, n_route, cus);
+        const long stream = long(s.stream.blocks) * kB1Waves * s.stream.rpw;
+        const bool ok = s.stream.rpw >= 1 && stream >= s.first_tail && stream - kB1Waves * s.stream.rpw < s.first_tail &&
+                        s.first_tail + long(s.tail_blocks) * kB1Waves * s.tail_rpw == I && s.tail_blocks * k <= n_route - 1 + (s.tail_blocks == 0);
+        shared += s.tail_blocks > 0;
+        if (!ok && ++bad <= 20) std::printf("cus %d E %d H %d I %d k %d wbytes %d\n", cus, E, H, I, k, wbytes);
+      }
     }
-  }
-  if (shared == 0) ++bad;""")
+    if (shared == 0) { ++bad; std::printf("cus %d: never\n", cus); }
+  }""")
 
 
 def test_cache_waves_stay_behind_a_prefetch_where_it_would_slow_them_down(tmp_path):
@@ -116,13 +123,14 @@ def test_short_prompts_are_routed_by_the_launches_of_a_decode_step(tmp_path):
 
 
 def test_routing_workgroups_take_rows_at_the_sizes_of_the_gpu_test(tmp_path):
-    # 16 of 200 experts of 344 x 1024 and 16 of 256 of 352 x 1016, bf16, on the whole device
+    # on the whole device, with the number of routing workgroups that the launch has
+    sizes = ", ".join("{%d, %d, %d, %d}" % s for s in SHARED_ROWS)
     sweep(tmp_path, r"""
-  const int sizes[][3] = {{1024, 344, 200}, {1016, 352, 256}};
+  const int sizes[][4] = {""" + sizes + r"""};
   for (const auto &v : sizes) for (int per_cu : {2, 3, 4}) {
-    const int nch = (v[0] + 511) / 512;
-    const SharedSplit s = share_with_routing(beside_routing_split(nch, v[1], v[0], 16, 2, v[2], per_cu, 256), v[1], v[0], 16, 2, v[2], 256);
-    if (s.tail_blocks < 1) { ++bad; std::printf("%d %d %d\n", v[0], v[1], v[2]); }
+    const int nch = (v[0] + 511) / 512, n_route = joint_routing_workgroups(v[2]);
+    const SharedSplit s = share_with_routing(beside_routing_split(nch, v[1], v[0], v[3], 2, n_route, per_cu, 256), v[1], v[0], v[3], 2, n_route, 256);
+    if (s.tail_blocks < 1) { ++bad; std::printf("%d %d %d %d\n", v[0], v[1], v[2], v[3]); }
   }""")
 
 
