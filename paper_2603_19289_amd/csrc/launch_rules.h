@@ -171,6 +171,15 @@ inline QueueDeal deal_to_queues(int n, std::size_t block, double share) {
   if (deal.cut > block - block / 8) { deal.cut = 0; deal.second += 1; }
   return deal;
 }
+// Of block `index` of a request's n: the bytes, from its first on, that the second queue takes (the first queue: the rest).
+// The cut block is the last one, the second queue's whole ones are spread evenly over the others.
+inline std::size_t second_queue_bytes(int n, std::size_t block, double share, int index) {
+  if (share == kEvenShare) return index % 2 ? block : 0;
+  const QueueDeal deal = deal_to_queues(n, block, share);
+  const int whole = n - (deal.cut > 0);
+  if (index >= whole) return deal.cut;
+  return (index + 1) * deal.second / whole > index * deal.second / whole ? block : 0;
+}
 // taken: the part of the request's bytes that the second queue had; late_us: how much later than the first it was done.
 // What is left when one queue is done travels at 30 to 55 GB/s, and some two thirds of it belong to the other queue.  Half of
 // the way there each time: a request's blocks are few and their times scatter.  first_sign: the even share was indicated to

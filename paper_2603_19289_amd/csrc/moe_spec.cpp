@@ -176,6 +176,7 @@ struct moe_spec_ctx {
   std::vector<hipStream_t> copy_aux;             // owned; further DMA queues of copy_engine 2
   std::vector<hipEvent_t> aux_done;
   double second_share = kEvenShare;              // copy_engine 2: the second queue's share of a request's bytes
+  bool share_fixed = false;                      // by a test: it does not follow the queues
   hipEvent_t queue_end[2] = {nullptr, nullptr};  // when the queues were done with the request that is being measured
   bool measuring = false;
   double measured_share = 0.0, measured_bytes = 0.0;
@@ -321,14 +322,7 @@ struct moe_spec_ctx {
     }
     // whole experts, dealt in turn over the queues (cutting every expert into one part per queue moved no more bytes per
     // second and made the timing erratic), or by their shares, one expert cut
-    std::size_t second = 0;                      // bytes for the second queue
-    if (!copy_aux.empty()) {
-      const QueueDeal deal = deal_to_queues(n, expert_bytes, share);
-      const int whole = n - (deal.cut > 0);
-      if (share == kEvenShare) second = index % 2 ? expert_bytes : 0;
-      else if (index >= whole) second = deal.cut;
-      else second = (index + 1) * deal.second / whole > index * deal.second / whole ? expert_bytes : 0;
-    }
+    const std::size_t second = copy_aux.empty() ? 0 : second_queue_bytes(n, expert_bytes, share, index);
     hipError_t c = hipSuccess;
     if (second > 0) c = hipMemcpyAsync(dst, src, second, hipMemcpyHostToDevice, copy_aux[0]);
     if (c == hipSuccess && second < expert_bytes)
@@ -351,7 +345,7 @@ struct moe_spec_ctx {
   // of such a request), of 8 MB and more (below, what a transfer costs beside its bytes weighs as much).
   void measure_queues(int n) {
     const double bytes = double(n) * double(expert_bytes);
-    if (copy_aux.empty() || measuring || n < 2 || bytes < 8e6) return;
+    if (copy_aux.empty() || share_fixed || measuring || n < 2 || bytes < 8e6) return;
     if (second_share == kEvenShare && !uneven_sign && ++since_measured < 8) return;
     since_measured = 0;
     const QueueDeal deal = deal_to_queues(n, expert_bytes, second_share);
@@ -1662,6 +1656,16 @@ int moe_spec_read_default_vectors(moe_spec_ctx *c, int layer, float *mean_dev, i
     if ((e = hipMemcpy(counts_host, cnt, size_t(E) * 8, hipMemcpyDeviceToHost)) != hipSuccess)
       return c->hip_fail(e, "read counts");
   }
+  return MOE_SPEC_OK;
+}
+
+// For tests, not part of the interface: fixes the second DMA queue's share of a request's bytes, which otherwise follows the
+// queues' speeds.
+int moe_spec_test_queue_share(moe_spec_ctx *c, double share) {
+  if (!c || c->copy_aux.empty() || !(share >= 0.1 && share <= 0.9)) return MOE_SPEC_EINVAL;
+  c->second_share = share;
+  c->share_fixed = true;
+  c->measuring = false;
   return MOE_SPEC_OK;
 }
 

@@ -1,6 +1,8 @@
 """GPU parity: the HIP path, called through the C ABI, against the CPU checker on the same
 seeded inputs.  Expert ids, hit counts and cache traffic must be equal; layer outputs within
 1e-5 (float32 weights) or 2e-2 (bf16 weights) relative L2 error per token row."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -280,6 +282,27 @@ def test_prefetch_hint_refetch_into_a_slot_the_prefetch_just_filled(engine):
     wl = small_workload(name="hint_reuse", n_layers=4, hidden=264, n_experts=12, top_k=3, inter=200,
                         dtype="bf16", batch=1, tokens=6, slots=3, seed=17)
     run_teacher_forced(wl, O.MODE_PREFETCH_HINT, copy_engine=getattr(M, engine))
+
+
+@pytest.mark.parametrize("mode,B,S", [("speculative", 1, 3), ("speculative", 6, 5), ("prefetch_hint", 1, 3), ("on_demand", 4, 7)])
+@pytest.mark.parametrize("share", [0.1, 0.29, 0.61, 0.9])
+def test_uneven_shares_of_the_copy_queues(monkeypatch, share, mode, B, S):
+    # The two DMA queues get uneven shares of every request, one block cut between them (a share that otherwise comes about
+    # only while something else uses an engine): requests of 1 to 7 blocks, slots reused before a kernel read them, cache waves
+    from paper_2603_19289_amd import engine
+    from paper_2603_19289_amd import moe_spec as M
+    plain = engine.engine_for
+
+    def with_share(*args, **kw):
+        eng = plain(*args, **kw)
+        fix = M.lib().moe_spec_test_queue_share
+        fix.argtypes = [ctypes.c_void_p, ctypes.c_double]
+        assert fix(eng.ctx, share) == M.OK and fix(eng.ctx, 0.95) == M.EINVAL
+        return eng
+    monkeypatch.setattr(engine, "engine_for", with_share)
+    wl = small_workload(name="shares", n_layers=4, hidden=264, n_experts=12, top_k=3, inter=200, dtype="bf16", batch=B, tokens=5,
+                        slots=S, seed=17)
+    run_teacher_forced(wl, MODES[mode], copy_engine=M.COPY_DMA2)
 
 
 @pytest.mark.parametrize("layers", [None, [1, 3]], ids=["est_pf", "hybrid_pf"])

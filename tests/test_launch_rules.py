@@ -160,6 +160,22 @@ def test_blocks_are_dealt_to_the_copy_queues_once_and_their_shares_settle(tmp_pa
                       (n < 2 || share == kEvenShare || block < 65536 || std::abs(d.second + double(d.cut) / block - share * n) <= 0.126);
       if (!ok && ++bad <= 20) std::printf("n %d block %zu share %g: %d %zu\n", n, block, share, d.second, d.cut);
     }
+  for (int n = 1; n <= 256; ++n) for (std::size_t block : {std::size_t(3) * 8 * 8 * 2, std::size_t(316800), std::size_t(9437184)})
+    for (int percent = 10; percent <= 90; ++percent) {
+      const double share = percent / 100.0;                  // 0.5: even
+      const QueueDeal d = deal_to_queues(n, block, share);
+      std::size_t second = 0;
+      int cuts = 0;
+      bool ok = true;
+      for (int i = 0; i < n; ++i) {
+        const std::size_t b = second_queue_bytes(n, block, share, i);
+        ok = ok && b <= block && (b == 0 || b == block || (b == d.cut && b % 4096 == 0 && i == n - 1));
+        cuts += b != 0 && b != block;
+        second += b;
+      }
+      ok = ok && second == d.second * block + d.cut && cuts == (d.cut > 0);
+      if (!ok && ++bad <= 20) std::printf("n %d block %zu share %g: %zu of %d + %zu\n", n, block, share, second, d.second, d.cut);
+    }
   const double block = 9437184, link = 57e3;               // bytes per us
   for (double slow : {1.0, 0.55, 0.7}) for (int which : {0, 1}) for (int n : {2, 3, 7, 8, 16}) {
     double share = kEvenShare, late = 0, length = 0;
