@@ -541,6 +541,52 @@ def test_rows_taken_by_the_routing_workgroups_equal_separate_launches(hidden, in
     assert all(torch.equal(a, b) for a, b in zip(*got)) and all(torch.isfinite(a).all() and a.abs().max() > 0 for a in got[0])
 
 
+@pytest.mark.parametrize("mode", ["ON_DEMAND", "PREFETCH_HINT"])
+@pytest.mark.parametrize("engine,dtype,like", [("KERNEL", "bf16", 0.0), ("DMA", "f32", 0.9), ("DMA2", "bf16", 0.9), ("DMA2", "f32", 0.0)])
+def test_experts_queued_behind_the_routing_in_vain(mode, engine, dtype, like):
+    """Batch one, true experts, as many slots as experts of a step, residuals that change every fourth token: after two steps that
+    found their experts in their slots they are queued behind the routing, which wins at the fourth token of a run and is in
+    vain at the first of the next one, where all experts (or, with like residuals, some) are absent.  Then they are copied and
+    launched again: bit for bit the launches that waited for the ids (profile = 1)."""
+    wl = small_workload(name="in_vain", n_layers=2, hidden=264, n_experts=40, top_k=4, inter=200, dtype=dtype, batch=1, tokens=12,
+                        slots=4, seed=29)
+    res, ex, _ = build(wl)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    r = torch.randn((2, wl.n_layers, 1, wl.hidden), generator=g, device="cuda")
+    r[1] = like * r[0] + (1.0 - like * like) ** 0.5 * r[1]
+    runs = []
+    for profile in (0, 1):
+        log = []
+
+        def tokens():
+            log.clear()
+            eng = _engine(wl, getattr(M, "MODE_" + mode), res, ex, profile=profile, copy_engine=getattr(M, "COPY_" + engine))
+            try:
+                for t in range(wl.tokens):
+                    eng.begin_token()
+                    for l in range(wl.n_layers):
+                        out, ids = eng.layer_step(l, r[t // 4 % 2, l], want_ids=True)
+                        log.append((out.clone(), ids["exec_ids"].clone(), ids["exec_gates"].clone()))
+                torch.cuda.synchronize()
+            finally:
+                eng.close()
+        counts = kernels_launched(tokens, {"route_": wl.tokens * wl.n_layers})
+        down = {kind: sum(n for name, n in counts.items() if name.startswith("down_combine_b1_kernel") and name.endswith(kind + ">"))
+                for kind in ("true", "false")}
+        runs.append((log, down))
+    (got, queued), (want, plain) = runs
+    steps = wl.tokens * wl.n_layers
+    assert plain == {"true": 0, "false": steps}
+    if mode == "ON_DEMAND":                       # per layer: three won, two in vain
+        assert queued == {"true": 5 * wl.n_layers, "false": 9 * wl.n_layers}, queued
+    else:                                         # layer 0 so; layer 1's slots also change with the prefetches
+        assert queued["true"] >= 5 and queued["true"] + queued["false"] >= steps + 2, queued
+    for a, b in zip(got, want):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+    before, after = (set(got[i][1].flatten().tolist()) for i in (3 * wl.n_layers, 4 * wl.n_layers))
+    assert before != after and (like == 0.0 or before & after)
+
+
 @pytest.mark.parametrize("hidden,experts,m,batch,kernel", [
     (520, 3, 1, 2, "<1, 4, true>"),          # one token tile, four wavefronts per 16 rows; more projection rows than router rows
     (72, 40, 9, 16, "<1, 1, true>"),         # latent size 8: most wavefronts have no row of it

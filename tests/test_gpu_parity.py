@@ -341,7 +341,7 @@ def test_estimator_projection_beside_the_routing(dtype, B, hidden, experts, m):
     ("f32", 520, 72, 6, 2, 5), ("f32", 2048, 264, 3, 2, 3), ("bf16", 136, 72, 40, 16, 40)])
 def test_experts_queued_behind_the_routing(mode, dtype, hidden, inter, experts, top_k, slots):
     """True experts, batch one: once a layer found them in their slots for two steps they are launched behind the routing and
-    find their slots on the device; in steps where one is absent after all, nothing is executed twice or missed."""
+    find their slots on the device (launches in vain: test_experts_queued_behind_the_routing_in_vain)."""
     wl = small_workload(name="behind routing", n_layers=2, hidden=hidden, n_experts=experts, top_k=top_k, inter=inter, dtype=dtype,
                         batch=1, tokens=30, slots=slots, seed=67)
     counts = kernels_launched(lambda: run_teacher_forced(wl, MODES[mode]), {})
