@@ -177,7 +177,10 @@ def test_blocks_are_dealt_to_the_copy_queues_once_and_their_shares_settle(tmp_pa
       if (!ok && ++bad <= 20) std::printf("n %d block %zu share %g: %zu of %d + %zu\n", n, block, share, second, d.second, d.cut);
     }
   const double block = 9437184, link = 57e3;               // bytes per us
-  for (double slow : {1.0, 0.55, 0.7}) for (int which : {0, 1}) for (int n : {2, 3, 7, 8, 16}) {
+  // lead: the second queue begins a request earlier, as it does where copies never pause (only the first waits at a request's
+  // end): being done earlier then says nothing about its speed; a slow first queue cannot be told from that and is left alone
+  for (double slow : {1.0, 0.55, 0.7}) for (int which : {0, 1}) for (int n : {2, 3, 7, 8, 16}) for (double lead : {0.0, 150.0, 600.0, 1200.0}) {
+    if (slow != 1.0 && which == 1 && lead > 0.0) continue;   // a queue that lags does not lead
     double share = kEvenShare, late = 0, length = 0;
     bool sign = false;
     for (int step = 0; step < 60; ++step) {
@@ -185,19 +188,24 @@ def test_blocks_are_dealt_to_the_copy_queues_once_and_their_shares_settle(tmp_pa
       const QueueDeal d = deal_to_queues(n, std::size_t(block), share);
       double left[2] = {n * block - (d.second * block + d.cut), d.second * block + d.cut};
       const double taken = left[1] / (n * block), own[2] = {55e3 * (which == 0 ? factor : 1.0), 55e3 * (which == 1 ? factor : 1.0)};
-      double at[2] = {0, 0}, t = 0;                          // both: the link shared by speed; one: its own speed
+      double at[2] = {0, 0}, t = -lead;                      // both: the link shared by speed; one: its own speed
       while (left[0] > 1 || left[1] > 1) {
-        const bool both = left[0] > 1 && left[1] > 1;
-        double v[2], go = 1e30;
-        for (int q = 0; q < 2; ++q) v[q] = both ? std::min(own[q], link * own[q] / (own[0] + own[1])) : own[q];
-        for (int q = 0; q < 2; ++q) if (left[q] > 1) go = std::min(go, left[q] / v[q]);
+        const bool runs[2] = {left[0] > 1 && t >= 0, left[1] > 1};
+        double v[2], go = t < 0 ? -t : 1e30;
+        for (int q = 0; q < 2; ++q) v[q] = runs[0] && runs[1] ? std::min(own[q], link * own[q] / (own[0] + own[1])) : own[q];
+        for (int q = 0; q < 2; ++q) if (runs[q]) go = std::min(go, left[q] / v[q]);
         t += go;
-        for (int q = 0; q < 2; ++q) if (left[q] > 1) { left[q] -= v[q] * go; if (left[q] <= 1) at[q] = t; }
+        for (int q = 0; q < 2; ++q) if (runs[q]) { left[q] -= v[q] * go; if (left[q] <= 1) at[q] = t; }
       }
       late = at[1] - at[0]; length = t;
       share = next_queue_share(share, taken, late, n * block, &sign);
-      if (slow == 1.0 && share != kEvenShare) { ++bad; std::printf("even n %d: %g\n", n, share); break; }
-      if (step == 39 && slow < 0.6 && n >= 7 && std::abs(late) > 0.25 * length) { ++bad; std::printf("slow %g queue %d n %d: %g of %g\n", slow, which, n, late, length); }
+      if ((slow == 1.0 || which == 0) && share != kEvenShare) { ++bad; std::printf("even n %d slow %g lead %g: %g\n", n, slow, lead, share); break; }
+      if (step == 39 && slow < 0.6 && which == 1 && n >= 7 && std::abs(late) > 0.25 * length) { ++bad; std::printf("slow %g n %d: %g of %g\n", slow, n, late, length); }
     }
-    if (share != kEvenShare) { ++bad; std::printf("not even again: slow %g queue %d n %d: %g\n", slow, which, n, share); }
-  }""")
+    if (share != kEvenShare) { ++bad; std::printf("not even again: slow %g queue %d n %d lead %g: %g\n", slow, which, n, lead, share); }
+  }
+  // requests of seven and of eight blocks measured in a decode loop bound by the link, no queue slow
+  const double seen[][3] = {{0.429, -1134.4, 66.1e6}, {0.429, -1120.2, 66.1e6}, {0.5, -989.5, 75.5e6}, {0.5, -392.9, 37.7e6}, {0.4, -875.8, 47.2e6}};
+  bool sign = false;
+  for (int step = 0; step < 20; ++step) if (next_queue_share(kEvenShare, seen[step % 5][0], seen[step % 5][1], seen[step % 5][2], &sign) != kEvenShare) ++bad;
+""")
